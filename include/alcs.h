@@ -413,7 +413,7 @@ int alcs_project_latency(const float *scores_dev, const long long *seg_starts_ho
  * host or on the device.
  *   - At most ALCS_TOPN_STATIC_MAX_SEGMENTS segments (ALCS_E_UNSUPPORTED beyond; n_blocks is
  *     limited only as in alcs_topn_mask: the state's size depends on the segments alone).
- *   - Every GPU the library is used on holds one copy of the array (about 33 KB) until the
+ *   - Every GPU the library is used on holds one copy of the array (about 49 KB) until the
  *     process ends; its address is looked up on the first call on that device.
  *   - All calls on one GPU share that array, whatever their stream: calls that overlap on one GPU
  *     race, the caller serialises them.  The array keeps the previous call's contents; each call

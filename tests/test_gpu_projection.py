@@ -118,6 +118,37 @@ def test_projection_matches_the_oracle(seed, scale, frac):
     assert t0 - 1e-9 <= alcs.alcs_network_latency(tau, tables, nnz) <= t1 + 1e-9
 
 
+@pytest.mark.parametrize("layers,blocks,knots,kind", [(1, 1, 2, "rising"), (2, 300, 3, "rising"), (65, 40, 11, "ties"),
+                                                      (5, 5000, 11, "equal"), (7, 900, 11, "falling"), (3, 700, 65, "rising"),
+                                                      (1025, 3, 2, "rising")])
+def test_projection_edges(layers, blocks, knots, kind):
+    """Bisection on the device at its edges - one block, more layers than a wavefront, equal scores
+    across layers, latency tables that do not rise - and the path beyond its layer and table limits."""
+    import torch
+    rng = np.random.default_rng(3400 + layers + blocks)
+    sizes = rng.integers(1, blocks + 1, layers)
+    sc = [(rng.random((int(m), 1, 1, 1)) ** 4 * (0.1 + rng.random())).astype(np.float32) for m in sizes]
+    if kind == "ties":
+        sc = [np.round(s * 20).astype(np.float32) for s in sc]
+    if kind == "equal":
+        sc = [np.full_like(s, 0.75) for s in sc]
+    tables = []
+    for m in sizes:
+        k = np.arange(knots) * (4.0 * m / (knots - 1))
+        t = 3.0 + 0.01 * k + 0.002 * m * rng.random(knots)
+        tables.append((k, t if kind == "falling" else np.maximum.accumulate(t)))
+    starts = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    allsc = torch.from_numpy(np.concatenate([s.reshape(-1) for s in sc])).cuda()
+    t_none, t_all = sum(t[0] for _, t in tables), sum(t[-1] for _, t in tables)
+    for frac, eps in ((0.0, 1e-3), (0.31, 1e-6), (0.7, 0.5), (2.0, 1e-3)):
+        budget = t_none + frac * (t_all - t_none)
+        N, mask, t0, t1 = alcs.alcs_project_latency(allsc, starts, [4] * layers, tables, 1.5, 1.5 + budget, eps)
+        Nr, masks_r, t0r, t1r = oracle.project_latency(sc, [4] * layers, tables, 1.5, 1.5 + budget, eps)
+        assert N == Nr, (frac, N, Nr)
+        assert abs(t0 - t0r) <= 1e-9 * abs(t0r) and abs(t1 - t1r) <= 1e-9 * abs(t1r)
+        assert mask.cpu().numpy().tobytes() == np.concatenate([m.reshape(-1) for m in masks_r]).tobytes(), frac
+
+
 def test_projection_feeds_the_packer():
     """The mask that comes out of the projection is the mask alcs_pack_weights takes."""
     import torch
