@@ -3,8 +3,8 @@
 // offset per kept column; when the nine columns of a channel are kept or dropped together one
 // record per CHANNEL says the same - the channel's index and its 9 x V weights - and the kernel
 // can fetch a pixel's three input rows once and take the left and right neighbours from the lanes
-// beside it, instead of one on-chip read per tap.  The records are derived on the device from the
-// layout every handle has (host- or device-built), so both kinds of handle get them the same way:
+// beside it, instead of one on-chip read per tap.  For handles that the host packs the records are
+// derived on the device from the uploaded layout (the device packer writes them with the layout):
 //   k_chan_scan  per (bundle, chunk): records = padded columns / 9 (the padding is < 8), and
 //                their first index by an exclusive scan;
 //   k_chan_fill  per record: the channel from the first tap's row selector, the weights of
@@ -76,16 +76,12 @@ int add_channel_records(alcs_packed *p, void *stream) {
     const size_t o_sel = align256(4 * (size_t)cwplane * L.planes);
     const size_t o_work = align256(o_sel + 4 * (size_t)cap);
     const size_t total = align256(o_work + 8 * (size_t)nseg) + 256;
-    void *blob = nullptr;
-    hipError_t e = hipMalloc(&blob, total);
-    if (e != hipSuccess) {
-        set_hip_error((int)e);
-        (void)hipGetLastError();
-        return e == hipErrorOutOfMemory ? ALCS_E_ALLOC : ALCS_E_HIP;
-    }
+    int rc = ALCS_OK;
+    void *blob = device_alloc(total, &rc);
+    if (!blob) return rc;
     char *bb = (char *)blob;
     hipStream_t st = (hipStream_t)stream;
-    e = hipMemsetAsync(bb + o_sel, 0, 4 * (size_t)cap, st);
+    hipError_t e = hipMemsetAsync(bb + o_sel, 0, 4 * (size_t)cap, st);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_chan_scan, dim3(1), dim3(1024), 0, st, p->dev.work, (int)nseg, (int32_t *)(bb + o_work));
         hipLaunchKernelGGL(k_chan_fill, dim3((unsigned)nseg), dim3(64), 0, st, p->dev.work, (const int32_t *)(bb + o_work),
@@ -95,7 +91,7 @@ int add_channel_records(alcs_packed *p, void *stream) {
     }
     if (e != hipSuccess) {
         set_hip_error((int)e);
-        (void)hipFree(blob);
+        device_free(blob);
         return ALCS_E_HIP;
     }
     p->dev.chan_blob = blob;

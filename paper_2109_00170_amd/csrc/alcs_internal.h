@@ -190,7 +190,7 @@ struct DeviceCopy {
     const uint16_t *w16 = nullptr;
     const int32_t *off16 = nullptr;
     const Work *work16 = nullptr;
-    // Channel records of a tap-shared 3x3 handle (an allocation of its own, null otherwise): per
+    // Channel records of a tap-shared 3x3 handle (host-packed: an allocation of its own; null otherwise): per
     // (bundle, chunk) the first record and the number of records (cwork, two ints), per record the
     // chunk-relative input channel (csel) and, in each plane of cwplane floats, 64 weights
     // [tap 0..15][row 0..3] of which taps 9..15 are zero (cw).
@@ -221,6 +221,12 @@ struct alcs_packed {
 namespace alcs {
 
 void set_hip_error(int e);
+// Device memory for handles and their temporaries, from a bounded pool of freed blocks (alcs_pack.cpp):
+// a re-packing loop frees and makes the same handles over and over, and hipMalloc / hipFree cost
+// 10-100 us each and wait for the device.  device_alloc: memory of the current device, or null with
+// the status in *rc.
+void *device_alloc(size_t bytes, int *rc);
+void device_free(void *p);
 // Compute units and XCDs (L2 domains; workgroups are dealt to them round-robin) of a device,
 // from its properties; looked up once per device and process (constants of the hardware).
 void device_shape(int device, int *cus, int *xcds);
@@ -235,7 +241,7 @@ void choose_tiles(const alcs_packed *p, int *KC, int *GS);
 // canonical arrays and layout arrays of a handle built on the device, fetched to the host (once)
 int fetch_host_arrays(alcs_packed *p);
 int upload(alcs_packed *p);
-// alcs_chanrec.hip: builds the channel records of a tap-shared 3x3 handle from its device arrays
+// alcs_chanrec.hip: builds the channel records of a host-packed tap-shared 3x3 handle from its device arrays
 // (kernels on `stream`, a hipStream_t; no wait); does nothing for other handles
 int add_channel_records(alcs_packed *p, void *stream);
 void release_device(alcs_packed *p);

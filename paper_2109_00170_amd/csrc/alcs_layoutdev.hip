@@ -1,25 +1,26 @@
-// The device layout of a packed tensor built on the GPU: alcs_pack_from_csr_device makes a handle
-// from the canonical arrays of Section 3.2.2 of arXiv 2109.00170 ("Storage format": kept columns
-// per group, ascending column offsets, one V-vector per kept column) that are already on the
-// device - what alcs_pack_csr_device leaves there - without a round trip of the arrays through
-// the host.  In a re-pruning loop (Section 3.4, Algorithm 1: scores -> projection -> flags ->
-// arrays -> handle) the host then sees a handful of scalars per layer.
+// The device layout of a packed tensor built on the GPU: handles from weights and flags
+// (alcs_pack_weights_device, alcs_pack_network_device) or from the canonical arrays of Section 3.2.2 of
+// arXiv 2109.00170 ("Storage format": kept columns per group, ascending column offsets, one V-vector
+// per kept column; alcs_pack_from_csr_device) that are already on the device.  In a re-pruning loop
+// (Section 3.4, Algorithm 1: scores -> projection -> flags -> handles) the host then sees a handful of
+// scalars per layer.
 //
 // The layout is the one alcs_pack.cpp builds on the host (alcs_internal.h: bundles of groups in
 // order of descending length, segments per channel chunk padded to runs, weight planes in the
 // lane order of the matrix instruction, selector tables; with several groups per wavefront the
-// parity-aware column order) and is built to the same bytes:
-//   1. per group: length and validity (columns ascend, lie below K)            k_ld_stats
-//   2. the groups' ranks by descending length, ties by index                   k_ld_rank
-//   3. per group: running count of even-channel columns (parity-aware order)   k_ld_parity
-//   4. per (bundle, chunk): the slots' column ranges, the segment's length     k_ld_segments
-//   5. segment starts = exclusive scan of the padded lengths                   k_ld_scan
-//   6. every kept block to its place: weights, selectors, parity note          k_ld_scatter
-//   7. padded places: selector of the zero row that avoids the partner's banks k_ld_pads
-// The host reads back two sets of scalars (longest group / block count, then padded columns /
-// longest segment) to choose the tiles and to size the allocation; values are moved, never
-// computed.  Several layers are built in one call (alcs_pack_network_device): every step is
-// enqueued for all of them before the host waits, so a network costs three waits, not three a layer.
+// parity-aware column order) and is built to the same bytes, by four kernels that each cover ALL
+// layers of the call (a workgroup finds its layer in a table of first workgroups):
+//   1. per (group, chunk): kept columns, even-channel ones, validity               k_ld_count
+//   2. the groups' ranks by descending length, ties by index                       k_ld_rank
+//   3. per layer: row pointers, groups per wavefront, work records with their
+//      starts (scans), the scalars the host needs to size the allocations          k_ld_plan
+//   4. per (bundle, chunk): every kept block to its place in the canonical arrays,
+//      the weight planes and the selector tables, padding, channel records         k_ld_fill
+// Everything that depends on counts only (the places of padding, a slot's parity order) is computed
+// from the counts, so no array is cleared, copied or re-read.  The work is a few megabytes and the
+// call is bound by launches and waits: one upload, three launches, one read-back, one upload, one
+// launch, one wait for a whole network, where launching the steps layer by layer (16 operations a
+// layer, 2-4 us each) took 1.03 ms for 13 layers and 4.0 ms for 48.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -31,91 +32,57 @@
 #include "alcs_internal.h"
 
 namespace alcs {
-
-// alcs_packdev.hip: the canonical arrays from weights and flags (counts + scan; compaction)
-int enqueue_csr_count(const uint8_t *mask_dev, int G, int K, int32_t *row_ptr_dev, hipStream_t st);
-int enqueue_csr_fill(const float *W_dev, const uint8_t *mask_dev, int Cout, int K, int V, int G,
-                     const int32_t *row_ptr_dev, int32_t *col_idx_dev, float *vals_dev, hipStream_t st);
-
 namespace {
 
 constexpr int kRankLimit = 16384;  // groups the quadratic rank kernel takes; beyond, the host builds the layout
 
-struct LdShape {
-    int G, K, kk, V, VV, planes, Cin, k, KC, nchunks, GS, nbundles, noff;
-    long long nnzb;
+// What the kernels know about a layer: shape and inputs, temporaries (from the workspace), and - for
+// the last kernel - the handle's arrays.
+struct LayerDev {
+    const float *W;            // weights and flags, or
+    const uint8_t *mask;
+    const int32_t *ci_in;      // canonical arrays
+    const int32_t *rp_in;
+    const float *va_in;
+    long long room;            // blocks the shape has
+    int Cout, Cin, G, K, k, kk, V, VV, planes, KC, nchunks, noff;
+    int gs_even, gs_uneven;    // groups per wavefront when the groups are of similar length / are not
+    // temporaries
+    int32_t *cnt;              // [G * nchunks] kept columns
+    int32_t *even;             // [G] of them in even channels (one chunk, kernel 1)
+    int32_t *order, *rp;       // [G], [G + 1]
+    Work *work;                // [G * nchunks] at most
+    int32_t *cwork;            // two ints each: first channel record, number of records (kernel 3)
+    int *scal;
+    // the handle's arrays
+    Work *o_work;
+    float *o_w;
+    int32_t *o_off, *o_order, *o_rp, *o_ci;
+    float *o_va;
+    float *o_cw;               // channel records, or null
+    int32_t *o_csel, *o_cwork;
+    long long wplane, offlen, cwplane, used, ncol;
+    int GS, nbundles;
 };
 
-// scal[0] = longest group, scal[1] = 1 if the arrays are not canonical, scal[2] = padded columns in
-// use, scal[3] = longest segment, scal[4] = 1 if the padded columns overflow
-// scal[5] = blocks in all (row_ptr[G]).  `walk` = 0 skips the columns (arrays the library's own
-// kernels have written).
-__global__ void __launch_bounds__(256) k_ld_stats(const int32_t *row_ptr, const int32_t *col_idx, int G, int K,
-                                                  long long room, int walk, int *scal) {
-    const int g = blockIdx.x * 256 + threadIdx.x;
-    if (g >= G) return;
-    const long long nnzb = row_ptr[G];
-    const long long lo = row_ptr[g], hi = row_ptr[g + 1];
-    if (g == G - 1) scal[5] = (int)nnzb;
-    bool bad = lo < 0 || hi < lo || hi > nnzb || nnzb > room || hi - lo > K || (g == 0 && lo != 0);
-    if (!bad) {
-        if (walk)
-            for (long long t = lo; t < hi; ++t) {
-                const int col = col_idx[t];
-                if (col < 0 || col >= K || (t > lo && col <= col_idx[t - 1])) { bad = true; break; }
-            }
-        atomicMax(&scal[0], (int)(hi - lo));
-    }
-    if (bad) atomicMax(&scal[1], 1);
-}
-
-// scal[6] = 1 unless every group's kept columns are whole channels of nine taps (3x3 handles)
-__global__ void __launch_bounds__(256) k_ld_tapshared(const int32_t *row_ptr, const int32_t *col_idx, int G, long long nnzb,
-                                                      int *scal) {
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (t >= nnzb) return;
-    int lo = 0, hi = G;
+// First workgroup of every layer in a launch over all layers.
+struct Spread {
+    int count, rank, fill;
+};
+__device__ __forceinline__ int layer_of(const Spread *sp, int n, int wg, int Spread::*what) {
+    int lo = 0, hi = n;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (row_ptr[mid] <= t) lo = mid;
+        if (sp[mid].*what <= wg) lo = mid;
         else hi = mid;
     }
-    const int rel = (int)(t - row_ptr[lo]);
-    bool ok = rel % 9 == 0 ? col_idx[t] % 9 == 0 : col_idx[t] == col_idx[t - 1] + 1;
-    if (rel == 0) ok = ok && (row_ptr[lo + 1] - row_ptr[lo]) % 9 == 0;
-    if (!ok) atomicMax(&scal[6], 1);
+    return lo;
 }
 
-// order[rank] = g with rank = groups that are longer, or as long with a lower index (the stable
-// descending sort of the host)
-__global__ void __launch_bounds__(256) k_ld_rank(const int32_t *row_ptr, int G, int32_t *order, int32_t *pos) {
-    const int g = blockIdx.x * 256 + threadIdx.x;
-    if (g >= G) return;
-    const int mine = row_ptr[g + 1] - row_ptr[g];
-    int rank = 0;
-    for (int h = 0; h < G; ++h) {
-        const int c = row_ptr[h + 1] - row_ptr[h];
-        rank += (c > mine) || (c == mine && h < g);
-    }
-    order[rank] = g;
-    pos[g] = rank;
-}
-
-// evens[t + g] = columns of even channel among the group's blocks before t, for t in
-// [row_ptr[g], row_ptr[g+1]] (one slot more per group for the total); one wavefront per group
-__global__ void __launch_bounds__(64) k_ld_parity(const int32_t *row_ptr, const int32_t *col_idx, int kk,
-                                                  int32_t *evens) {
-    const int g = blockIdx.x, lane = threadIdx.x;
-    const int lo = row_ptr[g], hi = row_ptr[g + 1];
-    int base = 0;
-    for (int t0 = lo; t0 <= hi; t0 += 64) {
-        const int t = t0 + lane;
-        const bool even = t < hi && (((col_idx[t] / kk) & 1) == 0);
-        const unsigned long long ballot = __ballot(even);
-        if (t <= hi) evens[t + g] = base + __popcll(ballot & ((1ull << lane) - 1ull));
-        base += __popcll(ballot);
-    }
-}
+// The layer's scalars: longest group, kept blocks, groups per wavefront, padded columns, longest
+// segment; flags: the arrays are not canonical, some channel keeps part of its taps, the padded
+// columns do not fit 32 bits.
+enum Scal { kMaxCount, kBlocks, kSlots, kUsed, kMaxSeg, kBad, kNotShared, kOverflow, kScalars };
 
 __device__ __forceinline__ int lower_bound_dev(const int32_t *a, int lo, int hi, int key) {
     while (lo < hi) {
@@ -126,143 +93,299 @@ __device__ __forceinline__ int lower_bound_dev(const int32_t *a, int lo, int hi,
     return lo;
 }
 
-// per (bundle, chunk): the work record (start filled by the scan), every slot's column range in
-// the canonical arrays, the padded length
-__global__ void __launch_bounds__(256) k_ld_segments(LdShape sh, const int32_t *row_ptr, const int32_t *col_idx,
-                                                     const int32_t *order, Work *work, int32_t *seg_lo,
-                                                     int32_t *seg_n, int32_t *span, int *scal) {
-    const int si = blockIdx.x * 256 + threadIdx.x;
-    if (si >= sh.nbundles * sh.nchunks) return;
-    const int b = si / sh.nchunks, ch = si - b * sh.nchunks;
-    const int c_lo = ch * sh.KC, c_hi = min(sh.Cin, c_lo + sh.KC);
-    Work wk;
-    wk.start = 0;
-    wk.reserved[0] = wk.reserved[1] = 0;
-    int longest = 0;
-    for (int s = 0; s < kMaxSlots; ++s) {
-        wk.group[s] = -1;
-        const int p = b * sh.GS + s;
-        if (s >= sh.GS || p >= sh.G) {
-            if (s < sh.GS) { seg_lo[si * kMaxSlots + s] = 0; seg_n[si * kMaxSlots + s] = 0; }
-            continue;
+// One wavefront per (group, chunk).
+__global__ void __launch_bounds__(64) k_ld_count(const LayerDev *layers, const Spread *sp, int n) {
+    const int li = layer_of(sp, n, blockIdx.x, &Spread::count);
+    const LayerDev &L = layers[li];
+    const int lane = threadIdx.x, i = blockIdx.x - sp[li].count;
+    const int g = i / L.nchunks, ch = i - g * L.nchunks;
+    const int c_lo = ch * L.KC, c_hi = min(L.Cin, c_lo + L.KC);
+    int cnt = 0, even = 0;
+    if (L.W) {
+        bool torn = false;
+        if (L.mask) {
+            const uint8_t *m = L.mask + (size_t)g * L.K;
+            for (int c0 = c_lo * L.kk; c0 < c_hi * L.kk; c0 += 64) {
+                const int col = c0 + lane;
+                const bool in = col < c_hi * L.kk;
+                const bool keep = in && m[col] != 0;
+                if (L.kk == 9) torn = torn || (in && keep != (m[col - col % 9] != 0));
+                cnt += __popcll(__ballot(keep));
+                if (L.kk == 1) even += __popcll(__ballot(keep && (col & 1) == 0));
+            }
+        } else {
+            cnt = (c_hi - c_lo) * L.kk;
+            even = (c_hi - c_lo + (1 - (c_lo & 1))) >> 1;
         }
-        const int g = order[p];
-        wk.group[s] = g;
-        const int lo = lower_bound_dev(col_idx, row_ptr[g], row_ptr[g + 1], c_lo * sh.kk);
-        const int hi = lower_bound_dev(col_idx, lo, row_ptr[g + 1], c_hi * sh.kk);
-        seg_lo[si * kMaxSlots + s] = lo;
-        seg_n[si * kMaxSlots + s] = hi - lo;
-        longest = max(longest, hi - lo);
+        if (__any(torn) && lane == 0) L.scal[kNotShared] = 1;
+    } else {
+        const long long nnzb = L.rp_in[L.G], lo = L.rp_in[g], hi = L.rp_in[g + 1];
+        bool bad = lo < 0 || hi < lo || hi > nnzb || nnzb > L.room || hi - lo > L.K || (g == 0 && lo != 0) ||
+                   (nnzb > 0 && (!L.ci_in || !L.va_in));
+        bool torn = false;
+        if (!bad) {
+            if (ch == 0) {  // the group's columns: ascending, below K
+                for (long long t = lo + lane; t < hi; t += 64) {
+                    const int col = L.ci_in[t];
+                    bad = bad || col < 0 || col >= L.K || (t > lo && col <= L.ci_in[t - 1]);
+                    if (L.kk == 9) torn = torn || ((t - lo) % 9 == 0 ? col % 9 != 0 : col != L.ci_in[t - 1] + 1);
+                }
+                torn = torn || (L.kk == 9 && (hi - lo) % 9 != 0);
+            }
+            const int first = lower_bound_dev(L.ci_in, (int)lo, (int)hi, c_lo * L.kk);
+            const int end = lower_bound_dev(L.ci_in, first, (int)hi, c_hi * L.kk);
+            cnt = end - first;
+            if (L.kk == 1)
+                for (int t0 = first; t0 < end; t0 += 64)
+                    even += __popcll(__ballot(t0 + lane < end && (L.ci_in[min(t0 + lane, end - 1)] & 1) == 0));
+        }
+        if (__any(bad) && lane == 0) L.scal[kBad] = 1;
+        if (__any(torn) && lane == 0) L.scal[kNotShared] = 1;
     }
-    wk.cnt = (longest + kCntAlign - 1) / kCntAlign * kCntAlign;
-    work[si] = wk;
-    span[si] = (wk.cnt + kSegAlign - 1) / kSegAlign * kSegAlign;
-    atomicMax(&scal[3], wk.cnt);
+    if (lane == 0) {
+        L.cnt[i] = cnt;
+        if (ch == 0) L.even[g] = even;
+    }
 }
 
-// exclusive scan of the padded lengths by one workgroup: the segments' first columns
-__global__ void __launch_bounds__(1024) k_ld_scan(const int32_t *span, Work *work, int n, int *scal) {
-    __shared__ long long buf[1024];
-    __shared__ long long carry;
-    if (threadIdx.x == 0) carry = 0;
+// order[rank] = g with rank = groups that are longer, or as long with a lower index (the stable
+// descending sort of the host).
+__global__ void __launch_bounds__(256) k_ld_rank(const LayerDev *layers, const Spread *sp, int n) {
+    __shared__ int len[1024];
+    const int li = layer_of(sp, n, blockIdx.x, &Spread::rank);
+    const LayerDev &L = layers[li];
+    auto length = [&](int g) {
+        int s = 0;
+        for (int ch = 0; ch < L.nchunks; ++ch) s += L.cnt[(size_t)g * L.nchunks + ch];
+        return s;
+    };
+    const int g = (blockIdx.x - sp[li].rank) * 256 + threadIdx.x;
+    const int mine = g < L.G ? length(g) : 0;
+    int rank = 0;
+    for (int h0 = 0; h0 < L.G; h0 += 1024) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < min(1024, L.G - h0); i += 256) len[i] = length(h0 + i);
+        __syncthreads();
+        for (int i = 0; i < min(1024, L.G - h0); ++i) rank += (len[i] > mine) || (len[i] == mine && h0 + i < g);
+    }
+    if (g < L.G) L.order[rank] = g;
+}
+
+// Inclusive scan over a workgroup of 1024 threads.
+__device__ __forceinline__ long long scan_1024(long long v, long long *part) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const long long t = __shfl_up(v, d);
+        if (lane >= d) v += t;
+    }
     __syncthreads();
-    for (int base = 0; base < n; base += 1024) {
-        const int i = base + threadIdx.x;
-        const long long v = i < n ? span[i] : 0;
-        buf[threadIdx.x] = v;
+    if (lane == 63) part[wave] = v;
+    __syncthreads();
+    long long before = 0;
+    for (int w = 0; w < wave; ++w) before += part[w];
+    return v + before;
+}
+
+// One workgroup per layer.
+__global__ void __launch_bounds__(1024) k_ld_plan(const LayerDev *layers) {
+    __shared__ long long part[16], carry, carry2;
+    __shared__ int longest;
+    const LayerDev &L = layers[blockIdx.x];
+    const int tid = threadIdx.x;
+    if (tid == 0) { carry = 0; longest = 0; L.rp[0] = 0; }
+    __syncthreads();
+    int most = 0;
+    for (int g0 = 0; g0 < L.G; g0 += 1024) {
+        const int g = g0 + tid;
+        int len = 0;
+        if (g < L.G)
+            for (int ch = 0; ch < L.nchunks; ++ch) len += L.cnt[(size_t)g * L.nchunks + ch];
+        most = max(most, len);
+        const long long incl = scan_1024(len, part) + carry;
+        if (g < L.G) L.rp[g + 1] = (int32_t)incl;
         __syncthreads();
-        for (int d = 1; d < 1024; d <<= 1) {
-            const long long add = threadIdx.x >= d ? buf[threadIdx.x - d] : 0;
-            __syncthreads();
-            buf[threadIdx.x] += add;
-            __syncthreads();
-        }
-        const long long start = carry + buf[threadIdx.x] - v;
-        if (i < n) work[i].start = (int32_t)min(start, (long long)INT32_MAX);
-        __syncthreads();
-        if (threadIdx.x == 0) carry += buf[1023];
+        if (tid == 1023) carry = incl;
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        scal[2] = (int)min(carry, (long long)INT32_MAX);
-        scal[4] = carry > (long long)INT32_MAX ? 1 : 0;
+    atomicMax(&longest, most);
+    __syncthreads();
+    const long long nnzb = carry;
+    const int GS = (long long)longest * L.G <= 2 * nnzb ? L.gs_even : L.gs_uneven;
+    const int nbundles = (L.G + GS - 1) / GS, nseg = nbundles * L.nchunks;
+    __syncthreads();
+    if (tid == 0) {
+        L.scal[kMaxCount] = longest;
+        L.scal[kBlocks] = (int)nnzb;
+        L.scal[kSlots] = GS;
+        carry = carry2 = 0;
+        longest = 0;
+    }
+    __syncthreads();
+    most = 0;
+    for (int s0 = 0; s0 < nseg; s0 += 1024) {
+        const int si = s0 + tid;
+        Work wk{0, 0, {-1, -1, -1, -1}, {0, 0}};
+        if (si < nseg) {
+            const int b = si / L.nchunks, ch = si - b * L.nchunks;
+            int len = 0;
+#pragma unroll
+            for (int s = 0; s < kMaxSlots; ++s) {
+                const int p = b * GS + s;
+                if (s >= GS || p >= L.G) continue;
+                wk.group[s] = L.order[p];
+                len = max(len, L.cnt[(size_t)wk.group[s] * L.nchunks + ch]);
+            }
+            wk.cnt = (len + kCntAlign - 1) / kCntAlign * kCntAlign;
+        }
+        most = max(most, wk.cnt);
+        const int span = (wk.cnt + kSegAlign - 1) / kSegAlign * kSegAlign, recs = wk.cnt / 9;
+        const long long incl = scan_1024(span, part) + carry, incl2 = scan_1024(recs, part) + carry2;
+        if (si < nseg) {
+            wk.start = (int32_t)min(incl - span, (long long)INT32_MAX);
+            L.work[si] = wk;
+            L.cwork[2 * si] = (int32_t)min(incl2 - recs, (long long)INT32_MAX);
+            L.cwork[2 * si + 1] = recs;
+        }
+        __syncthreads();
+        if (tid == 1023) { carry = incl; carry2 = incl2; }
+        __syncthreads();
+    }
+    atomicMax(&longest, most);
+    __syncthreads();
+    if (tid == 0) {
+        L.scal[kMaxSeg] = longest;
+        L.scal[kUsed] = (int)min(carry, (long long)INT32_MAX);
+        L.scal[kOverflow] = carry > (long long)INT32_MAX ? 1 : 0;
     }
 }
 
-// every kept block to its place
-__global__ void __launch_bounds__(256) k_ld_scatter(LdShape sh, const int32_t *row_ptr, const int32_t *col_idx,
-                                                    const float *vals, const int32_t *pos, const int32_t *evens,
-                                                    const Work *work, const int32_t *seg_lo, const int32_t *seg_n,
-                                                    float *w, long long wplane, int32_t *off, long long offlen,
-                                                    uint8_t *par) {
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (t >= sh.nnzb) return;
-    // the block's group: the last g with row_ptr[g] <= t
-    int lo = 0, hi = sh.G;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (row_ptr[mid] <= t) lo = mid;
-        else hi = mid;
-    }
-    const int g = lo;
-    const int col = col_idx[t];
-    const int c = col / sh.kk, ch = c / sh.KC;
-    const int p = pos[g], b = p / sh.GS, s = p - b * sh.GS;
-    const int si = b * sh.nchunks + ch;
-    const Work wk = work[si];
-    const int first = seg_lo[si * kMaxSlots + s], n = seg_n[si * kMaxSlots + s];
-    int j = (int)(t - first);
-    const int parity = c & 1;
-    if (sh.GS > 1) {
-        // even slots: even channels from the front, odd ones right-aligned at the back; odd slots
-        // the other way round
-        const int e_first = evens[first + g], e_here = evens[t + g], e_all = evens[first + n + g] - e_first;
-        const int front_parity = (s & 1) ? 1 : 0;
-        const int rank_even = e_here - e_first, rank_odd = j - rank_even;
-        const int n_back = front_parity == 0 ? n - e_all : e_all;
-        if (parity == front_parity) j = parity == 0 ? rank_even : rank_odd;
-        else j = wk.cnt - n_back + (parity == 0 ? rank_even : rank_odd);
-    }
-    const long long at = (long long)wk.start + j;
-    for (int v = 0; v < sh.V; ++v) {
-        const int q = sh.V < 4 ? 0 : v / 4, i = sh.V < 4 ? v : v % 4;
-        w[(size_t)q * wplane + layout_w_index(sh.GS, sh.VV, at, s, i)] = vals[t * sh.V + v];
-    }
-    const size_t oi = layout_off_index(sh.GS, at, s);
-    for (int tb = 0; tb < sh.noff; ++tb) off[(size_t)tb * offlen + oi] = layout_off_of(col, sh.k, tb, sh.GS);
-    par[oi] = (uint8_t)parity;
-}
-
-// the padded places of a segment (one workgroup per segment), and the spare run behind the last one
-__global__ void __launch_bounds__(256) k_ld_pads(LdShape sh, const Work *work, int32_t *off, long long offlen,
-                                                 const uint8_t *par, long long used, long long ncol) {
-    const int nseg = sh.nbundles * sh.nchunks;
-    if ((int)blockIdx.x == nseg) {
-        for (long long i = used * sh.GS + threadIdx.x; i < ncol * sh.GS; i += 256) {
-            const long long col = used + (i - used * sh.GS) / sh.GS;
-            const int s = (int)((i - used * sh.GS) % sh.GS);
-            const size_t oi = layout_off_index(sh.GS, col, s);
-            for (int tb = 0; tb < sh.noff; ++tb) off[(size_t)tb * offlen + oi] = layout_pad_off(0, sh.KC, sh.k, tb, sh.GS, 0);
-        }
+// One workgroup per (bundle, chunk), and one per layer for the spare run behind the last segment.
+__global__ void __launch_bounds__(256) k_ld_fill(const LayerDev *layers, const Spread *sp, int n) {
+    __shared__ int wave_kept[4], wave_even[4], red[4];
+    const int li = layer_of(sp, n, blockIdx.x, &Spread::fill);
+    const LayerDev &L = layers[li];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int si = blockIdx.x - sp[li].fill, GS = L.GS, kk = L.kk, V = L.V;
+    auto put_pad = [&](long long col, int s, int c0, int which) {
+        for (int q = 0; q < L.planes; ++q)
+            for (int i = 0; i < L.VV; ++i) L.o_w[(size_t)q * L.wplane + layout_w_index(GS, L.VV, col, s, i)] = 0.f;
+        const size_t oi = layout_off_index(GS, col, s);
+        for (int tb = 0; tb < L.noff; ++tb) L.o_off[(size_t)tb * L.offlen + oi] = layout_pad_off(c0, L.KC, L.k, tb, GS, which);
+    };
+    if (si == L.nbundles * L.nchunks) {
+        for (int i = tid; i < (int)(L.ncol - L.used) * GS; i += 256) put_pad(L.used + i / GS, i % GS, 0, 0);
+        for (int g = tid; g <= L.G; g += 256) L.o_rp[g] = L.rp[g];
+        for (int g = tid; g < L.G; g += 256) L.o_order[g] = L.order[g];
         return;
     }
-    const int si = blockIdx.x;
-    const int ch = si % sh.nchunks;
-    const Work wk = work[si];
-    const int c0 = ch * sh.KC;
+    const int b = si / L.nchunks, ch = si - b * L.nchunks;
+    const int c0 = ch * L.KC, c_lo = c0 * kk, c_hi = min(L.Cin, c0 + L.KC) * kk;
+    const Work wk = L.work[si];
     const int span = (wk.cnt + kSegAlign - 1) / kSegAlign * kSegAlign;
-    for (int i = threadIdx.x; i < span * sh.GS; i += 256) {
-        const int j = i / sh.GS, s = i - j * sh.GS;
-        const size_t oi = layout_off_index(sh.GS, (long long)wk.start + j, s);
-        if (par[oi] != 0xFF) continue;  // a kept block sits here
-        int which = 0;
-        if (sh.GS > 1 && j < wk.cnt) {
-            const int m = s ^ 1;
-            const uint8_t mate = (m < sh.GS && wk.group[m] >= 0) ? par[layout_off_index(sh.GS, (long long)wk.start + j, m)] : 0xFF;
-            if (mate != 0xFF) which = ((c0 + sh.KC) & 1) == mate ? 1 : 0;
-            else which = s & 1;
+    const int first_rec = L.o_cw ? L.cwork[2 * si] : 0;
+    if (tid == 0) {
+        L.o_work[si] = wk;
+        if (L.o_cw) { L.o_cwork[2 * si] = first_rec; L.o_cwork[2 * si + 1] = L.cwork[2 * si + 1]; }
+    }
+    // a slot's columns: `front` from the start, `back` right-aligned at the end (with several groups per
+    // wavefront: even slots take even channels to the front and odd ones to the back, odd slots the
+    // other way round)
+    auto shape_of = [&](int s, int &kept, int &front, int &back) {
+        const int g = wk.group[s];
+        kept = g >= 0 ? L.cnt[(size_t)g * L.nchunks + ch] : 0;
+        front = kept;
+        back = 0;
+        if (GS > 1) {
+            const int e = g >= 0 ? L.even[g] : 0;
+            front = (s & 1) ? kept - e : e;
+            back = kept - front;
         }
-        for (int tb = 0; tb < sh.noff; ++tb) off[(size_t)tb * offlen + oi] = layout_pad_off(c0, sh.KC, sh.k, tb, sh.GS, which);
+    };
+    for (int s = 0; s < GS; ++s) {
+        const int g = wk.group[s];
+        int kept, front, back;
+        shape_of(s, kept, front, back);
+        if (g >= 0) {
+            // first canonical index of the segment: the group's, and the chunks before this one
+            int before = 0;
+            for (int c = tid; c < ch; c += 256) before += L.cnt[(size_t)g * L.nchunks + c];
+            if (ch > 0) {
+#pragma unroll
+                for (int d = 32; d; d >>= 1) before += __shfl_down(before, d);
+                __syncthreads();
+                if (lane == 0) red[wave] = before;
+                __syncthreads();
+                before = red[0] + red[1] + red[2] + red[3];
+            }
+            const long long t0 = (long long)L.rp[g] + before;
+            const int steps = L.W ? c_hi - c_lo : kept;
+            int done = 0, done_even = 0;
+            for (int x0 = 0; x0 < steps; x0 += 256) {
+                const int x = x0 + tid;
+                int col = 0;
+                bool keep;
+                if (L.W) {
+                    col = c_lo + x;
+                    keep = x < steps && (!L.mask || L.mask[(size_t)g * L.K + col] != 0);
+                } else {
+                    keep = x < steps;
+                    if (keep) col = L.ci_in[t0 + x];
+                }
+                const bool even = keep && GS > 1 && (col & 1) == 0;
+                const unsigned long long bk = __ballot(keep), be = __ballot(even), below = (1ull << lane) - 1ull;
+                if (lane == 0) { wave_kept[wave] = __popcll(bk); wave_even[wave] = __popcll(be); }
+                __syncthreads();
+                int r = done + __popcll(bk & below), re = done_even + __popcll(be & below);
+                for (int w = 0; w < wave; ++w) { r += wave_kept[w]; re += wave_even[w]; }
+                if (keep) {
+                    const long long t = t0 + r;
+                    int j = r;
+                    if (GS > 1) {
+                        const bool to_front = even == ((s & 1) == 0);
+                        const int rank = even ? re : r - re;
+                        j = to_front ? rank : wk.cnt - back + rank;
+                    }
+                    const long long at = (long long)wk.start + j;
+                    L.o_ci[t] = col;
+                    for (int v = 0; v < V; ++v) {
+                        const int row = g * V + v;
+                        const float val = L.W ? (row < L.Cout ? L.W[(size_t)row * L.K + col] : 0.f) : L.va_in[(size_t)t * V + v];
+                        const int q = V < 4 ? 0 : v / 4, i = V < 4 ? v : v % 4;
+                        L.o_va[(size_t)t * V + v] = val;
+                        L.o_w[(size_t)q * L.wplane + layout_w_index(GS, L.VV, at, s, i)] = val;
+                        if (L.o_cw) L.o_cw[(size_t)q * L.cwplane + (size_t)(first_rec + j / 9) * 64 + (j % 9) * 4 + i] = val;
+                    }
+                    const size_t oi = layout_off_index(GS, at, s);
+                    for (int tb = 0; tb < L.noff; ++tb) L.o_off[(size_t)tb * L.offlen + oi] = layout_off_of(col, L.k, tb, GS);
+                    if (L.o_cw && j % 9 == 0) {
+                        L.o_csel[first_rec + j / 9] = col / 9 - c0;
+                        for (int q = 0; q < L.planes; ++q)
+                            for (int i = 36; i < 64; ++i) L.o_cw[(size_t)q * L.cwplane + (size_t)(first_rec + j / 9) * 64 + i] = 0.f;
+                    }
+                }
+                done += wave_kept[0] + wave_kept[1] + wave_kept[2] + wave_kept[3];
+                done_even += wave_even[0] + wave_even[1] + wave_even[2] + wave_even[3];
+                __syncthreads();
+            }
+        }
+        // padding: between front and back (one group per wavefront: behind the columns), and the rest
+        // of the last run.  With several groups it selects the zero row of the other parity than the
+        // partner slot's row at that step.
+        int mk = 0, mf = 0, mb = 0;
+        const bool mate = GS > 1 && wk.group[s ^ 1] >= 0;
+        if (mate) shape_of(s ^ 1, mk, mf, mb);
+        const int from = front, to = wk.cnt - back;
+        for (int x = tid; x < (to - from) + (span - wk.cnt); x += 256) {
+            const int j = x < to - from ? from + x : wk.cnt + (x - (to - from));
+            int which = 0;
+            if (GS > 1 && j < wk.cnt) {
+                const int fp = ((s ^ 1) & 1) ? 1 : 0;  // channel parity at the partner's front
+                const int parity = !mate ? -1 : j < mf ? fp : j >= wk.cnt - mb ? 1 - fp : -1;
+                which = parity < 0 ? (s & 1) : (((c0 + L.KC) & 1) == parity ? 1 : 0);
+            }
+            put_pad((long long)wk.start + j, s, c0, which);
+        }
     }
 }
 
@@ -316,75 +439,6 @@ int through_the_host(const int32_t *rp_dev, const int32_t *ci_dev, const float *
     return pack_from_csr_host(rp.data(), ci.data(), va.data(), Cout, Cin, kernel, V, options, out);
 }
 
-// One layer on its way to a handle.
-struct Job {
-    // what the caller gave: weights + flags, or the canonical arrays
-    const float *W = nullptr;
-    const uint8_t *mask = nullptr;
-    const int32_t *rp = nullptr, *ci = nullptr;
-    const float *va = nullptr;
-    bool own_arrays = false;  // rp / ci / va lie in the temporary and are filled here
-    alcs_packed *p = nullptr;
-    long long cap = 0;        // blocks the temporaries have room for
-    long long max_seg = 0;    // (bundle, chunk) pairs they have room for
-    // temporaries
-    int *scal = nullptr;
-    int32_t *t_rp = nullptr, *t_ci = nullptr, *pos = nullptr, *ev = nullptr, *lo = nullptr, *n = nullptr, *span = nullptr,
-            *order = nullptr;
-    float *t_va = nullptr;
-    Work *work = nullptr;
-    LdShape sh{};
-    long long used = 0;
-    void *blob = nullptr;
-};
-
-// Upper bound of the (bundle, chunk) pairs of a layer: one group per bundle, the chunk size of the
-// tile policy (which does not depend on the flags).
-long long seg_bound(int Cout, int Cin, int kernel, int V, const alcs_options *opt) {
-    alcs_packed probe;
-    probe.Cout = Cout; probe.Cin = Cin; probe.k = kernel; probe.V = V;
-    probe.G = (Cout + V - 1) / V;
-    probe.K = Cin * kernel * kernel;
-    if (opt) probe.opt = *opt;
-    int KC = 0, GS = 1;
-    choose_tiles(&probe, &KC, &GS);
-    return (long long)probe.G * ((Cin + KC - 1) / KC);
-}
-
-// Bytes of temporary a layer needs, and (carve != null) the pointers into one.
-size_t carve(Job *j, char *base, int Cout, int Cin, int kernel, int V, const alcs_options *opt, bool own_arrays) {
-    const int G = (Cout + V - 1) / V;
-    const long long cap = (long long)G * Cin * kernel * kernel;
-    const long long nseg = seg_bound(Cout, Cin, kernel, V, opt);
-    size_t o = 0;
-    auto take = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return at; };
-    const size_t o_rp = take(own_arrays ? 4 * (size_t)(G + 1) : 0);
-    const size_t o_ci = take(own_arrays ? 4 * (size_t)cap : 0);
-    const size_t o_va = take(own_arrays ? 4 * (size_t)cap * V : 0);
-    const size_t o_pos = take(4 * (size_t)G);
-    const size_t o_ev = take(4 * (size_t)(cap + G + 1));
-    const size_t o_lo = take(4 * (size_t)nseg * kMaxSlots);
-    const size_t o_n = take(4 * (size_t)nseg * kMaxSlots);
-    const size_t o_span = take(4 * (size_t)nseg);
-    const size_t o_work = take(sizeof(Work) * (size_t)nseg);
-    const size_t o_order = take(4 * (size_t)G);
-    if (j) {
-        j->cap = cap;
-        j->max_seg = nseg;
-        j->t_rp = (int32_t *)(base + o_rp);
-        j->t_ci = (int32_t *)(base + o_ci);
-        j->t_va = (float *)(base + o_va);
-        j->pos = (int32_t *)(base + o_pos);
-        j->ev = (int32_t *)(base + o_ev);
-        j->lo = (int32_t *)(base + o_lo);
-        j->n = (int32_t *)(base + o_n);
-        j->span = (int32_t *)(base + o_span);
-        j->work = (Work *)(base + o_work);
-        j->order = (int32_t *)(base + o_order);
-    }
-    return o;
-}
-
 struct LayerIn {
     const float *W;
     const uint8_t *mask;
@@ -394,191 +448,196 @@ struct LayerIn {
     const alcs_options *opt;
 };
 
-// All layers through the three steps; out[i] receive the handles (all or none).
+// Tiles of a layer: the chunk size does not depend on the flags, the groups per wavefront only on
+// whether the groups are of similar length.
+void tiles_of(const LayerIn &in, int *KC, int *gs_even, int *gs_uneven) {
+    alcs_packed probe;
+    probe.Cout = in.Cout; probe.Cin = in.Cin; probe.k = in.kernel; probe.V = in.V;
+    probe.G = (in.Cout + in.V - 1) / in.V;
+    probe.K = in.Cin * in.kernel * in.kernel;
+    if (in.opt) probe.opt = *in.opt;
+    probe.nnzb = 1;
+    probe.max_count = 0;
+    choose_tiles(&probe, KC, gs_even);
+    probe.max_count = 3;  // more than twice the mean of one block in G groups
+    choose_tiles(&probe, KC, gs_uneven);
+}
+
+// The call's own workspace: scalars, the two tables that are uploaded, and the layers' temporaries.
+size_t header_bytes(int n) {
+    return align256(kScalars * sizeof(int) * (size_t)n) + align256(sizeof(LayerDev) * (size_t)n) + align256(sizeof(Spread) * (size_t)n);
+}
+// Bytes of temporary a layer needs, and (d != null) the pointers into one.
+size_t carve(LayerDev *d, char *base, const LayerIn &in) {
+    int KC = 0, ge = 1, gu = 1;
+    tiles_of(in, &KC, &ge, &gu);
+    const size_t G = (size_t)(in.Cout + in.V - 1) / in.V, nseg = G * ((in.Cin + KC - 1) / KC);
+    size_t o = 0;
+    auto take = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return base + at; };
+    char *cnt = take(4 * nseg), *even = take(4 * G), *order = take(4 * G), *rp = take(4 * (G + 1));
+    char *work = take(sizeof(Work) * nseg), *cwork = take(8 * nseg);
+    if (d) {
+        d->cnt = (int32_t *)cnt; d->even = (int32_t *)even; d->order = (int32_t *)order; d->rp = (int32_t *)rp;
+        d->work = (Work *)work; d->cwork = (int32_t *)cwork;
+        d->KC = KC; d->gs_even = ge; d->gs_uneven = gu;
+    }
+    return o;
+}
+
+__global__ void k_ld_clear(int *scal, int n) {
+    for (int i = threadIdx.x; i < n; i += blockDim.x) scal[i] = 0;
+}
+
+// All layers through the steps; out[i] receive the handles (all or none).
 int build_all(const LayerIn *in, int n, void *workspace, size_t workspace_bytes, hipStream_t st, alcs_packed_t **out) {
     for (int i = 0; i < n; ++i) out[i] = nullptr;
+    size_t need = header_bytes(n);
     for (int i = 0; i < n; ++i) {
         int rc = check_shape(in[i].Cout, in[i].Cin, in[i].kernel, in[i].V);
         if (rc == ALCS_OK && too_many_groups(in[i].Cout, in[i].V)) rc = ALCS_E_UNSUPPORTED;
         if (rc == ALCS_OK && in[i].opt) rc = check_options(in[i].opt);
         if (rc != ALCS_OK) return rc;
         if (!in[i].W && !in[i].rp) return ALCS_E_INVALID_ARG;
+        need += carve(nullptr, nullptr, in[i]);
     }
     int dev = 0;
     int rc = check(hipGetDevice(&dev));
     if (rc != ALCS_OK) return rc;
     int cus = 0, xcds = 0;
     device_shape(dev, &cus, &xcds);
-    std::vector<Job> jobs;
+    std::vector<LayerDev> L;
+    std::vector<Spread> sp;
     std::vector<int> h_scal;
+    std::vector<alcs_packed *> made;
     try {
-        jobs.resize((size_t)n);
-        h_scal.resize((size_t)n * 8);
+        L.resize((size_t)n);
+        sp.resize((size_t)n);
+        h_scal.resize((size_t)n * kScalars);
+        made.resize((size_t)n, nullptr);
     } catch (const std::bad_alloc &) {
         return ALCS_E_ALLOC;
     }
-    // the jobs' scalars (8 ints each) lie together at the start, so that one copy reads them all
-    const size_t scal_bytes = align256(8 * sizeof(int) * (size_t)n);
-    size_t need = scal_bytes;
-    for (int i = 0; i < n; ++i) need += carve(nullptr, nullptr, in[i].Cout, in[i].Cin, in[i].kernel, in[i].V, in[i].opt, in[i].W != nullptr);
     void *own_ws = nullptr;
     if (!workspace) {
-        if ((rc = check(hipMalloc(&own_ws, need))) != ALCS_OK) return rc;
+        if (!(own_ws = device_alloc(need, &rc))) return rc;
         workspace = own_ws;
     } else if (workspace_bytes < need || ((uintptr_t)workspace & 255) != 0) {
         return ALCS_E_INVALID_ARG;
     }
     auto fail = [&](int code) {
         (void)hipStreamSynchronize(st);  // nothing may still write what is freed here
-        for (Job &j : jobs) {
-            if (j.blob) (void)hipFree(j.blob);
-            if (j.p && j.p->dev.chan_blob) (void)hipFree(j.p->dev.chan_blob);
-            delete j.p;
-        }
-        if (own_ws) (void)hipFree(own_ws);
+        for (alcs_packed *p : made)
+            if (p) { release_device(p); delete p; }
+        if (own_ws) device_free(own_ws);
         return code;
     };
-    {
-        char *base = (char *)workspace + scal_bytes;
-        for (int i = 0; i < n; ++i) {
-            Job &j = jobs[(size_t)i];
-            j.scal = (int *)workspace + 8 * i;
-            j.own_arrays = in[i].W != nullptr;
-            base += carve(&j, base, in[i].Cout, in[i].Cin, in[i].kernel, in[i].V, in[i].opt, j.own_arrays);
-            j.W = in[i].W; j.mask = in[i].mask;
-            j.rp = j.own_arrays ? j.t_rp : in[i].rp;
-            j.ci = j.own_arrays ? j.t_ci : in[i].ci;
-            j.va = j.own_arrays ? j.t_va : in[i].va;
-            j.p = new (std::nothrow) alcs_packed();
-            if (!j.p) return fail(ALCS_E_ALLOC);
-            alcs_packed *p = j.p;
-            p->Cout = in[i].Cout; p->Cin = in[i].Cin; p->k = in[i].kernel; p->V = in[i].V;
-            p->G = (p->Cout + p->V - 1) / p->V;
-            p->K = p->Cin * p->k * p->k;
-            if (in[i].opt) p->opt = *in[i].opt;
-        }
+    int *d_scal = (int *)workspace;
+    LayerDev *d_layers = (LayerDev *)((char *)workspace + align256(kScalars * sizeof(int) * (size_t)n));
+    Spread *d_spread = (Spread *)((char *)d_layers + align256(sizeof(LayerDev) * (size_t)n));
+    char *base = (char *)workspace + header_bytes(n);
+    long long wg_count = 0, wg_rank = 0;
+    for (int i = 0; i < n; ++i) {
+        LayerDev &d = L[(size_t)i];
+        d = LayerDev{};
+        base += carve(&d, base, in[i]);
+        d.W = in[i].W; d.mask = in[i].mask; d.rp_in = in[i].rp; d.ci_in = in[i].ci; d.va_in = in[i].va;
+        d.Cout = in[i].Cout; d.Cin = in[i].Cin; d.k = in[i].kernel; d.V = in[i].V;
+        d.kk = d.k * d.k;
+        d.G = (d.Cout + d.V - 1) / d.V;
+        d.K = d.Cin * d.kk;
+        d.room = (long long)d.G * d.K;
+        d.nchunks = (d.Cin + d.KC - 1) / d.KC;
+        d.planes = d.V >= 4 ? d.V / 4 : 1;
+        d.VV = d.V >= 4 ? 4 : d.V;
+        d.noff = d.k == 1 ? 1 : kMaxOff;
+        d.scal = d_scal + kScalars * i;
+        if ((d.gs_even > 1 || d.gs_uneven > 1) && (d.V < 4 || d.k != 1 || d.nchunks != 1)) return fail(ALCS_E_INVALID_ARG);
+        sp[(size_t)i] = Spread{(int)wg_count, (int)wg_rank, 0};
+        wg_count += (long long)d.G * d.nchunks;
+        wg_rank += (d.G + 255) / 256;
+        if (wg_count > INT32_MAX - 1024) return fail(ALCS_E_UNSUPPORTED);
     }
-    auto read_scalars = [&]() {
-        const int r = check(hipMemcpyAsync(h_scal.data(), workspace, 8 * sizeof(int) * (size_t)n, hipMemcpyDeviceToHost, st));
-        return r != ALCS_OK ? r : check(hipStreamSynchronize(st));
+    auto upload_tables = [&]() {
+        int r = check(hipMemcpyAsync(d_layers, L.data(), sizeof(LayerDev) * (size_t)n, hipMemcpyHostToDevice, st));
+        if (r == ALCS_OK) r = check(hipMemcpyAsync(d_spread, sp.data(), sizeof(Spread) * (size_t)n, hipMemcpyHostToDevice, st));
+        return r;
     };
-
-    // step 1: arrays' row pointers (own arrays), lengths, validity
-    if ((rc = check(hipMemsetAsync(workspace, 0, 8 * sizeof(int) * (size_t)n, st))) != ALCS_OK) return fail(rc);
-    for (Job &j : jobs) {
-        const alcs_packed *p = j.p;
-        if (j.own_arrays && (rc = enqueue_csr_count(j.mask, p->G, p->K, j.t_rp, st)) != ALCS_OK) return fail(rc);
-        hipLaunchKernelGGL(k_ld_stats, dim3((p->G + 255) / 256), dim3(256), 0, st, j.rp, j.ci, p->G, p->K, j.cap,
-                           j.own_arrays ? 0 : 1, j.scal);
-    }
+    if ((rc = upload_tables()) != ALCS_OK) return fail(rc);
+    hipLaunchKernelGGL(k_ld_clear, dim3(1), dim3(256), 0, st, d_scal, kScalars * n);
+    hipLaunchKernelGGL(k_ld_count, dim3((unsigned)wg_count), dim3(64), 0, st, d_layers, d_spread, n);
+    hipLaunchKernelGGL(k_ld_rank, dim3((unsigned)wg_rank), dim3(256), 0, st, d_layers, d_spread, n);
+    hipLaunchKernelGGL(k_ld_plan, dim3((unsigned)n), dim3(1024), 0, st, d_layers);
     if ((rc = check(hipGetLastError())) != ALCS_OK) return fail(rc);
-    if ((rc = read_scalars()) != ALCS_OK) return fail(rc);
+    rc = check(hipMemcpyAsync(h_scal.data(), d_scal, kScalars * sizeof(int) * (size_t)n, hipMemcpyDeviceToHost, st));
+    if (rc == ALCS_OK) rc = check(hipStreamSynchronize(st));
+    if (rc != ALCS_OK) return fail(rc);
 
-    // step 2: tiles, then order, segments and their starts
+    // the handles: tile parameters, one allocation each
+    long long wg_fill = 0;
     for (int i = 0; i < n; ++i) {
-        Job &j = jobs[(size_t)i];
-        alcs_packed *p = j.p;
-        const int *hs = &h_scal[(size_t)i * 8];
-        if (hs[1]) return fail(ALCS_E_INVALID_ARG);
-        p->max_count = hs[0];
-        p->nnzb = hs[5];
-        if (p->nnzb > 0 && !j.own_arrays && (!j.ci || !j.va)) return fail(ALCS_E_INVALID_ARG);
-        int KC = 0, GS = 1;
-        choose_tiles(p, &KC, &GS);
-        Layout &L = p->lay;
-        L.KC = KC;
-        L.nchunks = (p->Cin + KC - 1) / KC;
-        L.GS = GS;
-        L.nbundles = (p->G + GS - 1) / GS;
-        L.planes = p->V >= 4 ? p->V / 4 : 1;
-        L.VV = p->V >= 4 ? 4 : p->V;
-        L.noff = p->k == 1 ? 1 : kMaxOff;
-        if (GS > 1 && (p->V < 4 || p->k != 1 || L.nchunks != 1)) return fail(ALCS_E_INVALID_ARG);
-        const long long nseg = (long long)L.nbundles * L.nchunks;
-        if (nseg > j.max_seg) return fail(ALCS_E_INVALID_ARG);  // cannot happen: the bound takes one group per bundle
-        j.sh = LdShape{p->G, p->K, p->k * p->k, p->V, L.VV, L.planes, p->Cin, p->k, KC, L.nchunks, GS, L.nbundles, L.noff, p->nnzb};
-        if (j.own_arrays && p->nnzb &&
-            (rc = enqueue_csr_fill(j.W, j.mask, p->Cout, p->K, p->V, p->G, j.t_rp, j.t_ci, j.t_va, st)) != ALCS_OK)
-            return fail(rc);
-        if (p->k == 3 && p->nnzb > 0 && p->nnzb % 9 == 0)
-            hipLaunchKernelGGL(k_ld_tapshared, dim3((unsigned)((p->nnzb + 255) / 256)), dim3(256), 0, st, j.rp, j.ci, p->G,
-                               (long long)p->nnzb, j.scal);
-        hipLaunchKernelGGL(k_ld_rank, dim3((p->G + 255) / 256), dim3(256), 0, st, j.rp, p->G, j.order, j.pos);
-        if (GS > 1) hipLaunchKernelGGL(k_ld_parity, dim3(p->G), dim3(64), 0, st, j.rp, j.ci, p->k * p->k, j.ev);
-        hipLaunchKernelGGL(k_ld_segments, dim3((unsigned)((nseg + 255) / 256)), dim3(256), 0, st, j.sh, j.rp, j.ci, j.order,
-                           j.work, j.lo, j.n, j.span, j.scal);
-        hipLaunchKernelGGL(k_ld_scan, dim3(1), dim3(1024), 0, st, j.span, j.work, (int)nseg, j.scal);
-    }
-    if ((rc = check(hipGetLastError())) != ALCS_OK) return fail(rc);
-    if ((rc = read_scalars()) != ALCS_OK) return fail(rc);
-
-    // step 3: the handles' allocations, every block to its place
-    for (int i = 0; i < n; ++i) {
-        Job &j = jobs[(size_t)i];
-        alcs_packed *p = j.p;
-        Layout &L = p->lay;
-        const int *hs = &h_scal[(size_t)i * 8];
-        const int GS = L.GS, G = p->G, V = p->V;
-        const long long nnzb = p->nnzb, nseg = (long long)L.nbundles * L.nchunks;
-        j.used = hs[2];
-        if (hs[4] || j.used > INT32_MAX / (4 * GS) - 64) return fail(ALCS_E_UNSUPPORTED);
-        L.max_cnt = hs[3];
-        L.tap_shared = p->k == 3 && nnzb > 0 && nnzb % 9 == 0 && hs[6] == 0;
-        L.ncol = j.used + kSegAlign;
-        L.wplane = L.ncol * L.VV * GS;
-        // work | weight planes | selector tables | order | canonical arrays | (parity notes, build only)
-        const size_t b_work = sizeof(Work) * (size_t)nseg, b_w = 4 * (size_t)L.planes * (size_t)L.wplane;
-        const size_t b_off = 4 * (size_t)L.ncol * GS;
+        LayerDev &d = L[(size_t)i];
+        const int *hs = &h_scal[(size_t)i * kScalars];
+        if (hs[kBad]) return fail(ALCS_E_INVALID_ARG);
+        alcs_packed *p = made[(size_t)i] = new (std::nothrow) alcs_packed();
+        if (!p) return fail(ALCS_E_ALLOC);
+        p->Cout = d.Cout; p->Cin = d.Cin; p->k = d.k; p->V = d.V; p->G = d.G; p->K = d.K;
+        if (in[i].opt) p->opt = *in[i].opt;
+        p->max_count = hs[kMaxCount];
+        p->nnzb = hs[kBlocks];
+        Layout &lay = p->lay;
+        lay.KC = d.KC;
+        lay.nchunks = d.nchunks;
+        lay.GS = d.GS = hs[kSlots];
+        lay.nbundles = d.nbundles = (d.G + d.GS - 1) / d.GS;
+        lay.planes = d.planes;
+        lay.VV = d.VV;
+        lay.noff = d.noff;
+        d.used = hs[kUsed];
+        if (hs[kOverflow] || d.used > INT32_MAX / (4 * d.GS) - 64) return fail(ALCS_E_UNSUPPORTED);
+        lay.max_cnt = hs[kMaxSeg];
+        lay.tap_shared = d.k == 3 && p->nnzb > 0 && hs[kNotShared] == 0;
+        lay.ncol = d.ncol = d.used + kSegAlign;
+        lay.wplane = d.wplane = lay.ncol * lay.VV * d.GS;
+        d.offlen = lay.ncol * d.GS;
+        const size_t nseg = (size_t)d.nbundles * d.nchunks, nnzb = (size_t)p->nnzb;
+        const bool records = lay.tap_shared && d.V >= 4;
+        const size_t cap = records ? (size_t)lay.ncol / 9 + 1 : 0;
+        d.cwplane = (long long)cap * 64;
+        // work | weight planes | selector tables | order | canonical arrays | channel records
         size_t q = 0;
         auto take = [&](size_t bytes) { const size_t at = q; q = align256(q + bytes); return at; };
-        const size_t q_work = take(b_work), q_w = take(b_w), q_off = take(b_off * L.noff), q_order = take(4 * (size_t)G);
-        const size_t q_rp = take(4 * (size_t)(G + 1)), q_ci = take(4 * (size_t)nnzb), q_va = take(4 * (size_t)nnzb * V);
+        const size_t q_work = take(sizeof(Work) * nseg), q_w = take(4 * (size_t)d.planes * (size_t)d.wplane);
+        const size_t q_off = take(4 * (size_t)d.offlen * d.noff), q_order = take(4 * (size_t)d.G);
+        const size_t q_rp = take(4 * (size_t)(d.G + 1)), q_ci = take(4 * nnzb), q_va = take(4 * nnzb * d.V);
+        const size_t q_cw = take(4 * (size_t)d.cwplane * d.planes), q_sel = take(4 * cap), q_cwork = take(records ? 8 * nseg : 0);
         const size_t total = q + 256;
-        const size_t b_par = (size_t)L.ncol * GS;
-        if ((rc = check(hipMalloc(&j.blob, total + align256(b_par)))) != ALCS_OK) return fail(rc);
-        char *bb = (char *)j.blob;
-        uint8_t *d_par = (uint8_t *)(bb + total);
-        float *d_w = (float *)(bb + q_w);
-        int32_t *d_off = (int32_t *)(bb + q_off);
-        hipError_t e = hipMemsetAsync(d_w, 0, b_w, st);
-        if (e == hipSuccess) e = hipMemsetAsync(d_par, 0xFF, b_par, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(bb + q_work, j.work, b_work, hipMemcpyDeviceToDevice, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(bb + q_order, j.order, 4 * (size_t)G, hipMemcpyDeviceToDevice, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(bb + q_rp, j.rp, 4 * (size_t)(G + 1), hipMemcpyDeviceToDevice, st);
-        if (e == hipSuccess && nnzb) e = hipMemcpyAsync(bb + q_ci, j.ci, 4 * (size_t)nnzb, hipMemcpyDeviceToDevice, st);
-        if (e == hipSuccess && nnzb) e = hipMemcpyAsync(bb + q_va, j.va, 4 * (size_t)nnzb * V, hipMemcpyDeviceToDevice, st);
-        if ((rc = check(e)) != ALCS_OK) return fail(rc);
-        if (nnzb)
-            hipLaunchKernelGGL(k_ld_scatter, dim3((unsigned)((nnzb + 255) / 256)), dim3(256), 0, st, j.sh, j.rp, j.ci, j.va, j.pos,
-                               j.ev, (const Work *)(bb + q_work), j.lo, j.n, d_w, (long long)L.wplane, d_off,
-                               (long long)(b_off / 4), d_par);
-        hipLaunchKernelGGL(k_ld_pads, dim3((unsigned)nseg + 1), dim3(256), 0, st, j.sh, (const Work *)(bb + q_work), d_off,
-                           (long long)(b_off / 4), d_par, j.used, (long long)L.ncol);
-        p->host_arrays = false;
+        char *bb = (char *)device_alloc(total, &rc);
+        if (!bb) return fail(rc);
+        p->dev.blob = bb;
         p->dev.device = dev;
         p->dev.cus = cus;
         p->dev.xcds = xcds;
         p->dev.bytes = total;
-        p->dev.work = (const Work *)(bb + q_work);
-        p->dev.w = d_w;
-        for (int t = 0; t < kMaxOff; ++t) p->dev.off[t] = t < L.noff ? d_off + (size_t)t * (b_off / 4) : nullptr;
-        p->dev.order = (const int32_t *)(bb + q_order);
-        p->dev.row_ptr = (const int32_t *)(bb + q_rp);
-        p->dev.col_idx = (const int32_t *)(bb + q_ci);
-        p->dev.vals = (const float *)(bb + q_va);
-        p->dev.blob = j.blob;  // for the channel records; taken back below if the call fails
-        rc = add_channel_records(p, st);
-        p->dev.blob = nullptr;
-        if (rc != ALCS_OK) return fail(rc);
+        p->host_arrays = false;
+        d.o_work = (Work *)(bb + q_work); d.o_w = (float *)(bb + q_w); d.o_off = (int32_t *)(bb + q_off);
+        d.o_order = (int32_t *)(bb + q_order); d.o_rp = (int32_t *)(bb + q_rp); d.o_ci = (int32_t *)(bb + q_ci);
+        d.o_va = (float *)(bb + q_va);
+        p->dev.work = d.o_work; p->dev.w = d.o_w; p->dev.order = d.o_order; p->dev.row_ptr = d.o_rp;
+        p->dev.col_idx = d.o_ci; p->dev.vals = d.o_va;
+        for (int t = 0; t < kMaxOff; ++t) p->dev.off[t] = t < d.noff ? d.o_off + (size_t)t * d.offlen : nullptr;
+        if (records) {
+            d.o_cw = (float *)(bb + q_cw); d.o_csel = (int32_t *)(bb + q_sel); d.o_cwork = (int32_t *)(bb + q_cwork);
+            p->dev.cw = d.o_cw; p->dev.csel = d.o_csel; p->dev.cwork = d.o_cwork; p->dev.cwplane = d.cwplane;
+        }
+        sp[(size_t)i].fill = (int)wg_fill;
+        wg_fill += (long long)nseg + 1;
     }
+    if ((rc = upload_tables()) != ALCS_OK) return fail(rc);
+    hipLaunchKernelGGL(k_ld_fill, dim3((unsigned)wg_fill), dim3(256), 0, st, d_layers, d_spread, n);
     if ((rc = check(hipGetLastError())) != ALCS_OK) return fail(rc);
     if ((rc = check(hipStreamSynchronize(st))) != ALCS_OK) return fail(rc);  // the temporaries are free again
-    for (int i = 0; i < n; ++i) {
-        Job &j = jobs[(size_t)i];
-        j.p->dev.blob = j.blob;
-        out[i] = j.p;
-    }
-    if (own_ws) (void)hipFree(own_ws);
+    for (int i = 0; i < n; ++i) out[i] = made[(size_t)i];
+    if (own_ws) device_free(own_ws);
     return ALCS_OK;
 }
 
@@ -607,16 +666,16 @@ extern "C" int alcs_pack_weights_device(const float *W_dev, const uint8_t *mask_
         const int G = (Cout + V - 1) / V;
         const long long cap = (long long)G * Cin * kernel * kernel;
         const size_t o_ci = align256(4 * (size_t)(G + 1)), o_va = align256(o_ci + 4 * (size_t)cap);
-        void *tmp = nullptr;
-        int rc = check(hipMalloc(&tmp, o_va + 4 * (size_t)cap * V));
-        if (rc != ALCS_OK) return rc;
+        int rc = ALCS_OK;
+        void *tmp = device_alloc(o_va + 4 * (size_t)cap * V, &rc);
+        if (!tmp) return rc;
         char *tb = (char *)tmp;
         rc = alcs_pack_csr_device(W_dev, mask_dev, Cout, Cin, kernel, V, (int32_t *)tb, (int32_t *)(tb + o_ci),
                                   (float *)(tb + o_va), cap, nullptr, stream);
         if (rc == ALCS_OK)
             rc = through_the_host((const int32_t *)tb, (const int32_t *)(tb + o_ci), (const float *)(tb + o_va), Cout, Cin,
                                   kernel, V, options, (hipStream_t)stream, out);
-        (void)hipFree(tmp);
+        device_free(tmp);
         return rc;
     }
     const LayerIn in{W_dev, mask_dev, nullptr, nullptr, nullptr, Cout, Cin, kernel, V, options};
@@ -625,14 +684,14 @@ extern "C" int alcs_pack_weights_device(const float *W_dev, const uint8_t *mask_
 
 extern "C" long long alcs_pack_workspace_bytes(const alcs_layer_desc *layers, int n_layers) {
     if (!layers || n_layers <= 0) return ALCS_E_INVALID_ARG;
-    size_t need = align256(8 * sizeof(int) * (size_t)n_layers);
+    size_t need = header_bytes(n_layers);
     for (int i = 0; i < n_layers; ++i) {
         const alcs_layer_desc &d = layers[i];
         int rc = check_shape(d.Cout, d.Cin, d.kernel, d.V);
         if (rc == ALCS_OK && too_many_groups(d.Cout, d.V)) rc = ALCS_E_UNSUPPORTED;
         if (rc == ALCS_OK && d.options) rc = check_options(d.options);
         if (rc != ALCS_OK) return rc;
-        need += carve(nullptr, nullptr, d.Cout, d.Cin, d.kernel, d.V, d.options, true);
+        need += carve(nullptr, nullptr, LayerIn{d.W_dev, d.mask_dev, nullptr, nullptr, nullptr, d.Cout, d.Cin, d.kernel, d.V, d.options});
     }
     return (long long)need;
 }

@@ -7,6 +7,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <new>
 #include <numeric>
 
@@ -209,16 +210,122 @@ int build_layout(alcs_packed *p, int KC, int GS) {
 
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-void release_device(alcs_packed *p) {
-    if (p->dev.blob) {
-        int cur = -1;
-        const bool elsewhere = hipGetDevice(&cur) == hipSuccess && cur != p->dev.device;
-        if (elsewhere) (void)hipSetDevice(p->dev.device);
-        (void)hipFree(p->dev.blob);
-        if (p->dev.w16) (void)hipFree(const_cast<uint16_t *>(p->dev.w16));
-        if (p->dev.chan_blob) (void)hipFree(p->dev.chan_blob);
-        if (elsewhere) (void)hipSetDevice(cur);
+// The pool.  A freed block is kept (at most kPoolBlocks of them and kPoolBytes in all; the oldest go
+// back to the runtime) and handed out again for a request of about its size on the same device.
+// hipFree waits for everything the device has been given, which is what makes freeing a handle safe
+// while a kernel of any stream may still read it; here the same wait is made when a block is handed
+// out again, once for all blocks freed since the last one.
+namespace {
+constexpr size_t kPoolBlocks = 256, kPoolBytes = (size_t)512 << 20;
+struct PoolBlock {
+    void *p;
+    size_t bytes;
+    int device;
+    bool settled;  // the device has finished everything it was given before the block was freed
+};
+struct Pool {
+    std::mutex mu;
+    std::vector<PoolBlock> kept;          // oldest first
+    std::map<void *, PoolBlock> in_use;
+    size_t kept_bytes = 0;
+};
+Pool &pool() {
+    static Pool *p = new Pool();  // never destroyed: handles may be freed while the process ends
+    return *p;
+}
+// Sizes are rounded up to eighths of a power of two, so that a layer whose kept blocks change a
+// little from one packing to the next finds its old block again.
+size_t pool_size(size_t bytes) {
+    size_t step = 4096;
+    while (step * 16 <= bytes) step *= 2;
+    return (bytes + step - 1) / step * step;
+}
+void give_back(const PoolBlock &b) {
+    int cur = -1;
+    const bool elsewhere = hipGetDevice(&cur) == hipSuccess && cur != b.device;
+    if (elsewhere) (void)hipSetDevice(b.device);
+    (void)hipFree(b.p);
+    if (elsewhere) (void)hipSetDevice(cur);
+}
+}  // namespace
+
+void *device_alloc(size_t bytes, int *rc) {
+    *rc = ALCS_OK;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) { set_hip_error((int)e); *rc = ALCS_E_HIP; return nullptr; }
+    const size_t want = pool_size(bytes);
+    Pool &P = pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    size_t best = P.kept.size();
+    for (size_t i = 0; i < P.kept.size(); ++i)
+        if (P.kept[i].device == dev && P.kept[i].bytes >= want && P.kept[i].bytes <= want + want / 4 &&
+            (best == P.kept.size() || P.kept[i].bytes < P.kept[best].bytes))
+            best = i;
+    try {
+        if (best < P.kept.size()) {
+            PoolBlock b = P.kept[best];
+            if (!b.settled) {
+                if ((e = hipDeviceSynchronize()) != hipSuccess) { set_hip_error((int)e); *rc = ALCS_E_HIP; return nullptr; }
+                for (PoolBlock &k : P.kept)
+                    if (k.device == dev) k.settled = true;
+            }
+            P.in_use.emplace(b.p, b);
+            P.kept.erase(P.kept.begin() + (long)best);
+            P.kept_bytes -= b.bytes;
+            return b.p;
+        }
+        PoolBlock b{nullptr, want, dev, true};
+        e = hipMalloc(&b.p, want);
+        if (e == hipErrorOutOfMemory && !P.kept.empty()) {
+            (void)hipGetLastError();
+            for (const PoolBlock &k : P.kept) give_back(k);
+            P.kept.clear();
+            P.kept_bytes = 0;
+            e = hipMalloc(&b.p, want);
+        }
+        if (e != hipSuccess) {
+            set_hip_error((int)e);
+            (void)hipGetLastError();
+            *rc = e == hipErrorOutOfMemory ? ALCS_E_ALLOC : ALCS_E_HIP;
+            return nullptr;
+        }
+        P.in_use.emplace(b.p, b);
+        return b.p;
+    } catch (const std::bad_alloc &) {
+        *rc = ALCS_E_ALLOC;
+        return nullptr;
     }
+}
+
+void device_free(void *p) {
+    if (!p) return;
+    Pool &P = pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    auto it = P.in_use.find(p);
+    if (it == P.in_use.end()) return;
+    PoolBlock b = it->second;
+    P.in_use.erase(it);
+    b.settled = false;
+    if (b.bytes > kPoolBytes / 2) { give_back(b); return; }
+    try {
+        P.kept.push_back(b);
+    } catch (const std::bad_alloc &) {
+        give_back(b);
+        return;
+    }
+    P.kept_bytes += b.bytes;
+    while (P.kept.size() > kPoolBlocks || P.kept_bytes > kPoolBytes) {
+        give_back(P.kept.front());
+        P.kept_bytes -= P.kept.front().bytes;
+        P.kept.erase(P.kept.begin());
+    }
+}
+
+void release_device(alcs_packed *p) {
+    device_free(p->dev.blob);
+    device_free(const_cast<uint16_t *>(p->dev.w16));
+    device_free(p->dev.chan_blob);
     p->dev = DeviceCopy();
 }
 
@@ -242,12 +349,9 @@ int upload(alcs_packed *p) {
         total = align256(total + b_off);
     }
     total += 256;
-    void *blob = nullptr;
-    if ((e = hipMalloc(&blob, total)) != hipSuccess) {
-        set_hip_error((int)e);
-        (void)hipGetLastError();
-        return e == hipErrorOutOfMemory ? ALCS_E_ALLOC : ALCS_E_HIP;
-    }
+    int rc_alloc = ALCS_OK;
+    void *blob = device_alloc(total, &rc_alloc);
+    if (!blob) return rc_alloc;
     char *base = (char *)blob;
     auto put = [&](size_t o, const void *src, size_t n) -> hipError_t {
         return n ? hipMemcpy(base + o, src, n, hipMemcpyHostToDevice) : hipSuccess;
@@ -257,7 +361,7 @@ int upload(alcs_packed *p) {
     for (int t = 0; t < L.noff && e == hipSuccess; ++t) e = put(o_off[t], L.off[t].data(), b_off);
     if (e != hipSuccess) {
         set_hip_error((int)e);
-        (void)hipFree(blob);
+        device_free(blob);
         return ALCS_E_HIP;
     }
     int cus = 0, xcds = 0;

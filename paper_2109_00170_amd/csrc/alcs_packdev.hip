@@ -96,13 +96,13 @@ static int check(hipError_t e) {
     return ALCS_E_HIP;
 }
 
-int enqueue_csr_count(const uint8_t *mask_dev, int G, int K, int32_t *row_ptr_dev, hipStream_t st) {
+static int enqueue_csr_count(const uint8_t *mask_dev, int G, int K, int32_t *row_ptr_dev, hipStream_t st) {
     hipLaunchKernelGGL(k_pack_count, dim3(G), dim3(256), 0, st, mask_dev, K, row_ptr_dev);
     hipLaunchKernelGGL(k_pack_scan, dim3(1), dim3(1024), 0, st, row_ptr_dev, G);
     return check(hipGetLastError());
 }
 
-int enqueue_csr_fill(const float *W_dev, const uint8_t *mask_dev, int Cout, int K, int V, int G,
+static int enqueue_csr_fill(const float *W_dev, const uint8_t *mask_dev, int Cout, int K, int V, int G,
                      const int32_t *row_ptr_dev, int32_t *col_idx_dev, float *vals_dev, hipStream_t st) {
     void (*kern)(const float *, const uint8_t *, int, int, const int32_t *, int32_t *, float *) = nullptr;
     switch (V) {

@@ -487,8 +487,8 @@ extern "C" int alcs_packed_add_bf16_weights(alcs_packed_t *p, void *stream) {
     const size_t o_off = align256((size_t)wplane16 * L.planes * sizeof(uint16_t));
     const size_t o_work = align256(o_off + 4 * (size_t)ncol16);
     const size_t total = align256(o_work + sizeof(Work) * (size_t)L.nbundles * L.GS) + 256;
-    void *buf = nullptr;
-    if ((rc = m16::check(hipMalloc(&buf, total))) != ALCS_OK) return rc;
+    void *buf = device_alloc(total, &rc);
+    if (!buf) return rc;
     char *bb = (char *)buf;
     hipStream_t st = (hipStream_t)stream;
     // what no bundle covers (the spare run at the end): zero weights, selector of the zero row
@@ -501,7 +501,7 @@ extern "C" int alcs_packed_add_bf16_weights(alcs_packed_t *p, void *stream) {
         e = hipGetLastError();
     }
     if ((rc = m16::check(e)) != ALCS_OK) {
-        (void)hipFree(buf);
+        device_free(buf);
         return rc;
     }
     p->dev.w16 = (const uint16_t *)(bb + o_w);

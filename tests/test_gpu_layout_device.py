@@ -193,3 +193,28 @@ def test_more_groups_than_the_rank_kernel_takes_go_through_the_host():
     assert float(np.max(np.abs(Y.cpu().numpy() - ref))) <= TOL * float(np.max(np.abs(ref)))
     for h in (host, dev, dev2):
         h.free()
+
+
+def test_freed_blocks_are_reused_safely():
+    """A handle freed while its convolution is still in flight, and handles of slightly different sizes
+    packed into the blocks it leaves: every output stays what a fresh handle gives."""
+    import torch
+    rng = np.random.default_rng(4900)
+    W = torch.from_numpy((rng.standard_normal((256, 256, 1, 1)) * 0.2).astype(np.float32)).cuda()
+    X = torch.from_numpy(rng.standard_normal((16, 256, 28, 28)).astype(np.float32)).cuda()
+    masks = [torch.from_numpy(workloads.mask_exact(64, 256, 1, 0.8 + 0.002 * i, rng)).cuda() for i in range(6)]
+    keep = [alcs.alcs_pack_weights_device(W, m, 4) for m in masks]
+    want, got = [], []
+    for h in keep:
+        Y = torch.empty((16, 256, 28, 28), device="cuda")
+        alcs.alcs_sparse_conv(h, X, None, Y)
+        want.append(Y)
+    for m in masks:
+        h = alcs.alcs_pack_network_device([W], [m], 4)[0]
+        Y = torch.empty((16, 256, 28, 28), device="cuda")
+        alcs.alcs_sparse_conv(h, X, None, Y)
+        h.free()
+        got.append(Y)
+    torch.cuda.synchronize()
+    for a, b in zip(want, got):
+        assert torch.equal(a, b)
