@@ -1,7 +1,13 @@
-"""Argument marshalling for the C ABI declared in include/alcs.h.  No arithmetic here."""
+"""Argument marshalling for the C ABI declared in include/alcs.h.  No arithmetic here.
+
+The launches (convolutions, scores, packing a network) go through ``_launch``, a small extension module
+(csrc/alcs_launch.cpp) that reads the tensors natively; everything that is not called per layer and
+pass goes through ctypes.
+"""
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional
 
@@ -9,7 +15,19 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.environ.get("ALCS_LIBRARY") or os.path.join(_HERE, "libalcs.so")
+_LAUNCH_PATH = os.path.join(_HERE, "_launch.so")
 _lib = None
+
+
+class _Unloaded:
+    """Stands for the launch module until its first use."""
+
+    def __getattr__(self, name):
+        load_library()
+        return getattr(_launch, name)
+
+
+_launch = _Unloaded()
 
 EXPORTS = [
     "alcs_strerror", "alcs_last_hip_error", "alcs_version", "alcs_pack_weights", "alcs_packed_info",
@@ -63,12 +81,13 @@ def library_path() -> str:
 
 def load_library():
     """Load libalcs.so; raise ImportError if it has not been built (no fallback)."""
-    global _lib
+    global _lib, _launch
     if _lib is not None:
         return _lib
-    if not os.path.exists(_LIB_PATH):
-        raise ImportError("%s is missing: build it with `python -m paper_2109_00170_amd.build` "
-                          "(or __graft_entry__.build())" % _LIB_PATH)
+    for path in (_LIB_PATH, _LAUNCH_PATH):
+        if not os.path.exists(path):
+            raise ImportError("%s is missing: build it with `python -m paper_2109_00170_amd.build` "
+                              "(or __graft_entry__.build())" % path)
     # PyTorch ships its own HIP runtime (libamdhip64.so.7 under torch/lib).  It has to be
     # in the process before libalcs.so is loaded, so that both resolve to that one
     # runtime; otherwise two runtimes coexist and streams and the device cannot be shared.
@@ -93,7 +112,13 @@ def load_library():
     lib.alcs_packed_set_options.argtypes = [vp, vp]
     lib.alcs_packed_get_options.argtypes = [vp, vp]
     lib.alcs_last_launch.argtypes = [cip, ci]
-    _lib = lib
+    lib.alcs_select_workspace_bytes.restype = ctypes.c_size_t
+    lib.alcs_pack_workspace_bytes.restype = ctypes.c_longlong
+    spec = importlib.util.spec_from_file_location(__package__ + "._launch", _LAUNCH_PATH)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    mod.connect(AlcsError, {n: ctypes.cast(getattr(lib, n), vp).value for n in EXPORTS})
+    _lib, _launch = lib, mod
     return lib
 
 
@@ -119,12 +144,9 @@ class Packed:
 
     def __init__(self, handle, Cout, Cin, kernel, V):
         self._h = handle
+        self._ptr = handle.value or 0  # what the launch module reads; 0 = freed
         self.Cout, self.Cin, self.kernel, self.V = Cout, Cin, kernel, V
-        G, K, nnzb = ctypes.c_int(), ctypes.c_int(), ctypes.c_int64()
-        rc = load_library().alcs_packed_info(self._h, ctypes.byref(G), ctypes.byref(K), ctypes.byref(nnzb))
-        if rc != 0:
-            raise AlcsError(rc, "alcs_packed_info")
-        self.G, self.K, self.nnzb = G.value, K.value, nnzb.value
+        self.G, self.K, self.nnzb = _launch.packed_info(self._ptr)
 
     @property
     def handle(self):
@@ -178,8 +200,8 @@ class Packed:
 
     def free(self):
         if self._h is not None:
-            load_library().alcs_packed_free(self._h)
-            self._h = None
+            h, self._h, self._ptr = self._h, None, 0
+            load_library().alcs_packed_free(h)
 
     def __del__(self):
         try:
@@ -233,44 +255,25 @@ def _dev_ptr(t, name, dtype_name="torch.float32"):
 def alcs_sparse_conv(packed: Packed, X, bias, Y, stride: int = 1, stream=None, events=None) -> None:
     """Y[N,Cout,Ho,Wo] = sparse_conv(packed, X[N,Cin,H,W]) + bias; device tensors, async on stream.
     events = (start, stop) hipEvent_t handles (ints) routes the call to alcs_sparse_conv_timed."""
+    if events is None:
+        return _launch.sparse_conv(packed, X, bias, None, Y, stride, None, stream)
     N, Cin, H, W = X.shape
     k = packed.kernel
     exp = (N, packed.Cout, out_size(H, k, stride), out_size(W, k, stride))
     if tuple(Y.shape) != exp:
         raise ValueError("Y must have shape %r, got %r" % (exp, tuple(Y.shape)))
-    lib = load_library()
-    if events is None:
-        rc = lib.alcs_sparse_conv(packed.handle, _dev_ptr(X, "X"), _dev_ptr(bias, "bias"), _dev_ptr(Y, "Y"),
-                                  N, Cin, packed.Cout, H, W, k, int(stride), _stream_ptr(stream))
-    else:
-        rc = lib.alcs_sparse_conv_timed(packed.handle, _dev_ptr(X, "X"), _dev_ptr(bias, "bias"),
-                                        _dev_ptr(Y, "Y"), N, Cin, packed.Cout, H, W, k, int(stride),
-                                        _stream_ptr(stream), ctypes.c_void_p(events[0]),
-                                        ctypes.c_void_p(events[1]))
+    rc = load_library().alcs_sparse_conv_timed(
+        packed.handle, _dev_ptr(X, "X"), _dev_ptr(bias, "bias"), _dev_ptr(Y, "Y"), N, Cin, packed.Cout, H, W, k, int(stride),
+        _stream_ptr(stream), ctypes.c_void_p(events[0]), ctypes.c_void_p(events[1]))
     if rc != 0:
         raise AlcsError(rc, "alcs_sparse_conv")
-
-
-ACTIVATIONS = {None: 0, "none": 0, "relu": 1, "relu6": 2}
 
 
 def alcs_sparse_conv_fused(packed: Packed, X, bias, residual, Y, stride: int = 1, activation=None,
                            stream=None) -> None:
     """Y = act(sparse_conv(packed, X) + bias + residual); residual has Y's shape (or is None, or is Y);
     activation is None, "relu", "relu6" or an alcs_activation integer."""
-    N, Cin, H, W = X.shape
-    k = packed.kernel
-    exp = (N, packed.Cout, out_size(H, k, stride), out_size(W, k, stride))
-    if tuple(Y.shape) != exp:
-        raise ValueError("Y must have shape %r, got %r" % (exp, tuple(Y.shape)))
-    if residual is not None and tuple(residual.shape) != exp:
-        raise ValueError("residual must have shape %r, got %r" % (exp, tuple(residual.shape)))
-    act = activation if isinstance(activation, int) else ACTIVATIONS[activation]
-    rc = load_library().alcs_sparse_conv_fused(packed.handle, _dev_ptr(X, "X"), _dev_ptr(bias, "bias"),
-                                               _dev_ptr(residual, "residual"), _dev_ptr(Y, "Y"), N, Cin,
-                                               packed.Cout, H, W, k, int(stride), int(act), _stream_ptr(stream))
-    if rc != 0:
-        raise AlcsError(rc, "alcs_sparse_conv_fused")
+    return _launch.sparse_conv_fused(packed, X, bias, residual, Y, stride, activation, stream)
 
 
 def alcs_sparse_conv_bf16(packed: Packed, X, bias, residual, Y, stride: int = 1, activation=None, stream=None,
@@ -278,26 +281,13 @@ def alcs_sparse_conv_bf16(packed: Packed, X, bias, residual, Y, stride: int = 1,
     """alcs_sparse_conv_fused on torch.bfloat16 tensors X, residual (or None) and Y; bias stays float32.
     mfma16 routes the call to alcs_sparse_conv_bf16_mfma (weights rounded to bfloat16 as well; the
     handle needs Packed.add_bf16_weights() first)."""
-    N, Cin, H, W = X.shape
-    k = packed.kernel
-    exp = (N, packed.Cout, out_size(H, k, stride), out_size(W, k, stride))
-    if tuple(Y.shape) != exp:
-        raise ValueError("Y must have shape %r, got %r" % (exp, tuple(Y.shape)))
-    if residual is not None and tuple(residual.shape) != exp:
-        raise ValueError("residual must have shape %r, got %r" % (exp, tuple(residual.shape)))
-    act = activation if isinstance(activation, int) else ACTIVATIONS[activation]
-    bf = "torch.bfloat16"
-    lib = load_library()
-    fn, name = (lib.alcs_sparse_conv_bf16_mfma, "alcs_sparse_conv_bf16_mfma") if mfma16 else \
-        (lib.alcs_sparse_conv_bf16, "alcs_sparse_conv_bf16")
-    rc = fn(packed.handle, _dev_ptr(X, "X", bf), _dev_ptr(bias, "bias"), _dev_ptr(residual, "residual", bf),
-            _dev_ptr(Y, "Y", bf), N, Cin, packed.Cout, H, W, k, int(stride), int(act), _stream_ptr(stream))
-    if rc != 0:
-        raise AlcsError(rc, name)
+    if mfma16:
+        return _launch.sparse_conv_bf16_mfma(packed, X, bias, residual, Y, stride, activation, stream)
+    return _launch.sparse_conv_bf16(packed, X, bias, residual, Y, stride, activation, stream)
 
 
 def alcs_sparse_conv_bf16_mfma(packed: Packed, X, bias, residual, Y, stride: int = 1, activation=None, stream=None) -> None:
-    alcs_sparse_conv_bf16(packed, X, bias, residual, Y, stride=stride, activation=activation, stream=stream, mfma16=True)
+    return _launch.sparse_conv_bf16_mfma(packed, X, bias, residual, Y, stride, activation, stream)
 
 
 class HipEvents:
@@ -336,61 +326,20 @@ class HipEvents:
 
 def alcs_dense_conv(W_dev, X, bias, Y, stride: int = 1, stream=None) -> None:
     """Dense reference: W_dev [Cout,Cin,k,k] on the device."""
-    Cout, Cin, k, _ = W_dev.shape
-    N, Cin2, H, W = X.shape
-    if Cin != Cin2:
-        raise ValueError("channel mismatch")
-    exp = (N, Cout, out_size(H, k, stride), out_size(W, k, stride))
-    if tuple(Y.shape) != exp:
-        raise ValueError("Y must have shape %r, got %r" % (exp, tuple(Y.shape)))
-    rc = load_library().alcs_dense_conv(_dev_ptr(W_dev, "W"), _dev_ptr(X, "X"), _dev_ptr(bias, "bias"),
-                                        _dev_ptr(Y, "Y"), N, Cin, Cout, H, W, k, int(stride),
-                                        _stream_ptr(stream))
-    if rc != 0:
-        raise AlcsError(rc, "alcs_dense_conv")
-
-
-def _act(activation) -> int:
-    return int(activation if isinstance(activation, int) else ACTIVATIONS[activation])
+    return _launch.dense_conv(W_dev, X, bias, Y, stride, stream)
 
 
 def alcs_depthwise_conv(D_dev, X, bias, Y, stride: int = 1, activation=None, stream=None) -> None:
     """Y = act(depthwise3x3(X; D_dev) + bias): D_dev [C,3,3] on the device."""
-    N, C, H, W = X.shape
-    if tuple(D_dev.shape) != (C, 3, 3):
-        raise ValueError("depthwise weights must have shape %r" % ((C, 3, 3),))
-    exp = (N, C, out_size(H, 3, stride), out_size(W, 3, stride))
-    if tuple(Y.shape) != exp:
-        raise ValueError("Y must have shape %r, got %r" % (exp, tuple(Y.shape)))
-    rc = load_library().alcs_depthwise_conv(_dev_ptr(D_dev, "dw_weights"), _dev_ptr(X, "X"), _dev_ptr(bias, "bias"),
-                                            _dev_ptr(Y, "Y"), N, C, H, W, int(stride), _act(activation),
-                                            _stream_ptr(stream))
-    if rc != 0:
-        raise AlcsError(rc, "alcs_depthwise_conv")
+    return _launch.depthwise_conv(D_dev, X, bias, Y, stride, activation, stream)
 
 
 def alcs_dw_sparse_conv_fused(packed: Packed, D_dev, dw_bias, X, bias, residual, Y, dw_stride: int = 1,
                               dw_activation=None, activation=None, workspace=None, stream=None) -> None:
-    """Y = act(conv1x1(packed; dw_act(depthwise3x3(X; D_dev) + dw_bias)) + bias + residual) in one kernel;
-    ``workspace`` ([N,Cin,Ho,Wo] or None) is used only by layouts the fused kernels do not cover."""
-    N, Cin, H, W = X.shape
-    if tuple(D_dev.shape) != (Cin, 3, 3):
-        raise ValueError("depthwise weights must have shape %r" % ((Cin, 3, 3),))
-    Ho, Wo = out_size(H, 3, dw_stride), out_size(W, 3, dw_stride)
-    exp = (N, packed.Cout, Ho, Wo)
-    if tuple(Y.shape) != exp:
-        raise ValueError("Y must have shape %r, got %r" % (exp, tuple(Y.shape)))
-    if residual is not None and tuple(residual.shape) != exp:
-        raise ValueError("residual must have shape %r, got %r" % (exp, tuple(residual.shape)))
-    if workspace is not None and tuple(workspace.shape) != (N, Cin, Ho, Wo):
-        raise ValueError("workspace must have shape %r" % ((N, Cin, Ho, Wo),))
-    rc = load_library().alcs_dw_sparse_conv_fused(
-        packed.handle, _dev_ptr(D_dev, "dw_weights"), _dev_ptr(dw_bias, "dw_bias"), int(dw_stride),
-        _act(dw_activation), _dev_ptr(X, "X"), _dev_ptr(bias, "bias"), _dev_ptr(residual, "residual"),
-        _dev_ptr(Y, "Y"), _dev_ptr(workspace, "workspace"), N, Cin, packed.Cout, H, W, _act(activation),
-        _stream_ptr(stream))
-    if rc != 0:
-        raise AlcsError(rc, "alcs_dw_sparse_conv_fused")
+    """Y = act(conv1x1(packed; dw_act(depthwise3x3(X; D_dev) + dw_bias)) + bias + residual); ``workspace``
+    ([N,Cin,Ho,Wo] or None) holds the depthwise layer's output where the two layers run one after the other."""
+    return _launch.dw_sparse_conv_fused(packed, D_dev, dw_bias, X, bias, residual, Y, dw_stride, dw_activation, activation,
+                                        workspace, stream)
 
 
 def alcs_last_launch() -> dict:
@@ -445,25 +394,18 @@ def alcs_network_latency(tau, tables, nnz) -> float:
 def alcs_block_scores(W_dev, V: int, scores=None, stream=None):
     """Squared L2 norm of every block of V weights: W_dev [Cout,Cin,k,k] on the device ->
     float32 tensor [ceil(Cout/V), Cin, k, k] (allocated here unless ``scores`` is given)."""
-    import torch
-    Cout, Cin, k, _ = W_dev.shape
-    G = (Cout + V - 1) // V
     if scores is None:
+        import torch
+        Cout, Cin, k, _ = W_dev.shape
+        G = (Cout + V - 1) // V
         scores = torch.empty((G, Cin, k, k), dtype=torch.float32, device=W_dev.device)
-    if tuple(scores.shape) != (G, Cin, k, k):
-        raise ValueError("scores must have shape %r" % ((G, Cin, k, k),))
-    rc = load_library().alcs_block_scores(_dev_ptr(W_dev, "W"), Cout, Cin, k, int(V), _dev_ptr(scores, "scores"),
-                                          _stream_ptr(stream))
-    if rc != 0:
-        raise AlcsError(rc, "alcs_block_scores")
+    _launch.block_scores(W_dev, V, scores, stream)
     return scores
 
 
 def _select_workspace(n_seg, device):
     import torch
-    lib = load_library()
-    lib.alcs_select_workspace_bytes.restype = ctypes.c_size_t
-    nbytes = int(lib.alcs_select_workspace_bytes(int(n_seg)))
+    nbytes = int(load_library().alcs_select_workspace_bytes(int(n_seg)))
     return torch.empty(((nbytes + 7) // 8,), dtype=torch.int64, device=device)
 
 
@@ -516,10 +458,8 @@ def alcs_project_latency(scores, seg_starts, V_per_layer, tables, tau, budget, e
     if len(V_per_layer) != L or len(tables) != L:
         raise ValueError("one group size and one table per layer")
     Vs = np.ascontiguousarray(V_per_layer, dtype=np.int32)
-    ks = [_f64(k) for k, _ in tables]
-    ts = [_f64(t) for _, t in tables]
-    nn = np.array([k.size for k in ks], dtype=np.int32)
-    kk, tt = _f64(np.concatenate(ks)), _f64(np.concatenate(ts))
+    nn = np.array([len(k) for k, _ in tables], dtype=np.int32)
+    kk, tt = (np.concatenate([e[i] for e in tables], dtype=np.float64) for i in (0, 1))
     n = int(scores.numel())
     ws = _select_workspace(L, scores.device)
     mask = torch.empty((n,), dtype=torch.uint8, device=scores.device) if want_mask else None
@@ -642,9 +582,7 @@ def _layer_descs(Ws, masks, Vs, options):
 
 def alcs_pack_workspace_bytes(Ws, masks, Vs, options=None) -> int:
     descs, _keep, _ = _layer_descs(Ws, masks, Vs, options)
-    lib = load_library()
-    lib.alcs_pack_workspace_bytes.restype = ctypes.c_longlong
-    n = int(lib.alcs_pack_workspace_bytes(descs, len(Ws)))
+    n = int(load_library().alcs_pack_workspace_bytes(descs, len(Ws)))
     if n < 0:
         raise AlcsError(n, "alcs_pack_workspace_bytes")
     return n
@@ -653,16 +591,12 @@ def alcs_pack_workspace_bytes(Ws, masks, Vs, options=None) -> int:
 def alcs_pack_network_device(Ws, masks, Vs, options=None, workspace=None, stream=None):
     """Handles for a list of layers (device weights [Cout,Cin,k,k], device flags or None each) in one
     call; workspace: a uint8 device tensor of alcs_pack_workspace_bytes bytes, or None."""
-    descs, _keep, Vs = _layer_descs(Ws, masks, Vs, options)
     n = len(Ws)
-    out = (ctypes.c_void_p * n)()
-    ws_ptr, ws_bytes = None, 0
-    if workspace is not None:
-        ws_ptr, ws_bytes = _dev_ptr(workspace, "workspace", "torch.uint8"), workspace.numel()
-    rc = load_library().alcs_pack_network_device(descs, n, ws_ptr, ctypes.c_longlong(ws_bytes), _stream_ptr(stream), out)
-    if rc != 0:
-        raise AlcsError(rc, "alcs_pack_network_device")
-    return [Packed(ctypes.c_void_p(out[i]), W.shape[0], W.shape[1], W.shape[2], Vs[i]) for i, W in enumerate(Ws)]
+    Vs = [int(Vs)] * n if np.isscalar(Vs) else list(Vs)
+    opts = [Options.make(o) for o in (options if isinstance(options, (list, tuple)) else [options] * n)]
+    made = _launch.pack_network(list(Ws), list(masks), Vs, [0 if o is None else ctypes.addressof(o) for o in opts], workspace,
+                                stream)
+    return [Packed(ctypes.c_void_p(p), Cout, Cin, k, V) for p, Cout, Cin, k, V in made]
 
 
 def alcs_pack_on_device(W_dev, mask_dev, V: int, options=None) -> Packed:

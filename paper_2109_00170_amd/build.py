@@ -1,4 +1,5 @@
-"""Builds libalcs.so (HIP, gfx950) in-tree with hipcc.  Run as a script or call build()."""
+"""Builds libalcs.so (HIP, gfx950, hipcc) and _launch.so (the Python entry of the launches, g++ against
+PyTorch's headers) in-tree.  Run as a script or call build()."""
 from __future__ import annotations
 
 import os
@@ -17,9 +18,29 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Wall", "-Wno-u
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
+LAUNCH_LIB = os.path.join(HERE, "_launch.so")
+
+
+def launch_command(out: str):
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+            "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+            "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+            "-I", CSRC, os.path.join(CSRC, "alcs_launch.cpp"), "-o", out, "-L", os.path.join(t, "lib"),
+            "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build(verbose: bool = False) -> str:
     objs = []
-    procs = []
+    launch_tmp = LAUNCH_LIB + ".tmp%d" % os.getpid()
+    cmd = launch_command(launch_tmp)
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    procs = [("alcs_launch.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT))]
     for src in SOURCES:
         obj = os.path.join(CSRC, os.path.splitext(src)[0] + ".o")
         cmd = ["hipcc", "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj] + FLAGS
@@ -39,10 +60,11 @@ def build(verbose: bool = False) -> str:
         elif verbose and text.strip():
             print(text)
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("the build failed")
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.check_call(["hipcc", "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs)
     os.replace(tmp, LIB)
+    os.replace(launch_tmp, LAUNCH_LIB)
     return LIB
 
 
