@@ -41,11 +41,12 @@ def kernel_symbol(L, info):
     """Name of the kernel template instance a launch used, as rocprofv3 prints it."""
     b = lambda x: "true" if x else "false"
     mf = info["path"] == 2
-    vec = L.stride == 1 and (L.Ho * L.Wo) % 4 == 0
+    P = L.Ho * L.Wo   # the kernels' Access template argument: 0 aligned, 1 unaligned, 2 strided, 3 rows
+    ac = (0 if P % 4 == 0 else 1 if P >= 4 else 3 if P == 1 else 2) if L.stride == 1 else 2
     if info["mode"] == 1:
-        return "alcs::k_pw_resident<%d, %d, %s, %s, %d>" % (L.V, info["pv"], b(mf), b(vec), info["group_slots"])
+        return "alcs::k_pw_resident<%d, %d, %s, %d, %d>" % (L.V, info["pv"], b(mf), ac, info["group_slots"])
     if info["mode"] == 2:
-        return "alcs::k_pw_chunked<%d, %d, 4, %s, %s>" % (L.V, info["pv"], b(mf), b(vec))
+        return "alcs::k_pw_chunked<%d, %d, 4, %s, %d>" % (L.V, info["pv"], b(mf), ac)
     if info["mode"] in (3, 7):
         return "alcs::k_conv3<%d, %d" % (L.V, L.stride)          # prefix: tile shape and flags follow
     if info["mode"] == 5:

@@ -82,6 +82,9 @@ constexpr bool kDw = ALCS_DW_STAGE != 0;
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef int i4 __attribute__((ext_vector_type(4)));
+// The same vectors at element alignment: the hardware moves 8 and 16 bytes from and to any address.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
 
 // Element type of X, the residual and Y in memory, and 1 / 2 / 4 consecutive elements of it
 // as floats.  bfloat16 is the upper half of a float: widening is a shift, narrowing rounds to
@@ -89,6 +92,8 @@ typedef int i4 __attribute__((ext_vector_type(4)));
 #if ALCS_IO_BF16
 typedef unsigned short io_t;
 typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+typedef unsigned int u2u __attribute__((ext_vector_type(2), aligned(2)));
+typedef unsigned int u1u __attribute__((aligned(2)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float io_load1(const io_t *p) { return __builtin_bit_cast(float, (unsigned int)*p << 16); }
 __device__ __forceinline__ f2 io_load2(const io_t *p) {
@@ -99,6 +104,15 @@ __device__ __forceinline__ f4 io_load4(const io_t *p) {
     const u2v u = *reinterpret_cast<const u2v *>(p);
     return f4{__builtin_bit_cast(float, u.x << 16), __builtin_bit_cast(float, u.x & 0xffff0000u),
               __builtin_bit_cast(float, u.y << 16), __builtin_bit_cast(float, u.y & 0xffff0000u)};
+}
+__device__ __forceinline__ f4 io_load4u(const io_t *p) {
+    const u2u u = *reinterpret_cast<const u2u *>(p);
+    return f4{__builtin_bit_cast(float, u.x << 16), __builtin_bit_cast(float, u.x & 0xffff0000u),
+              __builtin_bit_cast(float, u.y << 16), __builtin_bit_cast(float, u.y & 0xffff0000u)};
+}
+__device__ __forceinline__ f2 io_load2u(const io_t *p) {
+    const unsigned int u = *reinterpret_cast<const u1u *>(p);
+    return f2{__builtin_bit_cast(float, u << 16), __builtin_bit_cast(float, u & 0xffff0000u)};
 }
 __device__ __forceinline__ unsigned int pack_bf2(float a, float b) {
     return __builtin_bit_cast(unsigned int, __builtin_convertvector(f2{a, b}, bf2));
@@ -112,6 +126,12 @@ __device__ __forceinline__ void io_store2(io_t *p, f2 v) {
 __device__ __forceinline__ void io_store4(io_t *p, f4 v) {
     __builtin_nontemporal_store(u2v{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])}, reinterpret_cast<u2v *>(p));
 }
+__device__ __forceinline__ void io_store2u(io_t *p, f2 v) {
+    __builtin_nontemporal_store(pack_bf2(v[0], v[1]), reinterpret_cast<u1u *>(p));
+}
+__device__ __forceinline__ void io_store4u(io_t *p, f4 v) {
+    __builtin_nontemporal_store((u2u){pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])}, reinterpret_cast<u2u *>(p));
+}
 #else
 typedef float io_t;
 __device__ __forceinline__ float io_load1(const io_t *p) { return *p; }
@@ -120,7 +140,21 @@ __device__ __forceinline__ f4 io_load4(const io_t *p) { return *reinterpret_cast
 __device__ __forceinline__ void io_store1(io_t *p, float v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ void io_store2(io_t *p, f2 v) { __builtin_nontemporal_store(v, reinterpret_cast<f2 *>(p)); }
 __device__ __forceinline__ void io_store4(io_t *p, f4 v) { __builtin_nontemporal_store(v, reinterpret_cast<f4 *>(p)); }
+__device__ __forceinline__ f4 io_load4u(const io_t *p) { return *reinterpret_cast<const f4u *>(p); }
+__device__ __forceinline__ f2 io_load2u(const io_t *p) { return *reinterpret_cast<const f2u *>(p); }
+__device__ __forceinline__ void io_store2u(io_t *p, f2 v) { __builtin_nontemporal_store((f2u)v, reinterpret_cast<f2u *>(p)); }
+__device__ __forceinline__ void io_store4u(io_t *p, f4 v) { __builtin_nontemporal_store((f4u)v, reinterpret_cast<f4u *>(p)); }
 #endif
+
+// How a kernel reaches the pixels of its tile in memory (a choice of the launcher, by the shape):
+//   kAligned    stride 1, pixels per image a multiple of 4: four neighbours are 16 bytes, aligned
+//   kUnaligned  stride 1, any other image of at least 4 pixels: 16 bytes at any address, and a quad
+//               may run from one image into the next
+//   kStrided    stride 2, or images of fewer than 4 pixels: one pixel at a time
+//   kRows       images of one pixel (a fully connected layer): the channels of a pixel are the
+//               contiguous axis, read 16 bytes at a time and transposed on the way into LDS
+//   kScattered  stores only: a lane's pixels lie in different rows (3x3 kernels)
+enum Access { kAligned = 0, kUnaligned = 1, kStrided = 2, kRows = 3, kScattered = 4 };
 // An ordinary (write-back) store of two elements: for runs that cover cache lines only in part and
 // whose neighbours are written soon after by the same workgroup, so that the L2 merges them into
 // whole lines before they leave for memory.
@@ -147,6 +181,7 @@ struct ConvArgs {
     int tile_px;        // resident 1x1 kernels: pixels of the flattened axis per workgroup (<= tile width)
     int G, nchunks, KC;
     int npt, ngt, gpt;  // pixel tiles, group tiles, groups per group tile
+    int ksplit;         // split kernel: wavefronts that share a bundle
     int tiles_x, tiles_y;  // 3x3: output tiles per image
     int wg_per_xcd, total_wgs, xcds;
     int ppw;            // streaming kernel: flattened pixels per workgroup (multiple of 4)
@@ -538,23 +573,13 @@ __device__ __forceinline__ void mac_segment(const ConvArgs &a, int start, int cn
 // ------------------------------------------------------------------ 1x1: staging
 
 // Rows [c0, c1) of the pixel tile [q0, q0 + TP) of the flattened (n, pixel) axis into
-// LDS rows 0.. (row length TP).  VEC: stride 1 and P % 4 == 0, so four consecutive
-// pixels never straddle an image and are 16-byte aligned.
-// Place of the tile's e-th pixel in an LDS row.  SPLIT (two pixels per lane without the
-// vector form, where a pair of neighbours may straddle two images): a lane owns pixels
-// e and e + TP/2, stored side by side so that one 8-byte read fetches both, and a store
-// instruction still writes a contiguous run of pixels.
-template <int TP, bool SPLIT>
-__device__ __forceinline__ int tile_pos(int e) {
-    if constexpr (SPLIT) return (e % (TP / 2)) * 2 + e / (TP / 2);
-    return e;
-}
-
-template <int TP, bool VEC, bool SPLIT = false>
+// LDS rows 0.. (row length TP).  Pixels at or beyond q_end are not stored by anyone: what their
+// places hold does not matter.
+template <int TP, int AC>
 __device__ __forceinline__ void stage_pw(const ConvArgs &a, float *lds, int q0, int c0, int c1, int q_end) {
-    static_assert(!(VEC && SPLIT), "the vector form keeps neighbouring pixels together");
     const int tid = threadIdx.x, nt = blockDim.x;
-    if constexpr (VEC) {
+    const int rows = c1 - c0;
+    if constexpr (AC == kAligned) {
         constexpr int NQ = TP / 4;
         const int quad = tid % NQ, r0 = tid / NQ, rpp = nt / NQ;
         const int q = q0 + quad * 4;
@@ -563,7 +588,6 @@ __device__ __forceinline__ void stage_pw(const ConvArgs &a, float *lds, int q0, 
         const int p = valid ? q - n * a.P : 0;
         const io_t *src = a.X + ((size_t)n * a.Cin + c0) * a.P + p;
         float *dst = lds + quad * 4;
-        const int rows = c1 - c0;
         constexpr int U = 8;  // independent 16-byte loads in flight per thread
         int r = r0;
         for (; r + (U - 1) * rpp < rows; r += U * rpp) {
@@ -581,6 +605,93 @@ __device__ __forceinline__ void stage_pw(const ConvArgs &a, float *lds, int q0, 
             if (valid) v0 = io_load4(src + (size_t)r * a.P);
             *reinterpret_cast<f4 *>(dst + r * TP) = v0;
         }
+    } else if constexpr (AC == kUnaligned) {
+        constexpr int NQ = TP / 4;
+        const int quad = tid % NQ, r0 = tid / NQ, rpp = nt / NQ;
+        const int q = q0 + quad * 4;
+        const bool valid = q < q_end;
+        const int n = valid ? q / a.P : 0;
+        const int p = valid ? q - n * a.P : 0;
+        // A quad that runs into the next image reads 16 bytes on either side of the seam (the words it
+        // does not take belong to the neighbouring planes) and selects; in the last image nothing lies
+        // behind the seam, and the quad reads the plane's last 16 bytes and shifts.  All loads are
+        // unconditional, from an address that is valid for every lane.
+        const bool seam = valid && p + 4 > a.P;
+        const bool last = seam && n + 1 >= a.N, both = seam && !last;
+        const int keep = a.P - p;  // words before the seam
+        const io_t *src = a.X + ((size_t)n * a.Cin + c0) * a.P + (last ? a.P - 4 : p);
+        const io_t *next = a.X + (((size_t)n + (both ? 1 : 0)) * a.Cin + c0) * a.P + (both ? p - a.P : 0);
+        float *dst = lds + quad * 4;
+        auto some = [&](auto count, int r) {
+            constexpr int U = decltype(count)::value;
+            f4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = io_load4u(src + (size_t)(r + u * rpp) * a.P);
+            if (both) {
+                f4 w[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) w[u] = io_load4u(next + (size_t)(r + u * rpp) * a.P);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    v[u][1] = keep <= 1 ? w[u][1] : v[u][1];
+                    v[u][2] = keep <= 2 ? w[u][2] : v[u][2];
+                    v[u][3] = w[u][3];
+                }
+            }
+            if (last) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const f4 t = v[u];
+                    v[u][0] = keep == 3 ? t[1] : keep == 2 ? t[2] : t[3];
+                    v[u][1] = keep == 3 ? t[2] : t[3];
+                    v[u][2] = t[3];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) *reinterpret_cast<f4 *>(dst + (r + u * rpp) * TP) = v[u];
+        };
+        int r = r0;
+        for (; r + 3 * rpp < rows; r += 4 * rpp) some(std::integral_constant<int, 4>{}, r);
+        for (; r < rows; r += rpp) some(std::integral_constant<int, 1>{}, r);
+    } else if constexpr (AC == kRows) {
+        // A wavefront takes 16 pixels x 16 channels at a time: lane = (pixel, quad of channels), so that
+        // a pixel's 64 bytes are read together.  The four words of a lane go to four rows; lane quads
+        // start with different ones, which puts the 64 words of a write on different banks.
+        static_assert(TP % 16 == 0, "16 pixels at a time");
+        const int lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
+        const int e16 = lane & 15, cq = lane >> 4;
+        constexpr int PG = TP / 16;
+        const int items = PG * ((rows + 15) / 16);
+        constexpr int U = 4;
+#pragma clang loop unroll(disable)
+        for (int i0 = wave; i0 < items; i0 += U * nw) {
+            f4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int it = i0 + u * nw;
+                const int e = (it % PG) * 16 + e16, c = (it / PG) * 16 + cq * 4;
+                v[u] = f4{0, 0, 0, 0};
+                if (it < items && q0 + e < q_end) {
+                    const io_t *src = a.X + (size_t)(q0 + e) * a.Cin + c0 + c;
+                    if (c + 4 <= rows) v[u] = io_load4u(src);
+                    else
+                        for (int i = 0; i < 3; ++i)
+                            if (c + i < rows) v[u][i] = io_load1(src + i);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int it = i0 + u * nw;
+                const int e = (it % PG) * 16 + e16, c = (it / PG) * 16 + cq * 4;
+                if (it >= items) continue;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int k = (i + cq) & 3;
+                    const float x = k == 0 ? v[u][0] : k == 1 ? v[u][1] : k == 2 ? v[u][2] : v[u][3];
+                    if (c + k < rows) lds[(c + k) * TP + e] = x;
+                }
+            }
+        }
     } else {
         const int e = tid % TP, r0 = tid / TP, rpp = nt / TP;
         const int q = q0 + e;
@@ -589,7 +700,6 @@ __device__ __forceinline__ void stage_pw(const ConvArgs &a, float *lds, int q0, 
         const int po = valid ? q - n * a.P : 0;
         const int ho = po / a.Wo, wo = po - ho * a.Wo;
         const io_t *src = a.X + ((size_t)n * a.Cin + c0) * a.Pin + (size_t)(ho * a.stride) * a.W + wo * a.stride;
-        const int rows = c1 - c0;
         constexpr int U = 16;  // independent 4-byte loads in flight per thread
         int r = r0;
         for (; r + (U - 1) * rpp < rows; r += U * rpp) {
@@ -597,9 +707,9 @@ __device__ __forceinline__ void stage_pw(const ConvArgs &a, float *lds, int q0, 
 #pragma unroll
             for (int u = 0; u < U; ++u) v[u] = valid ? io_load1(src + (size_t)(r + u * rpp) * a.Pin) : 0.f;
 #pragma unroll
-            for (int u = 0; u < U; ++u) lds[(r + u * rpp) * TP + tile_pos<TP, SPLIT>(e)] = v[u];
+            for (int u = 0; u < U; ++u) lds[(r + u * rpp) * TP + e] = v[u];
         }
-        for (; r < rows; r += rpp) lds[r * TP + tile_pos<TP, SPLIT>(e)] = valid ? io_load1(src + (size_t)r * a.Pin) : 0.f;
+        for (; r < rows; r += rpp) lds[r * TP + e] = valid ? io_load1(src + (size_t)r * a.Pin) : 0.f;
     }
 }
 
@@ -611,7 +721,7 @@ __device__ __forceinline__ void stage_pw(const ConvArgs &a, float *lds, int q0, 
 // thread owns one pixel of the tile and every (blockDim / TP)-th channel.  With TP >= 64 a
 // wavefront works on one channel at a time, so the filter and the bias come through scalar
 // loads.
-template <int TP, int MODE, bool SPLIT>
+template <int TP, int MODE>
 __device__ __forceinline__ void stage_dw_mode(const ConvArgs &a, float *lds, int q0, int q_end) {
     constexpr int SPAN = TP < 64 ? TP : 64;
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
@@ -642,7 +752,7 @@ __device__ __forceinline__ void stage_dw_mode(const ConvArgs &a, float *lds, int
             float acc = taps.apply(x, wts + c * 9, a.dw_bias ? bs[c] : 0.f);
             if (a.dw_act >= 1) acc = fmaxf(acc, 0.f);
             if (a.dw_act == 2) acc = fminf(acc, 6.f);
-            lds[c * TP + tile_pos<TP, SPLIT>(e)] = valid ? acc : 0.f;
+            lds[c * TP + e] = valid ? acc : 0.f;
         };
         int c = r0;  // the lane's channel; c - rl is wave-uniform
         // two channels' loads in flight (one on the narrow tiles, whose kernels hold the
@@ -662,10 +772,10 @@ __device__ __forceinline__ void stage_dw_mode(const ConvArgs &a, float *lds, int
     }
 }
 
-template <int TP, bool SPLIT>
+template <int TP>
 __device__ __forceinline__ void stage_dw(const ConvArgs &a, float *lds, int q0, int q_end) {
-    if (a.dw_mode == kDwPair) stage_dw_mode<TP, kDwPair, SPLIT>(a, lds, q0, q_end);
-    else stage_dw_mode<TP, kDwNine, SPLIT>(a, lds, q0, q_end);
+    if (a.dw_mode == kDwPair) stage_dw_mode<TP, kDwPair>(a, lds, q0, q_end);
+    else stage_dw_mode<TP, kDwNine>(a, lds, q0, q_end);
 }
 #endif
 
@@ -676,15 +786,16 @@ struct PixOut {
     bool valid[PV];
 };
 
-// PSTRIDE > 0: the lane's pixels are PSTRIDE apart (see tile_pos), else neighbours.
-template <int PV, bool VEC, int PSTRIDE = 0>
+template <int PV, int AC>
 __device__ __forceinline__ void pix_out(const ConvArgs &a, int q0, int lane, PixOut<PV> &px, int q_end) {
 #pragma unroll
     for (int pv = 0; pv < PV; ++pv) {
-        const int q = PSTRIDE > 0 ? q0 + lane + pv * PSTRIDE : q0 + lane * PV + pv;
+        const int q = q0 + lane * PV + pv;
         px.valid[pv] = q < q_end;
-        if (VEC && pv > 0) {
+        if (AC == kAligned && pv > 0) {
             px.yoff[pv] = px.yoff[0] + pv;
+        } else if (AC == kRows) {
+            px.yoff[pv] = px.valid[pv] ? (long long)q * a.Cout : 0;
         } else {
             const int n = px.valid[pv] ? q / a.P : 0;
             const int p = px.valid[pv] ? q - n * a.P : 0;
@@ -692,100 +803,137 @@ __device__ __forceinline__ void pix_out(const ConvArgs &a, int q0, int lane, Pix
         }
     }
 }
+// Whether the lane's pixels are neighbours in memory and all there: they move as one.
+template <int PV, int AC>
+__device__ __forceinline__ bool together(const PixOut<PV> &px) {
+    if constexpr (PV == 1 || AC == kScattered || AC == kRows) return false;
+    if constexpr (AC == kAligned) return px.valid[0];
+    return px.valid[PV - 1] && px.yoff[PV - 1] == px.yoff[0] + (PV - 1);
+}
 
-// The residual of one group for the lane's pixels, fetched before the group is multiplied
-// (a load issued in the epilogue would be waited for at once).
+// One channel of the lane's pixels: from p (the channel's plane), to p.
+template <int PV, int AC>
+__device__ __forceinline__ void load_pixels(const io_t *p, const PixOut<PV> &px, float (&x)[PV]) {
+    if constexpr (PV > 1 && AC != kScattered && AC != kRows) {
+        if (together<PV, AC>(px)) {
+            if constexpr (PV == 4) {
+                const f4 t = AC == kAligned ? io_load4(p + px.yoff[0]) : io_load4u(p + px.yoff[0]);
+                x[0] = t[0]; x[1] = t[1]; x[2] = t[2]; x[3] = t[3];
+            } else {
+                const f2 t = AC == kAligned ? io_load2(p + px.yoff[0]) : io_load2u(p + px.yoff[0]);
+                x[0] = t[0]; x[1] = t[1];
+            }
+            return;
+        }
+        if constexpr (AC == kAligned) return;
+    }
+#pragma unroll
+    for (int pv = 0; pv < PV; ++pv)
+        if (px.valid[pv]) x[pv] = io_load1(p + px.yoff[pv]);
+}
+template <int PV, int AC, bool CACHED = false>
+__device__ __forceinline__ void store_pixels(io_t *p, const PixOut<PV> &px, const float (&x)[PV]) {
+    if constexpr (PV > 1 && AC != kScattered && AC != kRows) {
+        if (together<PV, AC>(px)) {
+            if constexpr (PV == 4) {
+                if constexpr (AC == kAligned) io_store4(p + px.yoff[0], f4{x[0], x[1], x[2], x[3]});
+                else io_store4u(p + px.yoff[0], f4{x[0], x[1], x[2], x[3]});
+            } else {
+                if constexpr (CACHED) io_store2_cached(p + px.yoff[0], f2{x[0], x[1]});
+                else if constexpr (AC == kAligned) io_store2(p + px.yoff[0], f2{x[0], x[1]});
+                else io_store2u(p + px.yoff[0], f2{x[0], x[1]});
+            }
+            return;
+        }
+        if constexpr (AC == kAligned) return;
+    }
+#pragma unroll
+    for (int pv = 0; pv < PV; ++pv)
+        if (px.valid[pv]) io_store1(p + px.yoff[pv], x[pv]);
+}
+
+// The residual of one group for the lane's pixels: fetched before the group is multiplied where the
+// registers allow it (at most 16 values; a load in the epilogue is waited for at once), else for a
+// few channels at a time ahead of their stores - the residual may be Y itself, so the compiler cannot
+// move a channel's load over the previous channel's store, and one round trip per channel is what
+// such an epilogue would take.
+enum Residual { kNone = 0, kAhead = 1, kBehind = 2 };
 template <int V, int PV>
 struct Resid {
     float r[V][PV];
 };
-template <int V, int PV, bool VEC>
-__device__ __forceinline__ void load_residual(const ConvArgs &a, int g, const PixOut<PV> &px, Resid<V, PV> &rr) {
+constexpr int res_batch(int V, int PV) { return V * PV <= 8 ? V : 8 / PV; }
+// B channels from v0 on
+template <int V, int PV, int AC, int B>
+__device__ __forceinline__ void load_residual(const ConvArgs &a, int g, int v0, const PixOut<PV> &px, Resid<B, PV> &rr) {
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-        const int ch = g * V + v;
+    for (int v = 0; v < B; ++v) {
 #pragma unroll
         for (int pv = 0; pv < PV; ++pv) rr.r[v][pv] = 0.f;
-        if (ch >= a.Cout) continue;
-        const io_t *res = a.residual + (size_t)ch * a.P;
-        if constexpr (VEC && PV == 4) {
-            if (px.valid[0]) {
-                const f4 t = io_load4(res + px.yoff[0]);
-                rr.r[v][0] = t[0]; rr.r[v][1] = t[1]; rr.r[v][2] = t[2]; rr.r[v][3] = t[3];
-            }
-        } else if constexpr (VEC && PV == 2) {
-            if (px.valid[0]) {
-                const f2 t = io_load2(res + px.yoff[0]);
-                rr.r[v][0] = t[0]; rr.r[v][1] = t[1];
-            }
-        } else {
+        if (g >= 0 && g * V + v0 + v < a.Cout) load_pixels<PV, AC>(a.residual + (size_t)(g * V + v0 + v) * a.P, px, rr.r[v]);
+    }
+}
+
+// Channels of a pixel are neighbours in memory (kRows): quads of them move as one.
+template <int V, int PV, class F>
+__device__ __forceinline__ void store_rows(const ConvArgs &a, int first, const PixOut<PV> &px, F &&value) {
 #pragma unroll
-            for (int pv = 0; pv < PV; ++pv)
-                if (px.valid[pv]) rr.r[v][pv] = io_load1(res + px.yoff[pv]);
+    for (int pv = 0; pv < PV; ++pv) {
+        if (!px.valid[pv]) continue;
+        io_t *dst = a.Y + px.yoff[pv] + first;
+#pragma unroll
+        for (int v0 = 0; v0 < V; v0 += 4) {
+            if (V >= 4 && first + v0 + 4 <= a.Cout) {
+                io_store4u(dst + v0, f4{value(v0, pv), value(v0 + 1 < V ? v0 + 1 : 0, pv), value(v0 + 2 < V ? v0 + 2 : 0, pv),
+                                        value(v0 + 3 < V ? v0 + 3 : 0, pv)});
+            } else {
+#pragma unroll
+                for (int i = 0; i < (V < 4 ? V : 4); ++i)
+                    if (first + v0 + i < a.Cout) io_store1(dst + v0 + i, value(v0 + i, pv));
+            }
         }
     }
 }
 
 // Epilogue: Y = acc + bias for the V channels of group g (rows beyond Cout of a
-// ragged last group are not stored).
-template <int V, int PV, bool MF, bool VEC>
+// ragged last group are not stored).  Y is written once and not read again by this kernel: streaming
+// (non-temporal) stores.
+template <int V, int PV, bool MF, int AC, int RES>
 __device__ __forceinline__ void store_group(const ConvArgs &a, const Acc<V, PV, MF> &acc, int g,
-                                            const PixOut<PV> &px, const Resid<V, PV> *pre = nullptr) {
+                                            const PixOut<PV> &px, Resid<RES == kAhead ? V : 1, PV> &ahead) {
+    constexpr int B = RES == kBehind ? res_batch(V, PV) : V;
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-        const int ch = g * V + v;
-        if (ch >= a.Cout) break;
-        float b = a.bias ? as_const(a.bias)[ch] : 0.f;
-        io_t *dst = a.Y + (size_t)ch * a.P;
-        // the residual: already in registers (pre), or read here
-        const io_t *res = (residual_of(a) && !pre) ? residual_of(a) + (size_t)ch * a.P : nullptr;  // wave-uniform
-        if (kFused && pre) {
-            if constexpr (VEC && PV == 4) {
-                if (px.valid[0]) {
-                    f4 o = f4{acc.get(v, 0) + b + pre->r[v][0], acc.get(v, 1) + b + pre->r[v][1],
-                              acc.get(v, 2) + b + pre->r[v][2], acc.get(v, 3) + b + pre->r[v][3]};
-                    if (kFused && a.act) o = f4{activate(a, o[0]), activate(a, o[1]), activate(a, o[2]), activate(a, o[3])};
-                    io_store4(dst + px.yoff[0], o);
-                }
-            } else if constexpr (VEC && PV == 2) {
-                if (px.valid[0]) {
-                    f2 o = f2{acc.get(v, 0) + b + pre->r[v][0], acc.get(v, 1) + b + pre->r[v][1]};
-                    if (kFused && a.act) o = f2{activate(a, o[0]), activate(a, o[1])};
-                    io_store2(dst + px.yoff[0], o);
-                }
-            } else {
-#pragma unroll
-                for (int pv = 0; pv < PV; ++pv)
-                    if (px.valid[pv])
-                        io_store1(dst + px.yoff[pv], activate(a, acc.get(v, pv) + b + pre->r[v][pv]));
-            }
-            continue;
-        }
-        // Y is written once and not read again by this kernel: streaming (non-temporal) stores
-        if constexpr (VEC && PV == 4) {
-            if (px.valid[0]) {
-                f4 o = f4{acc.get(v, 0) + b, acc.get(v, 1) + b, acc.get(v, 2) + b, acc.get(v, 3) + b};
-                if (res) o += io_load4(res + px.yoff[0]);
-                if (kFused && a.act) o = f4{activate(a, o[0]), activate(a, o[1]), activate(a, o[2]), activate(a, o[3])};
-                io_store4(dst + px.yoff[0], o);
-            }
-        } else if constexpr (VEC && PV == 2) {
-            if (px.valid[0]) {
-                f2 o = f2{acc.get(v, 0) + b, acc.get(v, 1) + b};
-                if (res) o += io_load2(res + px.yoff[0]);
-                if (kFused && a.act) o = f2{activate(a, o[0]), activate(a, o[1])};
-                io_store2(dst + px.yoff[0], o);
-            }
+    for (int v0 = 0; v0 < V; v0 += B) {
+        Resid<RES == kBehind ? B : 1, PV> behind;
+        if constexpr (RES == kBehind) load_residual<V, PV, AC, B>(a, g, v0, px, behind);
+        auto value = [&](int v, int pv) __attribute__((always_inline)) {  // v counts from v0
+            const int ch = g * V + v0 + v;
+            float o = acc.get(v0 + v, pv) + (a.bias && ch < a.Cout ? as_const(a.bias)[ch] : 0.f);
+            if constexpr (RES == kAhead) o += ahead.r[v0 + v][pv];
+            if constexpr (RES == kBehind) o += behind.r[v][pv];
+            return kFused && a.act ? activate(a, o) : o;
+        };
+        if constexpr (AC == kRows) {
+            store_rows<B, PV>(a, g * V + v0, px, value);
         } else {
 #pragma unroll
-            for (int pv = 0; pv < PV; ++pv)
-                if (px.valid[pv]) {
-                    float o = acc.get(v, pv) + b;
-                    if (res) o += io_load1(res + px.yoff[pv]);
-                    io_store1(dst + px.yoff[pv], activate(a, o));
-                }
+            for (int v = 0; v < B; ++v) {
+                const int ch = g * V + v0 + v;
+                if (ch >= a.Cout) break;
+                float x[PV];
+#pragma unroll
+                for (int pv = 0; pv < PV; ++pv) x[pv] = value(v, pv);
+                store_pixels<PV, AC>(a.Y + (size_t)ch * a.P, px, x);
+            }
         }
     }
+}
+// For kernels that decide at run time whether there is a residual.
+template <int V, int PV, bool MF, int AC>
+__device__ __forceinline__ void store_group_here(const ConvArgs &a, const Acc<V, PV, MF> &acc, int g, const PixOut<PV> &px) {
+    Resid<1, PV> none;
+    if (kFused && residual_of(a)) store_group<V, PV, MF, AC, kBehind>(a, acc, g, px, none);
+    else store_group<V, PV, MF, AC, kNone>(a, acc, g, px, none);
 }
 
 // The group of the lane's slot: a select tree over the record's (scalar) fields by the bits
@@ -820,39 +968,43 @@ __device__ __forceinline__ void load_slot_bias(const ConvArgs &a, int g, SlotBia
     }
 }
 
-// Epilogue with GS groups per wavefront: g is the group of the lane's slot (-1: none).
-// In vector form the two pixels of a lane are an 8-byte aligned pair inside one image and
-// go out as one store.  The output address is formed once per group and advanced by one
-// image plane per channel.
-template <int V, int PV, int GS, bool VEC, bool PLAIN = false>
+// Epilogue with GS groups per wavefront: g is the group of the lane's slot (-1: none).  The output
+// address is formed once per group and advanced by one image plane per channel.
+template <int V, int PV, int GS, int AC, bool CACHED, int RES>
+__device__ __forceinline__ void store_slots_as(const ConvArgs &a, const Acc<V, PV, true> &acc, int g,
+                                               const PixOut<PV> &px, const SlotBias<V> &sb) {
+    constexpr int B = RES == kBehind ? res_batch(V, PV) : V;
+    io_t *plane = a.Y + (size_t)g * V * a.P;
+#pragma unroll
+    for (int v0 = 0; v0 < V; v0 += B) {
+        Resid<RES == kBehind ? B : 1, PV> behind;
+        if constexpr (RES == kBehind) load_residual<V, PV, AC, B>(a, g, v0, px, behind);
+        auto value = [&](int v, int pv) __attribute__((always_inline)) {
+            float o = acc.get(v0 + v, pv) + sb.b[v0 + v];
+            if constexpr (RES == kBehind) o += behind.r[v][pv];
+            return kFused && a.act ? activate(a, o) : o;
+        };
+        if constexpr (AC == kRows) {
+            store_rows<B, PV>(a, g * V + v0, px, value);
+        } else {
+#pragma unroll
+            for (int v = 0; v < B; ++v) {
+                if (g * V + v0 + v >= a.Cout) break;
+                float x[PV];
+#pragma unroll
+                for (int pv = 0; pv < PV; ++pv) x[pv] = value(v, pv);
+                store_pixels<PV, AC, CACHED>(plane + (size_t)(v0 + v) * a.P, px, x);
+            }
+        }
+    }
+}
+template <int V, int PV, int GS, int AC, bool CACHED = false>
 __device__ __forceinline__ void store_slots(const ConvArgs &a, const Acc<V, PV, true> &acc, int g,
                                             const PixOut<PV> &px, const SlotBias<V> &sb) {
     static_assert(PV == 1 || PV == 2, "several groups per wavefront: one or two pixels per lane");
     if (g < 0) return;
-    const size_t ch0 = (size_t)g * V * a.P;
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-        if (g * V + v >= a.Cout) break;
-        const size_t plane = ch0 + (size_t)v * a.P;
-        const float b = sb.b[v];
-        if constexpr (PV == 2 && VEC) {
-            if (px.valid[0]) {
-                f2 o = f2{acc.get(v, 0) + b, acc.get(v, 1) + b};
-                if (residual_of(a)) o += io_load2(residual_of(a) + plane + px.yoff[0]);
-                if (kFused && a.act) o = f2{activate(a, o[0]), activate(a, o[1])};
-                if constexpr (PLAIN) io_store2_cached(a.Y + plane + px.yoff[0], o);
-                else io_store2(a.Y + plane + px.yoff[0], o);
-            }
-        } else {
-#pragma unroll
-            for (int pv = 0; pv < PV; ++pv)
-                if (px.valid[pv]) {
-                    float o = acc.get(v, pv) + b;
-                    if (residual_of(a)) o += io_load1(residual_of(a) + plane + px.yoff[pv]);
-                    io_store1(a.Y + plane + px.yoff[pv], activate(a, o));
-                }
-        }
-    }
+    if (kFused && residual_of(a)) store_slots_as<V, PV, GS, AC, CACHED, kBehind>(a, acc, g, px, sb);
+    else store_slots_as<V, PV, GS, AC, CACHED, kNone>(a, acc, g, px, sb);
 }
 
 // ------------------------------------------------------------------ 1x1 kernels
@@ -863,20 +1015,19 @@ __device__ __forceinline__ void store_slots(const ConvArgs &a, const Acc<V, PV, 
 // first run of group k+1 are fetched while group k is multiplied, and always before
 // group k's output stores are issued (memory operations retire in order, so a load
 // queued behind stores would wait for them).
-template <int V, int PV, bool MF, bool VEC, int GS, bool RES, bool CACHED = false>
+template <int V, int PV, bool MF, int AC, int GS, int RES, bool CACHED = false>
 __device__ __forceinline__ void pw_resident_body(const ConvArgs &a) {
-    static_assert(!RES || GS == 1, "residual prefetch: one group per wavefront");
+    static_assert(RES == kNone || GS == 1, "several groups per wavefront find out at run time");
     static_assert(GS == 1 || (MF && PV <= 2), "several groups per wavefront: MFMA form, one or two pixels per lane");
     extern __shared__ float lds[];
     constexpr int TP = 64 * PV / GS;
     constexpr int SH = PV == 4 ? 2 : PV == 2 ? 1 : 0;
-    constexpr bool SPLIT = GS > 1 && PV == 2 && !VEC;  // the lane's two pixels are TP/2 apart
     const int logical = logical_wg(a);
     if (logical >= a.total_wgs || skip(a, 8)) return;
     const int pt = logical / a.ngt, gt = logical - pt * a.ngt;
     // the workgroup's pixels [q0, q_end): all TP of the tile, or fewer when the launcher
     // spreads the pixels over more workgroups than full tiles would give (the rest of the
-    // tile is staged as zeros and not stored)
+    // tile is not stored)
     const int q0 = pt * a.tile_px;
     const int q_end = min(a.NP, q0 + a.tile_px);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -896,9 +1047,9 @@ __device__ __forceinline__ void pw_resident_body(const ConvArgs &a) {
     }
 
 #if ALCS_DW_STAGE
-    if (!skip(a, 1)) stage_dw<TP, SPLIT>(a, lds, q0, q_end);
+    if (!skip(a, 1)) stage_dw<TP>(a, lds, q0, q_end);
 #else
-    if (!skip(a, 1)) stage_pw<TP, VEC, SPLIT>(a, lds, q0, 0, a.Cin, q_end);
+    if (!skip(a, 1)) stage_pw<TP, AC>(a, lds, q0, 0, a.Cin, q_end);
 #endif
     // the all-zero row(s) padded columns select: two, one of each channel parity, with several
     // groups per wavefront (the packer picks the one that keeps the slots' reads on different banks)
@@ -909,7 +1060,7 @@ __device__ __forceinline__ void pw_resident_body(const ConvArgs &a) {
 
     const int plane = lane & (64 / GS - 1);  // the lane's place among the pixels (pairs, quads) of the tile
     PixOut<PV> px;
-    pix_out<PV, VEC, SPLIT ? TP / 2 : 0>(a, q0, plane, px, q_end);
+    pix_out<PV, AC>(a, q0, plane, px, q_end);
     const char *ldsb = reinterpret_cast<const char *>(lds);
     const int base = plane * PV * 4;
     for (int k = 0;; ++k) {
@@ -921,8 +1072,8 @@ __device__ __forceinline__ void pw_resident_body(const ConvArgs &a) {
         }
         Acc<V, PV, MF> acc;
         acc.zero();
-        Resid<V, PV> rr;
-        if constexpr (RES) load_residual<V, PV, VEC>(a, w0.group[0], px, rr);
+        Resid<RES == kAhead ? V : 1, PV> rr;
+        if constexpr (RES == kAhead) load_residual<V, PV, AC, V>(a, w0.group[0], 0, px, rr);
         SlotBias<GS == 1 ? 1 : V> sb;
         int g_lane = w0.group[0];
         if constexpr (GS > 1) {
@@ -934,8 +1085,8 @@ __device__ __forceinline__ void pw_resident_body(const ConvArgs &a) {
         // group's stores join the queue (see touch_runs)
         if (more) touch_runs<V, GS>(run1);
         if (!skip(a, 4)) {
-            if constexpr (GS == 1) store_group<V, PV, MF, VEC>(a, acc, w0.group[0], px, RES ? &rr : nullptr);
-            else store_slots<V, PV, GS, VEC, CACHED>(a, acc, g_lane, px, sb);
+            if constexpr (GS == 1) store_group<V, PV, MF, AC, RES>(a, acc, w0.group[0], px, rr);
+            else store_slots<V, PV, GS, AC, CACHED>(a, acc, g_lane, px, sb);
         }
         if (!more) break;
         w0 = w1;
@@ -944,9 +1095,9 @@ __device__ __forceinline__ void pw_resident_body(const ConvArgs &a) {
     }
 }
 
-template <int V, int PV, bool MF, bool VEC, int GS>
+template <int V, int PV, bool MF, int AC, int GS>
 __global__ void __launch_bounds__(1024) k_pw_resident(const ConvArgs a) {
-    pw_resident_body<V, PV, MF, VEC, GS, false>(a);
+    pw_resident_body<V, PV, MF, AC, GS, kNone>(a);
 }
 // Four groups per wavefront on pixel pairs, with ordinary instead of streaming stores: for launches
 // of several rounds over images whose channel planes do not start on cache lines (14x14, 28x28).
@@ -955,19 +1106,109 @@ __global__ void __launch_bounds__(1024) k_pw_resident(const ConvArgs a) {
 // (512->512 @14x14, N=256, 90 % sparse: 89 -> 81 us; in a single round the streaming stores win).
 template <int V>
 __global__ void __launch_bounds__(1024) k_pw_resident_cached(const ConvArgs a) {
-    pw_resident_body<V, 2, true, true, 4, false, true>(a);
+    pw_resident_body<V, 2, true, kAligned, 4, kNone, true>(a);
 }
-// The same walk with every group's residual fetched ahead of its multiply (fused epilogue,
-// MFMA and vector form, one group per wavefront).
-template <int V, int PV>
+// The same walk with a residual, one group per wavefront (fused epilogue).
+template <int V, int PV, bool MF, int AC>
 __global__ void __launch_bounds__(1024) k_pw_resident_res(const ConvArgs a) {
-    pw_resident_body<V, PV, true, true, 1, true>(a);
+    pw_resident_body<V, PV, MF, AC, 1, V * PV <= 16 && MF ? kAhead : kBehind>(a);
 }
+
+#if !ALCS_DW_STAGE
+// Mode 1, split: the resident kernel for launches with fewer bundles per workgroup than wavefronts -
+// small batches and fully connected layers, where the pixel tiles are few and the bundles are dealt
+// to as many workgroups as there are compute units.  Such a launch is a chain of latencies (launch,
+// tile, multiply, stores) and the multiply of a bundle by one wavefront is its longest link: 200
+// columns x 35 cycles = 3 us.  Here a.ksplit wavefronts share a bundle, each with a run of its columns,
+// and the partial sums are added through LDS (the tile's memory, once everybody has read it), every
+// wavefront finishing and storing a share of the channels.
+// 2048 -> 1000 on 128 rows, V = 8, 90 % sparse: 24.6 -> 10.6 us (with kRows); 512->512 @14x14 on one image:
+// 7.8 -> 5.6 us.
+template <int V, int PV, int AC, int GS>
+__global__ void __launch_bounds__(1024) k_pw_split(const ConvArgs a) {
+    extern __shared__ float lds[];
+    constexpr int TP = 64 * PV / GS;
+    constexpr int SH = PV == 2 ? 1 : 0;
+    constexpr int UV = AC == kRows ? 4 : 1;  // channels that are finished and stored together
+    const int logical = logical_wg(a);
+    if (logical >= a.total_wgs || skip(a, 8)) return;
+    const int pt = logical / a.ngt, gt = logical - pt * a.ngt;
+    const int q0 = pt * a.tile_px;
+    const int q_end = min(a.NP, q0 + a.tile_px);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g_begin = gt * a.gpt;
+    const int ng = min(a.G, g_begin + a.gpt) - g_begin;
+    const int ks = a.ksplit, bundle = wave / ks, part = wave - bundle * ks;
+    const bool any = bundle < ng;
+    Work w = no_work();
+    Runs<V, true, GS> runs;
+    SlotBias<V> sb;
+    int g = -1, cnt = 0;
+    if (any) {
+        w = load_work(a.work, g_begin + bundle);
+        const int per = ((w.cnt + 15) / 16 + ks - 1) / ks * 16;  // columns per wavefront: whole runs
+        cnt = max(0, min(per, w.cnt - part * per));
+        if (cnt > 0) w.start += part * per;
+        runs = load_runs<V, true, GS>(a, w.start, cnt, lane);
+        g = lane_group<GS>(w, lane);
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            sb.b[v] = 0.f;
+            if ((v / UV) % ks == part && a.bias && g >= 0 && g * V + v < a.Cout) sb.b[v] = a.bias[g * V + v];
+        }
+    }
+    if (!skip(a, 1)) stage_pw<TP, AC>(a, lds, q0, 0, a.Cin, q_end);
+    for (int t = tid; t < 2 * TP; t += blockDim.x) lds[a.KC * TP + t] = 0.f;
+    __syncthreads();
+    const int plane = lane & (64 / GS - 1);
+    PixOut<PV> px;
+    pix_out<PV, AC>(a, q0, plane, px, q_end);
+    Acc<V, PV, true> acc;
+    acc.zero();
+    if (any && !skip(a, 2))
+        mac_segment<V, PV, SH, GS>(a, w.start, cnt, reinterpret_cast<const char *>(lds), plane * PV * 4, lane, runs, acc);
+    __syncthreads();
+    float *red = lds + (size_t)wave * (V * PV * 64) + lane;
+    if (any)
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+#pragma unroll
+            for (int pv = 0; pv < PV; ++pv) red[(v * PV + pv) * 64] = acc.get(v, pv);
+    __syncthreads();
+    if (!any || g < 0 || skip(a, 4)) return;
+    const float *sum = lds + (size_t)(bundle * ks) * (V * PV * 64) + lane;
+    const bool res = kFused && residual_of(a);
+#pragma unroll
+    for (int u = 0; u < V / UV; ++u) {
+        if (u % ks != part || g * V + u * UV >= a.Cout) continue;
+        float x[UV][PV];
+        Resid<UV, PV> rr;
+        if (res) load_residual<V, PV, AC, UV>(a, g, u * UV, px, rr);
+#pragma unroll
+        for (int i = 0; i < UV; ++i)
+#pragma unroll
+            for (int pv = 0; pv < PV; ++pv) {
+                const int v = u * UV + i;
+                float o = 0.f;
+                for (int k = 0; k < ks; ++k) o += sum[(size_t)(k * V * PV + v * PV + pv) * 64];
+                o += sb.b[v];
+                if (res) o += rr.r[i][pv];
+                x[i][pv] = kFused && a.act ? activate(a, o) : o;
+            }
+        if constexpr (AC == kRows) {
+            store_rows<4, PV>(a, g * V + u * UV, px, [&](int i, int pv) __attribute__((always_inline)) { return x[i][pv]; });
+        } else {
+            store_pixels<PV, AC>(a.Y + (size_t)(g * V + u) * a.P, px, x[0]);
+        }
+    }
+}
+#endif
 
 #if !ALCS_RESIDENT_ONLY
 // Mode 2: input channels streamed through LDS in chunks of KC; every wavefront owns
 // UG groups for the whole kernel and keeps their accumulators in registers.
-template <int V, int PV, int UG, bool MF, bool VEC>
+template <int V, int PV, int UG, bool MF, int AC>
 __global__ void __launch_bounds__(512) k_pw_chunked(const ConvArgs a) {
     extern __shared__ float lds[];
     constexpr int TP = 64 * PV;
@@ -1005,7 +1246,7 @@ __global__ void __launch_bounds__(512) k_pw_chunked(const ConvArgs a) {
             }
         }
         if (ch) __syncthreads();
-        if (!skip(a, 1)) stage_pw<TP, VEC>(a, lds, q0, c0, c1, a.NP);
+        if (!skip(a, 1)) stage_pw<TP, AC>(a, lds, q0, c0, c1, a.NP);
         __syncthreads();
         const int base = lane * PV * 4 - c0 * (kRowBytes1 << SH);
 #pragma unroll
@@ -1014,11 +1255,11 @@ __global__ void __launch_bounds__(512) k_pw_chunked(const ConvArgs a) {
                 mac_segment<V, PV, SH>(a, wk[u].start, wk[u].cnt, ldsb, base, lane, rn[u], acc[u]);
     }
     PixOut<PV> px;
-    pix_out<PV, VEC>(a, q0, lane, px, a.NP);
+    pix_out<PV, AC>(a, q0, lane, px, a.NP);
 #pragma unroll
     for (int u = 0; u < UG; ++u)
         if (slot[u] >= 0 && !skip(a, 4))
-            store_group<V, PV, MF, VEC>(a, acc[u], load_work(a.work, (size_t)slot[u] * a.nchunks).group[0], px);
+            store_group_here<V, PV, MF, AC>(a, acc[u], load_work(a.work, (size_t)slot[u] * a.nchunks).group[0], px);
 }
 
 
@@ -1116,7 +1357,7 @@ __global__ void __launch_bounds__(512) k_pw_stream(const ConvArgs a) {
                 Acc<V, PV, true> acc;
                 acc.zero();
                 if (!skip(a, 2)) mac_segment<V, PV, SH>(al, w0.start, w0.cnt, ldsb, base, lane, run0, acc);
-                if (!skip(a, 4)) store_group<V, PV, true, true>(a, acc, w0.group[0], px);
+                if (!skip(a, 4)) store_group_here<V, PV, true, kAligned>(a, acc, w0.group[0], px);
                 if (!more) break;
                 w0 = w1;
                 w1 = w2;
@@ -1336,7 +1577,7 @@ __global__ void __launch_bounds__(512) k_conv3(const ConvArgs a) {
 #pragma unroll
     for (int u = 0; u < UG; ++u)
         if (slot[u] >= 0 && !skip(a, 4))
-            store_group<V, PV, MF, false>(a, acc[u], load_work(a.work, (size_t)slot[u] * a.nchunks).group[0], px);
+            store_group_here<V, PV, MF, kScattered>(a, acc[u], load_work(a.work, (size_t)slot[u] * a.nchunks).group[0], px);
 }
 
 
@@ -1476,7 +1717,7 @@ __global__ void __launch_bounds__(NT) k_pw_pipe(const ConvArgs a) {
             SlotBias<V> sb;
 #pragma unroll
             for (int c = 0; c < V; ++c) sb.b[c] = (g_lane[k] >= 0 && g_lane[k] * V + c < a.Cout) ? lbias[g_lane[k] * V + c] : 0.f;
-            store_slots<V, PV, GS, true, CACHED>(a, acc[k], g_lane[k], px, sb);
+            store_slots<V, PV, GS, kAligned, CACHED>(a, acc[k], g_lane[k], px, sb);
         }
         oq += nranges * a.tile_px;
         on = oq / a.P;
@@ -1495,46 +1736,79 @@ static inline int ceil_div(long long a, long long b) { return (int)((a + b - 1) 
 
 typedef void (*kern_t)(const ConvArgs);
 
-template <int V, bool MF>
-static kern_t pick_resident(int pv, bool vec, int gs, bool res = false) {
-    if constexpr (kFused && !kDw && MF && V <= 8) {
-        // with a residual: the variants that fetch it ahead of the multiply (vector form, one
-        // group per wavefront, at most 16 values per lane)
-        if (res && vec && gs == 1) {
-            if constexpr (V * 4 <= 16) {
-                if (pv == 4) return k_pw_resident_res<V, 4>;
+template <int V, bool MF, int AC>
+static kern_t pick_resident_ac(int pv, int gs, bool res) {
+    if constexpr (kFused) {
+        if (res && gs == 1) {
+            if constexpr (AC == kAligned || AC == kUnaligned) {
+                if (pv == 4) return k_pw_resident_res<V, 4, MF, AC>;
             }
-            if (pv == 2) return k_pw_resident_res<V, 2>;
-            if (pv == 1) return k_pw_resident_res<V, 1>;
+            if constexpr (AC != kRows) {
+                if (pv == 2) return k_pw_resident_res<V, 2, MF, AC>;
+            }
+            return k_pw_resident_res<V, 1, MF, AC>;
         }
     }
     if constexpr (MF) {
-        if (gs == 2 && pv == 2) return vec ? k_pw_resident<V, 2, true, true, 2> : k_pw_resident<V, 2, true, false, 2>;
-        if (gs == 4 && pv == 2) return vec ? k_pw_resident<V, 2, true, true, 4> : k_pw_resident<V, 2, true, false, 4>;
-        if (gs == 2) return vec ? k_pw_resident<V, 1, true, true, 2> : k_pw_resident<V, 1, true, false, 2>;
-        if (gs == 4) return vec ? k_pw_resident<V, 1, true, true, 4> : k_pw_resident<V, 1, true, false, 4>;
+        if constexpr (AC == kAligned || AC == kUnaligned) {
+            if (gs == 2 && pv == 2) return k_pw_resident<V, 2, true, AC, 2>;
+        }
+        if (gs == 4 && pv == 2) return k_pw_resident<V, 2, true, AC, 4>;
+        if (gs == 2) return k_pw_resident<V, 1, true, AC, 2>;
+        if (gs == 4) return k_pw_resident<V, 1, true, AC, 4>;
     }
-    if (vec) {
-        if (pv == 4) return k_pw_resident<V, 4, MF, true, 1>;
-        if (pv == 2) return k_pw_resident<V, 2, MF, true, 1>;
-        return k_pw_resident<V, 1, MF, true, 1>;
+    if constexpr (AC == kAligned || AC == kUnaligned) {
+        if (pv == 4) return k_pw_resident<V, 4, MF, AC, 1>;
     }
-    return k_pw_resident<V, 1, MF, false, 1>;
+    if constexpr (AC != kRows) {
+        if (pv == 2) return k_pw_resident<V, 2, MF, AC, 1>;
+    }
+    return k_pw_resident<V, 1, MF, AC, 1>;
+}
+template <int V, bool MF>
+static kern_t pick_resident(int pv, Access ac, int gs, bool res = false) {
+    if (ac == kAligned) return pick_resident_ac<V, MF, kAligned>(pv, gs, res);
+    if constexpr (!kDw) {
+        if (ac == kStrided) return pick_resident_ac<V, MF, kStrided>(pv, gs, res);
+        if (ac == kRows) return pick_resident_ac<V, MF, kRows>(pv, gs, res);
+    }
+    return pick_resident_ac<V, MF, kUnaligned>(pv, gs, res);
 }
 
+#if !ALCS_DW_STAGE
+template <int V, int AC>
+static kern_t pick_split_ac(int pv, int gs) {
+    if (gs == 4) return pv == 2 ? k_pw_split<V, 2, AC, 4> : k_pw_split<V, 1, AC, 4>;
+    return pv == 1 ? k_pw_split<V, 1, AC, 2> : nullptr;
+}
+template <int V>
+static kern_t pick_split(int pv, Access ac, int gs) {
+    if (ac == kAligned) return pick_split_ac<V, kAligned>(pv, gs);
+    if (ac == kStrided) return pick_split_ac<V, kStrided>(pv, gs);
+    if (ac == kRows) return pick_split_ac<V, kRows>(pv, gs);
+    return pick_split_ac<V, kUnaligned>(pv, gs);
+}
+#endif
+
 #if !ALCS_RESIDENT_ONLY
-template <int V, bool MF>
-static kern_t pick_chunked(int pv, bool vec, int ug) {
-    if (vec) {
+template <int V, bool MF, int AC>
+static kern_t pick_chunked_ac(int pv, int ug) {
+    if constexpr (AC == kAligned) {
         if (pv == 4) {
             // 4 groups x 4 pixels x 16 channels of accumulators do not fit the register file
-            if constexpr (V * 4 * 4 > 128) return k_pw_chunked<V, 4, 2, MF, true>;
-            else return ug == 2 ? k_pw_chunked<V, 4, 2, MF, true> : k_pw_chunked<V, 4, 4, MF, true>;
+            if constexpr (V * 4 * 4 > 128) return k_pw_chunked<V, 4, 2, MF, AC>;
+            else return ug == 2 ? k_pw_chunked<V, 4, 2, MF, AC> : k_pw_chunked<V, 4, 4, MF, AC>;
         }
-        if (pv == 2) return ug == 2 ? k_pw_chunked<V, 2, 2, MF, true> : k_pw_chunked<V, 2, 4, MF, true>;
-        return ug == 2 ? k_pw_chunked<V, 1, 2, MF, true> : k_pw_chunked<V, 1, 4, MF, true>;
+        if (pv == 2) return ug == 2 ? k_pw_chunked<V, 2, 2, MF, AC> : k_pw_chunked<V, 2, 4, MF, AC>;
     }
-    return ug == 2 ? k_pw_chunked<V, 1, 2, MF, false> : k_pw_chunked<V, 1, 4, MF, false>;
+    return ug == 2 ? k_pw_chunked<V, 1, 2, MF, AC> : k_pw_chunked<V, 1, 4, MF, AC>;
+}
+template <int V, bool MF>
+static kern_t pick_chunked(int pv, Access ac, int ug) {
+    if (ac == kAligned) return pick_chunked_ac<V, MF, kAligned>(pv, ug);
+    if (ac == kStrided) return pick_chunked_ac<V, MF, kStrided>(pv, ug);
+    if (ac == kRows) return pick_chunked_ac<V, MF, kRows>(pv, ug);
+    return pick_chunked_ac<V, MF, kUnaligned>(pv, ug);
 }
 
 template <int V, int TI, bool MF>
@@ -1710,6 +1984,8 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
 
     if (kernel == 1) {
         const bool vec = stride == 1 && (P % 4 == 0);
+        const Access ac = vec ? kAligned : kDw ? kUnaligned : (P == 1 && Pin == 1) ? kRows : (stride == 1 && P >= 4) ? kUnaligned : kStrided;
+        const int pv_most = ac == kRows ? 1 : ac == kStrided ? 2 : 4;  // one group per wavefront
         // streaming kernel: everything (two input tiles, packed weights) fits in LDS and
         // there are enough pixels to give every compute unit several tiles
         bool stream_ok = false;
@@ -1811,8 +2087,8 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             const int GS = L.GS, NB = L.nbundles;
             if (GS > 1 && !mfma) return ALCS_E_UNSUPPORTED;  // the packer pairs groups only for V >= 4
             pv = 1;
-            if (vec && GS == 1) {
-                for (int cand = 4; cand >= 2; cand >>= 1) {
+            if (GS == 1) {
+                for (int cand = pv_most; cand >= 2; cand >>= 1) {
                     const long long need = (long long)(Cin + 1) * 64 * cand * 4;
                     const long long tiles = ((long long)a.NP + 64 * cand - 1) / (64 * cand);
                     if (need <= kTwoPerCu && tiles * (cand == 2 ? 2 : 1) >= kMinWgs) { pv = cand; break; }
@@ -1821,21 +2097,21 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
                 // pixel tiles x group tiles then make a single round that keeps at least 3/4 of the
                 // compute units busy: one wide workgroup beats two narrow ones that share a
                 // compute unit (28x28 and 14x14 layers at batch 32: 5-11 % faster).
-                for (int cand = 4; cand > pv; cand >>= 1) {
+                for (int cand = pv_most; cand > pv; cand >>= 1) {
                     const long long need = (long long)(Cin + 1) * 64 * cand * 4;
                     const long long tiles = ((long long)a.NP + 64 * cand - 1) / (64 * cand);
                     if (need > kMaxLds || tiles > kCUs) continue;
                     const long long gts = std::min<long long>(std::max(1, NB / 4), std::max<long long>(1, kCUs / tiles));
                     if (tiles * gts >= 3 * kCUs / 4) { pv = cand; break; }
                 }
-                if (T.pv == 1 || T.pv == 2 || T.pv == 4) pv = T.pv;
+                if (T.pv == 1 || T.pv == 2 || T.pv == 4) pv = std::min(T.pv, pv_most);
             }
             // Several groups per wavefront: four groups of 16 lanes with a pixel pair each read
             // half as many LDS rows per kept weight as two groups of 32 lanes with one pixel
             // (same 32-pixel tile; 512->512 @14x14: 17.4 -> 15.7 us).
             if (GS > 1) {
                 pv = (GS == 4 && (long long)(Cin + 2) * 32 * 4 <= kMaxLds) ? 2 : 1;
-                if (T.pv == 1 || T.pv == 2) pv = T.pv;
+                if (T.pv == 1 || (T.pv == 2 && (GS == 4 || ac == kAligned || ac == kUnaligned))) pv = T.pv;
             }
             const int TP = 64 * pv / GS;
             lds = (Cin + (GS > 1 ? 2 : 1)) * TP * 4;  // the rows and the zero row(s)
@@ -1849,7 +2125,11 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             int ngt = 1;
             const bool one_round = lds > 80 * 1024 || GS > 1;  // narrow tiles: measured best at <= 256 workgroups too
             const int want = one_round ? kCUs : kMinWgs;
-            if (a.npt < want) ngt = std::min(std::max(1, NB / 4), std::max(1, one_round ? want / a.npt : ceil_div(want, a.npt)));
+            // (with several groups per wavefront down to one bundle per workgroup: wavefronts then share
+            // bundles, see k_pw_split)
+            const bool can_split = GS > 1 && !kDw && !(GS == 2 && pv == 2);
+            const int most_gts = can_split ? NB : std::max(1, NB / 4);
+            if (a.npt < want) ngt = std::min(most_gts, std::max(1, one_round ? want / a.npt : ceil_div(want, a.npt)));
             if (T.group_tiles > 0) ngt = std::min(T.group_tiles, NB);
             a.gpt = ceil_div(NB, ngt);
             a.ngt = ceil_div(NB, a.gpt);
@@ -1874,11 +2154,11 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             // bundles): wavefronts without a bundle still help to stage it
             nw = std::min(nw, std::max(std::max(1, a.gpt), lds / (GS == 4 ? 4096 : 8192)));
             switch (V) {
-                case 1: kern = pick_resident<1, false>(pv, vec, GS); break;
-                case 2: kern = pick_resident<2, false>(pv, vec, GS); break;
-                case 4: kern = mfma ? pick_resident<4, true>(pv, vec, GS, a.residual != nullptr) : pick_resident<4, false>(pv, vec, GS); break;
-                case 8: kern = pick_resident<8, true>(pv, vec, GS, a.residual != nullptr); break;
-                case 16: kern = pick_resident<16, true>(pv, vec, GS, a.residual != nullptr); break;
+                case 1: kern = pick_resident<1, false>(pv, ac, GS, a.residual != nullptr); break;
+                case 2: kern = pick_resident<2, false>(pv, ac, GS, a.residual != nullptr); break;
+                case 4: kern = mfma ? pick_resident<4, true>(pv, ac, GS, a.residual != nullptr) : pick_resident<4, false>(pv, ac, GS, a.residual != nullptr); break;
+                case 8: kern = pick_resident<8, true>(pv, ac, GS, a.residual != nullptr); break;
+                case 16: kern = pick_resident<16, true>(pv, ac, GS, a.residual != nullptr); break;
             }
             if (GS == 4 && pv == 2 && vec && mfma && (long long)a.npt * a.ngt > 2LL * kCUs &&
                 ((long long)P * sizeof(io_t)) % 128 != 0) {
@@ -1896,6 +2176,18 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             // 10 or 12 wavefronts measured no better than 16); a single round is faster with 16.
             if (nw > 8 && (long long)a.npt * a.ngt > kCUs && 2 * lds <= kMaxLds && kernel_registers(kern) > 64) nw = 8;
             if (T.waves > 0) nw = std::min(T.waves, 16);
+            if (ac == kStrided) nw = std::max(nw, TP / 64);  // a thread stages one pixel of the tile
+#if !ALCS_DW_STAGE
+            // Wavefronts without a bundle of their own share the others': as many per bundle (a power of
+            // two) as there are, and as its longest segment has runs of 16 columns.
+            int ks = 1;
+            while (can_split && a.gpt * ks * 2 <= nw && ks * 2 * 16 <= L.max_cnt + 15) ks *= 2;
+            if (ks > 1) {
+                a.ksplit = ks;
+                lds = std::max(lds, nw * V * pv * 64 * 4);
+                kern = V == 4 ? pick_split<4>(pv, ac, GS) : V == 8 ? pick_split<8>(pv, ac, GS) : pick_split<16>(pv, ac, GS);
+            }
+#endif
         } else {
 #if ALCS_RESIDENT_ONLY
             return ALCS_E_UNSUPPORTED;  // this build holds the resident kernels only
@@ -1913,11 +2205,11 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             a.gpt = nw * ug;
             a.ngt = ceil_div(G, a.gpt);
             switch (V) {
-                case 1: kern = pick_chunked<1, false>(pv, vec, ug); break;
-                case 2: kern = pick_chunked<2, false>(pv, vec, ug); break;
-                case 4: kern = mfma ? pick_chunked<4, true>(pv, vec, ug) : pick_chunked<4, false>(pv, vec, ug); break;
-                case 8: kern = pick_chunked<8, true>(pv, vec, ug); break;
-                case 16: kern = pick_chunked<16, true>(pv, vec, ug); break;
+                case 1: kern = pick_chunked<1, false>(pv, ac, ug); break;
+                case 2: kern = pick_chunked<2, false>(pv, ac, ug); break;
+                case 4: kern = mfma ? pick_chunked<4, true>(pv, ac, ug) : pick_chunked<4, false>(pv, ac, ug); break;
+                case 8: kern = pick_chunked<8, true>(pv, ac, ug); break;
+                case 16: kern = pick_chunked<16, true>(pv, ac, ug); break;
             }
 #endif
         }
