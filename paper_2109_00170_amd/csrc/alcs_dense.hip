@@ -3,22 +3,18 @@
 // implicit GEMM  Y[o, q] = sum_k W[o, k] * I*[k, q]  on fp32 matrix cores
 // (v_mfma_f32_32x32x2_f32), with I* the virtual patch matrix of Section 3.2.2
 // ("Overview"): row k = (c*kernel + r)*kernel + s, column q = flattened (n, ho, wo).
-//
-// A workgroup of four wavefronts (2 x 2) owns a BM x 128 tile of Y and walks K in
-// steps of 16: the weight tile is transposed into LDS as As[k][m], the patch tile is
-// gathered as Bs[k][q]; each wavefront owns (BM/64) x 2 MFMA tiles of 32 x 32.  The
-// global loads of step k+1 are issued before the multiplies of step k and written to the
-// other half of a two-deep LDS buffer afterwards, so a step costs one barrier and the
-// load latency is covered by the matrix instructions.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "alcs_internal.h"
 
 namespace alcs {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 
 struct DenseArgs {
@@ -30,15 +26,308 @@ struct DenseArgs {
     int N, Cin, Cout, H, W, Ho, Wo, stride, k;
     int P, Pin, K;
     int mt, nt;  // tiles along Cout and along pixels
+    int npos;    // patch kernel: positions of the staged input per channel, at most
     int wg_per_xcd, total_wgs, xcds;
 };
 
-constexpr int BK = 16;
-constexpr int BN = 128;
+// The input is staged as it lies in the image and not as rows of the patch matrix: a workgroup's BN
+// pixels of the flattened axis need a few input rows of one or more images, and the nine taps of a
+// 3x3 filter read the same staged words at nine offsets, so global loads and LDS writes of the
+// activations are a ninth of the patch matrix's.  A step is 8 input channels x 9 taps (3x3) or 16
+// channels (1x1).  Four channels of a position lie side by side in LDS, and four channels of a weight
+// row likewise: the matrix instruction takes two rows of K, lanes 0-31 one and lanes 32-63 the other,
+// and since the order of K is free, lane half h takes channels 4h ... 4h+3 of a group of 8 in four
+// consecutive instructions - one 16-byte LDS read per operand for four of them.  The loads of step
+// i+1 are issued between the multiplies of step i.
+// What bounds a launch is the matrix pipe (65 to 75 % busy) and, on few tiles, how evenly they divide over
+// the compute units (the launcher picks the tile for that).  3x3, N=64, against the patch matrix
+// gathered word by word: 128->128 @28x28 260 -> 178 us (83 TFLOP/s), 512->512 @7x7 578 -> 187 us,
+// 40->23 @112x86 424 -> 175 us; 1x1 1024->256 @14x14 101 -> 80 us.  1x1 layers with few
+// output channels wait for their input: 16 channels a step leave room for 8 workgroups a compute unit
+// (256->64 @56x56, N=40: 59.5 -> 50 us against 32 channels and 3 workgroups).
+template <int BM, int BN>
+struct DenseTile {
+    static constexpr int WM = BM >= 64 && !(BM == 64 && BN == 128) ? 2 : 1;  // wavefronts along the channels
+    static constexpr int WN = 4 / WM;
+    static constexpr int TM = BM / 32 / WM, TN = BN / 32 / WN;  // 32x32 tiles per wavefront
+    static_assert(TM >= 1 && TN >= 1, "tile");
+};
+constexpr int kPosPerThread = 4;  // 3x3: staged positions per thread and quad of channels, at most
 
-template <int BM, bool PW_VEC>
-__global__ void __launch_bounds__(256) k_dense(const DenseArgs a) {
-    constexpr int LDA = BM + 4;
+// NPT: staged positions per thread (3x3).
+template <int BM, int BN, int KK, int NPT>
+__global__ void __launch_bounds__(256, KK == 1 ? 4 : BM == 128 ? 1 : 2) k_dense(const DenseArgs a) {
+    using T = DenseTile<BM, BN>;
+    constexpr int TM = T::TM, TN = T::TN;
+    constexpr int CH = KK == 9 ? 8 : 16;      // channels per step
+    constexpr int NKQ = KK == 9 ? 18 : CH / 4;    // (tap, quad of channels) pairs per step
+    constexpr int LDA = BM + 1;               // f4 units; the odd pitch spreads a row's quads over the banks
+    constexpr int NA = (BM * NKQ + 255) / 256;
+    constexpr int NB = KK == 9 ? NPT * 2 : BN * NKQ / 256;
+    constexpr int LDB = KK == 9 ? 256 * NPT : BN;
+    constexpr int BUF = NKQ * LDA + (KK == 9 ? 2 : NKQ) * LDB;  // one of the two LDS buffers, in quads
+    extern __shared__ f4 lds[];
+    const int id = blockIdx.x;
+    const int logical = (id % a.xcds) * a.wg_per_xcd + id / a.xcds;
+    if (logical >= a.total_wgs) return;
+    // consecutive logical ids share the pixel tile (the large operand) and differ in the channel tile
+    const int ntile = logical / a.mt, mtile = logical - ntile * a.mt;
+    const int m0 = mtile * BM;
+    const long long q0 = (long long)ntile * BN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / T::WN, wn = wave % T::WN;
+    const int h = lane >> 5, l32 = lane & 31;
+    const int S = a.stride;
+
+    // The tile's first image, pixel and output row.  Positions of the flattened axis are 64 bits wide,
+    // whose division takes some 150 instructions; it is done here once, and only where it has to be
+    // (the lanes divide what is left, 32 bits: 1x1 136 -> 35 @56x55, N=60, 50 -> 46 us).
+    const int n0 = q0 >> 32 ? (int)(q0 / a.P) : (int)((uint32_t)q0 / (uint32_t)a.P);
+    const uint32_t p0 = (uint32_t)(q0 - (long long)n0 * a.P);
+    const int ho0 = (int)(p0 / (uint32_t)a.Wo);
+    // image (from n0) and pixel of the tile's pixel e; images past the last for e behind the end
+    auto locate = [&](int e, int *dn, int *ho, int *wo) __attribute__((always_inline)) {
+        const uint32_t p = p0 + (uint32_t)e;
+        *dn = (int)(p / (uint32_t)a.P);
+        const uint32_t in = p - (uint32_t)*dn * (uint32_t)a.P;
+        *ho = (int)(in / (uint32_t)a.Wo);
+        *wo = (int)(in - (uint32_t)*ho * (uint32_t)a.Wo);
+    };
+    const int IW = (a.Wo - 1) * S + 3;               // staged columns of an input row, from column -1
+    const int rows_full = (a.Ho - 1) * S + 3;        // staged rows of an image that is there from its first row
+    const int rows_n0 = (a.Ho - 1 - ho0) * S + 3;    // and of the tile's first image
+    const float *xbase = a.X + (size_t)n0 * a.Cin * a.Pin;
+
+    // staged positions of this thread: element offset inside channel 0 of the tile's first image, or -1
+    constexpr int NOFF = KK == 9 ? NPT : 1;
+    int poff[NOFF];
+    if constexpr (KK == 9) {
+#pragma unroll
+        for (int i = 0; i < NPT; ++i) {
+            const int pos = tid + 256 * i;
+            poff[i] = -1;
+            if (pos < a.npos) {
+                const int row = pos / IW, ix = pos - row * IW - 1;
+                int n = n0, iy = ho0 * S - 1 + row;
+                if (row >= rows_n0) {
+                    const int r = row - rows_n0, im = r / rows_full;
+                    n = n0 + 1 + im;
+                    iy = r - im * rows_full - 1;
+                }
+                if (n < a.N && iy >= 0 && iy < a.H && ix >= 0 && ix < a.W)
+                    poff[i] = (n - n0) * a.Cin * a.Pin + iy * a.W + ix;
+            }
+        }
+    } else {
+        const long long q = q0 + tid % BN;
+        poff[0] = -1;
+        if (q < a.NP) {
+            int dn, ho, wo;
+            locate(tid % BN, &dn, &ho, &wo);
+            poff[0] = dn * a.Cin * a.Pin + ho * S * a.W + wo * S;
+        }
+    }
+    // the lane's columns of the B operand: position of tap (0, 0)
+    int bpos[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int e = (wn * TN + j) * 32 + l32;
+        bpos[j] = e;
+        if constexpr (KK == 9) {
+            int dn, ho, wo;
+            locate(q0 + e < a.NP ? e : 0, &dn, &ho, &wo);
+            const int row = dn == 0 ? (ho - ho0) * S : rows_n0 + (dn - 1) * rows_full + ho * S;
+            bpos[j] = row * IW + wo * S;
+        }
+    }
+
+    f16v acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    // Byte offsets of this thread's share of the weight tile from the tile's first row (rows beyond Cout
+    // read the last one and are not stored).
+    uint32_t aoff[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int idx = tid + 256 * i;
+        const int m = idx / NKQ, kq = idx - m * NKQ;
+        const int hh = kq / 9, tap = kq - hh * 9;
+        aoff[i] = 4u * ((uint32_t)min(m, a.Cout - 1 - m0) * (uint32_t)a.K + (uint32_t)(KK == 9 ? hh * 36 + tap : 4 * kq));
+    }
+    const float *wbase = a.Wt + (size_t)m0 * a.K;
+
+    f4 ra[NA], rb[NB];
+    // Item i of a step's loads, for a step whose channels are all there: unconditional, from addresses
+    // that are valid for every lane (places outside the image read place 0 and are zeroed when they are
+    // written to LDS - not here, where the select would wait for the load), as wave-uniform base +
+    // 32-bit offset.
+    auto load_a = [&](int i, int c0) __attribute__((always_inline)) {
+        uint32_t o = aoff[i];
+        asm volatile("" : "+v"(o));
+        const char *src = reinterpret_cast<const char *>(wbase + (size_t)c0 * KK) + o;
+        if constexpr (KK == 9) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) ra[i][t] = *reinterpret_cast<const float *>(src + 36 * t);
+        } else {
+            ra[i] = *reinterpret_cast<const f4u *>(src);
+        }
+    };
+    // 3x3: position i % NPT of this thread, quad i / NPT; 1x1: one position, quads tid / BN + i * 256 / BN
+    auto quad_of = [&](int i) { return KK == 9 ? i / NPT : __builtin_amdgcn_readfirstlane(tid / BN) + i * (256 / BN); };
+    auto load_b = [&](int i, int c0) __attribute__((always_inline)) {
+        uint32_t o = 4u * (uint32_t)max(poff[KK == 9 ? i % NPT : 0], 0);
+        asm volatile("" : "+v"(o));
+        const char *src = reinterpret_cast<const char *>(xbase + (size_t)(c0 + 4 * quad_of(i)) * a.Pin);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) rb[i][t] = *reinterpret_cast<const float *>(src + (size_t)t * a.Pin * 4 + o);
+    };
+    // The last step of a channel count that is no multiple of the step.
+    auto load_rest = [&](int c0) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int kq = (tid + 256 * i) % NKQ, c = c0 + 4 * (KK == 9 ? kq / 9 : kq);
+            const float *src = wbase + (size_t)c0 * KK + aoff[i] / 4u;
+            ra[i] = f4{0, 0, 0, 0};
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (c + t < a.Cin) ra[i][t] = src[KK * t];
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int c = c0 + 4 * quad_of(i);
+            const float *src = xbase + max(poff[KK == 9 ? i % NPT : 0], 0) + (size_t)c * a.Pin;
+            rb[i] = f4{0, 0, 0, 0};
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (c + t < a.Cin) rb[i][t] = src[(size_t)t * a.Pin];
+        }
+    };
+    auto store_a = [&](int i, f4 *buf) __attribute__((always_inline)) {
+        const int idx = tid + 256 * i;
+        const int m = idx / NKQ, kq = idx - m * NKQ;
+        // (places behind the tile's rows: into the row's spare quad)
+        buf[kq * LDA + ((BM * NKQ) % 256 == 0 ? m : min(m, BM))] = ra[i];
+    };
+    auto store_b = [&](int i, f4 *buf) __attribute__((always_inline)) {
+        const f4 x = poff[KK == 9 ? i % NPT : 0] < 0 ? f4{0, 0, 0, 0} : rb[i];
+        if constexpr (KK == 9) buf[NKQ * LDA + (i / NPT) * LDB + tid + 256 * (i % NPT)] = x;
+        else buf[NKQ * LDA + (tid / BN + i * (256 / BN)) * LDB + tid % BN] = x;
+    };
+
+    if (CH <= a.Cin) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) load_a(i, 0);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) load_b(i, 0);
+    } else {
+        load_rest(0);
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i) store_a(i, lds);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) store_b(i, lds);
+    __syncthreads();
+    constexpr int G = NKQ / 2;            // groups of 8 rows of K in a step: a tap's 8 channels, or 8 channels
+    constexpr int SLOTS = 4 * G, PER = KK == 9 ? 1 : 2, NI = NA + NB;
+    static_assert(2 * ((NI + PER - 1) / PER) <= SLOTS, "loads first, stores last");
+    auto read_group = [&](const f4 *As, int g, f4 (&av)[TM], f4 (&bv)[TN]) __attribute__((always_inline)) {
+        const f4 *Bs = As + NKQ * LDA;
+        const int kq = KK == 9 ? h * 9 + g : 2 * g + h;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) av[i] = As[kq * LDA + (wm * TM + i) * 32 + l32];
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            bv[j] = KK == 9 ? Bs[h * LDB + bpos[j] + (g / 3) * IW + g % 3] : Bs[(2 * g + h) * LDB + bpos[j]];
+    };
+    // One step.  A wavefront issues in order and mostly has the matrix pipe to itself, so whatever it
+    // issues in a row for longer than one matrix instruction takes (64 cycles) leaves the pipe idle.
+    // Everything else is therefore dealt out between the multiplies, TM * TN of them a slot: the next
+    // step's loads one by one over the first slots (1x1: all in the first, as the step is short
+    // and would wait for the last of them), their writes to the other buffer over the last
+    // ones in the same order (a wait then covers the oldest load only), the next group's operands one slot
+    // into the group.  The scheduling barriers keep the compiler from gathering them again.
+    auto step = [&](auto load, auto store, const f4 *As, f4 *other, int c0) __attribute__((always_inline)) {
+        constexpr bool LOAD = decltype(load)::value, STORE = decltype(store)::value;
+        f4 av[2][TM], bv[2][TN];
+        read_group(As, 0, av[0], bv[0]);
+#pragma unroll
+        for (int x = 0; x < SLOTS; ++x) {
+            const int g = x / 4, t = x % 4;
+            if (t == 1 && g + 1 < G) read_group(As, g + 1, av[(g + 1) & 1], bv[(g + 1) & 1]);
+            if (LOAD && KK == 1 && x == 0) {
+#pragma unroll
+                for (int i = 0; i < NB; ++i) load_b(i, c0 + CH);
+#pragma unroll
+                for (int i = 0; i < NA; ++i) load_a(i, c0 + CH);
+            } else if (LOAD && KK == 9) {
+#pragma unroll
+                for (int i = x * PER; i < (x + 1) * PER && i < NI; ++i) {
+                    if (i < NB) load_b(i, c0 + CH);
+                    else load_a(i - NB, c0 + CH);
+                }
+            }
+            if (STORE) {
+                constexpr int first = SLOTS - (NI + PER - 1) / PER;
+#pragma unroll
+                for (int i = (x - first) * PER; i >= 0 && i < (x - first + 1) * PER && i < NI; ++i) {
+                    if (i < NB) store_b(i, other);
+                    else store_a(i - NB, other);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[g & 1][i][t], bv[g & 1][j][t], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+    };
+    constexpr std::integral_constant<bool, true> yes{};
+    constexpr std::integral_constant<bool, false> no{};
+    f4 *cur = lds, *other = lds + BUF;
+    auto swap = [&]() { f4 *x = cur; cur = other; other = x; };
+    int c0 = 0;
+    for (; c0 + 2 * CH <= a.Cin; c0 += CH) {
+        step(yes, yes, cur, other, c0);
+        swap();
+    }
+    if (c0 + CH < a.Cin) {
+        load_rest(c0 + CH);
+        step(no, yes, cur, other, c0);
+        swap();
+    }
+    step(no, no, cur, other, c0);
+    // ---- epilogue: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32 ----
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int e = (wn * TN + j) * 32 + l32;
+        if (q0 + e >= a.NP) continue;
+        const int dn = (int)((p0 + (uint32_t)e) / (uint32_t)a.P);
+        float *ybase = a.Y + (size_t)(n0 + dn) * a.Cout * a.P + (p0 + (uint32_t)e - (uint32_t)dn * (uint32_t)a.P);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int o = m0 + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+                if (o < a.Cout) ybase[(size_t)o * a.P] = acc[i][j][r] + (a.bias ? a.bias[o] : 0.f);
+            }
+    }
+}
+
+constexpr int BK = 16;
+
+// Shapes the patch kernel does not take - images wider than its staging, or whose tile spans more than
+// 2^31 elements of the input: the patch matrix gathered word by word, 64 x 128 tiles, steps of 16 rows of
+// K through a two-deep LDS buffer.
+__global__ void __launch_bounds__(256) k_dense_gather(const DenseArgs a) {
+    constexpr int BN = 128, BM = 64, LDA = BM + 4;
     constexpr int TM = BM / 64;  // 32x32 tiles per wavefront along M
     constexpr int A_ROWS_PER_PASS = 128;  // 256 threads / 2
     constexpr int NA = (BM + A_ROWS_PER_PASS - 1) / A_ROWS_PER_PASS;  // weight-tile passes per thread
@@ -64,13 +353,7 @@ __global__ void __launch_bounds__(256) k_dense(const DenseArgs a) {
 
     // weight tile: thread -> (row of W, half of the 16 k's)
     const int a_row = tid >> 1, a_k = (tid & 1) * 8;
-    // patch tile, vector form (1x1, stride 1, P % 4 == 0): thread -> (k row, pixel quad)
-    const int bq = tid & 31, bk0 = tid >> 5;  // 32 quads x 8 rows per pass
-    long long vq = q0 + bq * 4;
-    const bool vvalid = vq < a.NP;
-    const int vn = vvalid ? (int)(vq / a.P) : 0;
-    const int vp = vvalid ? (int)(vq - (long long)vn * a.P) : 0;
-    // patch tile, gather form: thread -> (pixel column, k rows tid/128 + 2*i)
+    // patch tile: thread -> (pixel column, k rows tid/128 + 2*i)
     const int gcol = tid & 127, gk0 = tid >> 7;
     const long long gq = q0 + gcol;
     const bool gvalid = gq < a.NP;
@@ -86,8 +369,7 @@ __global__ void __launch_bounds__(256) k_dense(const DenseArgs a) {
     int gc = gk0 / kk, gtap = gk0 - gc * kk;
 
     float ra[NA][8];   // the step's weights: 8 consecutive k of one row of W per pass
-    f4 rbv[2];         // vector form: two rows of the patch tile
-    float rbg[8];      // gather form: 8 rows of one pixel column
+    float rbg[8];      // 8 rows of one pixel column
 
     auto load_tiles = [&](int k0) {
 #pragma unroll
@@ -108,15 +390,7 @@ __global__ void __launch_bounds__(256) k_dense(const DenseArgs a) {
                 }
             }
         }
-        if constexpr (PW_VEC) {
-#pragma unroll
-            for (int pass = 0; pass < 2; ++pass) {
-                const int c = k0 + bk0 + pass * 8;
-                rbv[pass] = f4{0, 0, 0, 0};
-                if (vvalid && c < a.K)
-                    rbv[pass] = *reinterpret_cast<const f4 *>(a.X + ((size_t)vn * a.Cin + c) * a.P + vp);
-            }
-        } else {
+        {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 float v = 0.f;
@@ -142,11 +416,7 @@ __global__ void __launch_bounds__(256) k_dense(const DenseArgs a) {
                 for (int i = 0; i < 8; ++i) As[buf][(a_k + i) * LDA + row] = ra[pass][i];
             }
         }
-        if constexpr (PW_VEC) {
-#pragma unroll
-            for (int pass = 0; pass < 2; ++pass)
-                *reinterpret_cast<f4 *>(&Bs[buf][(bk0 + pass * 8) * BN + bq * 4]) = rbv[pass];
-        } else {
+        {
 #pragma unroll
             for (int i = 0; i < 8; ++i) Bs[buf][(gk0 + 2 * i) * BN + gcol] = rbg[i];
         }
@@ -197,6 +467,26 @@ __global__ void __launch_bounds__(256) k_dense(const DenseArgs a) {
     }
 }
 
+// Tile shapes, with the rate the matrix work of a tile runs at against the largest tile's: measured on
+// 3x3 layers with 64 to 512 channels at stride 1 and (`wide`, more than 512 staged positions a tile,
+// which a stride of 2 or a wide image has) 2, and on 1x1 layers with 16 to 1024.  3x3 at 64 pixels a
+// tile, and larger 1x1 tiles, were slower than a shape listed here (1x1: or as fast).
+struct DenseShape {
+    int bm, bn;
+    double rate, wide;
+};
+static const DenseShape kShapes3x3[] = {{128, 128, 1.0, 0.97}, {64, 128, 0.97, 0.85}, {32, 128, 0.90, 0.72}};
+static const DenseShape kShapes1x1[] = {{64, 64, 1.0, 0}, {32, 128, 0.90, 0}};
+
+template <int NPT>
+static auto pick_3x3(int BM) -> void (*)(const DenseArgs) {
+    return BM == 128 ? k_dense<128, 128, 9, NPT> : BM == 64 ? k_dense<64, 128, 9, NPT> : k_dense<32, 128, 9, NPT>;
+}
+static auto pick_dense(int kernel, int BM, int npt) -> void (*)(const DenseArgs) {
+    if (kernel == 3) return npt == 2 ? pick_3x3<2>(BM) : npt == 3 ? pick_3x3<3>(BM) : pick_3x3<4>(BM);
+    return BM == 64 ? k_dense<64, 64, 1, 1> : k_dense<32, 128, 1, 1>;
+}
+
 }  // namespace alcs
 
 using namespace alcs;
@@ -221,23 +511,43 @@ extern "C" int alcs_dense_conv(const float *W_dev, const float *X_dev, const flo
     a.N = N; a.Cin = Cin; a.Cout = Cout; a.H = H; a.W = W; a.Ho = Ho; a.Wo = Wo;
     a.stride = stride; a.k = kernel; a.P = (int)P; a.Pin = (int)Pin; a.K = (int)K;
     a.NP = (long long)N * P;
-    const bool vec = kernel == 1 && stride == 1 && (P % 4 == 0);
-    const long long ntile = (a.NP + BN - 1) / BN;
-    // 128 output channels per workgroup, or 64 when that leaves fewer workgroups than compute units
     int cus = 0, xcds = 0;
     if (current_device_shape(&cus, &xcds) != ALCS_OK) return ALCS_E_HIP;
-    const int BM = (Cout > 64 && ntile * ((Cout + 127) / 128) >= cus) ? 128 : 64;
+    a.xcds = xcds;
+    // The tile whose launch gives the most loaded compute unit the least matrix work, at the shape's rate.
+    // (512 channels, 7x7, N = 64: 307 us on 128 x 128 tiles, 187 on 32 x 128; 40 -> 23 @112x86:
+    // 653 and 175.)  3x3 also needs a tile's input rows to fit its staging.
+    const DenseShape *best = nullptr, *shapes = kernel == 3 ? kShapes3x3 : kShapes1x1;
+    double best_cost = 0;
+    for (int i = 0; i < (kernel == 3 ? 3 : 2); ++i) {
+        const DenseShape &sh = shapes[i];
+        const long long rows = std::min<long long>((sh.bn + Wo - 2) / Wo + 1, (long long)N * Ho);  // output rows a tile can touch
+        const long long images = std::min<long long>((rows + Ho - 2) / Ho + 1, N);
+        const long long npos = kernel == 3 ? (rows * stride + images * (3 - stride)) * ((Wo - 1) * (long long)stride + 3) : 0;
+        if (npos > 256 * kPosPerThread) continue;
+        if ((images + 1) * (long long)Cin * Pin >= (1LL << 29) || K * sh.bm >= (1LL << 29)) continue;  // byte offsets are 32 bits
+        const long long tiles = ((a.NP + sh.bn - 1) / sh.bn) * ((Cout + sh.bm - 1) / sh.bm);
+        const double cost = (double)((tiles + cus - 1) / cus) * sh.bm * sh.bn / (npos > 512 ? sh.wide : sh.rate);
+        if (!best || cost < best_cost) { best = &sh; best_cost = cost; a.npos = (int)npos; }
+    }
+    const int BM = best ? best->bm : 64, BN = best ? best->bn : 128;
+    const long long ntile = (a.NP + BN - 1) / BN;
     a.mt = (Cout + BM - 1) / BM;
     const long long total = ntile * a.mt;
     if (total > (1LL << 30)) return ALCS_E_UNSUPPORTED;
     a.nt = (int)ntile;
     a.total_wgs = (int)total;
-    a.xcds = xcds;
     a.wg_per_xcd = (int)((total + xcds - 1) / xcds);
-    void (*kern)(const DenseArgs) = nullptr;
-    if (BM == 128) kern = vec ? k_dense<128, true> : k_dense<128, false>;
-    else kern = vec ? k_dense<64, true> : k_dense<64, false>;
-    hipLaunchKernelGGL(kern, dim3(a.wg_per_xcd * xcds), dim3(256), 0, (hipStream_t)stream, a);
+    void (*kern)(const DenseArgs) = k_dense_gather;
+    int lds = 0;
+    if (best) {
+        const int npt = kernel == 1 ? 1 : a.npos <= 512 ? 2 : a.npos <= 768 ? 3 : 4;
+        lds = 2 * 16 * (kernel == 3 ? 18 * (BM + 1) + 512 * npt : 4 * (BM + 1) + 4 * BN);
+        kern = pick_dense(kernel, BM, npt);
+        const int rc = allow_lds((const void *)kern, lds);
+        if (rc != ALCS_OK) return rc;
+    }
+    hipLaunchKernelGGL(kern, dim3(a.wg_per_xcd * xcds), dim3(256), lds, (hipStream_t)stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_hip_error((int)e); return ALCS_E_HIP; }
     return ALCS_OK;

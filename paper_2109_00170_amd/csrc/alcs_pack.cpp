@@ -10,6 +10,7 @@
 #include <map>
 #include <new>
 #include <numeric>
+#include <set>
 
 #include "alcs_internal.h"
 
@@ -46,6 +47,18 @@ int current_device_shape(int *cus, int *xcds) {
     const hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) { set_hip_error((int)e); return ALCS_E_HIP; }
     device_shape(dev, cus, xcds);
+    return ALCS_OK;
+}
+
+int allow_lds(const void *kernel, int bytes) {
+    if (bytes <= 64 * 1024) return ALCS_OK;
+    static std::mutex mu;
+    static std::set<const void *> done;
+    std::lock_guard<std::mutex> lock(mu);
+    if (done.count(kernel)) return ALCS_OK;
+    const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) { set_hip_error((int)e); return ALCS_E_HIP; }
+    done.insert(kernel);
     return ALCS_OK;
 }
 
