@@ -7,9 +7,11 @@
 // neighbouring lanes share taps (alcs_dw_taps.h).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "alcs_internal.h"
+#include "alcs_dw_strip.h"
 #include "alcs_dw_taps.h"
 
 namespace alcs {
@@ -20,7 +22,9 @@ struct DwArgs {
     const float *bias;  // [C] or null
     float *Z;           // [N, C, Ho, Wo]
     long long planes;   // N * C
-    int nchunks;        // 64-pixel chunks per plane
+    int nchunks;        // 64-pixel chunks (k_depthwise_rows: row ranges) per plane
+    int rows, planes_per_wave;  // k_depthwise_rows: rows and planes a wavefront covers,
+    int cblocks;                // and how many wavefronts share a row (more than 256 outputs wide)
     unsigned wg_per_xcd, total_wgs, xcds;
     int C, H, W, Ho, Wo, P, Pin, stride, act;
 };
@@ -82,75 +86,64 @@ __global__ void __launch_bounds__(256) k_depthwise(const DwArgs a) {
     }
 }
 
-// Stride 1 and a width that is a multiple of 4: a lane owns four consecutive pixels of a row, so
-// every tap row is one aligned 16-byte load plus its left and right neighbour, and the outputs
-// leave as one 16-byte store - a quarter of the memory instructions of the kernel above.  The
-// neighbours beyond the image are read from the row's own end (in bounds) and zeroed.
-typedef float dw_f4 __attribute__((ext_vector_type(4)));
-
-constexpr int kPlanesPerWaveQuad = 2;  // few planes per wavefront: four pixels per lane leave few wavefronts
-
-__global__ void __launch_bounds__(256) k_depthwise_quad(const DwArgs a) {
+// Images at least 4 wide: a lane owns four pixels of an output row (alcs_dw_strip.h) and a wavefront
+// covers the rows of as many planes as fit - four of 7x7, one of 14x14 - or some rows of one plane.
+// The layer moves its bytes once; what bounds it is the way there and back: on small tensors one trip to
+// memory and the launch (512 channels, 14x14, one image: 2.85 us, 4.9 with the
+// form above), on large ones the bytes (32 channels, 112x112, N=32: 25 us for 103 MB, 31.5 with four
+// pixels a lane and nine loads).  NU: units per wavefront whose loads are in flight together.
+template <int S, int NU>
+__global__ void __launch_bounds__(256) k_depthwise_rows(const DwArgs a) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // (the workgroup order, as above: neighbouring row ranges of a plane on one XCD)
     const unsigned logical = (blockIdx.x % a.xcds) * a.wg_per_xcd + blockIdx.x / a.xcds;
     if (logical >= a.total_wgs) return;
-    const unsigned chunk = logical % (unsigned)a.nchunks;
-    const long long pg = (long long)(logical / (unsigned)a.nchunks) * 4 + wave;
-    const long long p0 = pg * kPlanesPerWaveQuad;
-    if (p0 >= a.planes) return;  // the whole wavefront
-    const int po = ((int)chunk * 64 + lane) * 4;
-    const bool valid = po < a.P;
-    const int ho = valid ? po / a.W : 0, wo = valid ? po - ho * a.W : 0;   // stride 1: Wo == W
-    bool rok[3];
-    uint32_t roff[3], loff[3], qoff[3];
+    const int QW = (a.Wo + 3) >> 2, CW = a.planes_per_wave;
+    const bool wide = a.cblocks > 1;             // rows in blocks of 62 quads, a lane on each side for the neighbours
+    const int LPC = wide ? 64 : a.rows * QW;
+    const int pl = min(lane / LPC, CW - 1), item = lane - lane / LPC * LPC;
+    const int r = wide ? 0 : item / QW;
+    typename DwStrip<S>::Raw v[NU];
+    DwStrip<S> st;
+    float w[NU][9], b[NU];
+    long long plane[NU];
+    int row[NU], qx[NU];
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        const int hi = ho - 1 + r;
-        rok[r] = valid && hi >= 0 && hi < a.H;
-        const uint32_t at = (uint32_t)(min(max(hi, 0), a.H - 1) * a.W + wo);
-        roff[r] = at * 4u;
-        loff[r] = (wo > 0 ? at - 1u : at) * 4u;
-        qoff[r] = (wo + 4 < a.W ? at + 4u : at + 3u) * 4u;
+    for (int u = 0; u < NU; ++u) {
+        const unsigned unit = (logical * 4 + (unsigned)wave) * NU + u;  // (plane group, row range): ranges are neighbours
+        const unsigned chunk = unit % (unsigned)a.nchunks;
+        // groups past the last, and the last one's planes past the end, take the last planes once more
+        const long long p0 = min((long long)(unit / (unsigned)a.nchunks) * CW, a.planes - CW);
+        plane[u] = p0 + pl;
+        const int rc = wide ? (int)(chunk / (unsigned)a.cblocks) : (int)chunk;
+        row[u] = rc * a.rows + r;
+        qx[u] = wide ? ((int)chunk - rc * a.cblocks) * 62 + lane - 1 : item - r * QW;
+        st.init((uint32_t)pl * a.Pin, min(max(qx[u], 0), QW - 1), min(row[u], a.Ho - 1), a.H, a.W);
+        st.load(a.X + (size_t)p0 * a.Pin, v[u]);
+        const float *wp;
+        const unsigned c = (unsigned)(plane[u] % a.C);
+        wp = a.D + (size_t)c * 9;
+        const dws_f4 w0 = *reinterpret_cast<const dws_f4u *>(wp), w1 = *reinterpret_cast<const dws_f4u *>(wp + 4);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) { w[u][t] = w0[t]; w[u][4 + t] = w1[t]; }
+        w[u][8] = wp[8];
+        b[u] = a.bias ? a.bias[c] : 0.f;
     }
-    const bool hasl = wo > 0, hasr = wo + 4 < a.W;
-    const auto wts = reinterpret_cast<const float __attribute__((address_space(4))) *>((uintptr_t)a.D);
-    const auto bs = reinterpret_cast<const float __attribute__((address_space(4))) *>((uintptr_t)a.bias);
-    const int c0 = __builtin_amdgcn_readfirstlane((int)(p0 % a.C));
-    const long long left = a.planes - p0;
-    const int np = left < kPlanesPerWaveQuad ? (int)left : kPlanesPerWaveQuad;
 #pragma unroll
-    for (int i = 0; i < kPlanesPerWaveQuad; ++i) {
-        if (i >= np) break;  // wave-uniform
-        const int c = __builtin_amdgcn_readfirstlane((c0 + i) % a.C);
-        const char *b = reinterpret_cast<const char *>(a.X + (size_t)(p0 + i) * a.Pin);
-        float x[3][6];
+    for (int u = 0; u < NU; ++u) {
+        const bool mine = wide ? lane > 0 && lane < 63 && qx[u] < QW : lane < CW * LPC;
+        const int nout = mine ? min(4, a.Wo - 4 * qx[u]) : 0;
+        if (NU > 1) st.init(0, min(max(qx[u], 0), QW - 1), min(row[u], a.Ho - 1), a.H, a.W);
+        const dws_f4 o = st.filter(v[u], w[u], b[u], a.act);
+        if (row[u] >= a.Ho) continue;
+        float *d = a.Z + (size_t)plane[u] * a.P + (size_t)row[u] * a.Wo + 4 * qx[u];
+        if (nout == 4) __builtin_nontemporal_store((dws_f4u)o, reinterpret_cast<dws_f4u *>(d));
+        else {
 #pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const dw_f4 m = *reinterpret_cast<const dw_f4 *>(b + roff[r]);
-            const float l = *reinterpret_cast<const float *>(b + loff[r]);
-            const float q = *reinterpret_cast<const float *>(b + qoff[r]);
-            x[r][0] = (rok[r] && hasl) ? l : 0.f;
-            x[r][1] = rok[r] ? m[0] : 0.f;
-            x[r][2] = rok[r] ? m[1] : 0.f;
-            x[r][3] = rok[r] ? m[2] : 0.f;
-            x[r][4] = rok[r] ? m[3] : 0.f;
-            x[r][5] = (rok[r] && hasr) ? q : 0.f;
+            for (int j = 0; j < 3; ++j)
+                if (j < nout) __builtin_nontemporal_store(o[j], d + j);
         }
-        const float bias = a.bias ? bs[c] : 0.f;
-        dw_f4 o;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float acc = bias;   // taps in the order (r, t) ascending, as in the other forms
-#pragma unroll
-            for (int r = 0; r < 3; ++r)
-#pragma unroll
-                for (int t = 0; t < 3; ++t) acc = fmaf(wts[c * 9 + r * 3 + t], x[r][j + t], acc);
-            if (a.act >= 1) acc = fmaxf(acc, 0.f);
-            if (a.act == 2) acc = fminf(acc, 6.f);
-            o[j] = acc;
-        }
-        if (valid) __builtin_nontemporal_store(o, reinterpret_cast<dw_f4 *>(a.Z + (size_t)(p0 + i) * a.P + po));
     }
 }
 
@@ -173,21 +166,38 @@ extern "C" int alcs_depthwise_conv(const float *dw_weights_dev, const float *X_d
     DwArgs a{};
     a.D = dw_weights_dev; a.X = X_dev; a.bias = bias_dev; a.Z = Y_dev;
     a.planes = (long long)N * C;
-    const bool quad = stride == 1 && (W % 4) == 0 && ((((uintptr_t)X_dev) | ((uintptr_t)Y_dev)) & 15) == 0;
-    a.nchunks = (int)((P + (quad ? 255 : 63)) / (quad ? 256 : 64));
     a.C = C; a.H = H; a.W = W; a.Ho = Ho; a.Wo = Wo; a.P = (int)P; a.Pin = (int)Pin;
     a.stride = stride; a.act = activation;
-    const int ppw = quad ? kPlanesPerWaveQuad : kPlanesPerWave;
-    const long long groups = (a.planes + 4 * ppw - 1) / (4 * ppw);
-    const long long blocks = groups * a.nchunks;
-    if (blocks > INT32_MAX - 256) return ALCS_E_UNSUPPORTED;
     int cus = 0, xcds = 0;
     if (current_device_shape(&cus, &xcds) != ALCS_OK) return ALCS_E_HIP;
+    const int QW = (Wo + 3) / 4;
+    void (*kern)(const DwArgs) = nullptr;
+    long long blocks = 0;
+    // (rows wider than 256 outputs leave lanes idle at the block edges: at stride 2 the form that shares
+    // taps is then faster where it applies, 15.2 against 16.1 us for 24 channels of 200x600, N=4)
+    if (W >= 4 && (QW <= 64 || dw_mode_for(stride, W, X_dev) != kDwPair)) {
+        a.cblocks = QW <= 64 ? 1 : (QW + 61) / 62;
+        a.rows = QW <= 64 ? std::min(Ho, 64 / QW) : 1;
+        a.planes_per_wave = (int)std::min<long long>(a.cblocks == 1 && a.rows == Ho ? 64 / (a.rows * QW) : 1, a.planes);
+        const long long nchunks = (long long)((Ho + a.rows - 1) / a.rows) * a.cblocks;
+        const long long groups = (a.planes + a.planes_per_wave - 1) / a.planes_per_wave;
+        const bool two = groups > 64LL * cus / nchunks;   // more units than the compute units hold wavefronts
+        if (nchunks <= INT32_MAX && groups <= (1LL << 26) / nchunks) {
+            a.nchunks = (int)nchunks;
+            blocks = (groups * nchunks + (two ? 7 : 3)) / (two ? 8 : 4);
+            kern = stride == 1 ? (two ? k_depthwise_rows<1, 2> : k_depthwise_rows<1, 1>)
+                               : (two ? k_depthwise_rows<2, 2> : k_depthwise_rows<2, 1>);
+        }
+    }
+    if (!kern) {  // narrower images, and tensors of more units than a grid takes
+        a.nchunks = (int)((P + 63) / 64);
+        blocks = (a.planes + 4 * kPlanesPerWave - 1) / (4 * kPlanesPerWave) * a.nchunks;
+        if (blocks > INT32_MAX - 256) return ALCS_E_UNSUPPORTED;
+        kern = dw_mode_for(stride, W, X_dev) == kDwPair ? k_depthwise<kDwPair> : k_depthwise<kDwNine>;
+    }
     a.total_wgs = (unsigned)blocks;
     a.xcds = (unsigned)xcds;
     a.wg_per_xcd = (unsigned)((blocks + xcds - 1) / xcds);
-    const int mode = dw_mode_for(stride, W, X_dev);
-    void (*kern)(const DwArgs) = quad ? k_depthwise_quad : mode == kDwPair ? k_depthwise<kDwPair> : k_depthwise<kDwNine>;
     hipLaunchKernelGGL(kern, dim3(a.wg_per_xcd * a.xcds), dim3(256), 0, (hipStream_t)stream, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_hip_error((int)e); return ALCS_E_HIP; }

@@ -31,6 +31,7 @@
 
 #include "alcs_internal.h"
 #if ALCS_DW_STAGE
+#include "alcs_dw_strip.h"
 #include "alcs_dw_taps.h"
 #endif
 
@@ -200,6 +201,7 @@ struct ConvArgs {
     const float *dw_bias;  // [Cin] or null
     int dw_stride, dw_act;
     int dw_mode;           // DwMode: how lanes share taps
+    int dw_rows;           // tiles are this many whole rows (stage_dw_rows), or 0 (stage_dw_mode)
 #endif
 };
 
@@ -772,9 +774,93 @@ __device__ __forceinline__ void stage_dw_mode(const ConvArgs &a, float *lds, int
     }
 }
 
+// The same for tiles of a.dw_rows whole output rows: a lane works out four neighbouring pixels of a
+// row (alcs_dw_strip.h), the lanes of a wavefront cover the tile's rows for as many channels as fit -
+// 8 channels of 2 rows of 14, one channel of 4 rows of 56.  The form above is a chain of nine loads,
+// a wait and one write per channel and pixel, 16 times in a row at 512 channels on 32 pixels; this
+// one is bound by the bytes of the rows (three input rows per output row, out of L1 and L2).
+template <int TP, int S>
+__device__ __forceinline__ void stage_dw_rows_s(const ConvArgs &a, float *lds, int q0, int q_end) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+    const int QW = (a.Wo + 3) >> 2;              // lanes per row
+    const int RW = min(a.dw_rows, 64 / QW);      // rows per pass
+    const int LPC = RW * QW;                     // lanes per channel
+    const int CW = min(64 / LPC, a.Cin);         // channels per wavefront
+    const int ngrp = (a.Cin + CW - 1) / CW;
+    const bool uniform = CW == 1;
+    const int cl = min(lane / LPC, CW - 1), item = lane - lane / LPC * LPC;
+    const int r = item / QW, qx = item - r * QW;
+    const int R0 = q0 / a.Wo, n0 = R0 / a.Ho;    // the tile's first row and image
+    const int nrow = (q_end - q0) / a.Wo;        // rows of the tile that are there
+    const int nout = lane < CW * LPC ? min(4, a.Wo - 4 * qx) : 0;
+    const float *src = a.X + (size_t)n0 * a.Cin * a.Pin;
+    const float *wl = a.dw_w + (size_t)cl * 9;
+    const auto ws = as_const(a.dw_w);
+    for (int row0 = 0; row0 < nrow; row0 += RW) {
+        const int rr = row0 + r;
+        const int R = R0 + min(rr, nrow - 1), n = R / a.Ho;
+        DwStrip<S> st;
+        st.init(((uint32_t)(n - n0) * a.Cin + cl) * a.Pin, qx, R - n * a.Ho, a.H, a.W);
+        float *dst = lds + cl * TP + rr * a.Wo + 4 * qx;
+        const int put = rr < nrow && r < RW ? nout : 0;
+        const bool whole = put == 4 && (a.Wo & 3) == 0;
+        auto weights = [&](int c, float (&w)[9], float &b) __attribute__((always_inline)) {
+            if (uniform) {
+#pragma unroll
+                for (int t = 0; t < 9; ++t) w[t] = ws[(size_t)c * 9 + t];
+                b = a.dw_bias ? as_const(a.dw_bias)[c] : 0.f;
+            } else {
+                const float *p = wl + (size_t)c * 9;
+                const f4 w0 = *reinterpret_cast<const f4u *>(p), w1 = *reinterpret_cast<const f4u *>(p + 4);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) { w[t] = w0[t]; w[4 + t] = w1[t]; }
+                w[8] = p[8];
+                b = a.dw_bias ? a.dw_bias[c + cl] : 0.f;
+            }
+        };
+        auto finish = [&](int c, const typename DwStrip<S>::Raw &v, const float (&w)[9], float b) __attribute__((always_inline)) {
+            const dws_f4 o = st.filter(v, w, b, a.dw_act);
+            float *d = dst + c * TP;
+            if (whole) *reinterpret_cast<f4 *>(d) = o;
+            else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (j < put) d[j] = o[j];
+            }
+        };
+        // (the last wavefront's channels end with the tensor's: some are worked out twice)
+        auto first_channel = [&](int g) { return min(g * CW, a.Cin - CW); };
+        constexpr int U = S == 1 ? 2 : 1;
+        int g = wave;
+        for (; g + (U - 1) * nw < ngrp; g += U * nw) {
+            typename DwStrip<S>::Raw v[U];
+            float w[U][9], b[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int c = first_channel(g + u * nw);
+                st.load(src + (size_t)c * a.Pin, v[u]);
+                weights(c, w[u], b[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) finish(first_channel(g + u * nw), v[u], w[u], b[u]);
+        }
+        for (; U > 1 && g < ngrp; g += nw) {
+            typename DwStrip<S>::Raw v;
+            float w[9], b;
+            const int c = first_channel(g);
+            st.load(src + (size_t)c * a.Pin, v);
+            weights(c, w, b);
+            finish(c, v, w, b);
+        }
+    }
+}
+
 template <int TP>
 __device__ __forceinline__ void stage_dw(const ConvArgs &a, float *lds, int q0, int q_end) {
-    if (a.dw_mode == kDwPair) stage_dw_mode<TP, kDwPair>(a, lds, q0, q_end);
+    if (a.dw_rows > 0 && a.dw_stride == 1) stage_dw_rows_s<TP, 1>(a, lds, q0, q_end);
+    else if (a.dw_rows > 0) stage_dw_rows_s<TP, 2>(a, lds, q0, q_end);
+    else if (a.dw_mode == kDwPair) stage_dw_mode<TP, kDwPair>(a, lds, q0, q_end);
     else stage_dw_mode<TP, kDwNine>(a, lds, q0, q_end);
 }
 #endif
@@ -1114,7 +1200,6 @@ __global__ void __launch_bounds__(1024) k_pw_resident_res(const ConvArgs a) {
     pw_resident_body<V, PV, MF, AC, 1, V * PV <= 16 && MF ? kAhead : kBehind>(a);
 }
 
-#if !ALCS_DW_STAGE
 // Mode 1, split: the resident kernel for launches with fewer bundles per workgroup than wavefronts -
 // small batches and fully connected layers, where the pixel tiles are few and the bundles are dealt
 // to as many workgroups as there are compute units.  Such a launch is a chain of latencies (launch,
@@ -1158,7 +1243,11 @@ __global__ void __launch_bounds__(1024) k_pw_split(const ConvArgs a) {
             if ((v / UV) % ks == part && a.bias && g >= 0 && g * V + v < a.Cout) sb.b[v] = a.bias[g * V + v];
         }
     }
+#if ALCS_DW_STAGE
+    if (!skip(a, 1)) stage_dw<TP>(a, lds, q0, q_end);
+#else
     if (!skip(a, 1)) stage_pw<TP, AC>(a, lds, q0, 0, a.Cin, q_end);
+#endif
     for (int t = tid; t < 2 * TP; t += blockDim.x) lds[a.KC * TP + t] = 0.f;
     __syncthreads();
     const int plane = lane & (64 / GS - 1);
@@ -1203,7 +1292,6 @@ __global__ void __launch_bounds__(1024) k_pw_split(const ConvArgs a) {
         }
     }
 }
-#endif
 
 #if !ALCS_RESIDENT_ONLY
 // Mode 2: input channels streamed through LDS in chunks of KC; every wavefront owns
@@ -1775,7 +1863,6 @@ static kern_t pick_resident(int pv, Access ac, int gs, bool res = false) {
     return pick_resident_ac<V, MF, kUnaligned>(pv, gs, res);
 }
 
-#if !ALCS_DW_STAGE
 template <int V, int AC>
 static kern_t pick_split_ac(int pv, int gs) {
     if (gs == 4) return pv == 2 ? k_pw_split<V, 2, AC, 4> : k_pw_split<V, 1, AC, 4>;
@@ -1784,11 +1871,12 @@ static kern_t pick_split_ac(int pv, int gs) {
 template <int V>
 static kern_t pick_split(int pv, Access ac, int gs) {
     if (ac == kAligned) return pick_split_ac<V, kAligned>(pv, gs);
-    if (ac == kStrided) return pick_split_ac<V, kStrided>(pv, gs);
-    if (ac == kRows) return pick_split_ac<V, kRows>(pv, gs);
+    if constexpr (!kDw) {
+        if (ac == kStrided) return pick_split_ac<V, kStrided>(pv, gs);
+        if (ac == kRows) return pick_split_ac<V, kRows>(pv, gs);
+    }
     return pick_split_ac<V, kUnaligned>(pv, gs);
 }
-#endif
 
 #if !ALCS_RESIDENT_ONLY
 template <int V, bool MF, int AC>
@@ -2082,7 +2170,19 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             // pixels per lane - the widest tile whose Cin+1 rows stay below ~68 KB (two
             // workgroups per compute unit) and that still leaves >= 1.5 workgroups per
             // compute unit: wider tiles mean longer contiguous runs for loads and stores.
-            constexpr int kTwoPerCu = 68 * 1024;
+            constexpr int kTwoPerCu = (kDw ? 80 : 68) * 1024;
+            // Depthwise stage: tiles are whole rows where rows fill at least three quarters of a tile (and
+            // quads stay aligned); else, or when asked for full tiles, any pixels of the flattened axis.
+            auto rows_of = [&](int tp) {
+                if (!kDw || T.full_tiles || T.dw_own_taps || W < 4) return 0;
+                int R = (int)std::min<long long>(tp / Wo, (long long)N * Ho);
+                while (R > 0 && ac == kAligned && (R * Wo) % 4 && R < N * Ho) --R;
+                const long long images = std::min<long long>((R + Ho - 2) / Ho + 1, N);
+                if ((images * (long double)Cin + 64) * Pin * 4 >= 4.0e9L) return 0;  // 32-bit byte offsets
+                return 4 * R * Wo >= 3 * tp || R == N * Ho ? R : 0;
+            };
+            const bool dw_s2 = kDw && dw->stride == 2;
+            auto pixels_of = [&](int tp) { const int R = rows_of(tp); return R ? R * Wo : tp; };
             const int kMinWgs = 3 * kCUs / 2;
             const int GS = L.GS, NB = L.nbundles;
             if (GS > 1 && !mfma) return ALCS_E_UNSUPPORTED;  // the packer pairs groups only for V >= 4
@@ -2090,16 +2190,16 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             if (GS == 1) {
                 for (int cand = pv_most; cand >= 2; cand >>= 1) {
                     const long long need = (long long)(Cin + 1) * 64 * cand * 4;
-                    const long long tiles = ((long long)a.NP + 64 * cand - 1) / (64 * cand);
-                    if (need <= kTwoPerCu && tiles * (cand == 2 ? 2 : 1) >= kMinWgs) { pv = cand; break; }
+                    const long long tiles = ceil_div(a.NP, pixels_of(64 * cand));
+                    if (need <= kTwoPerCu && tiles * (cand == 2 && !dw_s2 ? 2 : 1) >= kMinWgs) { pv = cand; break; }
                 }
                 // Or a still wider tile with one workgroup per compute unit (up to 160 KB), when
                 // pixel tiles x group tiles then make a single round that keeps at least 3/4 of the
                 // compute units busy: one wide workgroup beats two narrow ones that share a
                 // compute unit (28x28 and 14x14 layers at batch 32: 5-11 % faster).
-                for (int cand = pv_most; cand > pv; cand >>= 1) {
+                for (int cand = dw_s2 ? 1 : pv_most; cand > pv; cand >>= 1) {
                     const long long need = (long long)(Cin + 1) * 64 * cand * 4;
-                    const long long tiles = ((long long)a.NP + 64 * cand - 1) / (64 * cand);
+                    const long long tiles = ceil_div(a.NP, pixels_of(64 * cand));
                     if (need > kMaxLds || tiles > kCUs) continue;
                     const long long gts = std::min<long long>(std::max(1, NB / 4), std::max<long long>(1, kCUs / tiles));
                     if (tiles * gts >= 3 * kCUs / 4) { pv = cand; break; }
@@ -2116,8 +2216,9 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             const int TP = 64 * pv / GS;
             lds = (Cin + (GS > 1 ? 2 : 1)) * TP * 4;  // the rows and the zero row(s)
             if (lds > kMaxLds) return ALCS_E_UNSUPPORTED;
-            a.npt = ceil_div(a.NP, TP);
-            a.tile_px = TP;
+            int rows = rows_of(TP);
+            a.tile_px = rows ? rows * Wo : TP;
+            a.npt = ceil_div(a.NP, a.tile_px);
             // Group tiles: split the bundles over several workgroups only when there are too
             // few pixel tiles (every extra group tile re-stages the pixel tile's rows).  With
             // one resident workgroup per compute unit aim at one round (<= 256 workgroups),
@@ -2127,9 +2228,12 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             const int want = one_round ? kCUs : kMinWgs;
             // (with several groups per wavefront down to one bundle per workgroup: wavefronts then share
             // bundles, see k_pw_split)
-            const bool can_split = GS > 1 && !kDw && !(GS == 2 && pv == 2);
+            const bool can_split = GS > 1 && !(GS == 2 && pv == 2);
             const int most_gts = can_split ? NB : std::max(1, NB / 4);
             if (a.npt < want) ngt = std::min(most_gts, std::max(1, one_round ? want / a.npt : ceil_div(want, a.npt)));
+            // Depthwise stage: every group tile works out its pixel tile again, so at most two (see
+            // restage_ok below), and one from about 5/8 of the compute units on.
+            if (kDw && GS == 1 && rows && a.npt >= 80) ngt = std::min(most_gts, a.npt >= kCUs * 5 / 8 ? 1 : 2);
             if (T.group_tiles > 0) ngt = std::min(T.group_tiles, NB);
             a.gpt = ceil_div(NB, ngt);
             a.ngt = ceil_div(NB, a.gpt);
@@ -2142,12 +2246,21 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             // idle compute units (256->256 @28x28: 17.0 -> 17.5 us).
             if (GS > 1 && (long long)a.npt * a.ngt < kCUs && !T.full_tiles) {
                 const int tiles_wanted = kCUs / a.ngt;
-                const int tp = (ceil_div(a.NP, tiles_wanted) + 3) & ~3;
-                if (tp < TP && 2 * tp >= TP) {
+                int tp = (ceil_div(a.NP, tiles_wanted) + 3) & ~3;
+                if (rows) {
+                    int R = ceil_div(tp, Wo);
+                    while (ac == kAligned && (R * Wo) % 4) ++R;
+                    tp = R * Wo;
+                }
+                if (tp < a.tile_px && 2 * tp >= TP) {
                     a.tile_px = tp;
                     a.npt = ceil_div(a.NP, tp);
+                    if (rows) rows = tp / Wo;
                 }
             }
+#if ALCS_DW_STAGE
+            a.dw_rows = rows;
+#endif
             nw = lds > 40 * 1024 ? 16 : 8;
             // fewer wavefronts when the group tile has fewer bundles, but at least one per 8 KB
             // of tile (4 KB with four groups per wavefront, whose group tiles hold few
@@ -2174,10 +2287,19 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             // workgroup let two workgroups overlap their phases (four groups per wavefront, 86
             // registers: 512->128 @28x28, N=64: 55 -> 43 us; 512->512 @14x14, N=256: 97 -> 89 us;
             // 10 or 12 wavefronts measured no better than 16); a single round is faster with 16.
-            if (nw > 8 && (long long)a.npt * a.ngt > kCUs && 2 * lds <= kMaxLds && kernel_registers(kern) > 64) nw = 8;
+            // Depthwise stage on whole rows: it is most of the work where the groups are few, and every
+            // wavefront takes part in it, whatever the number of bundles - 16 in a single round, else as
+            // many as fit a compute unit over the workgroups whose tiles fit it (144->24 @56x56, N=128:
+            // 112 us with 6 wavefronts on 56-pixel tiles, 88 with 12 on 112).
+            if (kDw && GS == 1 && rows) {
+                const int regs = kernel_registers(kern);
+                const int per_cu = 4 * std::min(8, 512 / std::max(1, (regs + 7) & ~7)), wgs = kMaxLds / lds;
+                if ((long long)a.npt * a.ngt <= kCUs) nw = 16;
+                else if (wgs >= 4) nw = NB <= 4 ? 4 : 8;
+                else nw = std::min(dw_s2 ? 8 : 16, std::max(8, per_cu / wgs));
+            } else if (nw > 8 && (long long)a.npt * a.ngt > kCUs && 2 * lds <= kMaxLds && kernel_registers(kern) > 64) nw = 8;
             if (T.waves > 0) nw = std::min(T.waves, 16);
             if (ac == kStrided) nw = std::max(nw, TP / 64);  // a thread stages one pixel of the tile
-#if !ALCS_DW_STAGE
             // Wavefronts without a bundle of their own share the others': as many per bundle (a power of
             // two) as there are, and as its longest segment has runs of 16 columns.
             int ks = 1;
@@ -2187,7 +2309,6 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
                 lds = std::max(lds, nw * V * pv * 64 * 4);
                 kern = V == 4 ? pick_split<4>(pv, ac, GS) : V == 8 ? pick_split<8>(pv, ac, GS) : pick_split<16>(pv, ac, GS);
             }
-#endif
         } else {
 #if ALCS_RESIDENT_ONLY
             return ALCS_E_UNSUPPORTED;  // this build holds the resident kernels only
@@ -2270,10 +2391,14 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
     }
     (void)ug; (void)ti; (void)G;
     if (!kern || lds > kMaxLds) return ALCS_E_UNSUPPORTED;
-    // Depthwise stage: every group tile of a pixel tile evaluates the depthwise layer again, so
-    // a launch that splits the groups is slower than the two layers run one after the other;
-    // the caller that can do that (it has a workspace) is told to.
-    if (kDw && decline_restaged && a.ngt > 1 && !T.dw_one_kernel) return ALCS_E_UNSUPPORTED;
+    // Depthwise stage: every group tile of a pixel tile works out the depthwise layer again, so a launch
+    // that splits the groups is slower than the two layers run one after the other - unless it splits
+    // them in two, over pixel tiles that fill the chip then, and the stage is not the larger part of it
+    // (128->256 stride 2 to 28x28, N=8: 11.2 us against 12.2; 256->256 @28x28, N=16: 17.3 against 18.9, but
+    // 256->512 stride 2 to 14x14, N=32: 19.3 against 18.2, and 192->32 @28x28, one image: 8.2 against 7.5).
+    // The caller that can run the two layers (it has a workspace) is told to.
+    const bool restage_ok = a.ngt == 1 || (a.ngt == 2 && a.npt >= 80 && (!dw || dw->stride == 1 || Cin * a.tile_px <= 8192));
+    if (kDw && decline_restaged && !restage_ok && !T.dw_one_kernel) return ALCS_E_UNSUPPORTED;
     const long long total = wg_count > 0 ? wg_count : (long long)a.npt * a.ngt;
     if (total > (1LL << 30)) return ALCS_E_UNSUPPORTED;
     a.total_wgs = (int)total;

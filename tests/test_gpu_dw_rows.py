@@ -1,0 +1,48 @@
+"""Depthwise 3x3 with four pixels of a row per lane (csrc/alcs_dw_strip.h) at the sizes where it can go
+wrong, in the stand-alone layer and as the stage of the fused block: widths that are no multiple of what
+the lanes read, rows of several images in a tile or a wavefront, fewer channels or planes than a wavefront
+takes, several passes over a tile, rows wider than a wavefront; and wavefronts that share bundles."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2109_00170_amd as alcs
+import workloads
+from gpu_util import TOL, rel_err
+from test_gpu_dw_block import dw_inputs, run_block
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("C,N,H,W", [(3, 2, 3, w) for w in range(4, 18)] + [
+    (70, 1, 7, 7), (5, 5, 7, 7), (1, 1, 1, 5), (9, 1, 64, 4), (3, 1, 65, 4), (2, 3, 30, 31),
+    (2, 1, 5, 255), (2, 1, 4, 257), (3, 1, 3, 500), (2, 1, 3, 513), (1, 2, 2, 1031)])
+def test_layer(C, N, H, W, stride):
+    import torch
+    D, X, b = dw_inputs(C, N, H, W, 31 * C + W)
+    Ho, Wo = oracle.out_size(H, 3, stride), oracle.out_size(W, 3, stride)
+    Y = torch.full((N, C, Ho, Wo), float("nan"), dtype=torch.float32, device="cuda")
+    alcs.alcs_depthwise_conv(torch.from_numpy(D).cuda(), torch.from_numpy(X).cuda(), torch.from_numpy(b).cuda(), Y,
+                             stride=stride)
+    got = Y.cpu().numpy()
+    assert not np.isnan(got).any()
+    assert rel_err(got, oracle.depthwise(D, X, bias=b, stride=stride)) <= TOL
+
+
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("Cin,H,W,N,pv", [
+    (33, 5, 5, 40, 4),      # 51 rows a tile: four passes of a wavefront
+    (1, 9, 8, 3, 1),        # one channel, eight channels' lanes
+    (7, 14, 14, 5, 2), (29, 7, 7, 9, 4), (18, 3, 13, 7, 1), (40, 12, 15, 4, 2), (21, 6, 50, 3, 1), (5, 3, 63, 3, 1),
+    (12, 4, 100, 2, 2), (9, 2, 121, 2, 4), (10, 3, 250, 2, 4), (16, 28, 28, 2, 4), (130, 2, 4, 3, 4)])
+def test_block_on_whole_rows(Cin, H, W, N, pv, stride):
+    Hin, Win = (H, W) if stride == 1 else (2 * H - H % 2, 2 * W - W % 2)   # odd and even inputs
+    L = workloads.Layer("rows", Cin, 20, H, W, N=N, V=4, sparsity=0.5, w_std=0.3)
+    run_block(L, Hin, Win, stride, 7000 + Cin + W, pv=pv)
+
+
+@pytest.mark.parametrize("Cin,slots,hw,stride,N", [(520, 4, 14, 1, 2), (600, 2, 7, 2, 3), (1100, 4, 7, 1, 40), (520, 4, 3, 1, 5)])
+def test_block_wavefronts_share_bundles(Cin, slots, hw, stride, N):
+    L = workloads.Layer("split", Cin, 90, hw, hw, N=N, V=4, sparsity=0.9, w_std=0.1)
+    run_block(L, hw * stride, hw * stride, stride, 7300 + Cin, pack_tuning={"group_slots": slots}, with_res=True, act="relu")
