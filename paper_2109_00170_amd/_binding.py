@@ -458,8 +458,9 @@ def alcs_project_latency(scores, seg_starts, V_per_layer, tables, tau, budget, e
     if len(V_per_layer) != L or len(tables) != L:
         raise ValueError("one group size and one table per layer")
     Vs = np.ascontiguousarray(V_per_layer, dtype=np.int32)
-    nn = np.array([len(k) for k, _ in tables], dtype=np.int32)
-    kk, tt = (np.concatenate([e[i] for e in tables], dtype=np.float64) for i in (0, 1))
+    ks, ts = [k for k, _ in tables], [t for _, t in tables]
+    nn = np.array([np.size(k) for k in ks], dtype=np.int32)
+    kk, tt = (np.concatenate(e, dtype=np.float64, casting="unsafe") for e in (ks, ts))
     n = int(scores.numel())
     ws = _select_workspace(L, scores.device)
     mask = torch.empty((n,), dtype=torch.uint8, device=scores.device) if want_mask else None
@@ -592,10 +593,10 @@ def alcs_pack_network_device(Ws, masks, Vs, options=None, workspace=None, stream
     """Handles for a list of layers (device weights [Cout,Cin,k,k], device flags or None each) in one
     call; workspace: a uint8 device tensor of alcs_pack_workspace_bytes bytes, or None."""
     n = len(Ws)
-    Vs = [int(Vs)] * n if np.isscalar(Vs) else list(Vs)
-    opts = [Options.make(o) for o in (options if isinstance(options, (list, tuple)) else [options] * n)]
-    made = _launch.pack_network(list(Ws), list(masks), Vs, [0 if o is None else ctypes.addressof(o) for o in opts], workspace,
-                                stream)
+    Vs = [int(Vs)] * n if np.isscalar(Vs) else list(Vs)[:n]
+    opts = [Options.make(o) for o in (options if isinstance(options, (list, tuple)) else [options] * n)][:n]
+    made = _launch.pack_network(list(Ws), list(masks)[:n], Vs, [0 if o is None else ctypes.addressof(o) for o in opts],
+                                workspace, stream)
     return [Packed(ctypes.c_void_p(p), Cout, Cin, k, V) for p, Cout, Cin, k, V in made]
 
 

@@ -12,6 +12,8 @@
 
 #include <cstdint>
 #include <cstring>
+#include <exception>
+#include <new>
 
 #include "alcs_internal.h"
 
@@ -64,17 +66,15 @@ bool four(const Arg &a, const char *name) {
     return false;
 }
 bool integer(PyObject *o, int &v) {
-    if (!PyLong_CheckExact(o)) {
-        PyObject *i = PyNumber_Long(o);
-        if (!i) return false;
-        const long x = PyLong_AsLong(i);
-        Py_DECREF(i);
-        if (x == -1 && PyErr_Occurred()) return false;
-        v = (int)x;
-        return true;
-    }
-    const long x = PyLong_AsLong(o);
+    PyObject *i = PyNumber_Long(o);
+    if (!i) return false;
+    const long x = PyLong_AsLong(i);
+    Py_DECREF(i);
     if (x == -1 && PyErr_Occurred()) return false;
+    if (x != (int)x) {
+        PyErr_Format(PyExc_ValueError, "%ld is no 32-bit integer", x);
+        return false;
+    }
     v = (int)x;
     return true;
 }
@@ -361,7 +361,24 @@ PyObject *connect(PyObject *, PyObject *const *a, Py_ssize_t n) {
     Py_RETURN_NONE;
 }
 
-#define ENTRY(f) {#f, (PyCFunction)(void (*)(void))f, METH_FASTCALL, nullptr}
+// Reading a tensor can throw (one without storage, as a tracer makes; a sparse one; no device): the
+// interpreter's C frames must not see that.
+typedef PyObject *(*Entry)(PyObject *, PyObject *const *, Py_ssize_t);
+template <Entry F>
+PyObject *guarded(PyObject *self, PyObject *const *a, Py_ssize_t n) noexcept {
+    try {
+        return F(self, a, n);
+    } catch (const std::bad_alloc &) {
+        return PyErr_NoMemory();
+    } catch (const c10::Error &e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
+    } catch (const std::exception &e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+    }
+    return nullptr;
+}
+
+#define ENTRY(f) {#f, (PyCFunction)(void (*)(void))guarded<f>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {ENTRY(connect),        ENTRY(sparse_conv),          ENTRY(sparse_conv_fused),
                          ENTRY(sparse_conv_bf16), ENTRY(sparse_conv_bf16_mfma), ENTRY(dense_conv),
                          ENTRY(depthwise_conv), ENTRY(dw_sparse_conv_fused), ENTRY(block_scores),
