@@ -231,7 +231,7 @@ void device_free(void *p);
 // from its properties; looked up once per device and process (constants of the hardware).
 void device_shape(int device, int *cus, int *xcds);
 int current_device_shape(int *cus, int *xcds);  // of the current device; ALCS_OK or ALCS_E_HIP
-// Dynamic LDS above 64 KB has to be allowed per kernel once; ALCS_OK or ALCS_E_HIP.
+// Dynamic LDS above 64 KB has to be allowed once per kernel and device; ALCS_OK or ALCS_E_HIP.
 int allow_lds(const void *kernel, int bytes);
 int check_options(const alcs_options *o);  // ALCS_OK or ALCS_E_INVALID_ARG
 // alcs_pack_from_csr with the handle's options (null = automatic)

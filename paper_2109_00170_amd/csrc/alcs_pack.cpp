@@ -11,6 +11,7 @@
 #include <new>
 #include <numeric>
 #include <set>
+#include <utility>
 
 #include "alcs_internal.h"
 
@@ -53,12 +54,17 @@ int current_device_shape(int *cus, int *xcds) {
 int allow_lds(const void *kernel, int bytes) {
     if (bytes <= 64 * 1024) return ALCS_OK;
     static std::mutex mu;
-    static std::set<const void *> done;
-    std::lock_guard<std::mutex> lock(mu);
-    if (done.count(kernel)) return ALCS_OK;
-    const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    static std::set<std::pair<int, const void *>> done;  // the attribute belongs to a device's copy of the kernel
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) { set_hip_error((int)e); return ALCS_E_HIP; }
-    done.insert(kernel);
+    std::lock_guard<std::mutex> lock(mu);
+    if (done.count({dev, kernel})) return ALCS_OK;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) { set_hip_error((int)e); return ALCS_E_HIP; }
+    try {
+        done.insert({dev, kernel});
+    } catch (const std::bad_alloc &) {}  // asked for again on the next launch
     return ALCS_OK;
 }
 
