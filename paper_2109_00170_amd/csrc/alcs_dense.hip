@@ -41,7 +41,7 @@ struct DenseArgs {
 // i+1 are issued between the multiplies of step i.
 // What bounds a launch is the matrix pipe (65 to 75 % busy) and, on few tiles, how evenly they divide over
 // the compute units (the launcher picks the tile for that).  3x3, N=64, against the patch matrix
-// gathered word by word: 128->128 @28x28 260 -> 178 us (83 TFLOP/s), 512->512 @7x7 578 -> 187 us,
+// gathered word by word: 128->128 @28x28 260 -> 147 us (101 TFLOP/s), 512->512 @7x7 577 -> 176 us,
 // 40->23 @112x86 424 -> 175 us; 1x1 1024->256 @14x14 101 -> 80 us.  1x1 layers with few
 // output channels wait for their input: 16 channels a step leave room for 8 workgroups a compute unit
 // (256->64 @56x56, N=40: 59.5 -> 50 us against 32 channels and 3 workgroups).
