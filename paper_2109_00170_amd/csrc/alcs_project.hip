@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -266,8 +267,8 @@ constexpr int kBisectMaxLayers = 1024;
 constexpr int kBisectKnots = 64;   // table entries per layer, on average, the workspace has room for
 constexpr int kSpan = kBins + 1;   // cumulative counts: at or above bin b, and a zero behind them
 
-// Bisection state.  t0 / t1, the latencies at N0 / N1, are known exactly (lo == hi) or to within
-// [lo, hi].  fine[1], fine[2]: whether the second / third level's counts are those of `bin[0]` /
+// Bisection state.  t0 / t1, the latencies at N0 / N1, are known exactly (lo == hi, which may be
+// infinite, or both NaN) or to within [lo, hi], lo < hi.  fine[1], fine[2]: whether the second / third level's counts are those of `bin[0]` /
 // of `bin[1]` inside it.  request: the level whose histogram the next launch has to fill, or -1.
 struct Bisect {
     unsigned int N0, N1, N;
@@ -282,6 +283,11 @@ struct BisectParams {
     int L, monotone, knots;
     double tau, budget, eps;
 };
+
+__device__ __forceinline__ bool known(double lo, double hi) { return !(lo < hi); }
+// Rounds of four steps that one launch makes at most.  A round decides a step, ends, asks for more counts
+// or works out an end's latency (two ends, after each request): 32 steps and a few rounds are enough.
+constexpr int kBisectRounds = 64;
 
 struct BisectArgs {
     const float *scores;
@@ -479,8 +485,8 @@ __device__ __forceinline__ void latency_of(const BisectArgs &a, const unsigned i
         lo = lo - room;
         hi = hi + room;
     } else {
-        lo = -1e300;
-        hi = 1e300;
+        lo = -__builtin_inf();
+        hi = __builtin_inf();
     }
     t_lo = lo;
     t_hi = hi;
@@ -493,8 +499,8 @@ __global__ void k_bisect_init(BisectArgs a, SelectState *sel) {
         Bisect st{};
         st.N0 = 0;
         st.N1 = a.par->n;
-        st.t0_lo = st.t1_lo = -1e300;
-        st.t0_hi = st.t1_hi = 1e300;
+        st.t0_lo = st.t1_lo = -__builtin_inf();
+        st.t0_hi = st.t1_hi = __builtin_inf();
         st.request = 0;
         *a.st = st;
         sel->cut = Cut{0, 0, 0, 0};
@@ -524,7 +530,7 @@ __global__ void __launch_bounds__(1024) k_bisect_steps(const BisectArgs a) {
         if (l == 0 || (l == 1 ? st.fine1 : st.fine2))
             for (int i = tid; i < kSpan; i += 1024) S[l][i] = cum_row(a, l, a.L)[i];
     const double budget = a.par->budget, eps = a.par->eps;
-    while (true) {
+    for (int turn = 0; turn < kBisectRounds; ++turn) {
         __syncthreads();
         if (stop) break;
         if (wave > 0) {
@@ -542,7 +548,7 @@ __global__ void __launch_bounds__(1024) k_bisect_steps(const BisectArgs a) {
             for (int e = 0; e < 2; ++e) {
                 double lo = e ? st.t1_lo : st.t0_lo, hi = e ? st.t1_hi : st.t0_hi;
                 bool exact;
-                if (lo != hi) latency_of(a, S, st, e ? st.N1 : st.N0, lane, lo, hi, exact);
+                if (!known(lo, hi)) latency_of(a, S, st, e ? st.N1 : st.N0, lane, lo, hi, exact);
                 if (lane == 0) { node_lo[16 + e] = lo; node_hi[16 + e] = hi; }
             }
         }
@@ -556,17 +562,17 @@ __global__ void __launch_bounds__(1024) k_bisect_steps(const BisectArgs a) {
             unsigned int open = 0;  // the N whose counts are needed
             for (int node = 1; node < 16 && !need && !ended;) {
                 if (s.N1 - s.N0 <= 1) { ended = true; break; }
-                const bool exact_ends = s.t0_lo == s.t0_hi && s.t1_lo == s.t1_hi;
+                const bool exact_ends = known(s.t0_lo, s.t0_hi) && known(s.t1_lo, s.t1_hi);
                 if (exact_ends ? !(s.t1_lo - s.t0_lo > eps) : s.t1_hi - s.t0_lo <= eps) { ended = true; break; }
                 if (!exact_ends && !(s.t1_lo - s.t0_hi > eps)) {
                     need = true;
-                    open = s.t0_lo != s.t0_hi ? s.N0 : s.N1;
+                    open = !known(s.t0_lo, s.t0_hi) ? s.N0 : s.N1;
                     break;
                 }
                 const unsigned int N = s.N0 + (s.N1 - s.N0) / 2;
                 const double lo = node_lo[node], hi = node_hi[node];
                 if (hi < budget) { s.t0_lo = lo; s.t0_hi = hi; s.N0 = N; node = 2 * node + 1; }
-                else if (lo >= budget) { s.t1_lo = lo; s.t1_hi = hi; s.N1 = N; node = 2 * node; }
+                else if (lo >= budget || known(lo, hi)) { s.t1_lo = lo; s.t1_hi = hi; s.N1 = N; node = 2 * node; }
                 else { need = true; open = N; }
             }
             s.request = -1;
@@ -574,9 +580,9 @@ __global__ void __launch_bounds__(1024) k_bisect_steps(const BisectArgs a) {
             if (ended) {
                 // both latencies exact, and the cut of the result
                 s.N = s.N0 + (s.N1 - s.N0) / 2;
-                if (s.t0_lo != s.t0_hi || s.t1_lo != s.t1_hi) {
+                if (!known(s.t0_lo, s.t0_hi) || !known(s.t1_lo, s.t1_hi)) {
                     need = true;
-                    open = s.t0_lo != s.t0_hi ? s.N0 : s.N1;
+                    open = !known(s.t0_lo, s.t0_hi) ? s.N0 : s.N1;
                 } else if (s.N == 0 || s.N == a.par->n) {
                     cut = Cut{s.N == 0 ? 0xFFFFFFFFu : 0u, s.N == 0 ? 0u : 0xFFFFFFFFu, s.N == 0 ? 1u : 0u, 1};
                     s.done = 1;
@@ -611,6 +617,7 @@ __global__ void __launch_bounds__(1024) k_bisect_steps(const BisectArgs a) {
             }
         }
     }
+    __syncthreads();
     if (tid == 0) *a.st = st;
 }
 
@@ -858,12 +865,20 @@ static int project_on_device(const float *scores_dev, long long n, const long lo
     *par = BisectParams{(unsigned int)n, L, 1, (int)knots, tau, budget, eps};
     first[0] = 0;
     for (int l = 0; l <= L; ++l) seg[l] = (unsigned int)seg_starts_host[l];
+    // Bounds from the ends of an interval need tables that rise, and sums that do not overflow (a table
+    // whose neighbours differ by more than a double holds does not rise between them: infinities, NaN).
+    double largest = std::fabs(tau);
     for (int l = 0; l < L; ++l) {
         V[l] = V_host[l];
         first[l + 1] = first[l] + n_host[l];
-        for (int i = first[l] + 1; i < first[l + 1]; ++i)
-            if (t_host[i] < t_host[i - 1]) par->monotone = 0;  // bounds from the ends of an interval need rising tables
+        double most = 0;
+        for (int i = first[l]; i < first[l + 1]; ++i) {
+            most = std::max(most, std::fabs(t_host[i]));
+            if (i > first[l] && t_host[i] < t_host[i - 1]) par->monotone = 0;
+        }
+        largest += most;
     }
+    if (!(largest < 1e300)) par->monotone = 0;
     std::memcpy(k, k_host, 8 * knots);
     std::memcpy(t, t_host, 8 * knots);
     int rc = check(hipMemcpyAsync(w.params, up.data(), up.size(), hipMemcpyHostToDevice, st));

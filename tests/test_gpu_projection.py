@@ -149,6 +149,47 @@ def test_projection_edges(layers, blocks, knots, kind):
         assert mask.cpu().numpy().tobytes() == np.concatenate([m.reshape(-1) for m in masks_r]).tobytes(), frac
 
 
+def bisect_on_host(scores, sizes, V, tables, tau, budget, eps):
+    """Algorithm 1 with the library's own latency model, a comparison at a time; NaN is "not below"."""
+    starts = np.concatenate([[0], np.cumsum(sizes)])
+
+    def latency(N):
+        m = oracle.topn_mask(scores, N)
+        return alcs.alcs_network_latency(tau, tables, [float(V * int(m[a:b].sum())) for a, b in zip(starts, starts[1:])])
+
+    N0, N1 = 0, int(scores.size)
+    t0, t1 = latency(N0), latency(N1)
+    while t1 - t0 > eps and N1 - N0 > 1:
+        N = (N0 + N1) // 2
+        t = latency(N)
+        if t < budget:
+            t0, N0 = t, N
+        else:
+            t1, N1 = t, N
+    return (N0 + N1) // 2, oracle.topn_mask(scores, (N0 + N1) // 2), t0, t1
+
+
+@pytest.mark.parametrize("times", [(0.0, -1e308, 1e308), (1.0, 1.7e308, 1.75e308), (-1.7e308, 0.5, 1.7e308), (0.0, 1e301, 2e301)])
+@pytest.mark.parametrize("layers,blocks", [(1, 64), (3, 900)])
+def test_projection_where_latencies_overflow(layers, blocks, times):
+    """Finite tables whose neighbouring entries, or whose sums over the layers, a double does not hold:
+    latencies are infinite or NaN, and the bisection ends as the comparisons say."""
+    import torch
+    rng = np.random.default_rng(3450 + layers)
+    sizes = [blocks] * layers
+    sc = (rng.random(blocks * layers) ** 3).astype(np.float32)
+    tables = [(np.array([0.0, 2.0 * m, 4.0 * m]), np.array(times)) for m in sizes]
+    starts = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    dev = torch.from_numpy(sc).cuda()
+    for budget in (-1e307, 0.25, 1e300, float("inf"), -float("inf")):
+        for eps in (1e-3, 1e305, float("inf")):
+            N, mask, t0, t1 = alcs.alcs_project_latency(dev, starts, [4] * layers, tables, 1.5, budget, eps)
+            Nr, mr, t0r, t1r = bisect_on_host(sc, sizes, 4, tables, 1.5, budget, eps)
+            assert N == Nr, (budget, eps)
+            assert np.array_equal([t0, t1], [t0r, t1r], equal_nan=True), (budget, eps)
+            assert mask.cpu().numpy().tobytes() == mr.tobytes()
+
+
 def test_projection_feeds_the_packer():
     """The mask that comes out of the projection is the mask alcs_pack_weights takes."""
     import torch
