@@ -386,11 +386,14 @@ int alcs_network_latency(double tau, const double *k_host, const double *t_host,
  *   that keeps the N largest blocks; t < budget moves (t0, N0) up, else (t1, N1) down; the
  *   result keeps the (N0+N1)/2 largest blocks.  Halves are integer divisions and the loop also
  *   ends when N1 - N0 <= 1.  Outputs: mask_dev [n_blocks] (device, may be NULL), *N_out,
- *   *t0_out, *t1_out (host, may be NULL).  Synchronises `stream` once per bisection step.
+ *   *t0_out, *t1_out (host, may be NULL).  Waits for `stream` once (seldom a few times: tables that
+ *   do not rise), or once per bisection step with more than 1024 layers or 64 table entries a layer.
  *
- * workspace_dev: device memory of at least alcs_select_workspace_bytes(n_segments) bytes, 8-byte
- * aligned, owned by the caller, overwritten by the call; calls that share a workspace must not
- * overlap.  Errors: ALCS_E_INVALID_ARG (null pointers, N outside [0, n_blocks], bad segment
+ * workspace_dev: device memory of at least alcs_select_workspace_bytes(n_segments) bytes (n_layers
+ * for alcs_project_latency), 8-byte aligned, owned by the caller, overwritten by the call; calls that
+ * share a workspace must not overlap.  The size never falls with n_segments: a workspace for many
+ * segments serves every call with fewer.  About 34 KB a segment, up to 1024 of them, are
+ * alcs_project_latency's histograms; alcs_topn_mask does not touch them.  Errors: ALCS_E_INVALID_ARG (null pointers, N outside [0, n_blocks], bad segment
  * table, negative eps), ALCS_E_UNSUPPORTED (V, kernel, 2^32 blocks or more), ALCS_E_HIP.
  */
 int alcs_block_scores(const float *W_dev, int Cout, int Cin, int kernel, int V, float *scores_dev,

@@ -621,9 +621,10 @@ __global__ void __launch_bounds__(1024) k_bisect_steps(const BisectArgs a) {
     if (tid == 0) *a.st = st;
 }
 
-// Workspace layout: SelectState | seg_starts[n_seg + 1] | counts[n_seg], and for up to kBisectMaxLayers
-// segments what the bisection keeps: its state, the uploaded parameters, histograms and cumulative
-// counts per layer.
+// Workspace layout: SelectState | seg_starts[n_seg + 1] | counts[n_seg], and what the bisection keeps for
+// up to kBisectMaxLayers segments: its state, the uploaded parameters, histograms and cumulative counts
+// per layer.  That part is reserved for more segments too, whose bisection does not use it: a workspace
+// sized for many segments is also given to calls with fewer, so the size must never fall.
 struct Workspace {
     SelectState *st;
     long long *seg_starts;
@@ -644,12 +645,11 @@ static Workspace carve(void *ws, int n_seg, size_t *bytes = nullptr) {
     w.st = (SelectState *)take(sizeof(SelectState));
     w.seg_starts = (long long *)take(sizeof(long long) * (size_t)(n_seg + 1));
     w.counts = (unsigned long long *)take(sizeof(unsigned long long) * (size_t)n_seg);
-    if (n_seg <= kBisectMaxLayers) {
-        w.bisect = (Bisect *)take(sizeof(Bisect));
-        w.params = take(params_bytes(n_seg, (size_t)n_seg * kBisectKnots));
-        w.raw = (unsigned int *)take(4 * (size_t)(n_seg + 1) * kBins);
-        w.cum = (unsigned int *)take(4 * (size_t)kLevels * (n_seg + 1) * kSpan);
-    }
+    const int L = std::min(n_seg, kBisectMaxLayers);
+    w.bisect = (Bisect *)take(sizeof(Bisect));
+    w.params = take(params_bytes(L, (size_t)L * kBisectKnots));
+    w.raw = (unsigned int *)take(4 * (size_t)(L + 1) * kBins);
+    w.cum = (unsigned int *)take(4 * (size_t)kLevels * (L + 1) * kSpan);
     if (bytes) *bytes = o;
     return w;
 }
