@@ -252,6 +252,13 @@ def _dev_ptr(t, name, dtype_name="torch.float32"):
     return ctypes.c_void_p(t.data_ptr())
 
 
+def _filters(W):
+    """(Cout, Cin, k) of weights [Cout, Cin, k, k]."""
+    if W.ndim != 4 or W.shape[2] != W.shape[3]:
+        raise ValueError("W must be [Cout, Cin, k, k], got %r" % (tuple(W.shape),))
+    return W.shape[:3]
+
+
 def alcs_sparse_conv(packed: Packed, X, bias, Y, stride: int = 1, stream=None, events=None) -> None:
     """Y[N,Cout,Ho,Wo] = sparse_conv(packed, X[N,Cin,H,W]) + bias; device tensors, async on stream.
     events = (start, stop) hipEvent_t handles (ints) routes the call to alcs_sparse_conv_timed."""
@@ -262,6 +269,8 @@ def alcs_sparse_conv(packed: Packed, X, bias, Y, stride: int = 1, stream=None, e
     exp = (N, packed.Cout, out_size(H, k, stride), out_size(W, k, stride))
     if tuple(Y.shape) != exp:
         raise ValueError("Y must have shape %r, got %r" % (exp, tuple(Y.shape)))
+    if bias is not None and bias.numel() < packed.Cout:
+        raise ValueError("bias must have %d entries, got %d" % (packed.Cout, bias.numel()))
     rc = load_library().alcs_sparse_conv_timed(
         packed.handle, _dev_ptr(X, "X"), _dev_ptr(bias, "bias"), _dev_ptr(Y, "Y"), N, Cin, packed.Cout, H, W, k, int(stride),
         _stream_ptr(stream), ctypes.c_void_p(events[0]), ctypes.c_void_p(events[1]))
@@ -396,7 +405,7 @@ def alcs_block_scores(W_dev, V: int, scores=None, stream=None):
     float32 tensor [ceil(Cout/V), Cin, k, k] (allocated here unless ``scores`` is given)."""
     if scores is None:
         import torch
-        Cout, Cin, k, _ = W_dev.shape
+        Cout, Cin, k = _filters(W_dev)
         G = (Cout + V - 1) // V
         scores = torch.empty((G, Cin, k, k), dtype=torch.float32, device=W_dev.device)
     _launch.block_scores(W_dev, V, scores, stream)
@@ -483,7 +492,7 @@ def alcs_pack_csr_device(W_dev, mask_dev, V: int, stream=None):
     col_idx int32 [nnzb], vals float32 [nnzb*V]) as device tensors.  mask_dev: uint8 device tensor
     [G,Cin,k,k] (or flat) or None."""
     import torch
-    Cout, Cin, k, _ = W_dev.shape
+    Cout, Cin, k = _filters(W_dev)
     G = (Cout + V - 1) // V
     if mask_dev is not None and mask_dev.numel() != G * Cin * k * k:
         raise ValueError("mask must have %d entries" % (G * Cin * k * k))
@@ -545,7 +554,7 @@ def alcs_pack_from_csr_device(row_ptr, col_idx, vals, Cout: int, Cin: int, kerne
 def alcs_pack_weights_device(W_dev, mask_dev, V: int, options=None, stream=None) -> Packed:
     """Device weights [Cout,Cin,k,k] and device flags (uint8 [G,Cin,k,k] or None) -> handle; arrays
     and layout are built by kernels, the host reads back a few scalars."""
-    Cout, Cin, k, _ = W_dev.shape
+    Cout, Cin, k = _filters(W_dev)
     G = (Cout + V - 1) // V
     if mask_dev is not None and mask_dev.numel() != G * Cin * k * k:
         raise ValueError("mask must have %d entries" % (G * Cin * k * k))
@@ -571,7 +580,7 @@ def _layer_descs(Ws, masks, Vs, options):
     opts = [Options.make(o) for o in (options if isinstance(options, (list, tuple)) else [options] * n)]
     descs = (LayerDesc * n)()
     for i, (W, m) in enumerate(zip(Ws, masks)):
-        Cout, Cin, k, _ = W.shape
+        Cout, Cin, k = _filters(W)
         G = (Cout + Vs[i] - 1) // Vs[i]
         if m is not None and m.numel() != G * Cin * k * k:
             raise ValueError("mask %d must have %d entries" % (i, G * Cin * k * k))

@@ -60,9 +60,30 @@ bool shape(const Arg &a, const char *name, std::initializer_list<int64_t> want) 
     if (!ok) PyErr_Format(PyExc_ValueError, "%s does not have the shape the call asks for", name);
     return ok;
 }
+// Four dimensions, each one that fits the C entries' int.
 bool four(const Arg &a, const char *name) {
-    if (a.t->dim() == 4) return true;
-    PyErr_Format(PyExc_ValueError, "%s must have four dimensions", name);
+    if (a.t->dim() != 4) {
+        PyErr_Format(PyExc_ValueError, "%s must have four dimensions", name);
+        return false;
+    }
+    for (int i = 0; i < 4; ++i)
+        if (a.dim(i) > INT32_MAX) {
+            PyErr_Format(PyExc_ValueError, "%s: a dimension of %lld is more than the library takes", name, (long long)a.dim(i));
+            return false;
+        }
+    return true;
+}
+// Weights [Cout, Cin, k, k].
+bool filters(const Arg &a, const char *name) {
+    if (!four(a, name)) return false;
+    if (a.dim(2) == a.dim(3)) return true;
+    PyErr_Format(PyExc_ValueError, "%s must be [Cout, Cin, k, k]", name);
+    return false;
+}
+// A value for every channel (a bias may have more, and any shape).
+bool per_channel(const Arg &a, const char *name, int64_t channels) {
+    if (!a.t || a.t->numel() >= channels) return true;
+    PyErr_Format(PyExc_ValueError, "%s must have %lld entries, got %lld", name, (long long)channels, (long long)a.t->numel());
     return false;
 }
 bool integer(PyObject *o, int &v) {
@@ -160,7 +181,7 @@ PyObject *conv(Kind kind, const char *where, PyObject *const *a, Py_ssize_t n) {
     if (stride == 0) { PyErr_SetString(PyExc_ZeroDivisionError, "stride is zero"); return nullptr; }
     const int64_t Ho = out_size(H, p->k, stride), Wo = out_size(W, p->k, stride);
     if (stride > 0 && (!shape(Y, "Y", {N, p->Cout, Ho, Wo}) || !shape(R, "residual", {N, p->Cout, Ho, Wo}))) return nullptr;
-    if (!stream_of(a[7], st)) return nullptr;
+    if (!per_channel(bias, "bias", p->Cout) || !stream_of(a[7], st)) return nullptr;
     int rc;
     Py_BEGIN_ALLOW_THREADS
     switch (kind) {
@@ -193,7 +214,7 @@ PyObject *dense_conv(PyObject *, PyObject *const *a, Py_ssize_t n) {
     Arg W, X, bias, Y;
     int stride = 1;
     void *st = nullptr;
-    if (!tensor(a[0], "W", at::kFloat, false, W) || !four(W, "W") || !tensor(a[1], "X", at::kFloat, false, X) || !four(X, "X") ||
+    if (!tensor(a[0], "W", at::kFloat, false, W) || !filters(W, "W") || !tensor(a[1], "X", at::kFloat, false, X) || !four(X, "X") ||
         !tensor(a[2], "bias", at::kFloat, true, bias) || !tensor(a[3], "Y", at::kFloat, false, Y) || !integer(a[4], stride))
         return nullptr;
     const int64_t N = X.dim(0), Cin = X.dim(1), H = X.dim(2), Wd = X.dim(3), Cout = W.dim(0);
@@ -201,7 +222,7 @@ PyObject *dense_conv(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (W.dim(1) != Cin) { PyErr_SetString(PyExc_ValueError, "channel mismatch"); return nullptr; }
     if (stride == 0) { PyErr_SetString(PyExc_ZeroDivisionError, "stride is zero"); return nullptr; }
     if (stride > 0 && !shape(Y, "Y", {N, Cout, out_size(H, k, stride), out_size(Wd, k, stride)})) return nullptr;
-    if (!stream_of(a[5], st)) return nullptr;
+    if (!per_channel(bias, "bias", Cout) || !stream_of(a[5], st)) return nullptr;
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = p_dense((const float *)W.p, (const float *)X.p, (const float *)bias.p, (float *)Y.p, (int)N, (int)Cin, (int)Cout, (int)H,
@@ -224,7 +245,7 @@ PyObject *depthwise_conv(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!shape(D, "dw_weights", {C, 3, 3})) return nullptr;
     if (stride == 0) { PyErr_SetString(PyExc_ZeroDivisionError, "stride is zero"); return nullptr; }
     if (stride > 0 && !shape(Y, "Y", {N, C, out_size(H, 3, stride), out_size(W, 3, stride)})) return nullptr;
-    if (!stream_of(a[6], st)) return nullptr;
+    if (!per_channel(bias, "bias", C) || !stream_of(a[6], st)) return nullptr;
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = p_depthwise((const float *)D.p, (const float *)X.p, (const float *)bias.p, (float *)Y.p, (int)N, (int)C, (int)H, (int)W,
@@ -255,7 +276,7 @@ PyObject *dw_sparse_conv_fused(PyObject *, PyObject *const *a, Py_ssize_t n) {
             !shape(ws, "workspace", {N, C, Ho, Wo}))
             return nullptr;
     }
-    if (!stream_of(a[11], st)) return nullptr;
+    if (!per_channel(db, "dw_bias", C) || !per_channel(bias, "bias", p->Cout) || !stream_of(a[11], st)) return nullptr;
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = p_dw(p, (const float *)D.p, (const float *)db.p, stride, dw_act, (const float *)X.p, (const float *)bias.p,
@@ -270,7 +291,7 @@ PyObject *block_scores(PyObject *, PyObject *const *a, Py_ssize_t n) {
     Arg W, S;
     int V = 0;
     void *st = nullptr;
-    if (!tensor(a[0], "W", at::kFloat, false, W) || !four(W, "W") || !integer(a[1], V) ||
+    if (!tensor(a[0], "W", at::kFloat, false, W) || !filters(W, "W") || !integer(a[1], V) ||
         !tensor(a[2], "scores", at::kFloat, false, S))
         return nullptr;
     const int64_t Cout = W.dim(0), Cin = W.dim(1), k = W.dim(2);
@@ -309,7 +330,7 @@ PyObject *pack_network(PyObject *, PyObject *const *a, Py_ssize_t n) {
     for (Py_ssize_t i = 0; i < layers; ++i) {
         Arg W, M;
         int V = 0;
-        if (!tensor(PyList_GET_ITEM(a[0], i), "W", at::kFloat, false, W) || !four(W, "W") ||
+        if (!tensor(PyList_GET_ITEM(a[0], i), "W", at::kFloat, false, W) || !filters(W, "W") ||
             !tensor(PyList_GET_ITEM(a[1], i), "mask", at::kByte, true, M) || !integer(PyList_GET_ITEM(a[2], i), V))
             return nullptr;
         const int64_t Cout = W.dim(0), Cin = W.dim(1), k = W.dim(2);
