@@ -814,8 +814,15 @@ static int project_stepwise(const float *scores_dev, long long n, const long lon
     int rc = check(hipMemcpyAsync(w.seg_starts, seg_starts_host, sizeof(long long) * (size_t)(n_layers + 1),
                                   hipMemcpyHostToDevice, st));
     if (rc != ALCS_OK) return rc;
-    std::vector<long long> counts(n_layers);
-    std::vector<double> nnz(n_layers);
+    std::vector<long long> counts;
+    std::vector<double> nnz;
+    try {
+        counts.resize((size_t)n_layers);
+        nnz.resize((size_t)n_layers);
+    } catch (const std::bad_alloc &) {
+        (void)hipStreamSynchronize(st);  // the copy above reads the caller's table
+        return ALCS_E_ALLOC;
+    }
     // the latency of the network that keeps the N largest blocks (Section 3.3, Eq. (2))
     auto latency = [&](long long N, double *t) -> int {
         int r = select_async(scores_dev, n, N, w, n_layers, nullptr, true, st);

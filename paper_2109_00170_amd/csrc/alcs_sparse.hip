@@ -26,7 +26,6 @@
 #include <cstdint>
 #include <mutex>
 #include <map>
-#include <set>
 #include <utility>
 
 #include "alcs_internal.h"
@@ -1956,20 +1955,6 @@ static int pick_ug(int G, int nw, int forced) {
     return G <= 2 * nw ? 2 : 4;
 }
 
-// Dynamic LDS above 64 KB has to be allowed per kernel once; remember which kernels
-// already have the full 160 KB enabled.
-static int set_lds_limit(kern_t k, int lds) {
-    if (lds <= 64 * 1024) return ALCS_OK;
-    static std::mutex mu;
-    static std::set<const void *> done;
-    std::lock_guard<std::mutex> lock(mu);
-    if (done.count((const void *)k)) return ALCS_OK;
-    hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
-    if (e != hipSuccess) { set_hip_error((int)e); return ALCS_E_HIP; }
-    done.insert((const void *)k);
-    return ALCS_OK;
-}
-
 // Vector registers per lane of a kernel (0 if the runtime cannot tell), looked up once.
 static int kernel_registers(kern_t k) {
     static std::mutex mu;
@@ -1981,7 +1966,9 @@ static int kernel_registers(kern_t k) {
     int regs = 0;
     if (hipFuncGetAttributes(&attr, (const void *)k) == hipSuccess) regs = attr.numRegs;
     else (void)hipGetLastError();
-    known[(const void *)k] = regs;
+    try {
+        known[(const void *)k] = regs;
+    } catch (const std::bad_alloc &) {}  // looked up again on the next launch
     return regs;
 }
 
@@ -2404,7 +2391,7 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
     a.total_wgs = (int)total;
     a.xcds = kXcds;
     a.wg_per_xcd = ceil_div(total, kXcds);
-    int rc = set_lds_limit(kern, lds);
+    int rc = allow_lds((const void *)kern, lds);
     if (rc != ALCS_OK) return rc;
     record_launch(mode, pv, nw, a.total_wgs, lds, a.ngt, L.KC, mfma ? 2 : 1, L.GS, (mode == 3 || mode == 7) ? tile_w3(ti) : 0);
     const int grid = mode == 4 ? a.npt : a.wg_per_xcd * kXcds;
