@@ -131,6 +131,12 @@ int alcs_packed_layout_hash(const alcs_packed_t *p, unsigned long long *hash_out
  * make sure no launch that reads it is still in flight. */
 void alcs_packed_free(alcs_packed_t *p);
 
+/* Device memory of freed handles, and of the packer's own temporaries, is kept for the next handles: at
+ * most 512 MB in 256 blocks per process, all GPUs together, oldest first back to the runtime.  While it
+ * is kept, other allocators of the process do not get it; alcs_release_memory gives all of it back
+ * (it waits for the GPU like hipFree; memory of live handles is not touched; any thread may call it). */
+void alcs_release_memory(void);
+
 /*
  * The sparse convolution (Section 3.2.2, "Efficient multiplication computation"):
  *   Y[n, g*V+v, ho, wo] = bias[g*V+v]

@@ -25,6 +25,7 @@ from ._binding import (  # noqa: F401
     alcs_pack_on_device,
     alcs_pack_weights,
     alcs_project_latency,
+    alcs_release_memory,
     alcs_sparse_conv,
     alcs_sparse_conv_bf16,
     alcs_sparse_conv_bf16_mfma,

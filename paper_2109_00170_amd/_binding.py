@@ -31,7 +31,7 @@ _launch = _Unloaded()
 
 EXPORTS = [
     "alcs_strerror", "alcs_last_hip_error", "alcs_version", "alcs_pack_weights", "alcs_packed_info",
-    "alcs_packed_on_device", "alcs_packed_export", "alcs_packed_selfcheck", "alcs_packed_free",
+    "alcs_packed_on_device", "alcs_packed_export", "alcs_packed_selfcheck", "alcs_packed_free", "alcs_release_memory",
     "alcs_sparse_conv", "alcs_sparse_conv_timed", "alcs_sparse_conv_fused", "alcs_dense_conv",
     "alcs_pack_weights_opt", "alcs_packed_set_options", "alcs_packed_get_options",
     "alcs_depthwise_conv", "alcs_dw_sparse_conv_fused", "alcs_sparse_conv_bf16", "alcs_block_scores", "alcs_select_workspace_bytes",
@@ -104,6 +104,7 @@ def load_library():
     lib.alcs_packed_layout_hash.argtypes = [vp, vp]
     lib.alcs_packed_free.argtypes = [vp]
     lib.alcs_packed_free.restype = None
+    lib.alcs_release_memory.restype = None
     lib.alcs_sparse_conv.argtypes = [vp, vp, vp, vp, ci, ci, ci, ci, ci, ci, ci, vp]
     lib.alcs_sparse_conv_timed.argtypes = [vp, vp, vp, vp, ci, ci, ci, ci, ci, ci, ci, vp, vp, vp]
     lib.alcs_sparse_conv_fused.argtypes = [vp, vp, vp, vp, vp, ci, ci, ci, ci, ci, ci, ci, ci, vp]
@@ -208,6 +209,11 @@ class Packed:
             self.free()
         except Exception:
             pass
+
+
+def alcs_release_memory() -> None:
+    """Give back the device memory that freed handles leave for the next ones (at most 512 MB)."""
+    load_library().alcs_release_memory()
 
 
 def alcs_pack_weights(W: np.ndarray, mask: Optional[np.ndarray], V: int, options=None) -> Packed:

@@ -227,6 +227,7 @@ void set_hip_error(int e);
 // the status in *rc.
 void *device_alloc(size_t bytes, int *rc);
 void device_free(void *p);
+void release_pool();  // the blocks that nobody uses go back to the runtime
 // Compute units and XCDs (L2 domains; workgroups are dealt to them round-robin) of a device,
 // from its properties; looked up once per device and process (constants of the hardware).
 void device_shape(int device, int *cus, int *xcds);

@@ -230,7 +230,8 @@ int build_layout(alcs_packed *p, int KC, int GS) {
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // The pool.  A freed block is kept (at most kPoolBlocks of them and kPoolBytes in all; the oldest go
-// back to the runtime) and handed out again for a request of about its size on the same device.
+// back to the runtime, alcs_release_memory gives all of them back) and handed out again for a request of
+// about its size on the same device.
 // hipFree waits for everything the device has been given, which is what makes freeing a handle safe
 // while a kernel of any stream may still read it; here the same wait is made when a block is handed
 // out again, once for all blocks freed since the last one.
@@ -266,7 +267,18 @@ void give_back(const PoolBlock &b) {
     (void)hipFree(b.p);
     if (elsewhere) (void)hipSetDevice(cur);
 }
+void give_back_all(Pool &P) {
+    for (const PoolBlock &k : P.kept) give_back(k);
+    P.kept.clear();
+    P.kept_bytes = 0;
+}
 }  // namespace
+
+void release_pool() {
+    Pool &P = pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    give_back_all(P);
+}
 
 void *device_alloc(size_t bytes, int *rc) {
     *rc = ALCS_OK;
@@ -281,9 +293,11 @@ void *device_alloc(size_t bytes, int *rc) {
         if (P.kept[i].device == dev && P.kept[i].bytes >= want && P.kept[i].bytes <= want + want / 4 &&
             (best == P.kept.size() || P.kept[i].bytes < P.kept[best].bytes))
             best = i;
+    PoolBlock b{nullptr, want, dev, true};
+    bool fresh = false;
     try {
         if (best < P.kept.size()) {
-            PoolBlock b = P.kept[best];
+            b = P.kept[best];
             if (!b.settled) {
                 if ((e = hipDeviceSynchronize()) != hipSuccess) { set_hip_error((int)e); *rc = ALCS_E_HIP; return nullptr; }
                 for (PoolBlock &k : P.kept)
@@ -294,13 +308,10 @@ void *device_alloc(size_t bytes, int *rc) {
             P.kept_bytes -= b.bytes;
             return b.p;
         }
-        PoolBlock b{nullptr, want, dev, true};
         e = hipMalloc(&b.p, want);
         if (e == hipErrorOutOfMemory && !P.kept.empty()) {
             (void)hipGetLastError();
-            for (const PoolBlock &k : P.kept) give_back(k);
-            P.kept.clear();
-            P.kept_bytes = 0;
+            give_back_all(P);
             e = hipMalloc(&b.p, want);
         }
         if (e != hipSuccess) {
@@ -309,9 +320,11 @@ void *device_alloc(size_t bytes, int *rc) {
             *rc = e == hipErrorOutOfMemory ? ALCS_E_ALLOC : ALCS_E_HIP;
             return nullptr;
         }
+        fresh = true;
         P.in_use.emplace(b.p, b);
         return b.p;
     } catch (const std::bad_alloc &) {
+        if (fresh) give_back(b);
         *rc = ALCS_E_ALLOC;
         return nullptr;
     }
@@ -831,6 +844,8 @@ int alcs_packed_get_options(const alcs_packed_t *p, alcs_options *options) {
     *options = p->opt;
     return ALCS_OK;
 }
+
+void alcs_release_memory(void) { release_pool(); }
 
 int alcs_last_launch(int *out, int cap) {
     if (!out || cap <= 0) return 0;

@@ -196,25 +196,50 @@ def test_more_groups_than_the_rank_kernel_takes_go_through_the_host():
 
 
 def test_freed_blocks_are_reused_safely():
-    """A handle freed while its convolution is still in flight, and handles of slightly different sizes
-    packed into the blocks it leaves: every output stays what a fresh handle gives."""
+    """A handle freed while a convolution of another stream still reads it, and handles of slightly different
+    sizes packed into the blocks it leaves: every output stays what a fresh handle gives."""
     import torch
     rng = np.random.default_rng(4900)
     W = torch.from_numpy((rng.standard_normal((256, 256, 1, 1)) * 0.2).astype(np.float32)).cuda()
     X = torch.from_numpy(rng.standard_normal((16, 256, 28, 28)).astype(np.float32)).cuda()
+    busy = torch.zeros(1 << 28, device="cuda")
     masks = [torch.from_numpy(workloads.mask_exact(64, 256, 1, 0.8 + 0.002 * i, rng)).cuda() for i in range(6)]
     keep = [alcs.alcs_pack_weights_device(W, m, 4) for m in masks]
+    other = torch.cuda.Stream()
     want, got = [], []
     for h in keep:
         Y = torch.empty((16, 256, 28, 28), device="cuda")
         alcs.alcs_sparse_conv(h, X, None, Y)
         want.append(Y)
+    torch.cuda.synchronize()
+    waiting = 0
     for m in masks:
         h = alcs.alcs_pack_network_device([W], [m], 4)[0]
         Y = torch.empty((16, 256, 28, 28), device="cuda")
-        alcs.alcs_sparse_conv(h, X, None, Y)
+        other.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(other):
+            for _ in range(8):
+                busy.add_(1.0)          # a few milliseconds ahead of the convolution
+            alcs.alcs_sparse_conv(h, X, None, Y)
+        waiting += not other.query()
         h.free()
         got.append(Y)
     torch.cuda.synchronize()
+    assert waiting == len(masks)
     for a, b in zip(want, got):
         assert torch.equal(a, b)
+
+
+def test_memory_of_freed_handles_can_be_given_back():
+    import torch
+    W = torch.randn((512, 512, 3, 3), device="cuda")
+    handles = [alcs.alcs_pack_weights_device(W, None, 4) for _ in range(4)]
+    alcs.alcs_release_memory()
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    for h in handles:
+        h.free()
+    assert torch.cuda.mem_get_info()[0] == free0
+    alcs.alcs_release_memory()
+    assert torch.cuda.mem_get_info()[0] >= free0 + 4 * W.numel() * 4
+    alcs.alcs_pack_weights_device(W, None, 4).free()
