@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <type_traits>
 
@@ -323,11 +324,12 @@ __global__ void __launch_bounds__(256, KK == 1 ? 4 : BM == 128 ? 1 : 2) k_dense(
 
 constexpr int BK = 16;
 
-// Shapes the patch kernel does not take - images wider than its staging, or whose tile spans more than
-// 2^31 elements of the input: the patch matrix gathered word by word, 64 x 128 tiles, steps of 16 rows of
-// K through a two-deep LDS buffer.
+// Shapes the patch kernel does not take - 3x3 on images wider than its staging (more than 254 pixels at
+// stride 1, 203 at stride 2), or a tile that spans 2^30 elements of the input: the patch matrix gathered
+// word by word, BM x 128 tiles, steps of 16 rows of K through a two-deep LDS buffer.
+template <int BM>
 __global__ void __launch_bounds__(256) k_dense_gather(const DenseArgs a) {
-    constexpr int BN = 128, BM = 64, LDA = BM + 4;
+    constexpr int BN = 128, LDA = BM + 4;
     constexpr int TM = BM / 64;  // 32x32 tiles per wavefront along M
     constexpr int A_ROWS_PER_PASS = 128;  // 256 threads / 2
     constexpr int NA = (BM + A_ROWS_PER_PASS - 1) / A_ROWS_PER_PASS;  // weight-tile passes per thread
@@ -470,7 +472,10 @@ __global__ void __launch_bounds__(256) k_dense_gather(const DenseArgs a) {
 // Tile shapes, with the rate the matrix work of a tile runs at against the largest tile's: measured on
 // 3x3 layers with 64 to 512 channels at stride 1 and (`wide`, more than 512 staged positions a tile,
 // which a stride of 2 or a wide image has) 2, and on 1x1 layers with 16 to 1024.  3x3 at 64 pixels a
-// tile, and larger 1x1 tiles, were slower than a shape listed here (1x1: or as fast).
+// tile, and larger 1x1 tiles, were slower than a shape listed here (1x1: or as fast).  1x1 against 128 x 128
+// tiles of the patch matrix (130 layers, 40 to 1016 channels): 1.0 to 2.7 times as fast, but for a few whose
+// channels fill those tiles, 3 to 7 % slower (392->760 @56x57, N=18: 374 against 347 us); staged 128 x 128 tiles
+// give these back and lose as much on others (472->232 @28x28, N=83: 165 -> 179 us).
 struct DenseShape {
     int bm, bn;
     double rate, wide;
@@ -482,7 +487,9 @@ template <int NPT>
 static auto pick_3x3(int BM) -> void (*)(const DenseArgs) {
     return BM == 128 ? k_dense<128, 128, 9, NPT> : BM == 64 ? k_dense<64, 128, 9, NPT> : k_dense<32, 128, 9, NPT>;
 }
-static auto pick_dense(int kernel, int BM, int npt) -> void (*)(const DenseArgs) {
+static auto pick_dense(int kernel, int BM, int BN, int npt) -> void (*)(const DenseArgs) {
+    // (64 pixels touch at least half the positions of 128, and are taken where those are more than 1024)
+    if (kernel == 3 && BN == 64) return npt == 3 ? k_dense<64, 64, 9, 3> : k_dense<64, 64, 9, 4>;
     if (kernel == 3) return npt == 2 ? pick_3x3<2>(BM) : npt == 3 ? pick_3x3<3>(BM) : pick_3x3<4>(BM);
     return BM == 64 ? k_dense<64, 64, 1, 1> : k_dense<32, 128, 1, 1>;
 }
@@ -517,20 +524,40 @@ extern "C" int alcs_dense_conv(const float *W_dev, const float *X_dev, const flo
     // The tile whose launch gives the most loaded compute unit the least matrix work, at the shape's rate.
     // (512 channels, 7x7, N = 64: 307 us on 128 x 128 tiles, 187 on 32 x 128; 40 -> 23 @112x86:
     // 653 and 175.)  3x3 also needs a tile's input rows to fit its staging.
-    const DenseShape *best = nullptr, *shapes = kernel == 3 ? kShapes3x3 : kShapes1x1;
+    const DenseShape *best = nullptr;
     double best_cost = 0;
-    for (int i = 0; i < (kernel == 3 ? 3 : 2); ++i) {
-        const DenseShape &sh = shapes[i];
+    auto consider = [&](const DenseShape &sh) {
         const long long rows = std::min<long long>((sh.bn + Wo - 2) / Wo + 1, (long long)N * Ho);  // output rows a tile can touch
         const long long images = std::min<long long>((rows + Ho - 2) / Ho + 1, N);
         const long long npos = kernel == 3 ? (rows * stride + images * (3 - stride)) * ((Wo - 1) * (long long)stride + 3) : 0;
-        if (npos > 256 * kPosPerThread) continue;
-        if ((images + 1) * (long long)Cin * Pin >= (1LL << 29) || K * sh.bm >= (1LL << 29)) continue;  // byte offsets are 32 bits
+        if (npos > 256 * kPosPerThread) return;
+        if (images * (long long)Cin * Pin >= (1LL << 30) || K * sh.bm >= (1LL << 29)) return;  // byte offsets are 32 bits
         const long long tiles = ((a.NP + sh.bn - 1) / sh.bn) * ((Cout + sh.bm - 1) / sh.bm);
         const double cost = (double)((tiles + cus - 1) / cus) * sh.bm * sh.bn / (npos > 512 ? sh.wide : sh.rate);
         if (!best || cost < best_cost) { best = &sh; best_cost = cost; a.npos = (int)npos; }
+    };
+    if (kernel == 1) {
+        for (const DenseShape &sh : kShapes1x1) consider(sh);
+    } else {
+        for (const DenseShape &sh : kShapes3x3) consider(sh);
     }
-    const int BM = best ? best->bm : 64, BN = best ? best->bn : 128;
+    int BM = best ? best->bm : 64, BN = best ? best->bn : 128;
+    if (!best) {
+        // 3x3 layers whose 128 pixels touch more input than the staging holds, mostly stride 2 on images more
+        // than about 100 wide: staged with 64 pixels a tile, or gathered on 64 or 128 channels, by what each
+        // takes a channel on the most loaded compute unit.  A staged tile has a cost of about 16 channels before the
+        // first; gathered tiles are slow alone and cover each other's waits (60 such layers, 16 to 448 channels:
+        // within 5 % of the fastest of the three, 59 of them; the gather alone, on 128 channels or 64 if that left
+        // compute units idle, took up to 5.6 times as long - 448->64 @62x124, one image: 494 against 111 us -
+        // and the staged form alone up to 1.6 times - 16->424 @82x118, N=43: 364 against 219).
+        auto load = [&](int bm, int bn) { return (double)(((a.NP + bn - 1) / bn) * ((Cout + bm - 1) / bm)) / cus; };
+        auto at_once = [](double t) { return t > 2 ? t : std::ceil(t); };
+        const double t128 = 0.45 + 0.95 * at_once(load(128, 128)), t64 = 0.65 + 0.52 * std::max(1.0, load(64, 128));
+        static const DenseShape kNarrow{64, 64, 1.0, 1.0};
+        if (kernel == 3 && 0.25 * std::ceil(load(64, 64)) * (Cin + 16) / Cin < std::min(t128, t64)) consider(kNarrow);
+        BM = best || t64 <= t128 ? 64 : 128;
+        if (best) BN = 64;
+    }
     const long long ntile = (a.NP + BN - 1) / BN;
     a.mt = (Cout + BM - 1) / BM;
     const long long total = ntile * a.mt;
@@ -538,12 +565,12 @@ extern "C" int alcs_dense_conv(const float *W_dev, const float *X_dev, const flo
     a.nt = (int)ntile;
     a.total_wgs = (int)total;
     a.wg_per_xcd = (int)((total + xcds - 1) / xcds);
-    void (*kern)(const DenseArgs) = k_dense_gather;
+    void (*kern)(const DenseArgs) = BM == 128 ? k_dense_gather<128> : k_dense_gather<64>;
     int lds = 0;
     if (best) {
         const int npt = kernel == 1 ? 1 : a.npos <= 512 ? 2 : a.npos <= 768 ? 3 : 4;
         lds = 2 * 16 * (kernel == 3 ? 18 * (BM + 1) + 512 * npt : 4 * (BM + 1) + 4 * BN);
-        kern = pick_dense(kernel, BM, npt);
+        kern = pick_dense(kernel, BM, BN, npt);
         const int rc = allow_lds((const void *)kern, lds);
         if (rc != ALCS_OK) return rc;
     }
