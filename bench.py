@@ -43,6 +43,8 @@ def kernel_symbol(L, info):
     mf = info["path"] == 2
     P = L.Ho * L.Wo   # the kernels' Access template argument: 0 aligned, 1 unaligned, 2 strided, 3 rows
     ac = (0 if P % 4 == 0 else 1 if P >= 4 else 3 if P == 1 else 2) if L.stride == 1 else 2
+    if info["mode"] == 1 and info["bundle_waves"] > 1:
+        return "alcs::k_pw_split<%d, %d, %d, %d>" % (L.V, info["pv"], ac, info["group_slots"])
     if info["mode"] == 1:
         return "alcs::k_pw_resident<%d, %d, %s, %d, %d>" % (L.V, info["pv"], b(mf), ac, info["group_slots"])
     if info["mode"] == 2:

@@ -501,10 +501,11 @@ int alcs_pack_weights_device(const float *W_dev, const uint8_t *mask_dev, int Co
  * ints {mode (1 = all input channels resident in LDS, 2 = chunked, 3 = 3x3,
  * 4 = persistent double-buffered with the weights in LDS, 5 = pipelined persistent,
  * 6 = the 16-bit kernel of alcs_sparse_conv_bf16_mfma, whose path reads 3,
- * 7 = 3x3 walking channel records (handles whose pattern is shared by the nine taps),
+ * 7 = 3x3 walking channel records (handles whose pattern is shared by the nine taps)),
  * pv, waves, workgroups, lds_bytes, group_tiles,
- * chunk_channels, path, group_slots, tile_width (3x3 only, else 0)} and returns how many were
- * written.  For tests and benchmarks. */
+ * chunk_channels, path, group_slots, tile_width (3x3 only, else 0),
+ * bundle_waves (mode 1: wavefronts that share a bundle of groups, else 1)} and returns how many
+ * were written.  For tests and benchmarks. */
 int alcs_last_launch(int *out, int cap);
 
 #ifdef __cplusplus

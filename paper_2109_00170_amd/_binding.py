@@ -358,10 +358,10 @@ def alcs_dw_sparse_conv_fused(packed: Packed, D_dev, dw_bias, X, bias, residual,
 
 
 def alcs_last_launch() -> dict:
-    buf = (ctypes.c_int * 10)()
-    n = load_library().alcs_last_launch(buf, 10)
+    buf = (ctypes.c_int * 11)()
+    n = load_library().alcs_last_launch(buf, 11)
     keys = ["mode", "pv", "waves", "workgroups", "lds_bytes", "group_tiles", "chunk_channels", "path",
-            "group_slots", "tile_width"]
+            "group_slots", "tile_width", "bundle_waves"]
     return {k: int(buf[i]) for i, k in enumerate(keys[:n])}
 
 

@@ -263,6 +263,6 @@ inline Tuning tuning_of(const alcs_options &o) {
     return t;
 }
 void record_launch(int mode, int pv, int waves, int wgs, int lds, int gtiles, int kc, int path, int gs,
-                   int tile_w);
+                   int tile_w, int bundle_waves = 1);
 
 }  // namespace alcs

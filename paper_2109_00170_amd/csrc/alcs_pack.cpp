@@ -18,12 +18,12 @@
 namespace alcs {
 
 static thread_local int g_last_hip = 0;
-static thread_local int g_last_launch[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+static thread_local int g_last_launch[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 void set_hip_error(int e) { g_last_hip = e; }
 
 void record_launch(int mode, int pv, int waves, int wgs, int lds, int gtiles, int kc, int path, int gs,
-                   int tile_w) {
-    int v[10] = {mode, pv, waves, wgs, lds, gtiles, kc, path, gs, tile_w};
+                   int tile_w, int bundle_waves) {
+    int v[11] = {mode, pv, waves, wgs, lds, gtiles, kc, path, gs, tile_w, bundle_waves};
     std::memcpy(g_last_launch, v, sizeof(v));
 }
 
@@ -849,7 +849,7 @@ void alcs_release_memory(void) { release_pool(); }
 
 int alcs_last_launch(int *out, int cap) {
     if (!out || cap <= 0) return 0;
-    int n = cap < 10 ? cap : 10;
+    int n = cap < 11 ? cap : 11;
     std::memcpy(out, g_last_launch, n * sizeof(int));
     return n;
 }

@@ -2393,7 +2393,8 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
     a.wg_per_xcd = ceil_div(total, kXcds);
     int rc = allow_lds((const void *)kern, lds);
     if (rc != ALCS_OK) return rc;
-    record_launch(mode, pv, nw, a.total_wgs, lds, a.ngt, L.KC, mfma ? 2 : 1, L.GS, (mode == 3 || mode == 7) ? tile_w3(ti) : 0);
+    record_launch(mode, pv, nw, a.total_wgs, lds, a.ngt, L.KC, mfma ? 2 : 1, L.GS, (mode == 3 || mode == 7) ? tile_w3(ti) : 0,
+                  std::max(1, a.ksplit));
     const int grid = mode == 4 ? a.npt : a.wg_per_xcd * kXcds;
     if (ev_start || ev_stop) {
         // the events take the kernel's own begin and end time stamps (no gap for event

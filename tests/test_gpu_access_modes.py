@@ -51,4 +51,6 @@ def test_wavefronts_share_bundles(Cin, Cout, V, H, N, stride, waves):
     a wavefront leave some of them without columns."""
     for sparsity in (0.7, 0.99):
         L = workloads.Layer("share", Cin, Cout, H, H, N=N, V=V, stride=stride, sparsity=sparsity, w_std=0.1)
-        run_fused(L, 6300 + Cin + H, "relu6", waves=waves)
+        info = run_fused(L, 6300 + Cin + H, "relu6", waves=waves)
+        # (at 99 % the longest segments may be one run of 16 columns, which nobody shares)
+        assert sparsity > 0.9 or info["bundle_waves"] > 1, info

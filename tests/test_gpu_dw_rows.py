@@ -45,4 +45,6 @@ def test_block_on_whole_rows(Cin, H, W, N, pv, stride):
 @pytest.mark.parametrize("Cin,slots,hw,stride,N", [(520, 4, 14, 1, 2), (600, 2, 7, 2, 3), (1100, 4, 7, 1, 40), (520, 4, 3, 1, 5)])
 def test_block_wavefronts_share_bundles(Cin, slots, hw, stride, N):
     L = workloads.Layer("split", Cin, 90, hw, hw, N=N, V=4, sparsity=0.9, w_std=0.1)
-    run_block(L, hw * stride, hw * stride, stride, 7300 + Cin, pack_tuning={"group_slots": slots}, with_res=True, act="relu")
+    info = run_block(L, hw * stride, hw * stride, stride, 7300 + Cin, pack_tuning={"group_slots": slots}, with_res=True,
+                     act="relu")
+    assert info["bundle_waves"] > 1, info
