@@ -182,7 +182,13 @@ extern "C" int alcs_depthwise_conv(const float *dw_weights_dev, const float *X_d
         const long long nchunks = (long long)((Ho + a.rows - 1) / a.rows) * a.cblocks;
         const long long groups = (a.planes + a.planes_per_wave - 1) / a.planes_per_wave;
         const bool two = groups > 64LL * cus / nchunks;   // more units than the compute units hold wavefronts
-        if (nchunks <= INT32_MAX && groups <= (1LL << 26) / nchunks) {
+        // Large tensors at stride 1 whose rows leave many lanes idle (131 pixels are 33 of 64 lanes) are faster with
+        // one pixel a lane: 202 channels of 105x131, N=10 79 us as rows, 52 not; where rows are 16-byte aligned only
+        // below 62 % (48 channels of 280x260, N=16: 124 us as rows, 96 not; 792 of
+        // 113x160, N=5, 62 %: 151 us as rows).
+        const double used = (double)P * a.planes_per_wave / (256.0 * (double)nchunks);
+        const bool idle = two && stride == 1 && used < (W % 4 ? 0.75 : 0.62);
+        if (!idle && nchunks <= INT32_MAX && groups <= (1LL << 26) / nchunks) {
             a.nchunks = (int)nchunks;
             blocks = (groups * nchunks + (two ? 7 : 3)) / (two ? 8 : 4);
             kern = stride == 1 ? (two ? k_depthwise_rows<1, 2> : k_depthwise_rows<1, 1>)

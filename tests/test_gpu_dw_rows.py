@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("stride", [1, 2])
 @pytest.mark.parametrize("C,N,H,W", [(3, 2, 3, w) for w in range(4, 18)] + [
     (70, 1, 7, 7), (5, 5, 7, 7), (1, 1, 1, 5), (9, 1, 64, 4), (3, 1, 65, 4), (2, 3, 30, 31),
-    (2, 1, 5, 255), (2, 1, 4, 257), (3, 1, 3, 500), (2, 1, 3, 513), (1, 2, 2, 1031)])
+    (2, 1, 5, 255), (2, 1, 4, 257), (3, 1, 3, 500), (2, 1, 3, 513), (1, 2, 2, 1031),
+    (13, 40, 60, 131), (11, 16, 90, 260), (20, 41, 22, 27)])   # large, with half of the lanes idle as rows or nearly none
 def test_layer(C, N, H, W, stride):
     import torch
     D, X, b = dw_inputs(C, N, H, W, 31 * C + W)
