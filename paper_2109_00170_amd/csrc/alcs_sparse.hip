@@ -223,6 +223,18 @@ __device__ __forceinline__ float activate(const ConvArgs &a, float v) {
     }
     return v;
 }
+// One branch for all pixels of a channel: per value it costs the layers with few input channels, which are mostly
+// stores, 5 to 10 % (40->928 @28x17, N=34, bfloat16: 14.8 against 16.6 us).  Behind a residual the values come one
+// by one anyway, and the branch per value is the faster form (24->376 @49x49, N=54, V=16: 78.7 against 83.2 us).
+template <int PV>
+__device__ __forceinline__ void activate_pixels(const ConvArgs &a, float (&x)[PV]) {
+    if constexpr (kFused) {
+        if (a.act) {
+#pragma unroll
+            for (int pv = 0; pv < PV; ++pv) x[pv] = activate(a, x[pv]);
+        }
+    }
+}
 // The residual tensor, or null where the epilogue is compiled out.
 __device__ __forceinline__ const io_t *residual_of(const ConvArgs &a) {
     if constexpr (kFused) return a.residual;
@@ -987,19 +999,26 @@ template <int V, int PV, bool MF, int AC, int RES>
 __device__ __forceinline__ void store_group(const ConvArgs &a, const Acc<V, PV, MF> &acc, int g,
                                             const PixOut<PV> &px, Resid<RES == kAhead ? V : 1, PV> &ahead) {
     constexpr int B = RES == kBehind ? res_batch(V, PV) : V;
+    // all of the group's biases in one round trip, not one behind the stores of the channel before
+    float bias[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) bias[v] = 0.f;
+    if (a.bias) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) bias[v] = as_const(a.bias)[min(g * V + v, a.Cout - 1)];
+    }
 #pragma unroll
     for (int v0 = 0; v0 < V; v0 += B) {
         Resid<RES == kBehind ? B : 1, PV> behind;
         if constexpr (RES == kBehind) load_residual<V, PV, AC, B>(a, g, v0, px, behind);
         auto value = [&](int v, int pv) __attribute__((always_inline)) {  // v counts from v0
-            const int ch = g * V + v0 + v;
-            float o = acc.get(v0 + v, pv) + (a.bias && ch < a.Cout ? as_const(a.bias)[ch] : 0.f);
+            float o = acc.get(v0 + v, pv) + bias[v0 + v];
             if constexpr (RES == kAhead) o += ahead.r[v0 + v][pv];
             if constexpr (RES == kBehind) o += behind.r[v][pv];
-            return kFused && a.act ? activate(a, o) : o;
+            return o;
         };
         if constexpr (AC == kRows) {
-            store_rows<B, PV>(a, g * V + v0, px, value);
+            store_rows<B, PV>(a, g * V + v0, px, [&](int v, int pv) __attribute__((always_inline)) { return activate(a, value(v, pv)); });
         } else {
 #pragma unroll
             for (int v = 0; v < B; ++v) {
@@ -1007,7 +1026,8 @@ __device__ __forceinline__ void store_group(const ConvArgs &a, const Acc<V, PV, 
                 if (ch >= a.Cout) break;
                 float x[PV];
 #pragma unroll
-                for (int pv = 0; pv < PV; ++pv) x[pv] = value(v, pv);
+                for (int pv = 0; pv < PV; ++pv) x[pv] = RES == kNone ? value(v, pv) : activate(a, value(v, pv));
+                if constexpr (RES == kNone) activate_pixels(a, x);
                 store_pixels<PV, AC>(a.Y + (size_t)ch * a.P, px, x);
             }
         }
@@ -1078,6 +1098,7 @@ __device__ __forceinline__ void store_slots_as(const ConvArgs &a, const Acc<V, P
                 float x[PV];
 #pragma unroll
                 for (int pv = 0; pv < PV; ++pv) x[pv] = value(v, pv);
+                activate_pixels(a, x);
                 store_pixels<PV, AC, CACHED>(plane + (size_t)(v0 + v) * a.P, px, x);
             }
         }
@@ -1196,7 +1217,7 @@ __global__ void __launch_bounds__(1024) k_pw_resident_cached(const ConvArgs a) {
 // The same walk with a residual, one group per wavefront (fused epilogue).
 template <int V, int PV, bool MF, int AC>
 __global__ void __launch_bounds__(1024) k_pw_resident_res(const ConvArgs a) {
-    pw_resident_body<V, PV, MF, AC, 1, V * PV <= 16 && MF ? kAhead : kBehind>(a);
+    pw_resident_body<V, PV, MF, AC, 1, V * PV <= (MF ? 16 : 4) ? kAhead : kBehind>(a);
 }
 
 // Mode 1, split: the resident kernel for launches with fewer bundles per workgroup than wavefronts -
