@@ -673,8 +673,12 @@ __device__ __forceinline__ void stage_pw(const ConvArgs &a, float *lds, int q0, 
         static_assert(TP % 16 == 0, "16 pixels at a time");
         const int lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
         const int e16 = lane & 15, cq = lane >> 4;
-        constexpr int PG = TP / 16;
-        const int items = PG * ((rows + 15) / 16);
+        // (only the pixels that are there, in groups of 16 rounded up to a power of two: 1523->10 on 10 rows
+        // 34 -> 18 us)
+        const int there = q_end - q0;
+        const int pgs = TP <= 16 || there <= 16 ? 0 : TP <= 32 || there <= 32 ? 1 : 2, pgm = (1 << pgs) - 1;
+        const int items = ((rows + 15) / 16) << pgs;
+        static_assert(TP <= 64, "at most four groups of pixels");
         constexpr int U = 4;
 #pragma clang loop unroll(disable)
         for (int i0 = wave; i0 < items; i0 += U * nw) {
@@ -682,7 +686,7 @@ __device__ __forceinline__ void stage_pw(const ConvArgs &a, float *lds, int q0, 
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int it = i0 + u * nw;
-                const int e = (it % PG) * 16 + e16, c = (it / PG) * 16 + cq * 4;
+                const int e = (it & pgm) * 16 + e16, c = (it >> pgs) * 16 + cq * 4;
                 v[u] = f4{0, 0, 0, 0};
                 if (it < items && q0 + e < q_end) {
                     const io_t *src = a.X + (size_t)(q0 + e) * a.Cin + c0 + c;
@@ -695,7 +699,7 @@ __device__ __forceinline__ void stage_pw(const ConvArgs &a, float *lds, int q0, 
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int it = i0 + u * nw;
-                const int e = (it % PG) * 16 + e16, c = (it / PG) * 16 + cq * 4;
+                const int e = (it & pgm) * 16 + e16, c = (it >> pgs) * 16 + cq * 4;
                 if (it >= items) continue;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {

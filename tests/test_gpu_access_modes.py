@@ -33,10 +33,10 @@ def test_unaligned_quads_several_groups_per_wavefront(Cin, V, slots, H, W, N):
 
 @pytest.mark.parametrize("Cin,Cout,V", [(16, 10, 4), (63, 33, 8), (130, 40, 1), (511, 24, 4), (513, 30, 4), (1025, 100, 8),
                                         (2558, 20, 16), (700, 12, 2), (2600, 17, 4)])
-@pytest.mark.parametrize("N", [1, 15, 17, 130])
+@pytest.mark.parametrize("N", [1, 15, 17, 40, 130])
 def test_rows(Cin, Cout, V, N):
-    """Fully connected: channels that are no multiple of 4 or 16, rows that are no multiple of 16, ragged
-    groups, the kernels that stream their channels in chunks."""
+    """Fully connected: channels that are no multiple of 4 or 16, rows that are no multiple of 16 and of one to
+    four groups of 16, ragged groups, the kernels that stream their channels in chunks."""
     L = workloads.Layer("rows", Cin, Cout, 1, 1, N=N, V=V, sparsity=0.8, w_std=0.1)
     run_fused(L, 6200 + Cin + N, "relu")
     if Cin <= (2558 if V >= 4 else 639):
