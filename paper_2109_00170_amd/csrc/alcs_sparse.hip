@@ -2085,7 +2085,15 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
     if (kernel == 1) {
         const bool vec = stride == 1 && (P % 4 == 0);
         const Access ac = vec ? kAligned : kDw ? kUnaligned : (P == 1 && Pin == 1) ? kRows : (stride == 1 && P >= 4) ? kUnaligned : kStrided;
-        const int pv_most = ac == kRows ? 1 : ac == kStrided ? 2 : 4;  // one group per wavefront
+        // Most pixels per lane, one group per wavefront.  Strided: a pair is two loads and two stores anyway; it
+        // pays where the multiply reads fewer LDS rows for it, not for a few wide groups, whose launch is staging
+        // and better spread over twice the tiles (stride 2: 64->32 @97x97, N=45, V=8, bfloat16 18.3 us as pairs, 14.0
+        // not; 64->192 @33x33, N=230 23.4 against 24.8).  Unaligned, images smaller than a wavefront's quads: every
+        // wavefront meets a seam, and where the stores are most of the launch the pixel-by-pixel ones beside it cost
+        // more than the quads save (75->1016 @7x7, N=198, V=16 54 us as quads, 28 not).
+        const bool few_wide = V >= 8 && L.nbundles < 16, seams = V >= 8 && P < 256 && Cout >= 2 * Cin;
+        const int pv_can = ac == kRows ? 1 : ac == kStrided ? 2 : 4;
+        const int pv_most = (ac == kStrided && few_wide) || (ac == kUnaligned && (kDw ? V == 16 : seams)) ? 1 : pv_can;
         // streaming kernel: everything (two input tiles, packed weights) fits in LDS and
         // there are enough pixels to give every compute unit several tiles
         bool stream_ok = false;
@@ -2194,6 +2202,10 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
                 return 4 * R * Wo >= 3 * tp || R == N * Ho ? R : 0;
             };
             const bool dw_s2 = kDw && dw->stride == 2;
+            // Stride 2: a row's pixels take twice the input, so one pixel a lane - unless the pointwise layer is most of
+            // the work: 34->776 to 56x56, N=4, V=1 42 us with one pixel a lane, 25.7 with two; 32->712 to 28x28, N=42,
+            // V=4 45.9 and 38.9; 18->624 to 56x56, N=13 49.5 and 41.9.
+            const bool one_px_s2 = dw_s2 && Cout < 4 * Cin;
             auto pixels_of = [&](int tp) { const int R = rows_of(tp); return R ? R * Wo : tp; };
             const int kMinWgs = 3 * kCUs / 2;
             const int GS = L.GS, NB = L.nbundles;
@@ -2203,20 +2215,21 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
                 for (int cand = pv_most; cand >= 2; cand >>= 1) {
                     const long long need = (long long)(Cin + 1) * 64 * cand * 4;
                     const long long tiles = ceil_div(a.NP, pixels_of(64 * cand));
-                    if (need <= kTwoPerCu && tiles * (cand == 2 && !dw_s2 ? 2 : 1) >= kMinWgs) { pv = cand; break; }
+                    if (need <= kTwoPerCu && tiles * (cand == 2 && !one_px_s2 ? 2 : 1) >= kMinWgs) { pv = cand; break; }
                 }
                 // Or a still wider tile with one workgroup per compute unit (up to 160 KB), when
                 // pixel tiles x group tiles then make a single round that keeps at least 3/4 of the
                 // compute units busy: one wide workgroup beats two narrow ones that share a
-                // compute unit (28x28 and 14x14 layers at batch 32: 5-11 % faster).
-                for (int cand = dw_s2 ? 1 : pv_most; cand > pv; cand >>= 1) {
+                // compute unit (28x28 and 14x14 layers at batch 32: 5-11 % faster).  Not for strided pixels, which every
+                // further group tile loads again one by one (104->248 @28x25 stride 2, N=41, V=4: 12.2 us, 9.2 not).
+                for (int cand = one_px_s2 || (ac == kStrided && V >= 4 && !a.residual) ? 1 : pv_most; cand > pv; cand >>= 1) {
                     const long long need = (long long)(Cin + 1) * 64 * cand * 4;
                     const long long tiles = ceil_div(a.NP, pixels_of(64 * cand));
                     if (need > kMaxLds || tiles > kCUs) continue;
                     const long long gts = std::min<long long>(std::max(1, NB / 4), std::max<long long>(1, kCUs / tiles));
                     if (tiles * gts >= 3 * kCUs / 4) { pv = cand; break; }
                 }
-                if (T.pv == 1 || T.pv == 2 || T.pv == 4) pv = std::min(T.pv, pv_most);
+                if (T.pv == 1 || T.pv == 2 || T.pv == 4) pv = std::min(T.pv, pv_can);
             }
             // Several groups per wavefront: four groups of 16 lanes with a pixel pair each read
             // half as many LDS rows per kept weight as two groups of 32 lanes with one pixel
