@@ -1091,10 +1091,10 @@ __device__ __forceinline__ void store_slots_as(const ConvArgs &a, const Acc<V, P
         auto value = [&](int v, int pv) __attribute__((always_inline)) {
             float o = acc.get(v0 + v, pv) + sb.b[v0 + v];
             if constexpr (RES == kBehind) o += behind.r[v][pv];
-            return kFused && a.act ? activate(a, o) : o;
+            return o;
         };
         if constexpr (AC == kRows) {
-            store_rows<B, PV>(a, g * V + v0, px, value);
+            store_rows<B, PV>(a, g * V + v0, px, [&](int v, int pv) __attribute__((always_inline)) { return activate(a, value(v, pv)); });
         } else {
 #pragma unroll
             for (int v = 0; v < B; ++v) {
@@ -2199,6 +2199,9 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
                 while (R > 0 && ac == kAligned && (R * Wo) % 4 && R < N * Ho) --R;
                 const long long images = std::min<long long>((R + Ho - 2) / Ho + 1, N);
                 if ((images * (long double)Cin + 64) * Pin * 4 >= 4.0e9L) return 0;  // 32-bit byte offsets
+                // (not where any pixels make one round of the chip and whole rows a second one: 144->864 @56x56, N=10
+                // 67 us as 245 tiles, 120 as 280)
+                if (R > 0 && ceil_div(a.NP, tp) <= kCUs && ceil_div(a.NP, R * Wo) > kCUs) return 0;
                 return 4 * R * Wo >= 3 * tp || R == N * Ho ? R : 0;
             };
             const bool dw_s2 = kDw && dw->stride == 2;
@@ -2416,14 +2419,19 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
     }
     (void)ug; (void)ti; (void)G;
     if (!kern || lds > kMaxLds) return ALCS_E_UNSUPPORTED;
+#if ALCS_DW_STAGE
     // Depthwise stage: every group tile of a pixel tile works out the depthwise layer again, so a launch
     // that splits the groups is slower than the two layers run one after the other - unless it splits
-    // them in two, over pixel tiles that fill the chip then, and the stage is not the larger part of it
-    // (128->256 stride 2 to 28x28, N=8: 11.2 us against 12.2; 256->256 @28x28, N=16: 17.3 against 18.9, but
-    // 256->512 stride 2 to 14x14, N=32: 19.3 against 18.2, and 192->32 @28x28, one image: 8.2 against 7.5).
-    // The caller that can run the two layers (it has a workspace) is told to.
-    const bool restage_ok = a.ngt == 1 || (a.ngt == 2 && a.npt >= 80 && (!dw || dw->stride == 1 || Cin * a.tile_px <= 8192));
-    if (kDw && decline_restaged && !restage_ok && !T.dw_one_kernel) return ALCS_E_UNSUPPORTED;
+    // them in two, over tiles of whole rows that fill the chip in a single round then, and the stage is not the
+    // larger part of it (128->256 stride 2 to 28x28, N=8: 11.2 us against 12.2; 256->256 @28x28, N=16: 17.3 against
+    // 18.9, but 256->512 stride 2 to 14x14, N=32: 19.3 against 18.2, 192->32 @28x28, one image: 8.2 against 7.5; not on
+    // whole rows, 816->80 @41x37, N=2: 38.3 against 21.8; in more than one round, 264->88 @28x19, N=22: 24.1 against
+    // 18.6).  The caller that can run the two layers (it has a workspace) is told to.
+    const bool restage_ok = a.ngt == 1 || (a.ngt == 2 && a.npt >= 80 && 2 * a.npt <= kCUs && a.dw_rows > 0 &&
+                                           (dw->stride == 1 || Cin * a.tile_px <= 8192));
+    if (decline_restaged && !restage_ok && !T.dw_one_kernel) return ALCS_E_UNSUPPORTED;
+#endif
+    (void)decline_restaged;
     const long long total = wg_count > 0 ? wg_count : (long long)a.npt * a.ngt;
     if (total > (1LL << 30)) return ALCS_E_UNSUPPORTED;
     a.total_wgs = (int)total;
