@@ -260,13 +260,17 @@ __global__ void __launch_bounds__(1024) k_ld_plan(const LayerDev *layers) {
     }
 }
 
-// One workgroup per (bundle, chunk), and one per layer for the spare run behind the last segment.
+// One workgroup per (bundle, chunk, slot), and one per layer for the spare run behind the last segment.  A
+// workgroup places its slot's columns 256 at a time, a chain of round trips that only more workgroups shorten:
+// 2048->1000, V=8, 90 % sparse takes 127 us to pack, 239 with the four slots of a bundle one after the other.  (All of
+// a column's values loaded ahead of the first store: 141, and 218 -> 265 for 4096->4096.)
 __global__ void __launch_bounds__(256) k_ld_fill(const LayerDev *layers, const Spread *sp, int n) {
     __shared__ int wave_kept[4], wave_even[4], red[4];
     const int li = layer_of(sp, n, blockIdx.x, &Spread::fill);
     const LayerDev &L = layers[li];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int si = blockIdx.x - sp[li].fill, GS = L.GS, kk = L.kk, V = L.V;
+    const int GS = L.GS, kk = L.kk, V = L.V, place = blockIdx.x - sp[li].fill;
+    const int si = place / GS, s = place - si * GS;
     auto put_pad = [&](long long col, int s, int c0, int which) {
         for (int q = 0; q < L.planes; ++q)
             for (int i = 0; i < L.VV; ++i) L.o_w[(size_t)q * L.wplane + layout_w_index(GS, L.VV, col, s, i)] = 0.f;
@@ -284,7 +288,7 @@ __global__ void __launch_bounds__(256) k_ld_fill(const LayerDev *layers, const S
     const Work wk = L.work[si];
     const int span = (wk.cnt + kSegAlign - 1) / kSegAlign * kSegAlign;
     const int first_rec = L.o_cw ? L.cwork[2 * si] : 0;
-    if (tid == 0) {
+    if (tid == 0 && s == 0) {
         L.o_work[si] = wk;
         if (L.o_cw) { L.o_cwork[2 * si] = first_rec; L.o_cwork[2 * si + 1] = L.cwork[2 * si + 1]; }
     }
@@ -302,90 +306,88 @@ __global__ void __launch_bounds__(256) k_ld_fill(const LayerDev *layers, const S
             back = kept - front;
         }
     };
-    for (int s = 0; s < GS; ++s) {
-        const int g = wk.group[s];
-        int kept, front, back;
-        shape_of(s, kept, front, back);
-        if (g >= 0) {
-            // first canonical index of the segment: the group's, and the chunks before this one
-            int before = 0;
-            for (int c = tid; c < ch; c += 256) before += L.cnt[(size_t)g * L.nchunks + c];
-            if (ch > 0) {
+    const int g = wk.group[s];
+    int kept, front, back;
+    shape_of(s, kept, front, back);
+    if (g >= 0) {
+        // first canonical index of the segment: the group's, and the chunks before this one
+        int before = 0;
+        for (int c = tid; c < ch; c += 256) before += L.cnt[(size_t)g * L.nchunks + c];
+        if (ch > 0) {
 #pragma unroll
-                for (int d = 32; d; d >>= 1) before += __shfl_down(before, d);
-                __syncthreads();
-                if (lane == 0) red[wave] = before;
-                __syncthreads();
-                before = red[0] + red[1] + red[2] + red[3];
-            }
-            const long long t0 = (long long)L.rp[g] + before;
-            const int steps = L.W ? c_hi - c_lo : kept;
-            int done = 0, done_even = 0;
-            for (int x0 = 0; x0 < steps; x0 += 256) {
-                const int x = x0 + tid;
-                int col = 0;
-                bool keep;
-                if (L.W) {
-                    col = c_lo + x;
-                    keep = x < steps && (!L.mask || L.mask[(size_t)g * L.K + col] != 0);
-                } else {
-                    keep = x < steps;
-                    if (keep) col = L.ci_in[t0 + x];
-                }
-                const bool even = keep && GS > 1 && (col & 1) == 0;
-                const unsigned long long bk = __ballot(keep), be = __ballot(even), below = (1ull << lane) - 1ull;
-                if (lane == 0) { wave_kept[wave] = __popcll(bk); wave_even[wave] = __popcll(be); }
-                __syncthreads();
-                int r = done + __popcll(bk & below), re = done_even + __popcll(be & below);
-                for (int w = 0; w < wave; ++w) { r += wave_kept[w]; re += wave_even[w]; }
-                if (keep) {
-                    const long long t = t0 + r;
-                    int j = r;
-                    if (GS > 1) {
-                        const bool to_front = even == ((s & 1) == 0);
-                        const int rank = even ? re : r - re;
-                        j = to_front ? rank : wk.cnt - back + rank;
-                    }
-                    const long long at = (long long)wk.start + j;
-                    L.o_ci[t] = col;
-                    for (int v = 0; v < V; ++v) {
-                        const int row = g * V + v;
-                        const float val = L.W ? (row < L.Cout ? L.W[(size_t)row * L.K + col] : 0.f) : L.va_in[(size_t)t * V + v];
-                        const int q = V < 4 ? 0 : v / 4, i = V < 4 ? v : v % 4;
-                        L.o_va[(size_t)t * V + v] = val;
-                        L.o_w[(size_t)q * L.wplane + layout_w_index(GS, L.VV, at, s, i)] = val;
-                        if (L.o_cw) L.o_cw[(size_t)q * L.cwplane + (size_t)(first_rec + j / 9) * 64 + (j % 9) * 4 + i] = val;
-                    }
-                    const size_t oi = layout_off_index(GS, at, s);
-                    for (int tb = 0; tb < L.noff; ++tb) L.o_off[(size_t)tb * L.offlen + oi] = layout_off_of(col, L.k, tb, GS);
-                    if (L.o_cw && j % 9 == 0) {
-                        L.o_csel[first_rec + j / 9] = col / 9 - c0;
-                        for (int q = 0; q < L.planes; ++q)
-                            for (int i = 36; i < 64; ++i) L.o_cw[(size_t)q * L.cwplane + (size_t)(first_rec + j / 9) * 64 + i] = 0.f;
-                    }
-                }
-                done += wave_kept[0] + wave_kept[1] + wave_kept[2] + wave_kept[3];
-                done_even += wave_even[0] + wave_even[1] + wave_even[2] + wave_even[3];
-                __syncthreads();
-            }
+            for (int d = 32; d; d >>= 1) before += __shfl_down(before, d);
+            __syncthreads();
+            if (lane == 0) red[wave] = before;
+            __syncthreads();
+            before = red[0] + red[1] + red[2] + red[3];
         }
-        // padding: between front and back (one group per wavefront: behind the columns), and the rest
-        // of the last run.  With several groups it selects the zero row of the other parity than the
-        // partner slot's row at that step.
-        int mk = 0, mf = 0, mb = 0;
-        const bool mate = GS > 1 && wk.group[s ^ 1] >= 0;
-        if (mate) shape_of(s ^ 1, mk, mf, mb);
-        const int from = front, to = wk.cnt - back;
-        for (int x = tid; x < (to - from) + (span - wk.cnt); x += 256) {
-            const int j = x < to - from ? from + x : wk.cnt + (x - (to - from));
-            int which = 0;
-            if (GS > 1 && j < wk.cnt) {
-                const int fp = ((s ^ 1) & 1) ? 1 : 0;  // channel parity at the partner's front
-                const int parity = !mate ? -1 : j < mf ? fp : j >= wk.cnt - mb ? 1 - fp : -1;
-                which = parity < 0 ? (s & 1) : (((c0 + L.KC) & 1) == parity ? 1 : 0);
+        const long long t0 = (long long)L.rp[g] + before;
+        const int steps = L.W ? c_hi - c_lo : kept;
+        int done = 0, done_even = 0;
+        for (int x0 = 0; x0 < steps; x0 += 256) {
+            const int x = x0 + tid;
+            int col = 0;
+            bool keep;
+            if (L.W) {
+                col = c_lo + x;
+                keep = x < steps && (!L.mask || L.mask[(size_t)g * L.K + col] != 0);
+            } else {
+                keep = x < steps;
+                if (keep) col = L.ci_in[t0 + x];
             }
-            put_pad((long long)wk.start + j, s, c0, which);
+            const bool even = keep && GS > 1 && (col & 1) == 0;
+            const unsigned long long bk = __ballot(keep), be = __ballot(even), below = (1ull << lane) - 1ull;
+            if (lane == 0) { wave_kept[wave] = __popcll(bk); wave_even[wave] = __popcll(be); }
+            __syncthreads();
+            int r = done + __popcll(bk & below), re = done_even + __popcll(be & below);
+            for (int w = 0; w < wave; ++w) { r += wave_kept[w]; re += wave_even[w]; }
+            if (keep) {
+                const long long t = t0 + r;
+                int j = r;
+                if (GS > 1) {
+                    const bool to_front = even == ((s & 1) == 0);
+                    const int rank = even ? re : r - re;
+                    j = to_front ? rank : wk.cnt - back + rank;
+                }
+                const long long at = (long long)wk.start + j;
+                L.o_ci[t] = col;
+                for (int v = 0; v < V; ++v) {
+                    const int row = g * V + v;
+                    const float val = L.W ? (row < L.Cout ? L.W[(size_t)row * L.K + col] : 0.f) : L.va_in[(size_t)t * V + v];
+                    const int q = V < 4 ? 0 : v / 4, i = V < 4 ? v : v % 4;
+                    L.o_va[(size_t)t * V + v] = val;
+                    L.o_w[(size_t)q * L.wplane + layout_w_index(GS, L.VV, at, s, i)] = val;
+                    if (L.o_cw) L.o_cw[(size_t)q * L.cwplane + (size_t)(first_rec + j / 9) * 64 + (j % 9) * 4 + i] = val;
+                }
+                const size_t oi = layout_off_index(GS, at, s);
+                for (int tb = 0; tb < L.noff; ++tb) L.o_off[(size_t)tb * L.offlen + oi] = layout_off_of(col, L.k, tb, GS);
+                if (L.o_cw && j % 9 == 0) {
+                    L.o_csel[first_rec + j / 9] = col / 9 - c0;
+                    for (int q = 0; q < L.planes; ++q)
+                        for (int i = 36; i < 64; ++i) L.o_cw[(size_t)q * L.cwplane + (size_t)(first_rec + j / 9) * 64 + i] = 0.f;
+                }
+            }
+            done += wave_kept[0] + wave_kept[1] + wave_kept[2] + wave_kept[3];
+            done_even += wave_even[0] + wave_even[1] + wave_even[2] + wave_even[3];
+            __syncthreads();
         }
+    }
+    // padding: between front and back (one group per wavefront: behind the columns), and the rest
+    // of the last run.  With several groups it selects the zero row of the other parity than the
+    // partner slot's row at that step.
+    int mk = 0, mf = 0, mb = 0;
+    const bool mate = GS > 1 && wk.group[s ^ 1] >= 0;
+    if (mate) shape_of(s ^ 1, mk, mf, mb);
+    const int from = front, to = wk.cnt - back;
+    for (int x = tid; x < (to - from) + (span - wk.cnt); x += 256) {
+        const int j = x < to - from ? from + x : wk.cnt + (x - (to - from));
+        int which = 0;
+        if (GS > 1 && j < wk.cnt) {
+            const int fp = ((s ^ 1) & 1) ? 1 : 0;  // channel parity at the partner's front
+            const int parity = !mate ? -1 : j < mf ? fp : j >= wk.cnt - mb ? 1 - fp : -1;
+            which = parity < 0 ? (s & 1) : (((c0 + L.KC) & 1) == parity ? 1 : 0);
+        }
+        put_pad((long long)wk.start + j, s, c0, which);
     }
 }
 
@@ -630,7 +632,7 @@ int build_all(const LayerIn *in, int n, void *workspace, size_t workspace_bytes,
             p->dev.cw = d.o_cw; p->dev.csel = d.o_csel; p->dev.cwork = d.o_cwork; p->dev.cwplane = d.cwplane;
         }
         sp[(size_t)i].fill = (int)wg_fill;
-        wg_fill += (long long)nseg + 1;
+        wg_fill += (long long)nseg * d.GS + 1;
     }
     if ((rc = upload_tables()) != ALCS_OK) return fail(rc);
     hipLaunchKernelGGL(k_ld_fill, dim3((unsigned)wg_fill), dim3(256), 0, st, d_layers, d_spread, n);
