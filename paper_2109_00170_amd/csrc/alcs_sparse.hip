@@ -224,8 +224,10 @@ __device__ __forceinline__ float activate(const ConvArgs &a, float v) {
     return v;
 }
 // One branch for all pixels of a channel: per value it costs the layers with few input channels, which are mostly
-// stores, 5 to 10 % (40->928 @28x17, N=34, bfloat16: 14.8 against 16.6 us).  Behind a residual the values come one
-// by one anyway, and the branch per value is the faster form (24->376 @49x49, N=54, V=16: 78.7 against 83.2 us).
+// stores, 5 to 10 % (40->928 @28x17, N=34, bfloat16: 14.8 against 16.6 us).  Behind a residual, and in
+// the blocks with a depthwise stage, the branch per value is the faster form (24->376 @49x49, N=54, V=16 with a
+// residual: 78.7 against 83.2 us; the block 32->64 @112x112, N=32: 35.8 against 37.0).
+constexpr bool kOneBranch = !kDw;
 template <int PV>
 __device__ __forceinline__ void activate_pixels(const ConvArgs &a, float (&x)[PV]) {
     if constexpr (kFused) {
@@ -1030,8 +1032,8 @@ __device__ __forceinline__ void store_group(const ConvArgs &a, const Acc<V, PV, 
                 if (ch >= a.Cout) break;
                 float x[PV];
 #pragma unroll
-                for (int pv = 0; pv < PV; ++pv) x[pv] = RES == kNone ? value(v, pv) : activate(a, value(v, pv));
-                if constexpr (RES == kNone) activate_pixels(a, x);
+                for (int pv = 0; pv < PV; ++pv) x[pv] = kOneBranch && RES == kNone ? value(v, pv) : activate(a, value(v, pv));
+                if constexpr (kOneBranch && RES == kNone) activate_pixels(a, x);
                 store_pixels<PV, AC>(a.Y + (size_t)ch * a.P, px, x);
             }
         }
