@@ -642,7 +642,7 @@ def report(kind, alcs, workloads, torch, np):
             for _ in range(reps):
                 alcs.alcs_topn_mask(allsc, n // 2, seg_starts=starts)
             t_sel = (time.perf_counter() - t0) * 1e6 / reps
-            by_sel = 9 * 4 * n + n
+            by_sel = 5 * 4 * n + n  # three histograms, the equal blocks, the flags
             # latency tables of the shape measured on this GPU: a floor plus a slope per kept weight
             tables = []
             for co, ci, k in shapes:

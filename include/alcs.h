@@ -53,8 +53,9 @@ typedef enum alcs_status {
  * alcs_packed_add_bf16_weights, neither of which may run while another thread uses the handle);
  * may be used from several streams at once.  The library keeps no state outside
  * handles except two per-thread diagnostics (alcs_last_hip_error, alcs_last_launch),
- * the device array of alcs_topn_mask_static and the compute-unit / XCD counts of each
- * device, read from its properties once. */
+ * the device array of alcs_topn_mask_static, freed device memory (alcs_release_memory),
+ * and, read or set once per device, its compute-unit / XCD counts, the register counts of
+ * kernels and their LDS allowance. */
 typedef struct alcs_packed alcs_packed_t;
 
 /* Human-readable name of a status code (static string, never NULL). */

@@ -40,7 +40,8 @@ struct DenseArgs {
 // and since the order of K is free, lane half h takes channels 4h ... 4h+3 of a group of 8 in four
 // consecutive instructions - one 16-byte LDS read per operand for four of them.  The loads of step
 // i+1 are issued between the multiplies of step i.
-// What bounds a launch is the matrix pipe (65 to 75 % busy) and, on few tiles, how evenly they divide over
+// What bounds a launch is the matrix pipe (3x3: 52 to 61 % of a single launch's cycles busy, start and
+// drain included; 64 % of its peak in a stream of launches) and, on few tiles, how evenly they divide over
 // the compute units (the launcher picks the tile for that).  3x3, N=64, against the patch matrix
 // gathered word by word: 128->128 @28x28 260 -> 147 us (101 TFLOP/s), 512->512 @7x7 577 -> 176 us,
 // 40->23 @112x86 424 -> 175 us; 1x1 1024->256 @14x14 101 -> 80 us.  1x1 layers with few
