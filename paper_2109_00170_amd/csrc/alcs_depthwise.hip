@@ -120,7 +120,7 @@ __global__ void __launch_bounds__(256) k_depthwise_rows(const DwArgs a) {
         row[u] = rc * a.rows + r;
         qx[u] = wide ? ((int)chunk - rc * a.cblocks) * 62 + lane - 1 : item - r * QW;
         st.init((uint32_t)pl * a.Pin, min(max(qx[u], 0), QW - 1), min(row[u], a.Ho - 1), a.H, a.W);
-        st.load(a.X + (size_t)p0 * a.Pin, v[u]);
+        st.load(DwStrip<S>::rows_from(a.X, p0 * a.Pin, a.planes * a.Pin), v[u]);
         const float *wp;
         const unsigned c = (unsigned)(plane[u] % a.C);
         wp = a.D + (size_t)c * 9;
@@ -135,7 +135,9 @@ __global__ void __launch_bounds__(256) k_depthwise_rows(const DwArgs a) {
         const bool mine = wide ? lane > 0 && lane < 63 && qx[u] < QW : lane < CW * LPC;
         const int nout = mine ? min(4, a.Wo - 4 * qx[u]) : 0;
         if (NU > 1) st.init(0, min(max(qx[u], 0), QW - 1), min(row[u], a.Ho - 1), a.H, a.W);
-        const dws_f4 o = st.filter(v[u], w[u], b[u], a.act);
+        dws_f4 out[1];
+        st.filter(v[u], w[u], b[u], a.act, false, out);
+        const dws_f4 o = out[0];
         if (row[u] >= a.Ho) continue;
         float *d = a.Z + (size_t)plane[u] * a.P + (size_t)row[u] * a.Wo + 4 * qx[u];
         if (nout == 4) __builtin_nontemporal_store((dws_f4u)o, reinterpret_cast<dws_f4u *>(d));

@@ -791,37 +791,41 @@ __device__ __forceinline__ void stage_dw_mode(const ConvArgs &a, float *lds, int
     }
 }
 
-// The same for tiles of a.dw_rows whole output rows: a lane works out four neighbouring pixels of a
-// row (alcs_dw_strip.h), the lanes of a wavefront cover the tile's rows for as many channels as fit -
-// 8 channels of 2 rows of 14, one channel of 4 rows of 56.  The form above is a chain of nine loads,
+// The same for tiles of a.dw_rows whole output rows: a lane works out four neighbouring pixels of K
+// rows (alcs_dw_strip.h), the lanes of a wavefront cover the tile's rows for as many channels as fit -
+// 16 channels of 2 rows of 14, four channels of 2 rows of 56.  The form above is a chain of nine loads,
 // a wait and one write per channel and pixel, 16 times in a row at 512 channels on 32 pixels; this
-// one is bound by the bytes of the rows (three input rows per output row, out of L1 and L2).
-template <int TP, int S>
+// one is bound by the instructions of a lane's pixels and one or two round trips to the rows.
+template <int TP, int S, int K, int U>
 __device__ __forceinline__ void stage_dw_rows_s(const ConvArgs &a, float *lds, int q0, int q_end) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
-    const int QW = (a.Wo + 3) >> 2;              // lanes per row
-    const int RW = min(a.dw_rows, 64 / QW);      // rows per pass
-    const int LPC = RW * QW;                     // lanes per channel
-    const int CW = min(64 / LPC, a.Cin);         // channels per wavefront
+    const int QW = (a.Wo + 3) >> 2;                          // lanes per row (or K rows)
+    const int RW = min((a.dw_rows + K - 1) / K, 64 / QW);    // sets of K rows per pass
+    const int LPC = RW * QW;                                 // lanes per channel
+    const int CW = min(64 / LPC, a.Cin);                     // channels per wavefront
     const int ngrp = (a.Cin + CW - 1) / CW;
-    const bool uniform = CW == 1;
+    const bool uniform = K == 1 && CW == 1;
     const int cl = min(lane / LPC, CW - 1), item = lane - lane / LPC * LPC;
     const int r = item / QW, qx = item - r * QW;
     const int R0 = q0 / a.Wo, n0 = R0 / a.Ho;    // the tile's first row and image
     const int nrow = (q_end - q0) / a.Wo;        // rows of the tile that are there
     const int nout = lane < CW * LPC ? min(4, a.Wo - 4 * qx) : 0;
-    const float *src = a.X + (size_t)n0 * a.Cin * a.Pin;
+    const bool crossing = K == 2 && ((a.Ho & 1) || (R0 & 1));  // a lane's two rows may lie in two images
+    const long long at = (long long)n0 * a.Cin * a.Pin, total = (long long)a.N * a.Cin * a.Pin;
     const float *wl = a.dw_w + (size_t)cl * 9;
     const auto ws = as_const(a.dw_w);
-    for (int row0 = 0; row0 < nrow; row0 += RW) {
-        const int rr = row0 + r;
-        const int R = R0 + min(rr, nrow - 1), n = R / a.Ho;
-        DwStrip<S> st;
-        st.init(((uint32_t)(n - n0) * a.Cin + cl) * a.Pin, qx, R - n * a.Ho, a.H, a.W);
+    for (int row0 = 0; row0 < nrow; row0 += RW * K) {
+        const int rr = row0 + r * K;
+        const int R = R0 + min(rr, nrow - 1), n = R / a.Ho, ho = R - n * a.Ho;
+        const uint32_t plane = ((uint32_t)(n - n0) * a.Cin + cl) * a.Pin;
+        DwStrip<S, K> st;
+        // (the next image only where the second row is one of the tile's)
+        st.init(plane, qx, ho, a.H, a.W, plane + (uint32_t)a.Cin * a.Pin, K == 2 && ho == a.Ho - 1 && rr + 1 < nrow);
         float *dst = lds + cl * TP + rr * a.Wo + 4 * qx;
-        const int put = rr < nrow && r < RW ? nout : 0;
-        const bool whole = put == 4 && (a.Wo & 3) == 0;
+        int put[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) put[k] = rr + k < nrow && r < RW ? nout : 0;
         auto weights = [&](int c, float (&w)[9], float &b) __attribute__((always_inline)) {
             if (uniform) {
 #pragma unroll
@@ -836,47 +840,58 @@ __device__ __forceinline__ void stage_dw_rows_s(const ConvArgs &a, float *lds, i
                 b = a.dw_bias ? a.dw_bias[c + cl] : 0.f;
             }
         };
-        auto finish = [&](int c, const typename DwStrip<S>::Raw &v, const float (&w)[9], float b) __attribute__((always_inline)) {
-            const dws_f4 o = st.filter(v, w, b, a.dw_act);
-            float *d = dst + c * TP;
-            if (whole) *reinterpret_cast<f4 *>(d) = o;
-            else {
+        auto finish = [&](int c, const typename DwStrip<S, K>::Raw &v, const float (&w)[9], float b) __attribute__((always_inline)) {
+            dws_f4 o[K];
+            st.filter(v, w, b, a.dw_act, crossing, o);
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (j < put) d[j] = o[j];
+            for (int k = 0; k < K; ++k) {
+                float *d = dst + c * TP + k * a.Wo;
+                if ((a.Wo & 3) == 0) {
+                    if (put[k]) *reinterpret_cast<f4 *>(d) = o[k];
+                } else if ((a.Wo & 1) == 0) {   // pairs: a row has an even number of pixels
+                    if (put[k]) *reinterpret_cast<f2 *>(d) = f2{o[k][0], o[k][1]};
+                    if (put[k] == 4) *reinterpret_cast<f2 *>(d + 2) = f2{o[k][2], o[k][3]};
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (j < put[k]) d[j] = o[k][j];
+                }
             }
         };
         // (the last wavefront's channels end with the tensor's: some are worked out twice)
         auto first_channel = [&](int g) { return min(g * CW, a.Cin - CW); };
-        constexpr int U = S == 1 ? 2 : 1;
+        auto rows_of = [&](int c) { return DwStrip<S, K>::rows_from(a.X, at + (long long)c * a.Pin, total); };
         int g = wave;
         for (; g + (U - 1) * nw < ngrp; g += U * nw) {
-            typename DwStrip<S>::Raw v[U];
+            typename DwStrip<S, K>::Raw v[U];
             float w[U][9], b[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int c = first_channel(g + u * nw);
-                st.load(src + (size_t)c * a.Pin, v[u]);
+                st.load(rows_of(c), v[u]);
                 weights(c, w[u], b[u]);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) finish(first_channel(g + u * nw), v[u], w[u], b[u]);
         }
         for (; U > 1 && g < ngrp; g += nw) {
-            typename DwStrip<S>::Raw v;
+            typename DwStrip<S, K>::Raw v;
             float w[9], b;
             const int c = first_channel(g);
-            st.load(src + (size_t)c * a.Pin, v);
+            st.load(rows_of(c), v);
             weights(c, w, b);
             finish(c, v, w, b);
         }
     }
 }
-
 template <int TP>
 __device__ __forceinline__ void stage_dw(const ConvArgs &a, float *lds, int q0, int q_end) {
-    if (a.dw_rows > 0 && a.dw_stride == 1) stage_dw_rows_s<TP, 1>(a, lds, q0, q_end);
-    else if (a.dw_rows > 0) stage_dw_rows_s<TP, 2>(a, lds, q0, q_end);
+    // Stride 2: one row per lane - the five input rows of a pair take 40 registers, which costs every block
+    // of the kernel a workgroup per compute unit (128->128 @56x56, N=32, V=4, stride 1: 43.2 us against 42.4; MobileNetV1's
+    // 13 blocks 401 against 388).
+    if (a.dw_rows > 1 && a.dw_stride == 1) stage_dw_rows_s<TP, 1, 2, 2>(a, lds, q0, q_end);
+    else if (a.dw_rows > 0 && a.dw_stride == 1) stage_dw_rows_s<TP, 1, 1, 1>(a, lds, q0, q_end);
+    else if (a.dw_rows > 0) stage_dw_rows_s<TP, 2, 1, 1>(a, lds, q0, q_end);
     else if (a.dw_mode == kDwPair) stage_dw_mode<TP, kDwPair>(a, lds, q0, q_end);
     else stage_dw_mode<TP, kDwNine>(a, lds, q0, q_end);
 }
@@ -2326,8 +2341,10 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
                 const int per_cu = 4 * std::min(8, 512 / std::max(1, (regs + 7) & ~7)), wgs = kMaxLds / lds;
                 if ((long long)a.npt * a.ngt <= kCUs) nw = 16;
                 else if (wgs >= 4) nw = NB <= 4 ? 4 : 8;
-                else nw = std::min(dw_s2 ? 8 : 16, std::max(8, per_cu / wgs));
+                else nw = std::min(dw_s2 ? 8 : 16, std::max(8, per_cu / wgs & ~3));
             } else if (nw > 8 && (long long)a.npt * a.ngt > kCUs && 2 * lds <= kMaxLds && kernel_registers(kern) > 64) nw = 8;
+            // The four SIMDs get as many wavefronts each (144->24 @56x56, N=128, V=8: 91 us with 8, 132 with 10).
+            if (nw > 4) nw = (nw + 3) & ~3;
             if (T.waves > 0) nw = std::min(T.waves, 16);
             if (ac == kStrided) nw = std::max(nw, TP / 64);  // a thread stages one pixel of the tile
             // Wavefronts without a bundle of their own share the others': as many per bundle (a power of

@@ -38,7 +38,10 @@ def test_layer(C, N, H, W, stride):
     (7, 14, 14, 5, 2), (29, 7, 7, 9, 4), (18, 3, 13, 7, 1), (40, 12, 15, 4, 2), (21, 6, 50, 3, 1), (5, 3, 63, 3, 1),
     (9, 14, 14, 80, 1),     # whole rows would make a second round of the chip
     (4, 56, 56, 10, 0),     # few input channels: pixel pairs at stride 2 too
-    (12, 4, 100, 2, 2), (9, 2, 121, 2, 4), (10, 3, 250, 2, 4), (16, 28, 28, 2, 4), (130, 2, 4, 3, 4)])
+    (12, 4, 100, 2, 2), (9, 2, 121, 2, 4), (10, 3, 250, 2, 4), (16, 28, 28, 2, 4), (130, 2, 4, 3, 4),
+    # a lane's two rows in two images: one-row images, an odd first row, the last image's odd row
+    (6, 1, 16, 9, 1), (13, 4, 21, 5, 1), (14, 5, 10, 7, 2), (17, 3, 4, 11, 4),
+    (19, 6, 17, 3, 1), (23, 4, 30, 4, 2)])   # widths of every remainder
 def test_block_on_whole_rows(Cin, H, W, N, pv, stride):
     Hin, Win = (H, W) if stride == 1 else (2 * H - H % 2, 2 * W - W % 2)   # odd and even inputs
     L = workloads.Layer("rows", Cin, 20, H, W, N=N, V=4, sparsity=0.5, w_std=0.3)
