@@ -200,7 +200,8 @@ struct ConvArgs {
     const float *dw_bias;  // [Cin] or null
     int dw_stride, dw_act;
     int dw_mode;           // DwMode: how lanes share taps
-    int dw_rows;           // tiles are this many whole rows (stage_dw_rows), or 0 (stage_dw_mode)
+    int dw_rows;           // tiles are this many whole rows (stage_dw_rows_s), or 0 (stage_dw_mode)
+    int dw_pairs;          // two of them per lane
 #endif
 };
 
@@ -884,12 +885,12 @@ __device__ __forceinline__ void stage_dw_rows_s(const ConvArgs &a, float *lds, i
         }
     }
 }
-template <int TP>
+template <int TP, int U>
 __device__ __forceinline__ void stage_dw(const ConvArgs &a, float *lds, int q0, int q_end) {
-    // Stride 2: one row per lane - the five input rows of a pair take 40 registers, which costs every block
-    // of the kernel a workgroup per compute unit (128->128 @56x56, N=32, V=4, stride 1: 43.2 us against 42.4; MobileNetV1's
-    // 13 blocks 401 against 388).
-    if (a.dw_rows > 1 && a.dw_stride == 1) stage_dw_rows_s<TP, 1, 2, 2>(a, lds, q0, q_end);
+    // Stride 2: one row per lane - the five input rows of a pair take 40 registers, and all kernels of a block would
+    // hold them (MobileNetV1's 13 blocks, N=32: 401 us against 388).  Two channels in flight only where the tile's
+    // kernel has one workgroup per compute unit anyway (160->113 @112x112, N=10: 75 us with two, 62 with one).
+    if (a.dw_pairs) stage_dw_rows_s<TP, 1, 2, U>(a, lds, q0, q_end);
     else if (a.dw_rows > 0 && a.dw_stride == 1) stage_dw_rows_s<TP, 1, 1, 1>(a, lds, q0, q_end);
     else if (a.dw_rows > 0) stage_dw_rows_s<TP, 2, 1, 1>(a, lds, q0, q_end);
     else if (a.dw_mode == kDwPair) stage_dw_mode<TP, kDwPair>(a, lds, q0, q_end);
@@ -1174,7 +1175,7 @@ __device__ __forceinline__ void pw_resident_body(const ConvArgs &a) {
     }
 
 #if ALCS_DW_STAGE
-    if (!skip(a, 1)) stage_dw<TP>(a, lds, q0, q_end);
+    if (!skip(a, 1)) stage_dw<TP, (GS > 1 && V < 16 ? 2 : 1)>(a, lds, q0, q_end);
 #else
     if (!skip(a, 1)) stage_pw<TP, AC>(a, lds, q0, 0, a.Cin, q_end);
 #endif
@@ -1285,7 +1286,7 @@ __global__ void __launch_bounds__(1024) k_pw_split(const ConvArgs a) {
         }
     }
 #if ALCS_DW_STAGE
-    if (!skip(a, 1)) stage_dw<TP>(a, lds, q0, q_end);
+    if (!skip(a, 1)) stage_dw<TP, (GS > 1 && V < 16 ? 2 : 1)>(a, lds, q0, q_end);
 #else
     if (!skip(a, 1)) stage_pw<TP, AC>(a, lds, q0, 0, a.Cin, q_end);
 #endif
@@ -2403,7 +2404,7 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             tall = false;
             ti = pick_tile3(Ho, Wo, T.tile_w, false);
         }
-        const bool shared = Wp->dev.cw && mfma && V <= 8 && T.path != 6 && (tall || T.path == 7);
+        const bool shared = Wp->dev.cw && mfma && V <= 8 && T.path != 6 && (tall || L.nchunks > 1 || T.path == 7);
         pv = tall ? 2 : 1;
         a.off = Wp->dev.off[off_table3(stride, ti, tall)];
         lds = (L.KC + 1) * halo_area3(stride, ti, tall) * 4;
