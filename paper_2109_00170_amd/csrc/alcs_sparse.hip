@@ -2446,8 +2446,10 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
     // larger part of it (128->256 stride 2 to 28x28, N=8: 11.2 us against 12.2; 256->256 @28x28, N=16: 17.3 against
     // 18.9, but 256->512 stride 2 to 14x14, N=32: 19.3 against 18.2, 192->32 @28x28, one image: 8.2 against 7.5; not on
     // whole rows, 816->80 @41x37, N=2: 38.3 against 21.8; in more than one round, 264->88 @28x19, N=22: 24.1 against
-    // 18.6).  The caller that can run the two layers (it has a workspace) is told to.
-    const bool restage_ok = a.ngt == 1 || (a.ngt == 2 && a.npt >= 80 && 2 * a.npt <= kCUs && a.dw_rows > 0 &&
+    // 18.6).  Nor do several groups per wavefront pay without whole rows, one pixel of one channel per lane and trip
+    // (584->24 @56x56, N=38, V=8: 271 us against 192).  The caller that can run the two layers (it has a
+    // workspace) is told to.
+    const bool restage_ok = (a.ngt == 1 && (L.GS == 1 || a.dw_rows > 0)) || (a.ngt == 2 && a.npt >= 80 && 2 * a.npt <= kCUs && a.dw_rows > 0 &&
                                            (dw->stride == 1 || Cin * a.tile_px <= 8192));
     if (decline_restaged && !restage_ok && !T.dw_one_kernel) return ALCS_E_UNSUPPORTED;
 #endif
