@@ -1507,60 +1507,77 @@ __global__ void __launch_bounds__(512) k_pw_stream(const ConvArgs a) {
 // One (group, chunk) of a handle whose kept channels keep all nine taps: one record per kept
 // CHANNEL (its chunk-relative index and its 9 x V weights, see alcs_chanrec.hip) instead of one
 // column per tap.  The nine LDS reads of a channel differ by compile-time offsets from one
-// address, so the per-column selector broadcast and address add of the column-by-column walk
-// (one vector instruction for every two matrix instructions) shrink to one v_readlane and one
-// add per channel, and a channel's weights are one 256-byte line per plane in block-broadcast
-// order (lane 4t + i = tap t, row i: abid = t) instead of nine sixteenths of two runs.
-// Measured on this GPU the multiply is bound by the sum of vector and matrix instructions
-// issued per SIMD, not by LDS bandwidth: a variant that read each input row once and took the
-// left and right taps from the neighbouring lanes (two DPP shifts per row and pixel, halo words
-// only in the row's end lanes: 3 + 3 narrow reads instead of 9) was 10-30 % SLOWER than the
-// column walk (64->64 @56x56: 91 against 83 us, 256->256 @14x14: 103 against 79), because its
-// 24 extra vector instructions per channel cost more than the 6 reads they saved.
+// address, so the selector add of the column-by-column walk - vector instructions do not overlap with the
+// matrix instructions of a SIMD, LDS reads do: 15.0 cycles a column with it, 11.2 without, one pixel per lane -
+// is paid once per channel.  A channel's weights are one 256-byte line per plane in block-broadcast order (lane
+// 4t + i = tap t, row i: abid = t).  The first eight channels' lines are requested with the selectors before the
+// chunk is staged, and every register is filled again right behind its use with the line eight channels on: with
+// one line ahead the walk waited for it at every channel (256->256 @14x14, N=64, 80 % sparse: 81 us, now 72).
+// (A variant that read each input row once and took the left and right taps from the neighbouring
+// lanes - two DPP shifts per row and pixel - was 10-30 % slower than the column walk: its 24 extra vector
+// instructions per channel cost more than the 6 reads they saved.)
+constexpr int kChanAhead = 8;  // channels whose weights are in registers
+template <int V>
+struct Chans {
+    float w[kChanAhead][V / 4];
+    int sel;  // lane l: byte offset of the plane of channel l % 8
+};
+template <int PLANE>
+__device__ __forceinline__ int load_chan_sel(const ConvArgs &a, int first, int j, int n, int lane) {
+    return a.csel[first + min(j + (lane & 7), max(n - 1, 0))] * PLANE;
+}
+// The first channels of a segment; beyond the last one it is read again (record `first` exists for an empty one too:
+// the arrays end with a spare record).
+template <int V, int PLANE>
+__device__ __forceinline__ Chans<V> load_chans(const ConvArgs &a, int first, int n, int lane) {
+    Chans<V> c;
+    c.sel = load_chan_sel<PLANE>(a, first, 0, n, lane);
+#pragma unroll
+    for (int i = 0; i < kChanAhead; ++i)
+#pragma unroll
+        for (int q = 0; q < V / 4; ++q)
+            c.w[i][q] = a.cw[(size_t)q * a.cwplane + (size_t)(first + min(i, max(n - 1, 0))) * 64 + lane];
+    return c;
+}
 template <int V, int STRIDE, int TI, bool TALL>
 __device__ __forceinline__ void mac_channels(const ConvArgs &a, int first, int n, const char *ldsb, int lane_byte,
-                                             int lane, Acc<V, TALL ? 2 : 1, true> &acc) {
+                                             int lane, Chans<V> c, Acc<V, TALL ? 2 : 1, true> &acc) {
     constexpr int PV = TALL ? 2 : 1;
     constexpr int PD = TALL ? tall_step3(TI) : 1;
     constexpr int PITCH = pitch3(STRIDE, TI);
     constexpr int PLANE = halo_area3(STRIDE, TI, TALL) * 4;
     constexpr int NACC = Acc<V, PV, true>::NACC;
-    if (n <= 0) return;
-    const float *wp = a.cw + (size_t)first * 64 + lane;
-    float wa[V / 4], wb[V / 4];
+    auto pass = [&](int j0) {
+        const int sel = c.sel;
+        if (j0 + kChanAhead < n) c.sel = load_chan_sel<PLANE>(a, first, j0 + kChanAhead, n, lane);
+        static_for<kChanAhead>([&](auto ii) {
+            constexpr int I = decltype(ii)::value;
+            const int j = j0 + I;
+            if (j < n) {
+                const char *pl = ldsb + lane_byte + bcast_sel<I>(sel);
+                float x[9][PV];
+                static_for<9>([&](auto tt) {
+                    constexpr int T = decltype(tt)::value;
+                    lds_read<PV, PD>(reinterpret_cast<const float *>(pl + ((T / 3) * PITCH + halo_col3(STRIDE, TI, T % 3)) * 4), x[T]);
+                });
+                static_for<9>([&](auto tt) {
+                    constexpr int T = decltype(tt)::value;
 #pragma unroll
-    for (int q = 0; q < V / 4; ++q) wa[q] = wp[(size_t)q * a.cwplane];
-    int selv = a.csel[first + min(lane, n - 1)];
-    auto channel = [&](int j, const float (&w)[V / 4]) {
-        const int crel = __builtin_amdgcn_readlane(selv, j & 63);
-        const char *pl = ldsb + lane_byte + crel * PLANE;
-        float x[9][PV];
-        static_for<9>([&](auto tt) {
-            constexpr int T = decltype(tt)::value;
-            lds_read<PV, PD>(reinterpret_cast<const float *>(pl + ((T / 3) * PITCH + halo_col3(STRIDE, TI, T % 3)) * 4), x[T]);
-        });
-        static_for<9>([&](auto tt) {
-            constexpr int T = decltype(tt)::value;
+                    for (int q = 0; q < V / 4; ++q)
 #pragma unroll
-            for (int q = 0; q < V / 4; ++q)
+                        for (int pv = 0; pv < PV; ++pv)
+                            acc.a[T % NACC][q][pv] = __builtin_amdgcn_mfma_f32_4x4x1f32(c.w[I][q], x[T][pv], acc.a[T % NACC][q][pv], 4, T, 0);
+                });
+                if (j + kChanAhead < n)
 #pragma unroll
-                for (int pv = 0; pv < PV; ++pv)
-                    acc.a[T % NACC][q][pv] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[q], x[T][pv], acc.a[T % NACC][q][pv], 4, T, 0);
+                    for (int q = 0; q < V / 4; ++q)
+                        c.w[I][q] = a.cw[(size_t)q * a.cwplane + (size_t)(first + j + kChanAhead) * 64 + lane];
+            }
         });
     };
-    for (int j = 0; j < n; j += 2) {
-        // the next record's weights are requested before this one is multiplied; beyond the last
-        // record the last one is read again
-        if ((j & 63) == 0 && j) selv = a.csel[first + j + min(lane, n - j - 1)];
-        const float *w1 = wp + (size_t)min(j + 1, n - 1) * 64;
-#pragma unroll
-        for (int q = 0; q < V / 4; ++q) wb[q] = w1[(size_t)q * a.cwplane];
-        channel(j, wa);
-        const float *w2 = wp + (size_t)min(j + 2, n - 1) * 64;
-#pragma unroll
-        for (int q = 0; q < V / 4; ++q) wa[q] = w2[(size_t)q * a.cwplane];
-        if (j + 1 < n) channel(j + 1, wb);
-    }
+    // (the first pass runs on registers that have been waited for, see mac_segment)
+    pass(0);
+    for (int j0 = kChanAhead; j0 < n; j0 += kChanAhead) pass(j0);
 }
 
 // ------------------------------------------------------------------ 3x3 kernel
@@ -1626,6 +1643,7 @@ __global__ void __launch_bounds__(512) k_conv3(const ConvArgs a) {
         // that their latency is covered by the staging (vector memory returns in order)
         Work wk[UG];
         Runs<V, MF> rn[UG];
+        Chans<TS ? V : 4> cr[UG];
         int cfirst[UG], cn[UG];
 #pragma unroll
         for (int u = 0; u < UG; ++u) {
@@ -1636,6 +1654,7 @@ __global__ void __launch_bounds__(512) k_conv3(const ConvArgs a) {
                     const cptr<int32_t> cwk = as_const(a.cwork) + 2 * ((size_t)slot[u] * a.nchunks + ch);
                     cfirst[u] = __builtin_amdgcn_readfirstlane(cwk[0]);
                     cn[u] = __builtin_amdgcn_readfirstlane(cwk[1]);
+                    cr[u] = load_chans<V, HA * 4>(a, cfirst[u], cn[u], lane);
                 } else {
                     wk[u] = load_work(a.work, (size_t)slot[u] * a.nchunks + ch);
                     rn[u] = load_runs<V, MF>(a, wk[u].start, wk[u].cnt, lane);
@@ -1689,7 +1708,7 @@ __global__ void __launch_bounds__(512) k_conv3(const ConvArgs a) {
 #pragma unroll
             for (int u = 0; u < UG; ++u)
                 if (slot[u] >= 0 && !skip(a, 2))
-                    mac_channels<V, STRIDE, TI, TALL>(a, cfirst[u], cn[u], ldsb, lane_base * 4, lane, acc[u]);
+                    mac_channels<V, STRIDE, TI, TALL>(a, cfirst[u], cn[u], ldsb, lane_base * 4, lane, cr[u], acc[u]);
         } else {
             const int base = (lane_base - c0 * HA) * 4;
 #pragma unroll
@@ -2347,6 +2366,18 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             // The four SIMDs get as many wavefronts each (144->24 @56x56, N=128, V=8: 91 us with 8, 132 with 10).
             if (nw > 4) nw = (nw + 3) & ~3;
             if (T.waves > 0) nw = std::min(T.waves, 16);
+#if ALCS_DW_STAGE
+            // Two rows per lane: a wavefront's turn takes about 1.6 times as long and there are half as many, unless
+            // few channels leave wavefronts without one (21->159 @112x112, N=13, V=1: 39 us in pairs, 34 not).
+            if (rows > 1 && !dw_s2) {
+                const int QW = (Wo + 3) / 4;
+                auto turns = [&](int K) {
+                    const int lpc = std::min(ceil_div(rows, K), 64 / QW) * QW;
+                    return ceil_div(ceil_div(Cin, std::min(64 / lpc, Cin)), nw) * ceil_div(ceil_div(rows, K), 64 / QW);
+                };
+                a.dw_pairs = 8 * turns(2) <= 5 * turns(1);
+            }
+#endif
             if (ac == kStrided) nw = std::max(nw, TP / 64);  // a thread stages one pixel of the tile
             // Wavefronts without a bundle of their own share the others': as many per bundle (a power of
             // two) as there are, and as its longest segment has runs of 16 columns.
