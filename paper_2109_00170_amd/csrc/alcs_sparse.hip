@@ -1510,16 +1510,20 @@ __global__ void __launch_bounds__(512) k_pw_stream(const ConvArgs a) {
 // address, so the selector add of the column-by-column walk - vector instructions do not overlap with the
 // matrix instructions of a SIMD, LDS reads do: 15.0 cycles a column with it, 11.2 without, one pixel per lane -
 // is paid once per channel.  A channel's weights are one 256-byte line per plane in block-broadcast order (lane
-// 4t + i = tap t, row i: abid = t).  The first eight channels' lines are requested with the selectors before the
-// chunk is staged, and every register is filled again right behind its use with the line eight channels on: with
+// 4t + i = tap t, row i: abid = t).  The first channels' lines (eight, or four with two planes) are requested with the selectors before the
+// chunk is staged, and every register is filled again right behind its use with the line as many channels on: with
 // one line ahead the walk waited for it at every channel (256->256 @14x14, N=64, 80 % sparse: 81 us, now 72).
 // (A variant that read each input row once and took the left and right taps from the neighbouring
 // lanes - two DPP shifts per row and pixel - was 10-30 % slower than the column walk: its 24 extra vector
 // instructions per channel cost more than the 6 reads they saved.)
-constexpr int kChanAhead = 8;  // channels whose weights are in registers
+// Channels whose weights are in registers: eight; four with two planes, or two workgroups no longer share a compute
+// unit.
+template <int V>
+constexpr int chans_ahead() { return V == 4 ? 8 : 4; }
 template <int V>
 struct Chans {
-    float w[kChanAhead][V / 4];
+    static constexpr int N = chans_ahead<V>();
+    float w[N][V / 4];
     int sel;  // lane l: byte offset of the plane of channel l % 8
 };
 template <int PLANE>
@@ -1532,11 +1536,18 @@ template <int V, int PLANE>
 __device__ __forceinline__ Chans<V> load_chans(const ConvArgs &a, int first, int n, int lane) {
     Chans<V> c;
     c.sel = load_chan_sel<PLANE>(a, first, 0, n, lane);
+    auto some = [&](auto i0, auto count) {
 #pragma unroll
-    for (int i = 0; i < kChanAhead; ++i)
+        for (int i = decltype(i0)::value; i < decltype(i0)::value + decltype(count)::value; ++i)
 #pragma unroll
-        for (int q = 0; q < V / 4; ++q)
-            c.w[i][q] = a.cw[(size_t)q * a.cwplane + (size_t)(first + min(i, max(n - 1, 0))) * 64 + lane];
+            for (int q = 0; q < V / 4; ++q)
+                c.w[i][q] = a.cw[(size_t)q * a.cwplane + (size_t)(first + min(i, max(n - 1, 0))) * 64 + lane];
+    };
+    // (in two steps: at 95 % sparsity a chunk has one or two channels of a group - 400->368 @14x19, N=90 140 us before
+    // there were lines ahead, 157 with eight each time)
+    constexpr int N = Chans<V>::N;
+    some(std::integral_constant<int, 0>{}, std::integral_constant<int, N / 2>{});
+    if (n > N / 2) some(std::integral_constant<int, N / 2>{}, std::integral_constant<int, N / 2>{});
     return c;
 }
 template <int V, int STRIDE, int TI, bool TALL>
@@ -1546,11 +1557,11 @@ __device__ __forceinline__ void mac_channels(const ConvArgs &a, int first, int n
     constexpr int PD = TALL ? tall_step3(TI) : 1;
     constexpr int PITCH = pitch3(STRIDE, TI);
     constexpr int PLANE = halo_area3(STRIDE, TI, TALL) * 4;
-    constexpr int NACC = Acc<V, PV, true>::NACC;
+    constexpr int NACC = Acc<V, PV, true>::NACC, N = Chans<V>::N;
     auto pass = [&](int j0) {
         const int sel = c.sel;
-        if (j0 + kChanAhead < n) c.sel = load_chan_sel<PLANE>(a, first, j0 + kChanAhead, n, lane);
-        static_for<kChanAhead>([&](auto ii) {
+        if (j0 + N < n) c.sel = load_chan_sel<PLANE>(a, first, j0 + N, n, lane);
+        static_for<N>([&](auto ii) {
             constexpr int I = decltype(ii)::value;
             const int j = j0 + I;
             if (j < n) {
@@ -1568,16 +1579,16 @@ __device__ __forceinline__ void mac_channels(const ConvArgs &a, int first, int n
                         for (int pv = 0; pv < PV; ++pv)
                             acc.a[T % NACC][q][pv] = __builtin_amdgcn_mfma_f32_4x4x1f32(c.w[I][q], x[T][pv], acc.a[T % NACC][q][pv], 4, T, 0);
                 });
-                if (j + kChanAhead < n)
+                if (j + N < n)
 #pragma unroll
                     for (int q = 0; q < V / 4; ++q)
-                        c.w[I][q] = a.cw[(size_t)q * a.cwplane + (size_t)(first + j + kChanAhead) * 64 + lane];
+                        c.w[I][q] = a.cw[(size_t)q * a.cwplane + (size_t)(first + j + N) * 64 + lane];
             }
         });
     };
     // (the first pass runs on registers that have been waited for, see mac_segment)
     pass(0);
-    for (int j0 = kChanAhead; j0 < n; j0 += kChanAhead) pass(j0);
+    for (int j0 = N; j0 < n; j0 += N) pass(j0);
 }
 
 // ------------------------------------------------------------------ 3x3 kernel
@@ -2435,7 +2446,7 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             tall = false;
             ti = pick_tile3(Ho, Wo, T.tile_w, false);
         }
-        const bool shared = Wp->dev.cw && mfma && V <= 8 && T.path != 6 && (tall || L.nchunks > 1 || T.path == 7);
+        const bool shared = Wp->dev.cw && mfma && V <= 8 && T.path != 6 && (tall || (V == 4 && L.nchunks > 1) || T.path == 7);
         pv = tall ? 2 : 1;
         a.off = Wp->dev.off[off_table3(stride, ti, tall)];
         lds = (L.KC + 1) * halo_area3(stride, ti, tall) * 4;
