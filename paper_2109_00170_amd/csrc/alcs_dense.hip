@@ -43,7 +43,7 @@ struct DenseArgs {
 // What bounds a launch is the matrix pipe (3x3: 52 to 61 % of a single launch's cycles busy, start and
 // drain included; 64 % of its peak in a stream of launches) and, on few tiles, how evenly they divide over
 // the compute units (the launcher picks the tile for that).  3x3, N=64, against the patch matrix
-// gathered word by word: 128->128 @28x28 260 -> 147 us (101 TFLOP/s), 512->512 @7x7 577 -> 176 us,
+// gathered word by word: 128->128 @28x28 260 -> 147 us (k_dense3 95), 512->512 @7x7 577 -> 176 us,
 // 40->23 @112x86 424 -> 175 us; 1x1 1024->256 @14x14 101 -> 80 us.  1x1 layers with few
 // output channels wait for their input: 16 channels a step leave room for 8 workgroups a compute unit
 // (256->64 @56x56, N=40: 59.5 -> 50 us against 32 channels and 3 workgroups).
@@ -323,6 +323,264 @@ __global__ void __launch_bounds__(256, KK == 1 ? 4 : BM == 128 ? 1 : 2) k_dense(
     }
 }
 
+// 3x3, the matrix cores' 16-bit instruction on float32 operands.  A float is the sum of three bfloat16 numbers
+// without a remainder (24 bits as 8 + 8 + 8: the upper half of the word, what is left rounded to nearest, what is left
+// then; below about 1e-33 the smaller parts may underflow), a product of two of them is exact in float32, and of the
+// nine partial products of two floats the three that lie 2^-23 and more below the largest are left out.
+// v_mfma_f32_32x32x16_bf16 does 16 rows of K in half the time v_mfma_f32_32x32x2_f32 does two, so six products take three
+// eighths of the float32 instruction's matrix time.  The largest product goes to one accumulator and the five smaller
+// ones to another: one rounding per 16 rows of K at full size, where the float32 instruction has eight.  Error against
+// 64 bits (2-norm, relative), 40 layers of 16 to 984 channels: 0.35 to 0.42 of the float32 instruction's (128->128: 1.5e-7
+// against 4.2e-7); with all six in one accumulator it was 1.17 of it.
+// Values are split once per workgroup, on the way into LDS: three planes of 8 channels side by side (16 bytes) per
+// weight (tap, row) and per staged position, so an operand of the matrix instruction - 8 consecutive rows of K per lane, lanes
+// 0-31 one tap and lanes 32-63 the next - is one 16-byte read.  Nine taps are four and a half pairs: the tenth reads
+// zeros.  What bounds a launch is the split: its vector instructions do not overlap with the matrix instructions of the
+// same SIMD, so the larger the tile the better (128->128 @28x28, N=64: 157 us on 32 x 128, 130 on 128 x 128, 99 on
+// 128 x 256; float32 on 32 x 128 153).
+// Infinities: their remainders are not numbers, which only the second accumulator sees; where the sum of both is
+// no number the first one stands.
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+
+// Two neighbours of a row of K as words of the three planes.
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t &hi, uint32_t &mid, uint32_t &lo) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const uint32_t u0 = __builtin_bit_cast(uint32_t, x0), u1 = __builtin_bit_cast(uint32_t, x1);
+    const float r0 = x0 - __builtin_bit_cast(float, u0 & 0xffff0000u), r1 = x1 - __builtin_bit_cast(float, u1 & 0xffff0000u);
+    mid = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{r0, r1}, bf2));
+    const float l0 = r0 - __builtin_bit_cast(float, mid << 16), l1 = r1 - __builtin_bit_cast(float, mid & 0xffff0000u);
+    hi = __builtin_amdgcn_perm(u1, u0, 0x07060302);
+    lo = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, l1), __builtin_bit_cast(uint32_t, l0), 0x07060302);
+}
+
+// NT threads; NPT: staged positions per thread.
+template <int BM, int BN, int NT, int NPT>
+__global__ void __launch_bounds__(NT, NT == 512 ? 2 : 3) k_dense3(const DenseArgs a) {
+    constexpr int WM = BM / 32 < 2 ? 1 : 2, WN = NT / 64 / WM;  // wavefronts along the channels and the pixels
+    constexpr int TM = BM / 32 / WM, TN = BN / 32 / WN;
+    constexpr int CH = 8;                     // channels per step
+    constexpr int LDA = BM + 1;               // the odd pitch spreads the taps of a row over the banks
+    constexpr int NA = (BM * 9 + NT - 1) / NT;  // (row, tap) pairs per thread
+    constexpr int NI = NA + NPT;              // items of 8 channels per thread and step
+    extern __shared__ u4 lds3[];
+    const int id = blockIdx.x;
+    const int logical = (id % a.xcds) * a.wg_per_xcd + id / a.xcds;
+    if (logical >= a.total_wgs) return;
+    // consecutive logical ids share the pixel tile (the large operand) and differ in the channel tile
+    const int ntile = logical / a.mt, mtile = logical - ntile * a.mt;
+    const int m0 = mtile * BM;
+    const long long q0 = (long long)ntile * BN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / WN, wn = wave % WN;
+    const int h = lane >> 5, l32 = lane & 31;
+    const int S = a.stride;
+    // a zero row of weights [LDA], and twice: planes of the weights [3][9 * LDA], planes of the input [3][npos + 1], the
+    // last position zero
+    const int LDB = a.npos + 1, BUF = 27 * LDA + 3 * LDB;
+    u4 *const Zs = lds3, *cur = lds3 + LDA, *next = cur + BUF;
+
+    // (the tile's first image, pixel and output row: as in k_dense)
+    const int n0 = q0 >> 32 ? (int)(q0 / a.P) : (int)((uint32_t)q0 / (uint32_t)a.P);
+    const uint32_t p0 = (uint32_t)(q0 - (long long)n0 * a.P);
+    const int ho0 = (int)(p0 / (uint32_t)a.Wo);
+    const int IW = (a.Wo - 1) * S + 3;               // staged columns of an input row, from column -1
+    const int rows_full = (a.Ho - 1) * S + 3;        // staged rows of an image that is there from its first row
+    const int rows_n0 = (a.Ho - 1 - ho0) * S + 3;    // and of the tile's first image
+    const float *xbase = a.X + (size_t)n0 * a.Cin * a.Pin;
+    const float *wbase = a.Wt + (size_t)m0 * a.K;
+
+    int poff[NPT];  // element offset of this thread's positions inside channel 0 of the tile's first image, or -1
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+        const int pos = tid + NT * i;
+        poff[i] = -1;
+        if (pos < a.npos) {
+            const int row = pos / IW, ix = pos - row * IW - 1;
+            int n = n0, iy = ho0 * S - 1 + row;
+            if (row >= rows_n0) {
+                const int r = row - rows_n0, im = r / rows_full;
+                n = n0 + 1 + im;
+                iy = r - im * rows_full - 1;
+            }
+            if (n < a.N && iy >= 0 && iy < a.H && ix >= 0 && ix < a.W)
+                poff[i] = (n - n0) * a.Cin * a.Pin + iy * a.W + ix;
+        }
+    }
+    int bpos[TN];  // the lane's columns of the B operand: position of tap (0, 0)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int e = (wn * TN + j) * 32 + l32;
+        const uint32_t p = p0 + (uint32_t)(q0 + e < a.NP ? e : 0);
+        const int dn = (int)(p / (uint32_t)a.P);
+        const uint32_t in = p - (uint32_t)dn * (uint32_t)a.P;
+        const int ho = (int)(in / (uint32_t)a.Wo), wo = (int)(in - (uint32_t)ho * (uint32_t)a.Wo);
+        const int row = dn == 0 ? (ho - ho0) * S : rows_n0 + (dn - 1) * rows_full + ho * S;
+        bpos[j] = row * IW + wo * S;
+    }
+    // Byte offsets of this thread's share of the weight tile from the tile's first row (rows beyond Cout
+    // read the last one and are not stored).
+    uint32_t aoff[NA];
+    int adst[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int idx = tid + NT * i, m = idx / 9, tap = idx - m * 9;
+        aoff[i] = 4u * ((uint32_t)min(m, a.Cout - 1 - m0) * (uint32_t)a.K + (uint32_t)tap);
+        adst[i] = m < BM ? tap * LDA + m : -1;
+    }
+    for (int i = tid; i < LDA; i += NT) Zs[i] = u4{0, 0, 0, 0};
+    if (tid < 6) (tid < 3 ? cur : next)[27 * LDA + tid % 3 * LDB + a.npos] = u4{0, 0, 0, 0};
+
+    constexpr bool kTwo = TM * TN == 1;  // a lone tile's small products alternate between two accumulators
+    f16v big[TM][TN], small[TM][TN], small2[1][1];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) big[i][j][r] = small[i][j][r] = small2[0][0][r] = 0.f;
+
+    // Item i of a step: (row, tap) pair i of the weights, or position i - NA.  Loads are unconditional, from
+    // addresses that are valid for every lane (places outside the image read place 0 and are zeroed on the way to
+    // LDS), as wave-uniform base + 32-bit offset; the last step of a channel count that is no multiple of 8 reads
+    // channels that are there and zeroes the others.
+    float x[NI][8];
+    auto load = [&](int i, int c0, auto all) __attribute__((always_inline)) {
+        uint32_t o = i < NA ? aoff[min(i, NA - 1)] : 4u * (uint32_t)max(poff[max(i - NA, 0)], 0);
+        asm volatile("" : "+v"(o));
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int c = decltype(all)::value ? c0 + t : min(c0 + t, a.Cin - 1);
+            const float *base = i < NA ? wbase + (size_t)c * 9 : xbase + (size_t)c * a.Pin;
+            x[i][t] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + o);
+            if (!decltype(all)::value && c0 + t >= a.Cin) x[i][t] = 0.f;
+        }
+    };
+    // Its way into LDS, in five parts: four pairs of channels split, and the writes.
+    u4 plane[3];
+    auto store = [&](int i, int part, u4 *buf) __attribute__((always_inline)) {
+        if (part < 4) {
+            float x0 = x[i][2 * part], x1 = x[i][2 * part + 1];
+            if (i >= NA && poff[max(i - NA, 0)] < 0) x0 = x1 = 0.f;
+            uint32_t h3, m3, l3;
+            split2(x0, x1, h3, m3, l3);
+            plane[0][part] = h3;
+            plane[1][part] = m3;
+            plane[2][part] = l3;
+        } else if (i < NA) {
+            if ((BM * 9) % NT == 0 || i < NA - 1 || adst[min(i, NA - 1)] >= 0)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) buf[p * 9 * LDA + adst[min(i, NA - 1)]] = plane[p];
+        } else {
+            const int pos = tid + NT * (i - NA);
+            if (pos < a.npos)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) buf[27 * LDA + p * LDB + pos] = plane[p];
+        }
+    };
+    struct Ops {
+        bf8 a[3][TM], b[3][TN];
+    };
+    auto read_ops = [&](const u4 *buf, int g, Ops &f) __attribute__((always_inline)) {  // taps 2g (lanes 0-31) and 2g + 1
+        const int t0 = 2 * g, t1 = 2 * g + 1;
+        const int d0 = (t0 / 3) * IW + t0 % 3, d1 = (t1 / 3) * IW + t1 % 3;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const int m = (wm * TM + i) * 32 + l32;
+                const u4 *at = g < 4 ? buf + p * 9 * LDA + (t0 + h) * LDA + m : h ? Zs + m : buf + p * 9 * LDA + 8 * LDA + m;
+                f.a[p][i] = __builtin_bit_cast(bf8, *at);
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int at = g < 4 ? bpos[j] + (h ? d1 : d0) : h ? a.npos : bpos[j] + d0;
+                f.b[p][j] = __builtin_bit_cast(bf8, buf[27 * LDA + p * LDB + at]);
+            }
+        }
+    };
+    // One step.  As in k_dense, everything but the multiplies is dealt out between them, so that a wavefront alone on
+    // its SIMD keeps the matrix pipe busy: a slot is one product of all the wavefront's tiles (32 cycles a tile, room for seven
+    // vector instructions), six slots a pair of taps.  The next step's loads go into the first slots, one item each,
+    // its way into the other buffer into the last ones, the next pair's operands into the pair's second slot.
+    constexpr int SLOTS = 30, PARTS = 5 * NI;
+    constexpr int PER = PARTS > 40 ? 3 : PARTS > 20 ? 2 : 1, FIRST = SLOTS - (PARTS + PER - 1) / PER;
+    static_assert(FIRST >= NI || PER == 3, "loads first, stores last");
+    auto step = [&](auto more, const u4 *buf, u4 *to, int c0) __attribute__((always_inline)) {
+        constexpr bool MORE = decltype(more)::value;
+        constexpr int AHEAD = TN == 1 ? 1 : 0;  // pairs of taps whose operands are read ahead
+        Ops f[1 + AHEAD];
+        if (AHEAD) read_ops(buf, 0, f[0]);
+#pragma unroll
+        for (int sl = 0; sl < SLOTS; ++sl) {
+            const int g = sl / 6, pr = sl % 6;
+            if (AHEAD && pr == 1 && g + 1 < 5) read_ops(buf, g + 1, f[(g + 1) & AHEAD]);
+            if (!AHEAD && pr == 0) read_ops(buf, g, f[0]);
+            if (MORE && sl < NI) load(sl, c0 + CH, std::integral_constant<bool, true>{});
+            if (MORE && sl >= FIRST) {
+#pragma unroll
+                for (int v = 0; v < PER; ++v) {
+                    const int u = (sl - FIRST) * PER + v;
+                    if (u < PARTS) store(u / 5, u % 5, to);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int pa[6] = {0, 1, 0, 1, 0, 2}, pb[6] = {1, 0, 0, 1, 2, 0};
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    auto &c = pr == 2 ? big[i][j] : kTwo && pr % 2 ? small2[0][0] : small[i][j];
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[g & AHEAD].a[pa[pr]][i], f[g & AHEAD].b[pb[pr]][j], c, 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+    };
+    constexpr std::integral_constant<bool, true> yes{};
+    constexpr std::integral_constant<bool, false> no{};
+    auto stage = [&](int c0, u4 *buf, auto all) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) load(i, c0, all);
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int part = 0; part < 5; ++part) store(i, part, buf);
+    };
+    if (CH <= a.Cin) stage(0, cur, yes);
+    else stage(0, cur, no);
+    __syncthreads();
+    auto swap = [&]() { u4 *t = cur; cur = next; next = t; };
+    int c0 = 0;
+    for (; c0 + 2 * CH <= a.Cin; c0 += CH) {
+        step(yes, cur, next, c0);
+        swap();
+    }
+    if (c0 + CH < a.Cin) {
+        stage(c0 + CH, next, no);
+        step(no, cur, next, c0);
+        swap();
+    }
+    step(no, cur, next, c0);
+    // ---- epilogue: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32 ----
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int e = (wn * TN + j) * 32 + l32;
+        if (q0 + e >= a.NP) continue;
+        const int dn = (int)((p0 + (uint32_t)e) / (uint32_t)a.P);
+        float *ybase = a.Y + (size_t)(n0 + dn) * a.Cout * a.P + (p0 + (uint32_t)e - (uint32_t)dn * (uint32_t)a.P);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int o = m0 + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+                const float both = big[i][j][r] + (kTwo ? small[i][j][r] + small2[0][0][r] : small[i][j][r]);
+                if (o < a.Cout) ybase[(size_t)o * a.P] = (both == both ? both : big[i][j][r]) + (a.bias ? a.bias[o] : 0.f);
+            }
+    }
+}
+
 constexpr int BK = 16;
 
 // Shapes the patch kernel does not take - 3x3 on images wider than its staging (more than 254 pixels at
@@ -470,29 +728,46 @@ __global__ void __launch_bounds__(256) k_dense_gather(const DenseArgs a) {
     }
 }
 
-// Tile shapes, with the rate the matrix work of a tile runs at against the largest tile's: measured on
-// 3x3 layers with 64 to 512 channels at stride 1 and (`wide`, more than 512 staged positions a tile,
-// which a stride of 2 or a wide image has) 2, and on 1x1 layers with 16 to 1024.  3x3 at 64 pixels a
-// tile, and larger 1x1 tiles, were slower than a shape listed here (1x1: or as fast).  1x1 against 128 x 128
+// Tile shapes.  1x1: with the rate the matrix work of a tile runs at against the largest tile's, measured on layers
+// with 16 to 1024 channels; larger tiles were slower than a shape listed here or as fast.  Against 128 x 128
 // tiles of the patch matrix (130 layers, 40 to 1016 channels): 1.0 to 2.7 times as fast, but for a few whose
 // channels fill those tiles, 3 to 7 % slower (392->760 @56x57, N=18: 374 against 347 us); staged 128 x 128 tiles
 // give these back and lose as much on others (472->232 @28x28, N=83: 165 -> 179 us).
+// 3x3: the float32 instruction on the smallest tile, and where the input of a tile is large against its multiplies
+// (stride 2, wide images), the split one on the others.
 struct DenseShape {
     int bm, bn;
-    double rate, wide;
+    double rate;  // 1x1
+    bool split;   // 3x3: k_dense3
 };
-static const DenseShape kShapes3x3[] = {{128, 128, 1.0, 0.97}, {64, 128, 0.97, 0.85}, {32, 128, 0.90, 0.72}};
-static const DenseShape kShapes1x1[] = {{64, 64, 1.0, 0}, {32, 128, 0.90, 0}};
+static const DenseShape kShapes3x3[] = {{128, 256, 0, true}, {128, 128, 0, true}, {64, 128, 0, true}, {128, 128, 0, false}, {64, 128, 0, false}, {32, 128, 0, false}};
+static const DenseShape kShapes1x1[] = {{64, 64, 1.0, false}, {32, 128, 0.90, false}};
+// Microseconds that a 3x3 tile's step takes: matrix instructions, and the way of its weights and positions into LDS
+// (vector instructions do not overlap with the matrix instructions of a SIMD).  Measured per step on 128->128 @28x28,
+// 512->512 @7x7 and 128->128 @56x56 stride 2: split 5.9 / 4.0 / 2.5 us, float32 1.4 to 1.7 us on 32 x 128.
+static double step_time(const DenseShape &sh, long long npos) {
+    return sh.split ? 0.98e-4 * sh.bm * sh.bn + 1.7e-3 * (9 * sh.bm + npos) : 2.34e-4 * sh.bm * sh.bn + 0.7e-3 * (9 * sh.bm + npos);
+}
+static int dense_lds(const DenseShape &sh, int kernel, long long npos, int npt) {
+    if (sh.split) return (int)(16 * (55 * (sh.bm + 1) + 6 * (npos + 1)));
+    return 2 * 16 * (kernel == 3 ? 18 * (sh.bm + 1) + 512 * npt : 4 * (sh.bm + 1) + 4 * sh.bn);
+}
 
+typedef void (*dense_t)(const DenseArgs);
 template <int NPT>
-static auto pick_3x3(int BM) -> void (*)(const DenseArgs) {
+static dense_t pick_3x3(int BM) {
     return BM == 128 ? k_dense<128, 128, 9, NPT> : BM == 64 ? k_dense<64, 128, 9, NPT> : k_dense<32, 128, 9, NPT>;
 }
-static auto pick_dense(int kernel, int BM, int BN, int npt) -> void (*)(const DenseArgs) {
+static dense_t pick_dense(int kernel, const DenseShape &sh, int npt) {
+    if (sh.split) {
+        if (sh.bn == 256) return k_dense3<128, 256, 512, 1>;
+        if (sh.bm == 128) return npt == 1 ? k_dense3<128, 128, 512, 1> : k_dense3<128, 128, 512, 2>;
+        return npt == 1 ? k_dense3<64, 128, 512, 1> : k_dense3<64, 128, 512, 2>;
+    }
     // (64 pixels touch at least half the positions of 128, and are taken where those are more than 1024)
-    if (kernel == 3 && BN == 64) return npt == 3 ? k_dense<64, 64, 9, 3> : k_dense<64, 64, 9, 4>;
-    if (kernel == 3) return npt == 2 ? pick_3x3<2>(BM) : npt == 3 ? pick_3x3<3>(BM) : pick_3x3<4>(BM);
-    return BM == 64 ? k_dense<64, 64, 1, 1> : k_dense<32, 128, 1, 1>;
+    if (kernel == 3 && sh.bn == 64) return npt == 3 ? k_dense<64, 64, 9, 3> : k_dense<64, 64, 9, 4>;
+    if (kernel == 3) return npt == 2 ? pick_3x3<2>(sh.bm) : npt == 3 ? pick_3x3<3>(sh.bm) : pick_3x3<4>(sh.bm);
+    return sh.bm == 64 ? k_dense<64, 64, 1, 1> : k_dense<32, 128, 1, 1>;
 }
 
 }  // namespace alcs
@@ -532,9 +807,11 @@ extern "C" int alcs_dense_conv(const float *W_dev, const float *X_dev, const flo
         const long long images = std::min<long long>((rows + Ho - 2) / Ho + 1, N);
         const long long npos = kernel == 3 ? (rows * stride + images * (3 - stride)) * ((Wo - 1) * (long long)stride + 3) : 0;
         if (npos > 256 * kPosPerThread) return;
+        if (sh.split && (dense_lds(sh, kernel, npos, 0) > 160 * 1024 || (sh.bn == 256 && npos > 512))) return;
         if (images * (long long)Cin * Pin >= (1LL << 30) || K * sh.bm >= (1LL << 29)) return;  // byte offsets are 32 bits
         const long long tiles = ((a.NP + sh.bn - 1) / sh.bn) * ((Cout + sh.bm - 1) / sh.bm);
-        const double cost = (double)((tiles + cus - 1) / cus) * sh.bm * sh.bn / (npos > 512 ? sh.wide : sh.rate);
+        const double rounds = (double)((tiles + cus - 1) / cus);
+        const double cost = kernel == 3 ? rounds * step_time(sh, npos) : rounds * sh.bm * sh.bn / sh.rate;
         if (!best || cost < best_cost) { best = &sh; best_cost = cost; a.npos = (int)npos; }
     };
     if (kernel == 1) {
@@ -554,7 +831,7 @@ extern "C" int alcs_dense_conv(const float *W_dev, const float *X_dev, const flo
         auto load = [&](int bm, int bn) { return (double)(((a.NP + bn - 1) / bn) * ((Cout + bm - 1) / bm)) / cus; };
         auto at_once = [](double t) { return t > 2 ? t : std::ceil(t); };
         const double t128 = 0.45 + 0.95 * at_once(load(128, 128)), t64 = 0.65 + 0.52 * std::max(1.0, load(64, 128));
-        static const DenseShape kNarrow{64, 64, 1.0, 1.0};
+        static const DenseShape kNarrow{64, 64, 0, false};
         if (kernel == 3 && 0.25 * std::ceil(load(64, 64)) * (Cin + 16) / Cin < std::min(t128, t64)) consider(kNarrow);
         BM = best || t64 <= t128 ? 64 : 128;
         if (best) BN = 64;
@@ -566,16 +843,17 @@ extern "C" int alcs_dense_conv(const float *W_dev, const float *X_dev, const flo
     a.nt = (int)ntile;
     a.total_wgs = (int)total;
     a.wg_per_xcd = (int)((total + xcds - 1) / xcds);
-    void (*kern)(const DenseArgs) = BM == 128 ? k_dense_gather<128> : k_dense_gather<64>;
-    int lds = 0;
+    dense_t kern = BM == 128 ? k_dense_gather<128> : k_dense_gather<64>;
+    int lds = 0, threads = 256;
     if (best) {
-        const int npt = kernel == 1 ? 1 : a.npos <= 512 ? 2 : a.npos <= 768 ? 3 : 4;
-        lds = 2 * 16 * (kernel == 3 ? 18 * (BM + 1) + 512 * npt : 4 * (BM + 1) + 4 * BN);
-        kern = pick_dense(kernel, BM, BN, npt);
+        threads = best->split ? 512 : 256;
+        const int npt = kernel == 1 ? 1 : best->split ? (a.npos + 511) / 512 : a.npos <= 512 ? 2 : a.npos <= 768 ? 3 : 4;
+        lds = dense_lds(*best, kernel, a.npos, npt);
+        kern = pick_dense(kernel, *best, npt);
         const int rc = allow_lds((const void *)kern, lds);
         if (rc != ALCS_OK) return rc;
     }
-    hipLaunchKernelGGL(kern, dim3(a.wg_per_xcd * xcds), dim3(256), lds, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(kern, dim3(a.wg_per_xcd * xcds), dim3(threads), lds, (hipStream_t)stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_hip_error((int)e); return ALCS_E_HIP; }
     return ALCS_OK;

@@ -35,6 +35,11 @@ pytestmark = pytest.mark.gpu
     (1, 2, 64, 30, 31, 17, 6),
     (1, 1, 160, 200, 56, 56, 5),   # several tiles a compute unit
     (3, 1, 64, 256, 30, 30, 12),   # 128 x 128
+    # split operands: 128 x 256 with and without remainders, 128 x 128, 64 x 128, one step, a step and a channel,
+    # more than 512 positions (float32 again)
+    (3, 1, 16, 128, 28, 28, 64), (3, 1, 9, 130, 27, 29, 70), (3, 1, 17, 250, 14, 14, 130),
+    (3, 1, 8, 736, 28, 28, 9), (3, 1, 13, 715, 14, 11, 10), (3, 1, 5, 330, 28, 28, 6), (3, 1, 24, 780, 7, 7, 70),
+    (3, 2, 12, 300, 30, 26, 40), (3, 1, 8, 400, 6, 90, 30),
 ])
 def test_dense_tiles(k, stride, Cin, Cout, H, W, N):
     L = workloads.Layer("tile", Cin, Cout, H, W, k=k, stride=stride, N=N, V=1, sparsity=0.0, w_std=0.1,
@@ -43,6 +48,33 @@ def test_dense_tiles(k, stride, Cin, Cout, H, W, N):
     got = run_dense(d)
     assert not np.isnan(got).any()
     assert rel_err(got, oracle_ref(d)) <= TOL
+
+
+def test_split_operands_with_infinities():
+    """Where one input is infinite the outputs that see it are, and all others are what they were; the largest finite
+    input stays finite."""
+    import torch
+
+    import paper_2109_00170_amd as alcs
+    g = torch.Generator().manual_seed(6)
+    X = torch.rand((64, 16, 28, 28), generator=g).cuda()
+    F = (0.1 + torch.rand((128, 16, 3, 3), generator=g)).cuda() * 0.01
+    Y = [torch.empty((64, 128, 28, 28), device="cuda") for _ in range(3)]
+    alcs.alcs_dense_conv(F, X, None, Y[0])
+    want = torch.nn.functional.conv2d(X.cpu().double(), F.cpu().double(), padding=1)
+    assert float((Y[0].cpu() - want).abs().max() / want.abs().max()) <= TOL
+    for big, y in ((float("inf"), Y[1]), (3.4e38, Y[2])):
+        Z = X.clone()
+        Z[5, 3, 10, 27] = big
+        alcs.alcs_dense_conv(F, Z, None, y)
+        sees = torch.zeros(Y[0].shape, dtype=torch.bool, device="cuda")
+        sees[5, :, 9:12, 26:28] = True
+        assert torch.equal(y[~sees], Y[0][~sees])
+        got = y[sees].cpu()
+        if big == float("inf"):
+            assert bool((got == big).all())
+        else:
+            assert bool(torch.isfinite(got).all()) and float(got.min()) > 1e35
 
 
 def test_dense_tile_beyond_2_31_bytes():
