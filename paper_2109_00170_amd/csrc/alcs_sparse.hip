@@ -2372,10 +2372,11 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
                 const int per_cu = 4 * std::min(8, 512 / std::max(1, (regs + 7) & ~7)), wgs = kMaxLds / lds;
                 if ((long long)a.npt * a.ngt <= kCUs) nw = 16;
                 else if (wgs >= 4) nw = NB <= 4 ? 4 : 8;
-                else nw = std::min(dw_s2 ? 8 : 16, std::max(8, per_cu / wgs & ~3));
+                else nw = std::min(dw_s2 ? 8 : 16, std::max(8, per_cu / wgs & ~3));  // (144->24 @56x56, N=128, V=8: 91 us with 8, 132 with 10)
             } else if (nw > 8 && (long long)a.npt * a.ngt > kCUs && 2 * lds <= kMaxLds && kernel_registers(kern) > 64) nw = 8;
-            // The four SIMDs get as many wavefronts each (144->24 @56x56, N=128, V=8: 91 us with 8, 132 with 10).
-            if (nw > 4) nw = (nw + 3) & ~3;
+            // Depthwise stage on whole rows, in which every wavefront takes part: as many for each of the four SIMDs
+            // (960->160 @7x7, N=128, V=8: 39.6 us with 16, 41.7 with 15; without the stage 11 are as good as 12, or better).
+            if (kDw && rows && nw > 4) nw = (nw + 3) & ~3;
             if (T.waves > 0) nw = std::min(T.waves, 16);
 #if ALCS_DW_STAGE
             // Two rows per lane: a wavefront's turn takes about 1.6 times as long and there are half as many, unless
@@ -2491,8 +2492,12 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
     // 18.6).  Nor do several groups per wavefront pay without whole rows, one pixel of one channel per lane and trip
     // (584->24 @56x56, N=38, V=8: 271 us against 192).  The caller that can run the two layers (it has a
     // workspace) is told to.
-    const bool restage_ok = (a.ngt == 1 && (L.GS == 1 || a.dw_rows > 0)) || (a.ngt == 2 && a.npt >= 80 && 2 * a.npt <= kCUs && a.dw_rows > 0 &&
-                                           (dw->stride == 1 || Cin * a.tile_px <= 8192));
+    // In up to four over whole rows at stride 1 and in a single round, up to 512 channels (512->512 @14x14, N=8: 12.5 us
+    // in four against 13.5; 32->64 @112x112, one image: 7.4 against 8.3; 1024->1024 @7x7, N=32: 25.1 against 23.7).
+    const bool restage_ok = (a.ngt == 1 && (L.GS == 1 || a.dw_rows > 0)) ||
+                            (a.ngt <= 4 && a.dw_rows > 0 && dw->stride == 1 && Cin <= 512 && a.npt * a.ngt <= kCUs) ||
+                            (a.ngt == 2 && a.npt >= 80 && 2 * a.npt <= kCUs && a.dw_rows > 0 &&
+                             (dw->stride == 1 || Cin * a.tile_px <= 8192));
     if (decline_restaged && !restage_ok && !T.dw_one_kernel) return ALCS_E_UNSUPPORTED;
 #endif
     (void)decline_restaged;

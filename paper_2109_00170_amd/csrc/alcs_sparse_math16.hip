@@ -586,6 +586,7 @@ extern "C" int alcs_sparse_conv_bf16_mfma(const alcs_packed_t *Wp, const uint16_
     // than groups in the group tile or 8 KB of tile each, whichever is larger
     int nw = lds > 40 * 1024 ? 16 : lds > 24 * 1024 ? 8 : 4;
     nw = std::min(nw, std::max(std::max(2, a.gpt), lds / 8192));
+    if (nw > 8) nw = (nw + 3) & ~3;  // the four SIMDs get as many wavefronts each (512->1024 @7x7, N=32: 13 are slower than 16)
     if (T.waves > 0) nw = std::min(std::max(T.waves, 2), 16);
     const long long total = (long long)npt * a.ngt;
     a.total_wgs = (int)total;
