@@ -581,6 +581,179 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 2 : 3) k_dense3(const DenseArg
     }
 }
 
+// 1x1 on split operands: 128 channels x BN pixels, 32 input channels a step.  As k_dense3, but a pixel's words serve one
+// tap, so most of the split work is the input's, and a tile has few steps to cover its first loads and its stores: large
+// layers gain (392->760 @56x57, N=18 369 -> 262 us, 512->512 @14x14, N=256 285 -> 205, 1024->256 @14x14, N=64 89 -> 60),
+// layers of few input channels or few tiles do not (128->64 @56x56, N=32: 27 us, 41 split).
+template <int BN>
+__global__ void __launch_bounds__(512, 2) k_dense1(const DenseArgs a) {
+    constexpr int BM = 128, CH = 32, NQ = CH / 8, NT = 512;  // NQ: groups of 8 channels
+    constexpr int WM = 2, WN = 4, TM = 2, TN = BN / 32 / WN;
+    constexpr int LDA = BM + 1, LDB = BN + 1, BUF = 3 * NQ * (LDA + LDB);
+    constexpr int NB = BN * NQ / NT, NI = 1 + NB;
+    static_assert(BM * NQ == NT, "one item of the weights per thread");
+    extern __shared__ u4 lds3[];
+    const int id = blockIdx.x;
+    const int logical = (id % a.xcds) * a.wg_per_xcd + id / a.xcds;
+    if (logical >= a.total_wgs) return;
+    const int ntile = logical / a.mt, mtile = logical - ntile * a.mt;
+    const int m0 = mtile * BM;
+    const long long q0 = (long long)ntile * BN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / WN, wn = wave % WN;
+    const int h = lane >> 5, l32 = lane & 31;
+    u4 *cur = lds3, *next = lds3 + BUF;
+    const int n0 = q0 >> 32 ? (int)(q0 / a.P) : (int)((uint32_t)q0 / (uint32_t)a.P);
+    const uint32_t p0 = (uint32_t)(q0 - (long long)n0 * a.P);
+    const float *xbase = a.X + (size_t)n0 * a.Cin * a.Pin;
+    const float *wbase = a.Wt + (size_t)m0 * a.K;
+    // this thread's row and group of 8 channels of the weights, and its pixel and groups of the input (pixels behind the
+    // end read the tile's first one and are not stored)
+    const int arow = tid / NQ, aq = tid % NQ;
+    const uint32_t aoff = 4u * ((uint32_t)min(arow, a.Cout - 1 - m0) * (uint32_t)a.K + 8u * (uint32_t)aq);
+    const int bpix = tid % BN, bq = __builtin_amdgcn_readfirstlane(tid / BN);
+    uint32_t boff;
+    {
+        const uint32_t p = p0 + (uint32_t)(q0 + bpix < a.NP ? bpix : 0);
+        const uint32_t dn = p / (uint32_t)a.P, in = p - dn * (uint32_t)a.P;
+        const uint32_t ho = in / (uint32_t)a.Wo, wo = in - ho * (uint32_t)a.Wo;
+        boff = 4u * (dn * (uint32_t)a.Cin * (uint32_t)a.Pin + ho * (uint32_t)a.stride * (uint32_t)a.W + wo * (uint32_t)a.stride);
+    }
+    f16v big[TM][TN], small[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) big[i][j][r] = small[i][j][r] = 0.f;
+    float x[NI][8];
+    // item 0: the weights; item i: group bq + (i - 1) * NT / BN of the input.  The last step of a channel count that is
+    // no multiple of 32 reads channels that are there and zeroes the others.
+    auto load = [&](int i, int c0, auto all) __attribute__((always_inline)) {
+        constexpr bool ALL = decltype(all)::value;
+        if (i == 0) {
+            uint32_t o = aoff;
+            asm volatile("" : "+v"(o));
+            if (ALL) {
+                const f4u *src = reinterpret_cast<const f4u *>(reinterpret_cast<const char *>(wbase + c0) + o);
+                const f4 w0 = src[0], w1 = src[1];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) { x[0][t] = w0[t]; x[0][4 + t] = w1[t]; }
+            } else {
+                const float *src = reinterpret_cast<const float *>(reinterpret_cast<const char *>(wbase) + (o - 32u * (uint32_t)aq));
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const int c = c0 + 8 * aq + t;
+                    x[0][t] = src[min(c, a.Cin - 1)];
+                    if (c >= a.Cin) x[0][t] = 0.f;
+                }
+            }
+        } else {
+            uint32_t o = boff;
+            asm volatile("" : "+v"(o));
+            const int first = c0 + 8 * (bq + (i - 1) * (NT / BN));
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const int c = ALL ? first + t : min(first + t, a.Cin - 1);
+                x[i][t] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(xbase + (size_t)c * a.Pin) + o);
+                if (!ALL && first + t >= a.Cin) x[i][t] = 0.f;
+            }
+        }
+    };
+    u4 plane[3];
+    auto store = [&](int i, int part, u4 *buf) __attribute__((always_inline)) {
+        if (part < 4) {
+            uint32_t hi, mid, lo;
+            split2(x[i][2 * part], x[i][2 * part + 1], hi, mid, lo);
+            plane[0][part] = hi;
+            plane[1][part] = mid;
+            plane[2][part] = lo;
+        } else {
+            u4 *to = i == 0 ? buf + aq * LDA + arow : buf + 3 * NQ * LDA + (bq + (i - 1) * (NT / BN)) * LDB + bpix;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) to[p * NQ * (i == 0 ? LDA : LDB)] = plane[p];
+        }
+    };
+    constexpr int SLOTS = 6 * NQ / 2, PARTS = 5 * NI, PER = 2, FIRST = SLOTS - (PARTS + PER - 1) / PER;
+    static_assert(FIRST >= NI, "loads first, stores last");
+    auto step = [&](auto more, const u4 *buf, u4 *to, int c0) __attribute__((always_inline)) {
+        constexpr bool MORE = decltype(more)::value;
+        bf8 av[3][TM], bv[3][TN];
+#pragma unroll
+        for (int sl = 0; sl < SLOTS; ++sl) {
+            const int g = sl / 6, pr = sl % 6;
+            if (pr == 0) {
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) av[p][i] = __builtin_bit_cast(bf8, buf[(p * NQ + 2 * g + h) * LDA + (wm * TM + i) * 32 + l32]);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) bv[p][j] = __builtin_bit_cast(bf8, buf[3 * NQ * LDA + (p * NQ + 2 * g + h) * LDB + (wn * TN + j) * 32 + l32]);
+                }
+            }
+            if (MORE && sl < NI) load(sl, c0 + CH, std::integral_constant<bool, true>{});
+            if (MORE && sl >= FIRST) {
+#pragma unroll
+                for (int v = 0; v < PER; ++v) {
+                    const int u = (sl - FIRST) * PER + v;
+                    if (u < PARTS) store(u / 5, u % 5, to);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int pa[6] = {0, 1, 0, 1, 0, 2}, pb[6] = {1, 0, 0, 1, 2, 0};
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    auto &c = pr == 2 ? big[i][j] : small[i][j];
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[pa[pr]][i], bv[pb[pr]][j], c, 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+    };
+    constexpr std::integral_constant<bool, true> yes{};
+    constexpr std::integral_constant<bool, false> no{};
+    auto stage = [&](int c0, u4 *buf, auto all) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) load(i, c0, all);
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int part = 0; part < 5; ++part) store(i, part, buf);
+    };
+    if (CH <= a.Cin) stage(0, cur, yes);
+    else stage(0, cur, no);
+    __syncthreads();
+    auto swap = [&]() { u4 *t = cur; cur = next; next = t; };
+    int c0 = 0;
+    for (; c0 + 2 * CH <= a.Cin; c0 += CH) {
+        step(yes, cur, next, c0);
+        swap();
+    }
+    if (c0 + CH < a.Cin) {
+        stage(c0 + CH, next, no);
+        step(no, cur, next, c0);
+        swap();
+    }
+    step(no, cur, next, c0);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int e = (wn * TN + j) * 32 + l32;
+        if (q0 + e >= a.NP) continue;
+        const int dn = (int)((p0 + (uint32_t)e) / (uint32_t)a.P);
+        float *ybase = a.Y + (size_t)(n0 + dn) * a.Cout * a.P + (p0 + (uint32_t)e - (uint32_t)dn * (uint32_t)a.P);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int o = m0 + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+                const float both = big[i][j][r] + small[i][j][r];
+                if (o < a.Cout) ybase[(size_t)o * a.P] = (both == both ? both : big[i][j][r]) + (a.bias ? a.bias[o] : 0.f);
+            }
+    }
+}
+
 constexpr int BK = 16;
 
 // Shapes the patch kernel does not take - 3x3 on images wider than its staging (more than 254 pixels at
@@ -728,8 +901,8 @@ __global__ void __launch_bounds__(256) k_dense_gather(const DenseArgs a) {
     }
 }
 
-// Tile shapes.  1x1: with the rate the matrix work of a tile runs at against the largest tile's, measured on layers
-// with 16 to 1024 channels; larger tiles were slower than a shape listed here or as fast.  Against 128 x 128
+// Tile shapes.  1x1, float32: with the rate the matrix work of a tile runs at against the largest tile's, measured on
+// layers with 16 to 1024 channels; larger tiles were slower than a shape listed here or as fast.  Against 128 x 128
 // tiles of the patch matrix (130 layers, 40 to 1016 channels): 1.0 to 2.7 times as fast, but for a few whose
 // channels fill those tiles, 3 to 7 % slower (392->760 @56x57, N=18: 374 against 347 us); staged 128 x 128 tiles
 // give these back and lose as much on others (472->232 @28x28, N=83: 165 -> 179 us).
@@ -737,18 +910,26 @@ __global__ void __launch_bounds__(256) k_dense_gather(const DenseArgs a) {
 // (stride 2, wide images), the split one on the others.
 struct DenseShape {
     int bm, bn;
-    double rate;  // 1x1
-    bool split;   // 3x3: k_dense3
+    double rate;  // 1x1, float32
+    bool split;   // k_dense3, k_dense1
 };
 static const DenseShape kShapes3x3[] = {{128, 256, 0, true}, {128, 128, 0, true}, {64, 128, 0, true}, {128, 128, 0, false}, {64, 128, 0, false}, {32, 128, 0, false}};
-static const DenseShape kShapes1x1[] = {{64, 64, 1.0, false}, {32, 128, 0.90, false}};
+static const DenseShape kShapes1x1[] = {{128, 256, 0, true}, {128, 128, 0, true}, {64, 64, 1.0, false}, {32, 128, 0.90, false}};
 // Microseconds that a 3x3 tile's step takes: matrix instructions, and the way of its weights and positions into LDS
 // (vector instructions do not overlap with the matrix instructions of a SIMD).  Measured per step on 128->128 @28x28,
 // 512->512 @7x7 and 128->128 @56x56 stride 2: split 5.9 / 4.0 / 2.5 us, float32 1.4 to 1.7 us on 32 x 128.
 static double step_time(const DenseShape &sh, long long npos) {
     return sh.split ? 0.98e-4 * sh.bm * sh.bn + 1.7e-3 * (9 * sh.bm + npos) : 2.34e-4 * sh.bm * sh.bn + 0.7e-3 * (9 * sh.bm + npos);
 }
+// Microseconds of a 1x1 tile: measured on 64 to 1024 input channels; the split tiles' first part is their first loads and
+// their stores.
+static double tile_time(const DenseShape &sh, int Cin) {
+    if (!sh.split) return (0.8 + 0.021 * Cin) * sh.bm * sh.bn / (4096 * sh.rate);
+    const int steps = (Cin + 31) / 32;
+    return sh.bn == 256 ? 12.6 + 2.4 * steps : 5.0 + 1.6 * steps;
+}
 static int dense_lds(const DenseShape &sh, int kernel, long long npos, int npt) {
+    if (sh.split && kernel == 1) return 2 * 16 * 12 * (sh.bm + 1 + sh.bn + 1);
     if (sh.split) return (int)(16 * (55 * (sh.bm + 1) + 6 * (npos + 1)));
     return 2 * 16 * (kernel == 3 ? 18 * (sh.bm + 1) + 512 * npt : 4 * (sh.bm + 1) + 4 * sh.bn);
 }
@@ -759,6 +940,7 @@ static dense_t pick_3x3(int BM) {
     return BM == 128 ? k_dense<128, 128, 9, NPT> : BM == 64 ? k_dense<64, 128, 9, NPT> : k_dense<32, 128, 9, NPT>;
 }
 static dense_t pick_dense(int kernel, const DenseShape &sh, int npt) {
+    if (sh.split && kernel == 1) return sh.bn == 256 ? k_dense1<256> : k_dense1<128>;
     if (sh.split) {
         if (sh.bn == 256) return k_dense3<128, 256, 512, 1>;
         if (sh.bm == 128) return npt == 1 ? k_dense3<128, 128, 512, 1> : k_dense3<128, 128, 512, 2>;
@@ -807,11 +989,11 @@ extern "C" int alcs_dense_conv(const float *W_dev, const float *X_dev, const flo
         const long long images = std::min<long long>((rows + Ho - 2) / Ho + 1, N);
         const long long npos = kernel == 3 ? (rows * stride + images * (3 - stride)) * ((Wo - 1) * (long long)stride + 3) : 0;
         if (npos > 256 * kPosPerThread) return;
-        if (sh.split && (dense_lds(sh, kernel, npos, 0) > 160 * 1024 || (sh.bn == 256 && npos > 512))) return;
+        if (kernel == 3 && sh.split && (dense_lds(sh, kernel, npos, 0) > 160 * 1024 || (sh.bn == 256 && npos > 512))) return;
         if (images * (long long)Cin * Pin >= (1LL << 30) || K * sh.bm >= (1LL << 29)) return;  // byte offsets are 32 bits
         const long long tiles = ((a.NP + sh.bn - 1) / sh.bn) * ((Cout + sh.bm - 1) / sh.bm);
         const double rounds = (double)((tiles + cus - 1) / cus);
-        const double cost = kernel == 3 ? rounds * step_time(sh, npos) : rounds * sh.bm * sh.bn / sh.rate;
+        const double cost = rounds * (kernel == 3 ? step_time(sh, npos) : tile_time(sh, Cin));
         if (!best || cost < best_cost) { best = &sh; best_cost = cost; a.npos = (int)npos; }
     };
     if (kernel == 1) {

@@ -40,6 +40,8 @@ pytestmark = pytest.mark.gpu
     (3, 1, 16, 128, 28, 28, 64), (3, 1, 9, 130, 27, 29, 70), (3, 1, 17, 250, 14, 14, 130),
     (3, 1, 8, 736, 28, 28, 9), (3, 1, 13, 715, 14, 11, 10), (3, 1, 5, 330, 28, 28, 6), (3, 1, 24, 780, 7, 7, 70),
     (3, 2, 12, 300, 30, 26, 40), (3, 1, 8, 400, 6, 90, 30),
+    (1, 1, 300, 256, 28, 28, 64), (1, 1, 320, 250, 27, 29, 64), (1, 2, 333, 512, 56, 55, 60),   # 1x1, 128 x 256
+    (1, 1, 1001, 250, 14, 14, 64), (1, 1, 992, 255, 13, 15, 64), (1, 1, 993, 256, 1, 1, 20000),  # 128 x 128, and images of one pixel
 ])
 def test_dense_tiles(k, stride, Cin, Cout, H, W, N):
     L = workloads.Layer("tile", Cin, Cout, H, W, k=k, stride=stride, N=N, V=1, sparsity=0.0, w_std=0.1,
