@@ -339,7 +339,8 @@ __global__ void __launch_bounds__(256, KK == 1 ? 4 : BM == 128 ? 1 : 2) k_dense(
 // same SIMD, so the larger the tile the better (128->128 @28x28, N=64: 157 us on 32 x 128, 130 on 128 x 128, 99 on
 // 128 x 256; float32 on 32 x 128 153).
 // Infinities: their remainders are not numbers, which only the second accumulator sees; where the sum of both is
-// no number the first one stands.
+// no number the first one stands.  (A NaN whose set bits all lie in the lower half of the word, which no arithmetic makes,
+// reads as an infinity; rounding the upper half in place of cutting it would turn the largest finite floats into one.)
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
