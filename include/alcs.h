@@ -253,12 +253,12 @@ int alcs_sparse_conv_bf16_mfma(const alcs_packed_t *Wp, const uint16_t *X_dev, c
  *     tensor of Y's shape, may be Y_dev itself) are [N,Cout,Ho,Wo].  workspace_dev is NULL or
  *     [N,Cin,Ho,Wo] floats of scratch.  With a workspace the library runs the two layers one
  *     after the other through it (same result to rounding; the workspace's contents afterwards
- *     are unspecified) where that is the faster or the only way: small layers whose output
- *     groups are split over several workgroups per pixel tile (each would evaluate the
- *     depthwise layer again), handles whose input channels do not fit one on-chip tile (more
- *     than 2558 input channels, or V < 4 with more than 639), inputs of more than about 10^9
- *     elements per image.  Without a workspace the first kind still runs as one kernel and
- *     the other two return ALCS_E_UNSUPPORTED.
+ *     are unspecified) where that is the faster or the only way: layers whose output groups
+ *     are split over many workgroups per pixel tile (each would evaluate the depthwise layer
+ *     again) or shared several to a wavefront on tiles that are not whole rows, handles whose
+ *     input channels do not fit one on-chip tile (more than 2558 input channels, or V < 4 with
+ *     more than 639), inputs of more than about 10^9 elements per image.  Without a workspace
+ *     the first two kinds still run as one kernel and the others return ALCS_E_UNSUPPORTED.
  *
  * Both: stride in {1, 2} (else ALCS_E_UNSUPPORTED); activations are alcs_activation values
  * (else ALCS_E_INVALID_ARG); X_dev / Y_dev / residual_dev 16-byte aligned for the fused call;
