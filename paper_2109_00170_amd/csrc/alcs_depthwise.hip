@@ -119,8 +119,12 @@ __global__ void __launch_bounds__(256) k_depthwise_rows(const DwArgs a) {
         const int rc = wide ? (int)(chunk / (unsigned)a.cblocks) : (int)chunk;
         row[u] = rc * a.rows + r;
         qx[u] = wide ? ((int)chunk - rc * a.cblocks) * 62 + lane - 1 : item - r * QW;
-        st.init((uint32_t)pl * a.Pin, min(max(qx[u], 0), QW - 1), min(row[u], a.Ho - 1), a.H, a.W);
-        st.load(DwStrip<S>::rows_from(a.X, p0 * a.Pin, a.planes * a.Pin), v[u]);
+        // from the unit's first input row (and, of a wide row, its block's first column) on: what a descriptor reaches ends a
+        // few floats short of the largest planes, but never short of three rows' parts
+        const int y0 = max(rc * a.rows * S - 1, 0), x0 = wide ? max(((int)chunk - rc * a.cblocks) * 62 - 1, 0) * 4 * S : 0;
+        const int from = y0 * a.W + x0;
+        st.init((uint32_t)pl * a.Pin - (uint32_t)from, min(max(qx[u], 0), QW - 1), min(row[u], a.Ho - 1), a.H, a.W);
+        st.load(DwStrip<S>::rows_from(a.X, p0 * a.Pin + from, a.planes * a.Pin), v[u]);
         const float *wp;
         const unsigned c = (unsigned)(plane[u] % a.C);
         wp = a.D + (size_t)c * 9;

@@ -10,7 +10,8 @@
 // Loads go through a buffer descriptor that ends with the tensor: rows outside the image are addressed
 // beyond it and read as zero without a mask, and so do the words of a row's last load that lie past the
 // tensor's end.  Elsewhere such words are the next row's; of those an output that is stored sees only the column
-// right of the row, which is masked.  W >= 4.
+// right of the row, which is masked.  W >= 4, and no input lies kDwsBeyond bytes or more behind its base: the blocks'
+// launcher sees to that, the stand-alone layer's kernel takes a base near its rows.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -180,3 +180,29 @@ def test_bf16_pointwise_input_beyond_2_31_elements():
     bound = 2.0 ** -8 * np.abs(ref) + TOL * min(np.max(np.abs(pre)), np.max(np.abs(ref)))
     assert float(np.max(np.abs(got - ref) - bound)) <= 0.0
     packed.free()
+
+
+@pytest.mark.parametrize("H,W,stride", [(32769, 32767, 1), (32768, 32766, 1), (32769, 32767, 2), (3, 2 ** 30 // 3, 1),
+                                        (1, 2 ** 30 - 1, 1), (1, 2 ** 30 - 1, 2), (2 ** 27, 7, 1)])
+def test_depthwise_plane_of_nearly_2_30_elements(H, W, stride):
+    """The largest planes the depthwise layer takes end beyond byte 0xffffff00, as far as a buffer descriptor reaches: every
+    input up to the last one counts."""
+    import torch
+    assert 0.85 * 2 ** 30 < H * W < 2 ** 30
+    free_b, _ = torch.cuda.mem_get_info()
+    if free_b < 10 * 2 ** 30:
+        pytest.skip("needs 10 GiB of device memory")
+    rows, cols = min(H, 5 if H % 2 else 6), min(W, 40 + W % 2)   # the last corner, from an even row and column on
+    corner = torch.rand((rows, cols), generator=torch.Generator().manual_seed(3)) + 0.5
+    X = torch.zeros((1, 1, H, W), device="cuda")
+    X[0, 0, H - rows:, W - cols:] = corner.cuda()
+    D = torch.arange(1.0, 10.0).reshape(1, 3, 3)
+    Y = torch.full((1, 1, (H + stride - 1) // stride, (W + stride - 1) // stride), float("nan"), device="cuda")
+    alcs.alcs_depthwise_conv(D.cuda(), X, None, Y, stride=stride)
+    padded = torch.zeros((1, 1, H if H <= rows else rows + 2, W if W <= cols else cols + 2), dtype=torch.float64)
+    padded[0, 0, -rows:, -cols:] = corner
+    want = torch.nn.functional.conv2d(padded, D.double()[None], padding=1, stride=stride)[0, 0]
+    got = Y[0, 0, -want.shape[0]:, -want.shape[1]:].cpu()
+    assert float((got - want).abs().max() / want.abs().max()) <= TOL
+    del X, Y
+    torch.cuda.empty_cache()
