@@ -5,11 +5,10 @@
 // ("Overview"): row k = (c*kernel + r)*kernel + s, column q = flattened (n, ho, wo).
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-#include <cmath>
 #include <cstdint>
 #include <type_traits>
 
+#include "alcs_dense_plan.h"
 #include "alcs_internal.h"
 
 namespace alcs {
@@ -43,7 +42,7 @@ struct DenseArgs {
 // What bounds a launch is the matrix pipe (3x3: 52 to 61 % of a single launch's cycles busy, start and
 // drain included; 64 % of its peak in a stream of launches) and, on few tiles, how evenly they divide over
 // the compute units (the launcher picks the tile for that).  3x3, N=64, against the patch matrix
-// gathered word by word: 128->128 @28x28 260 -> 147 us (k_dense3 95), 512->512 @7x7 577 -> 176 us,
+// gathered word by word: 128->128 @28x28 260 -> 147 us (k_dense3 112), 512->512 @7x7 577 -> 176 us,
 // 40->23 @112x86 424 -> 175 us; 1x1 1024->256 @14x14 101 -> 80 us.  1x1 layers with few
 // output channels wait for their input: 16 channels a step leave room for 8 workgroups a compute unit
 // (256->64 @56x56, N=40: 59.5 -> 50 us against 32 channels and 3 workgroups).
@@ -54,7 +53,6 @@ struct DenseTile {
     static constexpr int TM = BM / 32 / WM, TN = BN / 32 / WN;  // 32x32 tiles per wavefront
     static_assert(TM >= 1 && TN >= 1, "tile");
 };
-constexpr int kPosPerThread = 4;  // 3x3: staged positions per thread and quad of channels, at most
 
 // NPT: staged positions per thread (3x3).
 template <int BM, int BN, int KK, int NPT>
@@ -325,41 +323,84 @@ __global__ void __launch_bounds__(256, KK == 1 ? 4 : BM == 128 ? 1 : 2) k_dense(
 
 // 3x3, the matrix cores' 16-bit instruction on float32 operands.  A float is the sum of three bfloat16 numbers
 // without a remainder (24 bits as 8 + 8 + 8: the upper half of the word, what is left rounded to nearest, what is left
-// then; below about 1e-33 the smaller parts may underflow), a product of two of them is exact in float32, and of the
-// nine partial products of two floats the three that lie 2^-23 and more below the largest are left out.
-// v_mfma_f32_32x32x16_bf16 does 16 rows of K in half the time v_mfma_f32_32x32x2_f32 does two, so six products take three
-// eighths of the float32 instruction's matrix time.  The largest product goes to one accumulator and the five smaller
-// ones to another: one rounding per 16 rows of K at full size, where the float32 instruction has eight.  Error against
-// 64 bits (2-norm, relative), 40 layers of 16 to 984 channels: 0.35 to 0.42 of the float32 instruction's (128->128: 1.5e-7
-// against 4.2e-7); with all six in one accumulator it was 1.17 of it.
+// then), a product of two of them is exact in float32, and of the nine partial products of two floats only the product of
+// the two lowest parts is left out, 2^-30 of the whole: far below the rounding of a float32 multiply-add.  (Without
+// the two products of a middle and a lowest part as well, 2^-22 together, an output that one term carries was off by up to 3.5
+// times that rounding.)
+// v_mfma_f32_32x32x16_bf16 does 16 rows of K in half the time v_mfma_f32_32x32x2_f32 does two, so eight products take half
+// of the float32 instruction's matrix time.  The largest product goes to one accumulator and the seven smaller
+// ones to another: one rounding per 16 rows of K at full size, where the float32 instruction has eight.
+// Error against 64 bits (2-norm, relative) over 48 layers of 16 to 1018 channels: 0.31 to 0.48 of the float32
+// instruction's (128->128 3x3: 1.9e-7 against 6.0e-7); outputs of 1 to 16 terms: 1.0 to 0.45 of it.
 // Values are split once per workgroup, on the way into LDS: three planes of 8 channels side by side (16 bytes) per
 // weight (tap, row) and per staged position, so an operand of the matrix instruction - 8 consecutive rows of K per lane, lanes
 // 0-31 one tap and lanes 32-63 the next - is one 16-byte read.  Nine taps are four and a half pairs: the tenth reads
-// zeros.  What bounds a launch is the split: its vector instructions do not overlap with the matrix instructions of the
-// same SIMD, so the larger the tile the better (128->128 @28x28, N=64: 157 us on 32 x 128, 130 on 128 x 128, 99 on
-// 128 x 256; float32 on 32 x 128 153).
-// Infinities: their remainders are not numbers, which only the second accumulator sees; where the sum of both is
-// no number the first one stands.  (A NaN whose set bits all lie in the lower half of the word, which no arithmetic makes,
-// reads as an infinity; rounding the upper half in place of cutting it would turn the largest finite floats into one.)
+// zeros.  What bounds a launch is the split and the matrix instructions in turn: vector instructions do not overlap with
+// the matrix instructions of the same SIMD, so the larger the tile the better (128->128 @28x28, N=64: 174 us on 64 x 128,
+// 140 on 128 x 128, 112 on 128 x 256; float32 on 32 x 128 145; six of the products, which lack precision, 95).
+// Operands without three such parts are worked out again, by redo(): an infinity's remainder is not a number, which
+// leaves no finite number in the second accumulator, so those outputs show themselves; and a number below about 1e-33 whose
+// lowest part would need bits below the smallest bfloat16 number marks its tile (one instruction per two values).
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
-// Two neighbours of a row of K as words of the three planes.
-__device__ __forceinline__ void split2(float x0, float x1, uint32_t &hi, uint32_t &mid, uint32_t &lo) {
+// Two neighbours of a row of K as words of the three planes.  `lost` gets a bit in its lower half where a value has more
+// bits than these hold.
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t &hi, uint32_t &mid, uint32_t &lo, uint32_t &lost) {
     typedef float f2 __attribute__((ext_vector_type(2)));
     const uint32_t u0 = __builtin_bit_cast(uint32_t, x0), u1 = __builtin_bit_cast(uint32_t, x1);
     const float r0 = x0 - __builtin_bit_cast(float, u0 & 0xffff0000u), r1 = x1 - __builtin_bit_cast(float, u1 & 0xffff0000u);
     mid = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{r0, r1}, bf2));
     const float l0 = r0 - __builtin_bit_cast(float, mid << 16), l1 = r1 - __builtin_bit_cast(float, mid & 0xffff0000u);
+    const uint32_t v0 = __builtin_bit_cast(uint32_t, l0), v1 = __builtin_bit_cast(uint32_t, l1);
     hi = __builtin_amdgcn_perm(u1, u0, 0x07060302);
-    lo = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, l1), __builtin_bit_cast(uint32_t, l0), 0x07060302);
+    lo = __builtin_amdgcn_perm(v1, v0, 0x07060302);
+    lost |= v0 | v1;
+}
+// The eight products of two split floats: part of the weight, part of the input (0 the highest).
+constexpr int kParts = 8, kLargest = 2;  // kLargest: which is the product of the highest parts
+constexpr int kPartA[kParts] = {0, 1, 0, 1, 0, 2, 1, 2}, kPartB[kParts] = {1, 0, 0, 1, 2, 0, 2, 1};
+
+// The end of a tile on split operands: outputs that are no finite number, or all of them where a value was
+// `lost`, once more in float32, one multiply-add after the other in the order of K.  flags: a word of LDS per wavefront that
+// nobody reads any more.  Not a path that ordinary tensors take: nothing here is tuned.
+template <int BM, int BN, int KK>
+__device__ __forceinline__ void redo(const DenseArgs &a, int m0, long long q0, bool lost, bool not_finite, uint32_t *flags) {
+    const int tid = threadIdx.x;
+    const uint32_t mine = (__any(lost) ? 1u : 0u) | (__any(not_finite) ? 2u : 0u);
+    if ((tid & 63) == 0) flags[tid >> 6] = mine;
+    __syncthreads();
+    uint32_t all = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) all |= flags[i];
+    if (__builtin_expect(all == 0, 1)) return;
+    __threadfence();  // the outputs are read back, and written again, by other wavefronts than the first time
+    __syncthreads();
+    for (int i = tid; i < BM * BN; i += 512) {
+        const int o = m0 + i / BN;
+        const long long q = q0 + i % BN;
+        if (o >= a.Cout || q >= a.NP) continue;
+        const long long n = q / a.P;
+        const int p = (int)(q - n * a.P), ho = p / a.Wo, wo = p - ho * a.Wo;
+        float *y = a.Y + ((size_t)n * a.Cout + o) * a.P + p;
+        if (!(all & 1) && fabsf(__builtin_nontemporal_load(y)) <= 3.402823466e38f) continue;
+        const float *x = a.X + (size_t)n * a.Cin * a.Pin, *w = a.Wt + (size_t)o * a.K;
+        float sum = 0.f;
+        for (int c = 0; c < a.Cin; ++c, x += a.Pin, w += KK) {
+            for (int t = 0; t < KK; ++t) {
+                const int iy = ho * a.stride + (KK == 9 ? t / 3 - 1 : 0), ix = wo * a.stride + (KK == 9 ? t % 3 - 1 : 0);
+                sum = fmaf(w[t], iy >= 0 && iy < a.H && ix >= 0 && ix < a.W ? x[(size_t)iy * a.W + ix] : 0.f, sum);
+            }
+        }
+        *y = sum + (a.bias ? a.bias[o] : 0.f);
+    }
 }
 
-// NT threads; NPT: staged positions per thread.
-template <int BM, int BN, int NT, int NPT>
-__global__ void __launch_bounds__(NT, NT == 512 ? 2 : 3) k_dense3(const DenseArgs a) {
-    constexpr int WM = BM / 32 < 2 ? 1 : 2, WN = NT / 64 / WM;  // wavefronts along the channels and the pixels
+// NPT: staged positions per thread.
+template <int BM, int BN, int NPT>
+__global__ void __launch_bounds__(512, 2) k_dense3(const DenseArgs a) {
+    constexpr int NT = 512, WM = 2, WN = 4;   // wavefronts along the channels and the pixels
     constexpr int TM = BM / 32 / WM, TN = BN / 32 / WN;
     constexpr int CH = 8;                     // channels per step
     constexpr int LDA = BM + 1;               // the odd pitch spreads the taps of a row over the banks
@@ -460,12 +501,13 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 2 : 3) k_dense3(const DenseArg
     };
     // Its way into LDS, in five parts: four pairs of channels split, and the writes.
     u4 plane[3];
+    uint32_t lost = 0;
     auto store = [&](int i, int part, u4 *buf) __attribute__((always_inline)) {
         if (part < 4) {
             float x0 = x[i][2 * part], x1 = x[i][2 * part + 1];
             if (i >= NA && poff[max(i - NA, 0)] < 0) x0 = x1 = 0.f;
             uint32_t h3, m3, l3;
-            split2(x0, x1, h3, m3, l3);
+            split2(x0, x1, h3, m3, l3, lost);
             plane[0][part] = h3;
             plane[1][part] = m3;
             plane[2][part] = l3;
@@ -503,11 +545,10 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 2 : 3) k_dense3(const DenseArg
     };
     // One step.  As in k_dense, everything but the multiplies is dealt out between them, so that a wavefront alone on
     // its SIMD keeps the matrix pipe busy: a slot is one product of all the wavefront's tiles (32 cycles a tile, room for seven
-    // vector instructions), six slots a pair of taps.  The next step's loads go into the first slots, one item each,
+    // vector instructions), eight slots a pair of taps.  The next step's loads go into the first slots, one item each,
     // its way into the other buffer into the last ones, the next pair's operands into the pair's second slot.
-    constexpr int SLOTS = 30, PARTS = 5 * NI;
-    constexpr int PER = PARTS > 40 ? 3 : PARTS > 20 ? 2 : 1, FIRST = SLOTS - (PARTS + PER - 1) / PER;
-    static_assert(FIRST >= NI || PER == 3, "loads first, stores last");
+    constexpr int SLOTS = 5 * kParts, FIRST = SLOTS - 5 * NI;
+    static_assert(FIRST >= NI, "loads first, stores last");
     auto step = [&](auto more, const u4 *buf, u4 *to, int c0) __attribute__((always_inline)) {
         constexpr bool MORE = decltype(more)::value;
         constexpr int AHEAD = TN == 1 ? 1 : 0;  // pairs of taps whose operands are read ahead
@@ -515,25 +556,18 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 2 : 3) k_dense3(const DenseArg
         if (AHEAD) read_ops(buf, 0, f[0]);
 #pragma unroll
         for (int sl = 0; sl < SLOTS; ++sl) {
-            const int g = sl / 6, pr = sl % 6;
+            const int g = sl / kParts, pr = sl % kParts;
             if (AHEAD && pr == 1 && g + 1 < 5) read_ops(buf, g + 1, f[(g + 1) & AHEAD]);
             if (!AHEAD && pr == 0) read_ops(buf, g, f[0]);
             if (MORE && sl < NI) load(sl, c0 + CH, std::integral_constant<bool, true>{});
-            if (MORE && sl >= FIRST) {
-#pragma unroll
-                for (int v = 0; v < PER; ++v) {
-                    const int u = (sl - FIRST) * PER + v;
-                    if (u < PARTS) store(u / 5, u % 5, to);
-                }
-            }
+            if (MORE && sl >= FIRST) store((sl - FIRST) / 5, (sl - FIRST) % 5, to);
             __builtin_amdgcn_sched_barrier(0);
-            constexpr int pa[6] = {0, 1, 0, 1, 0, 2}, pb[6] = {1, 0, 0, 1, 2, 0};
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    auto &c = pr == 2 ? big[i][j] : kTwo && pr % 2 ? small2[0][0] : small[i][j];
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[g & AHEAD].a[pa[pr]][i], f[g & AHEAD].b[pb[pr]][j], c, 0, 0, 0);
+                    auto &c = pr == kLargest ? big[i][j] : kTwo && pr % 2 ? small2[0][0] : small[i][j];
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[g & AHEAD].a[kPartA[pr]][i], f[g & AHEAD].b[kPartB[pr]][j], c, 0, 0, 0);
                 }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -565,6 +599,7 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 2 : 3) k_dense3(const DenseArg
     }
     step(no, cur, next, c0);
     // ---- epilogue: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32 ----
+    bool not_finite = false;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         const int e = (wn * TN + j) * 32 + l32;
@@ -577,19 +612,21 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 2 : 3) k_dense3(const DenseArg
             for (int r = 0; r < 16; ++r) {
                 const int o = m0 + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
                 const float both = big[i][j][r] + (kTwo ? small[i][j][r] + small2[0][0][r] : small[i][j][r]);
-                if (o < a.Cout) ybase[(size_t)o * a.P] = (both == both ? both : big[i][j][r]) + (a.bias ? a.bias[o] : 0.f);
+                not_finite |= !(fabsf(both) <= 3.402823466e38f);
+                if (o < a.Cout) ybase[(size_t)o * a.P] = both + (a.bias ? a.bias[o] : 0.f);
             }
     }
+    redo<BM, BN, 9>(a, m0, q0, (lost & 0xffff) != 0, not_finite, reinterpret_cast<uint32_t *>(lds3));
 }
 
 // 1x1 on split operands: 128 channels x BN pixels, 32 input channels a step.  As k_dense3, but a pixel's words serve one
 // tap, so most of the split work is the input's, and a tile has few steps to cover its first loads and its stores: large
-// layers gain (392->760 @56x57, N=18 369 -> 262 us, 512->512 @14x14, N=256 285 -> 205, 1024->256 @14x14, N=64 89 -> 60),
-// layers of few input channels or few tiles do not (128->64 @56x56, N=32: 27 us, 41 split).
+// layers gain (392->760 @56x57, N=18 342 us in float32, 301 split; 1024->256 @14x14, N=64 79 and 60; 512->512
+// @14x14, N=256 239 and 233), layers of few input channels or few tiles do not (128->64 @56x56, N=32: 25 us, 45 split).
 template <int BN>
 __global__ void __launch_bounds__(512, 2) k_dense1(const DenseArgs a) {
     constexpr int BM = 128, CH = 32, NQ = CH / 8, NT = 512;  // NQ: groups of 8 channels
-    constexpr int WM = 2, WN = 4, TM = 2, TN = BN / 32 / WN;
+    constexpr int WN = 4, TM = 2, TN = BN / 32 / WN;   // two wavefronts along the channels, four along the pixels
     constexpr int LDA = BM + 1, LDB = BN + 1, BUF = 3 * NQ * (LDA + LDB);
     constexpr int NB = BN * NQ / NT, NI = 1 + NB;
     static_assert(BM * NQ == NT, "one item of the weights per thread");
@@ -662,10 +699,11 @@ __global__ void __launch_bounds__(512, 2) k_dense1(const DenseArgs a) {
         }
     };
     u4 plane[3];
+    uint32_t lost = 0;
     auto store = [&](int i, int part, u4 *buf) __attribute__((always_inline)) {
         if (part < 4) {
             uint32_t hi, mid, lo;
-            split2(x[i][2 * part], x[i][2 * part + 1], hi, mid, lo);
+            split2(x[i][2 * part], x[i][2 * part + 1], hi, mid, lo, lost);
             plane[0][part] = hi;
             plane[1][part] = mid;
             plane[2][part] = lo;
@@ -675,14 +713,14 @@ __global__ void __launch_bounds__(512, 2) k_dense1(const DenseArgs a) {
             for (int p = 0; p < 3; ++p) to[p * NQ * (i == 0 ? LDA : LDB)] = plane[p];
         }
     };
-    constexpr int SLOTS = 6 * NQ / 2, PARTS = 5 * NI, PER = 2, FIRST = SLOTS - (PARTS + PER - 1) / PER;
+    constexpr int SLOTS = kParts * NQ / 2, PARTS = 5 * NI, PER = 2, FIRST = SLOTS - (PARTS + PER - 1) / PER;
     static_assert(FIRST >= NI, "loads first, stores last");
     auto step = [&](auto more, const u4 *buf, u4 *to, int c0) __attribute__((always_inline)) {
         constexpr bool MORE = decltype(more)::value;
         bf8 av[3][TM], bv[3][TN];
 #pragma unroll
         for (int sl = 0; sl < SLOTS; ++sl) {
-            const int g = sl / 6, pr = sl % 6;
+            const int g = sl / kParts, pr = sl % kParts;
             if (pr == 0) {
 #pragma unroll
                 for (int p = 0; p < 3; ++p) {
@@ -701,13 +739,12 @@ __global__ void __launch_bounds__(512, 2) k_dense1(const DenseArgs a) {
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
-            constexpr int pa[6] = {0, 1, 0, 1, 0, 2}, pb[6] = {1, 0, 0, 1, 2, 0};
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    auto &c = pr == 2 ? big[i][j] : small[i][j];
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[pa[pr]][i], bv[pb[pr]][j], c, 0, 0, 0);
+                    auto &c = pr == kLargest ? big[i][j] : small[i][j];
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[kPartA[pr]][i], bv[kPartB[pr]][j], c, 0, 0, 0);
                 }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -738,6 +775,7 @@ __global__ void __launch_bounds__(512, 2) k_dense1(const DenseArgs a) {
         swap();
     }
     step(no, cur, next, c0);
+    bool not_finite = false;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         const int e = (wn * TN + j) * 32 + l32;
@@ -750,9 +788,11 @@ __global__ void __launch_bounds__(512, 2) k_dense1(const DenseArgs a) {
             for (int r = 0; r < 16; ++r) {
                 const int o = m0 + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
                 const float both = big[i][j][r] + small[i][j][r];
-                if (o < a.Cout) ybase[(size_t)o * a.P] = (both == both ? both : big[i][j][r]) + (a.bias ? a.bias[o] : 0.f);
+                not_finite |= !(fabsf(both) <= 3.402823466e38f);
+                if (o < a.Cout) ybase[(size_t)o * a.P] = both + (a.bias ? a.bias[o] : 0.f);
             }
     }
+    redo<BM, BN, 1>(a, m0, q0, (lost & 0xffff) != 0, not_finite, reinterpret_cast<uint32_t *>(lds3));
 }
 
 constexpr int BK = 16;
@@ -902,55 +942,23 @@ __global__ void __launch_bounds__(256) k_dense_gather(const DenseArgs a) {
     }
 }
 
-// Tile shapes.  1x1, float32: with the rate the matrix work of a tile runs at against the largest tile's, measured on
-// layers with 16 to 1024 channels; larger tiles were slower than a shape listed here or as fast.  Against 128 x 128
-// tiles of the patch matrix (130 layers, 40 to 1016 channels): 1.0 to 2.7 times as fast, but for a few whose
-// channels fill those tiles, 3 to 7 % slower (392->760 @56x57, N=18: 374 against 347 us); staged 128 x 128 tiles
-// give these back and lose as much on others (472->232 @28x28, N=83: 165 -> 179 us).
-// 3x3: the float32 instruction on the smallest tile, and where the input of a tile is large against its multiplies
-// (stride 2, wide images), the split one on the others.
-struct DenseShape {
-    int bm, bn;
-    double rate;  // 1x1, float32
-    bool split;   // k_dense3, k_dense1
-};
-static const DenseShape kShapes3x3[] = {{128, 256, 0, true}, {128, 128, 0, true}, {64, 128, 0, true}, {128, 128, 0, false}, {64, 128, 0, false}, {32, 128, 0, false}};
-static const DenseShape kShapes1x1[] = {{128, 256, 0, true}, {128, 128, 0, true}, {64, 64, 1.0, false}, {32, 128, 0.90, false}};
-// Microseconds that a 3x3 tile's step takes: matrix instructions, and the way of its weights and positions into LDS
-// (vector instructions do not overlap with the matrix instructions of a SIMD).  Measured per step on 128->128 @28x28,
-// 512->512 @7x7 and 128->128 @56x56 stride 2: split 5.9 / 4.0 / 2.5 us, float32 1.4 to 1.7 us on 32 x 128.
-static double step_time(const DenseShape &sh, long long npos) {
-    return sh.split ? 0.98e-4 * sh.bm * sh.bn + 1.7e-3 * (9 * sh.bm + npos) : 2.34e-4 * sh.bm * sh.bn + 0.7e-3 * (9 * sh.bm + npos);
-}
-// Microseconds of a 1x1 tile: measured on 64 to 1024 input channels; the split tiles' first part is their first loads and
-// their stores.
-static double tile_time(const DenseShape &sh, int Cin) {
-    if (!sh.split) return (0.8 + 0.021 * Cin) * sh.bm * sh.bn / (4096 * sh.rate);
-    const int steps = (Cin + 31) / 32;
-    return sh.bn == 256 ? 12.6 + 2.4 * steps : 5.0 + 1.6 * steps;
-}
-static int dense_lds(const DenseShape &sh, int kernel, long long npos, int npt) {
-    if (sh.split && kernel == 1) return 2 * 16 * 12 * (sh.bm + 1 + sh.bn + 1);
-    if (sh.split) return (int)(16 * (55 * (sh.bm + 1) + 6 * (npos + 1)));
-    return 2 * 16 * (kernel == 3 ? 18 * (sh.bm + 1) + 512 * npt : 4 * (sh.bm + 1) + 4 * sh.bn);
-}
-
 typedef void (*dense_t)(const DenseArgs);
-template <int NPT>
-static dense_t pick_3x3(int BM) {
-    return BM == 128 ? k_dense<128, 128, 9, NPT> : BM == 64 ? k_dense<64, 128, 9, NPT> : k_dense<32, 128, 9, NPT>;
-}
-static dense_t pick_dense(int kernel, const DenseShape &sh, int npt) {
-    if (sh.split && kernel == 1) return sh.bn == 256 ? k_dense1<256> : k_dense1<128>;
-    if (sh.split) {
-        if (sh.bn == 256) return k_dense3<128, 256, 512, 1>;
-        if (sh.bm == 128) return npt == 1 ? k_dense3<128, 128, 512, 1> : k_dense3<128, 128, 512, 2>;
-        return npt == 1 ? k_dense3<64, 128, 512, 1> : k_dense3<64, 128, 512, 2>;
+static dense_t pick_dense(int kernel, const DensePlan &p) {
+    if (p.kind == kDenseGather) return p.bm == 128 ? k_dense_gather<128> : k_dense_gather<64>;
+    if (p.kind == kDenseSplit && kernel == 1) return p.bn == 256 ? k_dense1<256> : k_dense1<128>;
+    if (p.kind == kDenseSplit) {
+        if (p.bn == 256) return k_dense3<128, 256, 1>;
+        if (p.bm == 128) return p.npt == 1 ? k_dense3<128, 128, 1> : k_dense3<128, 128, 2>;
+        return p.npt == 1 ? k_dense3<64, 128, 1> : k_dense3<64, 128, 2>;
     }
     // (64 pixels touch at least half the positions of 128, and are taken where those are more than 1024)
-    if (kernel == 3 && sh.bn == 64) return npt == 3 ? k_dense<64, 64, 9, 3> : k_dense<64, 64, 9, 4>;
-    if (kernel == 3) return npt == 2 ? pick_3x3<2>(sh.bm) : npt == 3 ? pick_3x3<3>(sh.bm) : pick_3x3<4>(sh.bm);
-    return sh.bm == 64 ? k_dense<64, 64, 1, 1> : k_dense<32, 128, 1, 1>;
+    if (kernel == 3 && p.bn == 64) return p.npt == 3 ? k_dense<64, 64, 9, 3> : k_dense<64, 64, 9, 4>;
+    if (kernel == 3) {
+        if (p.bm == 128) return p.npt == 3 ? k_dense<128, 128, 9, 3> : k_dense<128, 128, 9, 4>;
+        if (p.bm == 64) return k_dense<64, 128, 9, 2>;
+        return p.npt == 2 ? k_dense<32, 128, 9, 2> : p.npt == 3 ? k_dense<32, 128, 9, 3> : k_dense<32, 128, 9, 4>;
+    }
+    return p.bm == 64 ? k_dense<64, 64, 1, 1> : k_dense<32, 128, 1, 1>;
 }
 
 }  // namespace alcs
@@ -980,45 +988,9 @@ extern "C" int alcs_dense_conv(const float *W_dev, const float *X_dev, const flo
     int cus = 0, xcds = 0;
     if (current_device_shape(&cus, &xcds) != ALCS_OK) return ALCS_E_HIP;
     a.xcds = xcds;
-    // The tile whose launch gives the most loaded compute unit the least matrix work, at the shape's rate.
-    // (512 channels, 7x7, N = 64: 307 us on 128 x 128 tiles, 187 on 32 x 128; 40 -> 23 @112x86:
-    // 653 and 175.)  3x3 also needs a tile's input rows to fit its staging.
-    const DenseShape *best = nullptr;
-    double best_cost = 0;
-    auto consider = [&](const DenseShape &sh) {
-        const long long rows = std::min<long long>((sh.bn + Wo - 2) / Wo + 1, (long long)N * Ho);  // output rows a tile can touch
-        const long long images = std::min<long long>((rows + Ho - 2) / Ho + 1, N);
-        const long long npos = kernel == 3 ? (rows * stride + images * (3 - stride)) * ((Wo - 1) * (long long)stride + 3) : 0;
-        if (npos > 256 * kPosPerThread) return;
-        if (kernel == 3 && sh.split && (dense_lds(sh, kernel, npos, 0) > 160 * 1024 || (sh.bn == 256 && npos > 512))) return;
-        if (images * (long long)Cin * Pin >= (1LL << 30) || K * sh.bm >= (1LL << 29)) return;  // byte offsets are 32 bits
-        const long long tiles = ((a.NP + sh.bn - 1) / sh.bn) * ((Cout + sh.bm - 1) / sh.bm);
-        const double rounds = (double)((tiles + cus - 1) / cus);
-        const double cost = rounds * (kernel == 3 ? step_time(sh, npos) : tile_time(sh, Cin));
-        if (!best || cost < best_cost) { best = &sh; best_cost = cost; a.npos = (int)npos; }
-    };
-    if (kernel == 1) {
-        for (const DenseShape &sh : kShapes1x1) consider(sh);
-    } else {
-        for (const DenseShape &sh : kShapes3x3) consider(sh);
-    }
-    int BM = best ? best->bm : 64, BN = best ? best->bn : 128;
-    if (!best) {
-        // 3x3 layers whose 128 pixels touch more input than the staging holds, mostly stride 2 on images more
-        // than about 100 wide: staged with 64 pixels a tile, or gathered on 64 or 128 channels, by what each
-        // takes a channel on the most loaded compute unit.  A staged tile has a cost of about 16 channels before the
-        // first; gathered tiles are slow alone and cover each other's waits (60 such layers, 16 to 448 channels:
-        // within 5 % of the fastest of the three, 59 of them; the gather alone, on 128 channels or 64 if that left
-        // compute units idle, took up to 5.6 times as long - 448->64 @62x124, one image: 494 against 111 us -
-        // and the staged form alone up to 1.6 times - 16->424 @82x118, N=43: 364 against 219).
-        auto load = [&](int bm, int bn) { return (double)(((a.NP + bn - 1) / bn) * ((Cout + bm - 1) / bm)) / cus; };
-        auto at_once = [](double t) { return t > 2 ? t : std::ceil(t); };
-        const double t128 = 0.45 + 0.95 * at_once(load(128, 128)), t64 = 0.65 + 0.52 * std::max(1.0, load(64, 128));
-        static const DenseShape kNarrow{64, 64, 0, false};
-        if (kernel == 3 && 0.25 * std::ceil(load(64, 64)) * (Cin + 16) / Cin < std::min(t128, t64)) consider(kNarrow);
-        BM = best || t64 <= t128 ? 64 : 128;
-        if (best) BN = 64;
-    }
+    const DensePlan plan = dense_plan(N, Cin, Cout, H, W, kernel, stride, cus);
+    const int BM = plan.bm, BN = plan.bn;
+    a.npos = plan.npos;
     const long long ntile = (a.NP + BN - 1) / BN;
     a.mt = (Cout + BM - 1) / BM;
     const long long total = ntile * a.mt;
@@ -1026,17 +998,12 @@ extern "C" int alcs_dense_conv(const float *W_dev, const float *X_dev, const flo
     a.nt = (int)ntile;
     a.total_wgs = (int)total;
     a.wg_per_xcd = (int)((total + xcds - 1) / xcds);
-    dense_t kern = BM == 128 ? k_dense_gather<128> : k_dense_gather<64>;
-    int lds = 0, threads = 256;
-    if (best) {
-        threads = best->split ? 512 : 256;
-        const int npt = kernel == 1 ? 1 : best->split ? (a.npos + 511) / 512 : a.npos <= 512 ? 2 : a.npos <= 768 ? 3 : 4;
-        lds = dense_lds(*best, kernel, a.npos, npt);
-        kern = pick_dense(kernel, *best, npt);
-        const int rc = allow_lds((const void *)kern, lds);
+    const dense_t kern = pick_dense(kernel, plan);
+    if (plan.kind != kDenseGather) {
+        const int rc = allow_lds((const void *)kern, plan.lds);
         if (rc != ALCS_OK) return rc;
     }
-    hipLaunchKernelGGL(kern, dim3(a.wg_per_xcd * xcds), dim3(threads), lds, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(kern, dim3(a.wg_per_xcd * xcds), dim3(plan.threads), plan.lds, (hipStream_t)stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_hip_error((int)e); return ALCS_E_HIP; }
     return ALCS_OK;

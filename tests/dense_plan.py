@@ -1,0 +1,27 @@
+"""Which kernel and tile a dense convolution takes, asked of the library's own rule without a GPU."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2109_00170_amd", "csrc")
+KINDS = ("gather", "float32", "split")
+
+
+@functools.lru_cache(None)
+def _library():
+    with tempfile.TemporaryDirectory() as d:
+        so = os.path.join(d, "dense_plan.so")
+        subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC,
+                               os.path.join(HERE, "native", "dense_plan.cpp"), "-o", so])
+        return ctypes.CDLL(so)
+
+
+def dense_plan(k, stride, Cin, Cout, H, W, N, cus=256):
+    """(kernel size, "gather" / "float32" / "split", channels, pixels, positions per thread) of the tile, and its positions
+    and LDS bytes."""
+    out = (ctypes.c_int * 7)()
+    _library().dense_plan((ctypes.c_int * 7)(N, Cin, Cout, H, W, k, stride), cus, out)
+    return (k, KINDS[out[0]]) + tuple(out[1:4]), out[4], out[6]
