@@ -103,7 +103,8 @@ inline DensePlan dense_plan(int N, int Cin, int Cout, int H, int W, int kernel, 
         auto load = [&](int bm, int bn) { return (double)(((NP + bn - 1) / bn) * ((Cout + bm - 1) / bm)) / cus; };
         auto at_once = [](double t) { return t > 2 ? t : std::ceil(t); };
         const double t128 = 0.45 + 0.95 * at_once(load(128, 128)), t64 = 0.65 + 0.52 * std::max(1.0, load(64, 128));
-        static const DenseShape kNarrow{64, 64, false, 0, 1024, 0, 0, 0, 0, 0, 0};
+        // (fewer positions: a layer refused above for its size in bytes; the kernel has three or four a thread)
+        static const DenseShape kNarrow{64, 64, false, 512, 1024, 0, 0, 0, 0, 0, 0};
         if (kernel == 3 && 0.25 * std::ceil(load(64, 64)) * (Cin + 16) / Cin < std::min(t128, t64)) consider(kNarrow);
         BM = best || t64 <= t128 ? 64 : 128;
         if (best) BN = 64;
