@@ -92,7 +92,10 @@ __global__ void __launch_bounds__(256) k_depthwise(const DwArgs a) {
 // memory and the launch (512 channels, 14x14, one image: 2.85 us, 4.9 with the
 // form above), on large ones the bytes (32 channels, 112x112, N=32: 25 us for 103 MB, 31.5 with four
 // pixels a lane and nine loads).  NU: units per wavefront whose loads are in flight together.
-template <int S, int NU>
+// FAR: planes that end beyond a descriptor's reach (the last 63 floats of the largest).  A unit's base is then its
+// first input row and, of a wide row, its block's first column, never more than three rows' parts away (for all planes it
+// would cost 1 % in the mean and up to 4, 352 channels of 56x56, N=24 39.9 -> 41.5 us).
+template <int S, int NU, bool FAR = false>
 __global__ void __launch_bounds__(256) k_depthwise_rows(const DwArgs a) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -119,10 +122,11 @@ __global__ void __launch_bounds__(256) k_depthwise_rows(const DwArgs a) {
         const int rc = wide ? (int)(chunk / (unsigned)a.cblocks) : (int)chunk;
         row[u] = rc * a.rows + r;
         qx[u] = wide ? ((int)chunk - rc * a.cblocks) * 62 + lane - 1 : item - r * QW;
-        // from the unit's first input row (and, of a wide row, its block's first column) on: what a descriptor reaches ends a
-        // few floats short of the largest planes, but never short of three rows' parts
-        const int y0 = max(rc * a.rows * S - 1, 0), x0 = wide ? max(((int)chunk - rc * a.cblocks) * 62 - 1, 0) * 4 * S : 0;
-        const int from = y0 * a.W + x0;
+        int from = 0;
+        if constexpr (FAR) {
+            const int x0 = wide ? max(((int)chunk - rc * a.cblocks) * 62 - 1, 0) * 4 * S : 0;
+            from = max(rc * a.rows * S - 1, 0) * a.W + x0;
+        }
         st.init((uint32_t)pl * a.Pin - (uint32_t)from, min(max(qx[u], 0), QW - 1), min(row[u], a.Ho - 1), a.H, a.W);
         st.load(DwStrip<S>::rows_from(a.X, p0 * a.Pin + from, a.planes * a.Pin), v[u]);
         const float *wp;
@@ -187,7 +191,8 @@ extern "C" int alcs_depthwise_conv(const float *dw_weights_dev, const float *X_d
         a.planes_per_wave = (int)std::min<long long>(a.cblocks == 1 && a.rows == Ho ? 64 / (a.rows * QW) : 1, a.planes);
         const long long nchunks = (long long)((Ho + a.rows - 1) / a.rows) * a.cblocks;
         const long long groups = (a.planes + a.planes_per_wave - 1) / a.planes_per_wave;
-        const bool two = groups > 64LL * cus / nchunks;   // more units than the compute units hold wavefronts
+        // more units than the compute units hold wavefronts
+        const bool two = groups > 64LL * cus / nchunks || 4 * Pin > kDwsBeyond;
         // Large tensors at stride 1 whose rows leave many lanes idle (131 pixels are 33 of 64 lanes) are faster with
         // one pixel a lane: 202 channels of 105x131, N=10 79 us as rows, 52 not; where rows are 16-byte aligned only
         // below 62 % (48 channels of 280x260, N=16: 124 us as rows, 96 not; 792 of
@@ -199,6 +204,7 @@ extern "C" int alcs_depthwise_conv(const float *dw_weights_dev, const float *X_d
             blocks = (groups * nchunks + (two ? 7 : 3)) / (two ? 8 : 4);
             kern = stride == 1 ? (two ? k_depthwise_rows<1, 2> : k_depthwise_rows<1, 1>)
                                : (two ? k_depthwise_rows<2, 2> : k_depthwise_rows<2, 1>);
+            if (4 * Pin > kDwsBeyond) kern = stride == 1 ? k_depthwise_rows<1, 2, true> : k_depthwise_rows<2, 2, true>;
         }
     }
     if (!kern) {  // narrower images, and tensors of more units than a grid takes
