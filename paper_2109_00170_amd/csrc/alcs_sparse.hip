@@ -2438,16 +2438,10 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
         bool tall = stride == 1 && mfma && V <= 8 &&
                     (T.pv == 2 || (T.pv == 0 && Ho >= 12 && Wo >= 12));
         ti = pick_tile3(Ho, Wo, T.tile_w, tall);
-        // Handles with channel records (the pattern is shared by the nine taps) and groups of 4 or 8
-        // channels walk records instead of columns; "path" = 6 keeps the column-by-column kernel.
-        // By default only with tall tiles, where it measures 0-7 % faster (128->128 @28x28, N=64: 71.4
-        // -> 66.5 us; 256->256 @14x14: 80.6 -> 78.3; 64->64 @56x56 equal); with one pixel per lane it
-        // is slower (512->512 stride 2: 129 -> 157 us), "path" = 7 asks for it anyway.
         if (tall && (L.KC + 1) * halo_area3(stride, ti, true) * 4 > kMaxLds) {
             tall = false;
             ti = pick_tile3(Ho, Wo, T.tile_w, false);
         }
-        const bool shared = Wp->dev.cw && mfma && V <= 8 && T.path != 6 && (tall || (V == 4 && L.nchunks > 1) || T.path == 7);
         pv = tall ? 2 : 1;
         a.off = Wp->dev.off[off_table3(stride, ti, tall)];
         lds = (L.KC + 1) * halo_area3(stride, ti, tall) * 4;
@@ -2473,7 +2467,15 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             case 8: kern = pick_conv3<8, true>(stride, ti, ug, tall); break;
             case 16: kern = pick_conv3<16, true>(stride, ti, ug, tall); break;
         }
-        if (shared) {
+        // Handles with channel records (the pattern is shared by the nine taps) and groups of 4 or 8
+        // channels walk records instead of columns; "path" = 6 keeps the column-by-column kernel, 7 asks for records.
+        // By default with tall tiles, and with one pixel per lane, groups of 4 and several chunks, where workgroups share a
+        // compute unit: the records' lines ahead are a chain of waits for a workgroup alone (110 such layers, 80 with
+        // up to 256 workgroups: stride 1 0.88 to 0.99 of the column walk's speed, stride 2 0.86 to 1.03 on chunks of 64
+        // channels and 0.97 to 1.04 on chunks of 32; in more workgroups 0.99 to 1.14 - 800->775 @7x9, N=9 145 us by columns,
+        // 165 by records, 495->502 @8x8, N=122 235 and 217, 466->151 @14x14 stride 2, N=232 109 and 98).
+        const bool one_px = V == 4 && L.nchunks > 1 && ((long long)a.npt * a.ngt > kCUs || (stride == 2 && L.KC <= 32));
+        if (Wp->dev.cw && mfma && V <= 8 && T.path != 6 && (tall || one_px || T.path == 7)) {
             a.cw = Wp->dev.cw; a.csel = Wp->dev.csel; a.cwork = Wp->dev.cwork; a.cwplane = Wp->dev.cwplane;
             kern = V == 4 ? pick_conv3_shared<4>(stride, ti, ug, tall) : pick_conv3_shared<8>(stride, ti, ug, tall);
             mode = 7;

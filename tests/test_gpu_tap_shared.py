@@ -13,10 +13,10 @@ from gpu_util import TOL, rel_err
 pytestmark = pytest.mark.gpu
 
 
-def run(L, seed, options=None, on_device=False, expect_mode=7):
+def run(L, seed, options=None, on_device=False, expect_mode=7, ask=True):
     import torch
     d = workloads.make_layer(L, seed, with_bias=True)
-    if expect_mode == 7:
+    if expect_mode == 7 and ask:
         options = dict(options or {}, path=7)       # the record walk also where it is not the default
     if on_device:
         packed = alcs.alcs_pack_weights_device(torch.from_numpy(d.W).cuda(), torch.from_numpy(d.mask).cuda(), L.V, options=options)
@@ -67,7 +67,8 @@ def test_tap_shared_launch_shapes(pv, ug):
 
 
 def test_more_than_64_channels_in_a_chunk():
-    """A chunk of 100 input channels, all kept: the records' channel indices are fetched 64 at a time."""
+    """A chunk of 100 input channels, all kept: the records' channel indices are fetched eight at a time, the
+    weights' lines are eight ahead."""
     L = workloads.Layer("ts_long", 100, 12, 14, 14, k=3, N=2, V=4, sparsity=0.0, w_std=0.1, tap_shared=True)
     run(L, 6160, options={"chunk_channels": 100})
 
@@ -91,6 +92,18 @@ def test_tall_tiles_walk_records_by_default():
     assert info["mode"] == 7 and info["pv"] == 2, info
     assert rel_err(Y.cpu().numpy(), oracle.sparse_conv(d.W, d.mask, d.X, 4)) <= TOL
     packed.free()
+
+
+@pytest.mark.parametrize("V,Cin,Cout,hw,stride,N,mode", [
+    (4, 40, 40, 7, 1, 300, 7),     # one pixel per lane, two chunks, more workgroups than compute units
+    (4, 40, 40, 7, 1, 3, 3),       # fewer
+    (4, 40, 24, 15, 2, 3, 7),      # stride 2, chunks of 32 channels
+    (4, 600, 24, 14, 2, 2, 3),     # and of 64
+    (8, 40, 40, 7, 1, 300, 3)])    # groups of 8
+def test_one_pixel_per_lane_by_default(V, Cin, Cout, hw, stride, N, mode):
+    L = workloads.Layer("ts_one_px", Cin, Cout, hw, hw, k=3, stride=stride, N=N, V=V, sparsity=0.7, w_std=0.2, tap_shared=True)
+    info, _ = run(L, 6177, options={}, expect_mode=mode, ask=False)
+    assert info["pv"] == 1 and info["chunk_channels"] == (64 if Cin == 600 else 32), info
 
 
 def test_independent_taps_keep_the_column_kernel():
