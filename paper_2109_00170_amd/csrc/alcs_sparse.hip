@@ -2307,8 +2307,8 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             const bool can_split = GS > 1 && !(GS == 2 && pv == 2);
             const int most_gts = can_split ? NB : std::max(1, NB / 4);
             if (a.npt < want) ngt = std::min(most_gts, std::max(1, one_round ? want / a.npt : ceil_div(want, a.npt)));
-            // Depthwise stage: every group tile works out its pixel tile again, so at most two (see
-            // restage_ok below), and one from about 5/8 of the compute units on.
+            // Depthwise stage: every group tile works out its pixel tile again, so at most two from 80 pixel tiles
+            // on (fewer may have four, see restage_ok below), and one from about 5/8 of the compute units on.
             if (kDw && GS == 1 && rows && a.npt >= 80) ngt = std::min(most_gts, a.npt >= kCUs * 5 / 8 ? 1 : 2);
             if (T.group_tiles > 0) ngt = std::min(T.group_tiles, NB);
             a.gpt = ceil_div(NB, ngt);
@@ -2380,7 +2380,7 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             if (T.waves > 0) nw = std::min(T.waves, 16);
 #if ALCS_DW_STAGE
             // Two rows per lane: a wavefront's turn takes about 1.6 times as long and there are half as many, unless
-            // few channels leave wavefronts without one (21->159 @112x112, N=13, V=1: 39 us in pairs, 34 not).
+            // few channels leave wavefronts without one (21->159 @112x112, N=13, V=1: 39 us in pairs, 36 not).
             if (rows > 1 && !dw_s2) {
                 const int QW = (Wo + 3) / 4;
                 auto turns = [&](int K) {
@@ -2495,9 +2495,13 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
     // (584->24 @56x56, N=38, V=8: 271 us against 192).  The caller that can run the two layers (it has a
     // workspace) is told to.
     // In up to four over whole rows at stride 1 and in a single round, up to 512 channels (512->512 @14x14, N=8: 12.5 us
-    // in four against 13.5; 32->64 @112x112, one image: 7.4 against 8.3; 1024->1024 @7x7, N=32: 25.1 against 23.7).
+    // in four against 13.5; 32->64 @112x112, one image: 7.4 against 8.3; 1024->1024 @7x7, N=32: 25.1 against 23.7).  With four
+    // pixels per lane a tile is four times as much to work out again: in three or four up to 80 channels (70 such layers: 0.97 to
+    // 1.28x of the two layers' speed up to 83 channels, 0.74 to 1.23x, 0.94 in the mean, above - 104->24 @14x14, N=84, V=2
+    // 14.9 us in three against 13.6, 134->208 @14x14, N=99, V=2 26.6 against 24.6).
     const bool restage_ok = (a.ngt == 1 && (L.GS == 1 || a.dw_rows > 0)) ||
-                            (a.ngt <= 4 && a.dw_rows > 0 && dw->stride == 1 && Cin <= 512 && a.npt * a.ngt <= kCUs) ||
+                            (a.ngt <= (pv == 4 && Cin > 80 ? 2 : 4) && a.dw_rows > 0 && dw->stride == 1 && Cin <= 512 &&
+                             a.npt * a.ngt <= kCUs) ||
                             (a.ngt == 2 && a.npt >= 80 && 2 * a.npt <= kCUs && a.dw_rows > 0 &&
                              (dw->stride == 1 || Cin * a.tile_px <= 8192));
     if (decline_restaged && !restage_ok && !T.dw_one_kernel) return ALCS_E_UNSUPPORTED;
