@@ -279,7 +279,9 @@ int alcs_dw_sparse_conv_fused(const alcs_packed_t *Wp, const float *dw_weights_d
  * paper's Section 4.1 timing protocol).
  *   W_dev [Cout, Cin, kernel, kernel] fp32 on the device; other arguments as above.
  * Every bit of the operands counts, small numbers, infinities and NaNs among them, and sums are float32's or
- * better, whichever matrix instruction the library takes for the shape.
+ * better, whichever matrix instruction the library takes for the shape.  The shape that decides includes N: an image's
+ * result may differ in its last bits with the batch it is in (about 5e-7 of the result, either within float32's error),
+ * and from alcs_sparse_conv at sparsity 0.  Equal calls give equal bits.
  */
 int alcs_dense_conv(const float *W_dev, const float *X_dev, const float *bias_dev, float *Y_dev,
                     int N, int Cin, int Cout, int H, int W, int kernel, int stride, void *stream);

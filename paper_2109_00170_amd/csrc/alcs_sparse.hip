@@ -1507,9 +1507,11 @@ __global__ void __launch_bounds__(512) k_pw_stream(const ConvArgs a) {
 // One (group, chunk) of a handle whose kept channels keep all nine taps: one record per kept
 // CHANNEL (its chunk-relative index and its 9 x V weights, see alcs_chanrec.hip) instead of one
 // column per tap.  The nine LDS reads of a channel differ by compile-time offsets from one
-// address, so the selector add of the column-by-column walk - vector instructions do not overlap with the
-// matrix instructions of a SIMD, LDS reads do: 15.0 cycles a column with it, 11.2 without, one pixel per lane -
-// is paid once per channel.  A channel's weights are one 256-byte line per plane in block-broadcast order (lane
+// address, so the selector add of the column-by-column walk is paid once per channel.  Vector instructions do not overlap with
+// the matrix instructions of a SIMD; LDS reads do in large part (cycles a SIMD, four wavefronts: a 4-byte read 9.4, a matrix
+// instruction 10.1, both 15.2, with an address add 24.2; an 8-byte read 17.0, two matrix instructions 19.1, all three 24.0,
+// with the add 39.1).
+// A channel's weights are one 256-byte line per plane in block-broadcast order (lane
 // 4t + i = tap t, row i: abid = t).  The first channels' lines (eight, or four with two planes) are requested with the selectors before the
 // chunk is staged, and every register is filled again right behind its use with the line as many channels on: with
 // one line ahead the walk waited for it at every channel (256->256 @14x14, N=64, 80 % sparse: 81 us, now 72).
