@@ -42,7 +42,7 @@ struct DenseArgs {
 // What bounds a launch is the matrix pipe (3x3: 52 to 61 % of a single launch's cycles busy, start and
 // drain included; 64 % of its peak in a stream of launches) and, on few tiles, how evenly they divide over
 // the compute units (the launcher picks the tile for that).  3x3, N=64, against the patch matrix
-// gathered word by word: 128->128 @28x28 260 -> 147 us (k_dense3 112), 512->512 @7x7 577 -> 176 us,
+// gathered word by word: 128->128 @28x28 260 -> 147 us (k_dense3 113), 512->512 @7x7 577 -> 176 us,
 // 40->23 @112x86 424 -> 175 us; 1x1 1024->256 @14x14 101 -> 80 us.  1x1 layers with few
 // output channels wait for their input: 16 channels a step leave room for 8 workgroups a compute unit
 // (256->64 @56x56, N=40: 59.5 -> 50 us against 32 channels and 3 workgroups).
@@ -337,18 +337,23 @@ __global__ void __launch_bounds__(256, KK == 1 ? 4 : BM == 128 ? 1 : 2) k_dense(
 // 0-31 one tap and lanes 32-63 the next - is one 16-byte read.  Nine taps are four and a half pairs: the tenth reads
 // zeros.  What bounds a launch is the split and the matrix instructions in turn: vector instructions do not overlap with
 // the matrix instructions of the same SIMD, so the larger the tile the better (128->128 @28x28, N=64: 174 us on 64 x 128,
-// 140 on 128 x 128, 112 on 128 x 256; float32 on 32 x 128 145; six of the products, which lack precision, 95).
-// Operands without three such parts are worked out again, by redo(): an infinity's remainder is not a number, which
-// leaves no finite number in the second accumulator, so those outputs show themselves; and a number below about 1e-33 whose
-// lowest part would need bits below the smallest bfloat16 number marks its tile (one instruction per two values).
+// 140 on 128 x 128, 113 on 128 x 256; float32 on 32 x 128 145; six of the products, which lack precision, 95).
+// Operands without three such parts: a number below about 1e-33 whose lowest part would need bits below the smallest
+// bfloat16 number marks its tile while it is split (one instruction per two values), and the tile is worked out once more with
+// both operands 2^24 times as large.  An infinity's remainder is not a number, which leaves no finite number in
+// the second accumulator: such outputs, and what overflows only because of the 2^48, are worked out one by one (redo).
+// (128->128 @28x28, N=64: twice the time with a filter of 1e-37 in every tile, as much with one of infinities; 20 times
+// when such tiles were worked out again one output at a time.)
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
 // Two neighbours of a row of K as words of the three planes.  `lost` gets a bit in its lower half where a value has more
-// bits than these hold.
+// bits than these hold.  LARGE: of 2^24 times the values, which always do, but for those of 2^104 and more.
+template <bool LARGE>
 __device__ __forceinline__ void split2(float x0, float x1, uint32_t &hi, uint32_t &mid, uint32_t &lo, uint32_t &lost) {
     typedef float f2 __attribute__((ext_vector_type(2)));
+    if (LARGE) { x0 *= 0x1p24f; x1 *= 0x1p24f; }
     const uint32_t u0 = __builtin_bit_cast(uint32_t, x0), u1 = __builtin_bit_cast(uint32_t, x1);
     const float r0 = x0 - __builtin_bit_cast(float, u0 & 0xffff0000u), r1 = x1 - __builtin_bit_cast(float, u1 & 0xffff0000u);
     mid = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{r0, r1}, bf2));
@@ -356,35 +361,51 @@ __device__ __forceinline__ void split2(float x0, float x1, uint32_t &hi, uint32_
     const uint32_t v0 = __builtin_bit_cast(uint32_t, l0), v1 = __builtin_bit_cast(uint32_t, l1);
     hi = __builtin_amdgcn_perm(u1, u0, 0x07060302);
     lo = __builtin_amdgcn_perm(v1, v0, 0x07060302);
-    lost |= v0 | v1;
+    if (!LARGE) lost |= v0 | v1;
 }
 // The eight products of two split floats: part of the weight, part of the input (0 the highest).
 constexpr int kParts = 8, kLargest = 2;  // kLargest: which is the product of the highest parts
 constexpr int kPartA[kParts] = {0, 1, 0, 1, 0, 2, 1, 2}, kPartB[kParts] = {1, 0, 0, 1, 2, 0, 2, 1};
 
-// The end of a tile on split operands: outputs that are no finite number, or all of them where a value was
-// `lost`, once more in float32, one multiply-add after the other in the order of K.  flags: a word of LDS per wavefront that
-// nobody reads any more.  Not a path that ordinary tensors take: nothing here is tuned.
-template <int BM, int BN, int KK>
-__device__ __forceinline__ void redo(const DenseArgs &a, int m0, long long q0, bool lost, bool not_finite, uint32_t *flags) {
-    const int tid = threadIdx.x;
-    const uint32_t mine = (__any(lost) ? 1u : 0u) | (__any(not_finite) ? 2u : 0u);
-    if ((tid & 63) == 0) flags[tid >> 6] = mine;
+// The lane's number without the register it came in (the tile of 128 x 256 has none to keep it in).
+__device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)); }
+
+// What any thread of a workgroup of eight wavefronts says, as bits.  flags: 8 words of LDS that nobody reads any more.
+__device__ __forceinline__ uint32_t any_of(bool bit0, bool bit1, uint32_t *flags, int wave) {
+    const uint32_t mine = (__any(bit0) ? 1u : 0u) | (__any(bit1) ? 2u : 0u);
+    if (lane_id() == 0) flags[wave] = mine;
     __syncthreads();
     uint32_t all = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) all |= flags[i];
-    if (__builtin_expect(all == 0, 1)) return;
+    return all;
+}
+
+// An output of a tile on split operands from its two sums: infinite, to be worked out again, where their sum is no finite number
+// but the products of the highest parts add up to one or to an infinity.  (Where they do not, an operand is no number, or
+// infinities cancel or meet zeros, and so it is in float32.  LARGE: or the 2^48 made the infinities.)
+template <bool LARGE>
+__device__ __forceinline__ float settle(float big, float small, float bias, bool &again) {
+    const float both = big + small;
+    const bool good = (fabsf(both) <= 3.402823466e38f) | (!LARGE & (big != big));
+    again |= !good;
+    return good ? both * (LARGE ? 0x1p-48f : 1.f) + bias : __builtin_inff();
+}
+
+// The infinite outputs of a tile once more in float32, one multiply-add after the other in the order of K.  Not a path that
+// ordinary tensors take: nothing here is tuned.
+template <int BM, int BN, int KK>
+__device__ __forceinline__ void redo(const DenseArgs &a, int m0, long long q0, int wave) {
     __threadfence();  // the outputs are read back, and written again, by other wavefronts than the first time
     __syncthreads();
-    for (int i = tid; i < BM * BN; i += 512) {
+    for (int i = 64 * wave + lane_id(); i < BM * BN; i += 512) {
         const int o = m0 + i / BN;
         const long long q = q0 + i % BN;
         if (o >= a.Cout || q >= a.NP) continue;
         const long long n = q / a.P;
         const int p = (int)(q - n * a.P), ho = p / a.Wo, wo = p - ho * a.Wo;
         float *y = a.Y + ((size_t)n * a.Cout + o) * a.P + p;
-        if (!(all & 1) && fabsf(__builtin_nontemporal_load(y)) <= 3.402823466e38f) continue;
+        if (fabsf(__builtin_nontemporal_load(y)) != __builtin_inff()) continue;
         const float *x = a.X + (size_t)n * a.Cin * a.Pin, *w = a.Wt + (size_t)o * a.K;
         float sum = 0.f;
         for (int c = 0; c < a.Cin; ++c, x += a.Pin, w += KK) {
@@ -397,24 +418,18 @@ __device__ __forceinline__ void redo(const DenseArgs &a, int m0, long long q0, b
     }
 }
 
-// NPT: staged positions per thread.
-template <int BM, int BN, int NPT>
-__global__ void __launch_bounds__(512, 2) k_dense3(const DenseArgs a) {
+// A tile; the bits of any_of: a value was lost, an output has to be worked out again.  NPT: staged positions per thread.
+template <int BM, int BN, int NPT, bool LARGE>
+__device__ __forceinline__ uint32_t dense3_tile(const DenseArgs &a, int m0, long long q0, u4 *lds3, int wave) {
     constexpr int NT = 512, WM = 2, WN = 4;   // wavefronts along the channels and the pixels
     constexpr int TM = BM / 32 / WM, TN = BN / 32 / WN;
     constexpr int CH = 8;                     // channels per step
     constexpr int LDA = BM + 1;               // the odd pitch spreads the taps of a row over the banks
     constexpr int NA = (BM * 9 + NT - 1) / NT;  // (row, tap) pairs per thread
     constexpr int NI = NA + NPT;              // items of 8 channels per thread and step
-    extern __shared__ u4 lds3[];
-    const int id = blockIdx.x;
-    const int logical = (id % a.xcds) * a.wg_per_xcd + id / a.xcds;
-    if (logical >= a.total_wgs) return;
-    // consecutive logical ids share the pixel tile (the large operand) and differ in the channel tile
-    const int ntile = logical / a.mt, mtile = logical - ntile * a.mt;
-    const int m0 = mtile * BM;
-    const long long q0 = (long long)ntile * BN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int lane = lane_id();
+    if (LARGE) asm volatile("" : "+v"(lane));  // nothing is kept in registers for this from the first time
+    const int tid = 64 * wave + lane;
     const int wm = wave / WN, wn = wave % WN;
     const int h = lane >> 5, l32 = lane & 31;
     const int S = a.stride;
@@ -507,7 +522,7 @@ __global__ void __launch_bounds__(512, 2) k_dense3(const DenseArgs a) {
             float x0 = x[i][2 * part], x1 = x[i][2 * part + 1];
             if (i >= NA && poff[max(i - NA, 0)] < 0) x0 = x1 = 0.f;
             uint32_t h3, m3, l3;
-            split2(x0, x1, h3, m3, l3, lost);
+            split2<LARGE>(x0, x1, h3, m3, l3, lost);
             plane[0][part] = h3;
             plane[1][part] = m3;
             plane[2][part] = l3;
@@ -599,10 +614,12 @@ __global__ void __launch_bounds__(512, 2) k_dense3(const DenseArgs a) {
     }
     step(no, cur, next, c0);
     // ---- epilogue: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32 ----
-    bool not_finite = false;
+    bool again = false;
+    int l = lane_id();
+    asm volatile("" : "+v"(l));  // (the columns are worked out again: the main loop has no register for them)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-        const int e = (wn * TN + j) * 32 + l32;
+        const int e = (wn * TN + j) * 32 + (l & 31);
         if (q0 + e >= a.NP) continue;
         const int dn = (int)((p0 + (uint32_t)e) / (uint32_t)a.P);
         float *ybase = a.Y + (size_t)(n0 + dn) * a.Cout * a.P + (p0 + (uint32_t)e - (uint32_t)dn * (uint32_t)a.P);
@@ -610,34 +627,47 @@ __global__ void __launch_bounds__(512, 2) k_dense3(const DenseArgs a) {
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int o = m0 + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-                const float both = big[i][j][r] + (kTwo ? small[i][j][r] + small2[0][0][r] : small[i][j][r]);
-                not_finite |= !(fabsf(both) <= 3.402823466e38f);
-                if (o < a.Cout) ybase[(size_t)o * a.P] = both + (a.bias ? a.bias[o] : 0.f);
+                const int o = m0 + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
+                const float low = kTwo ? small[i][j][r] + small2[0][0][r] : small[i][j][r];
+                if (o < a.Cout) ybase[(size_t)o * a.P] = settle<LARGE>(big[i][j][r], low, a.bias ? a.bias[o] : 0.f, again);
             }
     }
-    redo<BM, BN, 9>(a, m0, q0, (lost & 0xffff) != 0, not_finite, reinterpret_cast<uint32_t *>(lds3));
+    return any_of((lost & 0xffff) != 0, again, reinterpret_cast<uint32_t *>(Zs + LDA), wave);
+}
+
+template <int BM, int BN, int NPT>
+__global__ void __launch_bounds__(512, 2) k_dense3(const DenseArgs a) {
+    extern __shared__ u4 lds3[];
+    const int id = blockIdx.x;
+    const int logical = (id % a.xcds) * a.wg_per_xcd + id / a.xcds;
+    if (logical >= a.total_wgs) return;
+    // consecutive logical ids share the pixel tile (the large operand) and differ in the channel tile
+    const int ntile = logical / a.mt, mtile = logical - ntile * a.mt;
+    const int m0 = mtile * BM;
+    const long long q0 = (long long)ntile * BN;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t what = dense3_tile<BM, BN, NPT, false>(a, m0, q0, lds3, wave);
+    if (__builtin_expect(what & 1, 0)) {
+        __syncthreads();
+        what = dense3_tile<BM, BN, NPT, true>(a, m0, q0, lds3, wave);
+    }
+    if (__builtin_expect(what & 2, 0)) redo<BM, BN, 9>(a, m0, q0, wave);
 }
 
 // 1x1 on split operands: 128 channels x BN pixels, 32 input channels a step.  As k_dense3, but a pixel's words serve one
 // tap, so most of the split work is the input's, and a tile has few steps to cover its first loads and its stores: large
 // layers gain (392->760 @56x57, N=18 342 us in float32, 301 split; 1024->256 @14x14, N=64 79 and 60; 512->512
 // @14x14, N=256 239 and 233), layers of few input channels or few tiles do not (128->64 @56x56, N=32: 25 us, 45 split).
-template <int BN>
-__global__ void __launch_bounds__(512, 2) k_dense1(const DenseArgs a) {
+template <int BN, bool LARGE>
+__device__ __forceinline__ uint32_t dense1_tile(const DenseArgs &a, int m0, long long q0, u4 *lds3, int wave) {
     constexpr int BM = 128, CH = 32, NQ = CH / 8, NT = 512;  // NQ: groups of 8 channels
     constexpr int WN = 4, TM = 2, TN = BN / 32 / WN;   // two wavefronts along the channels, four along the pixels
     constexpr int LDA = BM + 1, LDB = BN + 1, BUF = 3 * NQ * (LDA + LDB);
     constexpr int NB = BN * NQ / NT, NI = 1 + NB;
     static_assert(BM * NQ == NT, "one item of the weights per thread");
-    extern __shared__ u4 lds3[];
-    const int id = blockIdx.x;
-    const int logical = (id % a.xcds) * a.wg_per_xcd + id / a.xcds;
-    if (logical >= a.total_wgs) return;
-    const int ntile = logical / a.mt, mtile = logical - ntile * a.mt;
-    const int m0 = mtile * BM;
-    const long long q0 = (long long)ntile * BN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int lane = lane_id();
+    if (LARGE) asm volatile("" : "+v"(lane));
+    const int tid = 64 * wave + lane;
     const int wm = wave / WN, wn = wave % WN;
     const int h = lane >> 5, l32 = lane & 31;
     u4 *cur = lds3, *next = lds3 + BUF;
@@ -703,7 +733,7 @@ __global__ void __launch_bounds__(512, 2) k_dense1(const DenseArgs a) {
     auto store = [&](int i, int part, u4 *buf) __attribute__((always_inline)) {
         if (part < 4) {
             uint32_t hi, mid, lo;
-            split2(x[i][2 * part], x[i][2 * part + 1], hi, mid, lo, lost);
+            split2<LARGE>(x[i][2 * part], x[i][2 * part + 1], hi, mid, lo, lost);
             plane[0][part] = hi;
             plane[1][part] = mid;
             plane[2][part] = lo;
@@ -775,7 +805,7 @@ __global__ void __launch_bounds__(512, 2) k_dense1(const DenseArgs a) {
         swap();
     }
     step(no, cur, next, c0);
-    bool not_finite = false;
+    bool again = false;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         const int e = (wn * TN + j) * 32 + l32;
@@ -787,12 +817,28 @@ __global__ void __launch_bounds__(512, 2) k_dense1(const DenseArgs a) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int o = m0 + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-                const float both = big[i][j][r] + small[i][j][r];
-                not_finite |= !(fabsf(both) <= 3.402823466e38f);
-                if (o < a.Cout) ybase[(size_t)o * a.P] = both + (a.bias ? a.bias[o] : 0.f);
+                if (o < a.Cout) ybase[(size_t)o * a.P] = settle<LARGE>(big[i][j][r], small[i][j][r], a.bias ? a.bias[o] : 0.f, again);
             }
     }
-    redo<BM, BN, 1>(a, m0, q0, (lost & 0xffff) != 0, not_finite, reinterpret_cast<uint32_t *>(lds3));
+    return any_of((lost & 0xffff) != 0, again, reinterpret_cast<uint32_t *>(lds3), wave);
+}
+
+template <int BN>
+__global__ void __launch_bounds__(512, 2) k_dense1(const DenseArgs a) {
+    extern __shared__ u4 lds3[];
+    const int id = blockIdx.x;
+    const int logical = (id % a.xcds) * a.wg_per_xcd + id / a.xcds;
+    if (logical >= a.total_wgs) return;
+    const int ntile = logical / a.mt, mtile = logical - ntile * a.mt;
+    const int m0 = mtile * 128;
+    const long long q0 = (long long)ntile * BN;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t what = dense1_tile<BN, false>(a, m0, q0, lds3, wave);
+    if (__builtin_expect(what & 1, 0)) {
+        __syncthreads();
+        what = dense1_tile<BN, true>(a, m0, q0, lds3, wave);
+    }
+    if (__builtin_expect(what & 2, 0)) redo<128, BN, 1>(a, m0, q0, wave);
 }
 
 constexpr int BK = 16;
