@@ -381,15 +381,70 @@ __device__ __forceinline__ uint32_t any_of(bool bit0, bool bit1, uint32_t *flags
     return all;
 }
 
-// An output of a tile on split operands from its two sums: infinite, to be worked out again, where their sum is no finite number
-// but the products of the highest parts add up to one or to an infinity.  (Where they do not, an operand is no number, or
-// infinities cancel or meet zeros, and so it is in float32.  LARGE: or the 2^48 made the infinities.)
-template <bool LARGE>
-__device__ __forceinline__ float settle(float big, float small, float bias, bool &again) {
-    const float both = big + small;
-    const bool good = (fabsf(both) <= 3.402823466e38f) | (!LARGE & (big != big));
-    again |= !good;
-    return good ? both * (LARGE ? 0x1p-48f : 1.f) + bias : __builtin_inff();
+// The outputs of a wavefront's tiles on split operands from their two sums: register r of lane l holds row 8*(r/4) +
+// 4*(l/32) + r%4, column l%32.  An output whose sums add up to no finite number is stored as infinite, to be worked out
+// again, and reported, if the products of the highest parts add up to a number or an infinity.  (Where they do not, an operand is
+// no number, or infinities cancel or meet zeros, and so it is in float32.  LARGE: or the 2^48 made the infinities.)
+// The biases are asked for together: one by one, beside their outputs, each waited for its own (416->656 @56x56, N=11 204 us,
+// 178 together; 160->112 @112x112, N=36 212 and 171).
+template <bool LARGE, int BM, int TM, int TN>
+__device__ __forceinline__ bool put(const DenseArgs &a, int m0, long long q0, int n0, uint32_t p0, int wm, int wn,
+                                    const f16v (&big)[TM][TN], f16v (&small)[TM][TN]) {
+    int l = lane_id();
+    asm volatile("" : "+v"(l));  // (the columns are worked out again: the main loop has no register for them)
+    const int o0 = m0 + wm * TM * 32 + 4 * (l >> 5);
+    auto row = [&](int i, int r) { return o0 + 32 * i + 8 * (r >> 2) + (r & 3); };
+    float bias[TM][16], check = 0.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) bias[i][r] = 0.f;
+    if (a.bias) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) bias[i][r] = a.bias[min(row(i, r), a.Cout - 1)];
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                small[i][j][r] += big[i][j][r];
+                check = fmaf(small[i][j][r], 0.f, check);   // no number once one of them is not finite
+            }
+    bool again = false;
+    if (__builtin_expect(__any(check != check), 0)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const bool good = (fabsf(small[i][j][r]) <= 3.402823466e38f) | (!LARGE & (big[i][j][r] != big[i][j][r]));
+                    again |= !good;
+                    small[i][j][r] = good ? small[i][j][r] : __builtin_inff();
+                }
+    }
+    auto store = [&](auto whole) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int e = (wn * TN + j) * 32 + (l & 31);
+            if (q0 + e >= a.NP) continue;
+            const int dn = (int)((p0 + (uint32_t)e) / (uint32_t)a.P);
+            float *y = a.Y + (size_t)(n0 + dn) * a.Cout * a.P + (p0 + (uint32_t)e - (uint32_t)dn * (uint32_t)a.P);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (decltype(whole)::value || row(i, r) < a.Cout)
+                        y[(size_t)row(i, r) * a.P] = small[i][j][r] * (LARGE ? 0x1p-48f : 1.f) + bias[i][r];
+        }
+    };
+    if (m0 + BM <= a.Cout) store(std::integral_constant<bool, true>{});
+    else store(std::integral_constant<bool, false>{});
+    return again;
 }
 
 // The infinite outputs of a tile once more in float32, one multiply-add after the other in the order of K.  Not a path that
@@ -613,25 +668,10 @@ __device__ __forceinline__ uint32_t dense3_tile(const DenseArgs &a, int m0, long
         swap();
     }
     step(no, cur, next, c0);
-    // ---- epilogue: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32 ----
-    bool again = false;
-    int l = lane_id();
-    asm volatile("" : "+v"(l));  // (the columns are worked out again: the main loop has no register for them)
+    if (kTwo)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int e = (wn * TN + j) * 32 + (l & 31);
-        if (q0 + e >= a.NP) continue;
-        const int dn = (int)((p0 + (uint32_t)e) / (uint32_t)a.P);
-        float *ybase = a.Y + (size_t)(n0 + dn) * a.Cout * a.P + (p0 + (uint32_t)e - (uint32_t)dn * (uint32_t)a.P);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int o = m0 + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
-                const float low = kTwo ? small[i][j][r] + small2[0][0][r] : small[i][j][r];
-                if (o < a.Cout) ybase[(size_t)o * a.P] = settle<LARGE>(big[i][j][r], low, a.bias ? a.bias[o] : 0.f, again);
-            }
-    }
+        for (int r = 0; r < 16; ++r) small[0][0][r] += small2[0][0][r];
+    const bool again = put<LARGE, BM>(a, m0, q0, n0, p0, wm, wn, big, small);
     return any_of((lost & 0xffff) != 0, again, reinterpret_cast<uint32_t *>(Zs + LDA), wave);
 }
 
@@ -665,10 +705,9 @@ __device__ __forceinline__ uint32_t dense1_tile(const DenseArgs &a, int m0, long
     constexpr int LDA = BM + 1, LDB = BN + 1, BUF = 3 * NQ * (LDA + LDB);
     constexpr int NB = BN * NQ / NT, NI = 1 + NB;
     static_assert(BM * NQ == NT, "one item of the weights per thread");
-    int lane = lane_id();
-    if (LARGE) asm volatile("" : "+v"(lane));
-    const int tid = 64 * wave + lane;
-    const int wm = wave / WN, wn = wave % WN;
+    int tid = threadIdx.x;  // (registers are left here: lane_id() costs 2 to 6 %)
+    if (LARGE) asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wm = (tid >> 6) / WN, wn = (tid >> 6) % WN;
     const int h = lane >> 5, l32 = lane & 31;
     u4 *cur = lds3, *next = lds3 + BUF;
     const int n0 = q0 >> 32 ? (int)(q0 / a.P) : (int)((uint32_t)q0 / (uint32_t)a.P);
@@ -805,21 +844,7 @@ __device__ __forceinline__ uint32_t dense1_tile(const DenseArgs &a, int m0, long
         swap();
     }
     step(no, cur, next, c0);
-    bool again = false;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int e = (wn * TN + j) * 32 + l32;
-        if (q0 + e >= a.NP) continue;
-        const int dn = (int)((p0 + (uint32_t)e) / (uint32_t)a.P);
-        float *ybase = a.Y + (size_t)(n0 + dn) * a.Cout * a.P + (p0 + (uint32_t)e - (uint32_t)dn * (uint32_t)a.P);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int o = m0 + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-                if (o < a.Cout) ybase[(size_t)o * a.P] = settle<LARGE>(big[i][j][r], small[i][j][r], a.bias ? a.bias[o] : 0.f, again);
-            }
-    }
+    const bool again = put<LARGE, BM>(a, m0, q0, n0, p0, wm, wn, big, small);
     return any_of((lost & 0xffff) != 0, again, reinterpret_cast<uint32_t *>(lds3), wave);
 }
 
