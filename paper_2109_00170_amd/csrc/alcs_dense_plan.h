@@ -16,15 +16,16 @@ struct DensePlan {
 
 // Tile shapes, which numbers of staged positions (3x3) they take, and what their tiles cost: microseconds of a tile's first
 // loads and its stores, of a step (3x3: 8 input channels; 1x1: 32 on split operands, 16 in float32) and of a step's
-// staged position.  Fits over 90 layers each of 16 to 1024 channels on 7x7 to 112x151 images, every shape on every layer:
-// rms error of a shape 4 to 11 %, and the shape they pick is about 1 % slower than the fastest in the mean (at most 15 %).
-// 3x3: split operands where their tiles divide well over the compute units (128->128 @28x28, N=64: 113 us on 128 x
-// 256, 140 and 174 on the smaller ones, float32 145 to 164), float32 on 32 x 128 on most others.  Several float32 workgroups
+// staged position.  Fits over 90 layers each of 16 to 1024 channels on 7x7 to 112x151 images, with biases, every shape on
+// every layer: rms error of a shape 4 to 14 %, and the shape they pick is 0.9 (3x3) and 0.2 % (1x1) slower than the fastest in
+// the mean, at most 19 and 10.
+// 3x3: split operands where their tiles divide well over the compute units (128->128 @28x28, N=64: 109 us on 128 x
+// 256, 136 and 172 on the smaller ones, float32 148 to 165), float32 on 32 x 128 on most others.  Several float32 workgroups
 // share a compute unit and cover each other's first loads and stores (the second triple: more than one round of them),
-// 64->64 @56x56, N=64: 141 us on 32 x 128, 158 split.  The number of positions at which the larger float32 tiles end
+// 64->64 @56x56, N=64: 141 us on 32 x 128, 156 split.  The number of positions at which the larger float32 tiles end
 // is where another shape was always the cheaper one.
-// 1x1: split operands from some hundred input channels on (1024->256 @14x14, N=64: 60 us split, 79 in float32; 256->64
-// @56x56: 133 and 70).  (The second triple: more than one round.)
+// 1x1: split operands from some hundred input channels on, or many outputs (1024->256 @14x14, N=64: 59 us split, 80 in
+// float32; 138->412 @28x28, N=205 220 and 261; 256->64 @56x56 120 and 76).  (The second triple: more than one round.)
 struct DenseShape {
     int bm, bn;
     bool split;
@@ -32,16 +33,16 @@ struct DenseShape {
     double tile, step, pos;
     double tile2, step2, pos2;
 };
-static const DenseShape kShapes3x3[] = {{128, 256, true, 0, 512, 10.0, 5.80, 0.0001, 0, 0, 0},
-                                        {128, 128, true, 0, 1024, 7.3, 3.60, 0.0005, 0, 0, 0},
-                                        {64, 128, true, 0, 1024, 5.0, 2.07, 0.0008, 0, 0, 0},
-                                        {128, 128, false, 512, 1024, 10.5, 4.32, 0.0005, 0, 0, 0},
+static const DenseShape kShapes3x3[] = {{128, 256, true, 0, 512, 9.0, 5.65, 0.0002, 0, 0, 0},
+                                        {128, 128, true, 0, 1024, 6.8, 3.60, 0.0005, 0, 0, 0},
+                                        {64, 128, true, 0, 1024, 4.4, 2.07, 0.0008, 0, 0, 0},
+                                        {128, 128, false, 512, 1024, 12.0, 4.32, 0.0005, 0, 0, 0},
                                         {64, 128, false, 0, 512, 5.0, 2.06, 0.0011, 3.0, 2.0, 0.0008},
                                         {32, 128, false, 0, 1024, 3.0, 1.05, 0.0008, 1.5, 1.05, 0.0005}};
-static const DenseShape kShapes1x1[] = {{128, 256, true, -1, 0, 9.5, 3.0, 0, 9.2, 3.2, 0},
-                                        {128, 128, true, -1, 0, 6.8, 1.65, 0, 5.5, 1.8, 0},
-                                        {64, 64, false, -1, 0, 4.4, 0.43, 0, 0.35, 0.33, 0},
-                                        {32, 128, false, -1, 0, 4.4, 0.51, 0, 0.32, 0.387, 0}};
+static const DenseShape kShapes1x1[] = {{128, 256, true, -1, 0, 6.3, 2.80, 0, 4.9, 3.30, 0},
+                                        {128, 128, true, -1, 0, 4.9, 1.68, 0, 3.4, 1.85, 0},
+                                        {64, 64, false, -1, 0, 4.6, 0.43, 0, 0.39, 0.348, 0},
+                                        {32, 128, false, -1, 0, 4.7, 0.51, 0, 0.42, 0.397, 0}};
 inline int dense_npt(const DenseShape &sh, int kernel, long long npos) {
     return kernel == 1 ? 1 : sh.split ? (int)(npos + 511) / 512 : npos <= 512 ? 2 : npos <= 768 ? 3 : 4;
 }
@@ -59,7 +60,7 @@ inline double launch_time(const DenseShape &sh, int kernel, int Cin, long long n
         if (rounds == 1) return sh.tile + sh.step * steps;
         // (float32: eight workgroups share a compute unit, there are no rounds)
         return sh.split ? rounds * (sh.tile2 + sh.step2 * steps)
-                        : 5.2 + (double)tiles / cus * (sh.tile2 + sh.step2 * steps);
+                        : 5.6 + (double)tiles / cus * (sh.tile2 + sh.step2 * steps);
     }
     const int steps = (Cin + 7) / 8;
     const bool shared = sh.step2 > 0 && rounds > 1 && 2 * dense_lds(sh, kernel, npos) <= 160 * 1024;

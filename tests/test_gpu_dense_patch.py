@@ -46,7 +46,8 @@ TILES = [
     (1, 1, 1001, 250, 14, 14, 64), (1, 1, 992, 255, 13, 15, 64), (1, 1, 993, 256, 1, 1, 20000),  # 128 x 128, and images of one pixel
     # tiles that none of these takes
     (1, 2, 10, 9, 10, 30, 219),                             # 1x1, 32 x 128
-    (3, 2, 33, 105, 55, 33, 59), (3, 2, 13, 71, 71, 84, 19),   # float32, 128 x 128: 700 and 1020 positions
+    (3, 2, 73, 204, 13, 52, 82), (3, 2, 41, 94, 11, 99, 77),   # float32, 128 x 128: 742 and 1010 positions
+    (3, 2, 33, 105, 55, 33, 59), (3, 2, 13, 71, 71, 84, 19),   # split, 64 x 128: 700 and 1020
     (3, 1, 10, 33, 40, 8, 166),                             # float32, 64 x 128
     (3, 1, 133, 39, 81, 57, 4), (3, 2, 10, 35, 12, 57, 95),   # split, 64 x 128: 472 and 826 positions
     (3, 1, 9, 118, 19, 70, 19), (3, 1, 20, 419, 25, 72, 4),   # split, 128 x 128: 504 and 518
