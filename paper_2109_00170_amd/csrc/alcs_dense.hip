@@ -42,7 +42,7 @@ struct DenseArgs {
 // What bounds a launch is the matrix pipe (3x3: 52 to 61 % of a single launch's cycles busy, start and
 // drain included; 64 % of its peak in a stream of launches) and, on few tiles, how evenly they divide over
 // the compute units (the launcher picks the tile for that).  3x3, N=64, against the patch matrix
-// gathered word by word: 128->128 @28x28 260 -> 147 us (k_dense3 113), 512->512 @7x7 577 -> 176 us,
+// gathered word by word: 128->128 @28x28 260 -> 147 us (k_dense3 106), 512->512 @7x7 577 -> 176 us,
 // 40->23 @112x86 424 -> 175 us; 1x1 1024->256 @14x14 101 -> 80 us.  1x1 layers with few
 // output channels wait for their input: 16 channels a step leave room for 8 workgroups a compute unit
 // (256->64 @56x56, N=40: 59.5 -> 50 us against 32 channels and 3 workgroups).
@@ -337,7 +337,7 @@ __global__ void __launch_bounds__(256, KK == 1 ? 4 : BM == 128 ? 1 : 2) k_dense(
 // 0-31 one tap and lanes 32-63 the next - is one 16-byte read.  Nine taps are four and a half pairs: the tenth reads
 // zeros.  What bounds a launch is the split and the matrix instructions in turn: vector instructions do not overlap with
 // the matrix instructions of the same SIMD, so the larger the tile the better (128->128 @28x28, N=64: 174 us on 64 x 128,
-// 140 on 128 x 128, 113 on 128 x 256; float32 on 32 x 128 145; six of the products, which lack precision, 95).
+// 140 on 128 x 128, 106 on 128 x 256; float32 on 32 x 128 146; six of the products, which lack precision, 95).
 // Operands without three such parts: a number below about 1e-33 whose lowest part would need bits below the smallest
 // bfloat16 number marks its tile while it is split (one instruction per two values), and the tile is worked out once more with
 // both operands 2^24 times as large.  An infinity's remainder is not a number, which leaves no finite number in
@@ -696,8 +696,8 @@ __global__ void __launch_bounds__(512, 2) k_dense3(const DenseArgs a) {
 
 // 1x1 on split operands: 128 channels x BN pixels, 32 input channels a step.  As k_dense3, but a pixel's words serve one
 // tap, so most of the split work is the input's, and a tile has few steps to cover its first loads and its stores: large
-// layers gain (392->760 @56x57, N=18 342 us in float32, 301 split; 1024->256 @14x14, N=64 79 and 60; 512->512
-// @14x14, N=256 239 and 233), layers of few input channels or few tiles do not (128->64 @56x56, N=32: 25 us, 45 split).
+// layers gain (392->760 @56x57, N=18 369 us in float32, 281 split; 1024->256 @14x14, N=64 80 and 59; 512->512
+// @14x14, N=256 256 and 223), layers of few input channels or few tiles do not (128->64 @56x56, N=32: 26 us, 36 split).
 template <int BN, bool LARGE>
 __device__ __forceinline__ uint32_t dense1_tile(const DenseArgs &a, int m0, long long q0, u4 *lds3, int wave) {
     constexpr int BM = 128, CH = 32, NQ = CH / 8, NT = 512;  // NQ: groups of 8 channels
