@@ -69,14 +69,16 @@ struct LayerDev {
 struct Spread {
     int count, rank, fill;
 };
+// (64 entries at a time, one per lane: a search by halves is a chain of cold loads, four for 13 layers)
 __device__ __forceinline__ int layer_of(const Spread *sp, int n, int wg, int Spread::*what) {
-    int lo = 0, hi = n;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (sp[mid].*what <= wg) lo = mid;
-        else hi = mid;
+    const int lane = threadIdx.x & 63;
+    int before = 0;
+    for (int i0 = 0; i0 < n; i0 += 64) {
+        const int here = __popcll(__ballot(i0 + lane < n && sp[min(i0 + lane, n - 1)].*what <= wg));
+        before += here;
+        if (here < 64) break;
     }
-    return lo;
+    return __builtin_amdgcn_readfirstlane(max(before, 1) - 1);
 }
 
 // The layer's scalars: longest group, kept blocks, groups per wavefront, padded columns, longest
@@ -96,7 +98,7 @@ __device__ __forceinline__ int lower_bound_dev(const int32_t *a, int lo, int hi,
 // One wavefront per (group, chunk).
 __global__ void __launch_bounds__(64) k_ld_count(const LayerDev *layers, const Spread *sp, int n) {
     const int li = layer_of(sp, n, blockIdx.x, &Spread::count);
-    const LayerDev &L = layers[li];
+    const LayerDev L = layers[li];
     const int lane = threadIdx.x, i = blockIdx.x - sp[li].count;
     const int g = i / L.nchunks, ch = i - g * L.nchunks;
     const int c_lo = ch * L.KC, c_hi = min(L.Cin, c_lo + L.KC);
@@ -105,6 +107,7 @@ __global__ void __launch_bounds__(64) k_ld_count(const LayerDev *layers, const S
         bool torn = false;
         if (L.mask) {
             const uint8_t *m = L.mask + (size_t)g * L.K;
+#pragma unroll 4
             for (int c0 = c_lo * L.kk; c0 < c_hi * L.kk; c0 += 64) {
                 const int col = c0 + lane;
                 const bool in = col < c_hi * L.kk;
@@ -149,26 +152,40 @@ __global__ void __launch_bounds__(64) k_ld_count(const LayerDev *layers, const S
 }
 
 // order[rank] = g with rank = groups that are longer, or as long with a lower index (the stable
-// descending sort of the host).
+// descending sort of the host).  A workgroup ranks 64 groups, every wavefront against a quarter of a block of 1024
+// lengths, four to an LDS read: 13 layers of up to 256 groups 5.6 us, with one thread per group and one length at a time 18.
+constexpr int kRankGroups = 64;
 __global__ void __launch_bounds__(256) k_ld_rank(const LayerDev *layers, const Spread *sp, int n) {
-    __shared__ int len[1024];
+    __shared__ alignas(16) int len[1024];
+    __shared__ int part[4][64];
     const int li = layer_of(sp, n, blockIdx.x, &Spread::rank);
-    const LayerDev &L = layers[li];
+    const LayerDev L = layers[li];
     auto length = [&](int g) {
         int s = 0;
         for (int ch = 0; ch < L.nchunks; ++ch) s += L.cnt[(size_t)g * L.nchunks + ch];
         return s;
     };
-    const int g = (blockIdx.x - sp[li].rank) * 256 + threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g = (blockIdx.x - sp[li].rank) * kRankGroups + lane;
     const int mine = g < L.G ? length(g) : 0;
     int rank = 0;
     for (int h0 = 0; h0 < L.G; h0 += 1024) {
+        const int here = min(1024, L.G - h0), quarter = ((here + 3) / 4 + 3) & ~3;
         __syncthreads();
-        for (int i = threadIdx.x; i < min(1024, L.G - h0); i += 256) len[i] = length(h0 + i);
+        for (int i = threadIdx.x; i < 1024; i += 256) len[i] = i < here ? length(h0 + i) : -1;  // (no group is shorter than 0)
         __syncthreads();
-        for (int i = 0; i < min(1024, L.G - h0); ++i) rank += (len[i] > mine) || (len[i] == mine && h0 + i < g);
+        const int first = wave * quarter, end = min(1024, first + quarter);
+        for (int i = first; i < end; i += 4) {
+            const int4 l = *reinterpret_cast<const int4 *>(len + i);
+            rank += (l.x > mine) || (l.x == mine && h0 + i < g);
+            rank += (l.y > mine) || (l.y == mine && h0 + i + 1 < g);
+            rank += (l.z > mine) || (l.z == mine && h0 + i + 2 < g);
+            rank += (l.w > mine) || (l.w == mine && h0 + i + 3 < g);
+        }
     }
-    if (g < L.G) L.order[rank] = g;
+    part[wave][lane] = rank;
+    __syncthreads();
+    if (wave == 0 && g < L.G) L.order[part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane]] = g;
 }
 
 // Inclusive scan over a workgroup of 1024 threads.
@@ -182,16 +199,17 @@ __device__ __forceinline__ long long scan_1024(long long v, long long *part) {
     __syncthreads();
     if (lane == 63) part[wave] = v;
     __syncthreads();
-    long long before = 0;
-    for (int w = 0; w < wave; ++w) before += part[w];
-    return v + before;
+    long long before = lane < wave ? part[lane & 15] : 0;  // (16 wavefronts: lanes 0 to 14 at most)
+#pragma unroll
+    for (int d = 8; d; d >>= 1) before += __shfl_xor(before, d);
+    return v + __shfl(before, 0);
 }
 
 // One workgroup per layer.
 __global__ void __launch_bounds__(1024) k_ld_plan(const LayerDev *layers) {
     __shared__ long long part[16], carry, carry2;
     __shared__ int longest;
-    const LayerDev &L = layers[blockIdx.x];
+    const LayerDev L = layers[blockIdx.x];  // (a copy: the stores below could be to the table, for all the compiler knows)
     const int tid = threadIdx.x;
     if (tid == 0) { carry = 0; longest = 0; L.rp[0] = 0; }
     __syncthreads();
@@ -260,30 +278,48 @@ __global__ void __launch_bounds__(1024) k_ld_plan(const LayerDev *layers) {
     }
 }
 
-// One workgroup per (bundle, chunk, slot), and one per layer for the spare run behind the last segment.  A
-// workgroup places its slot's columns 256 at a time, a chain of round trips that only more workgroups shorten:
-// 2048->1000, V=8, 90 % sparse takes 127 us to pack, 239 with the four slots of a bundle one after the other.  (All of
-// a column's values loaded ahead of the first store: 141, and 218 -> 265 for 4096->4096.)
+// One workgroup per (bundle, chunk, slot), and one per layer for the spare run behind the last segment.  A workgroup
+// first lists its slot's kept columns and their places in LDS, 1024 columns of the shape at a time, all flags of a turn
+// requested together; then a thread per kept column moves its values, four rows and 16 bytes a store.  What such a small
+// launch waits for besides memory is its own code, each line of it fetched cold, and its address arithmetic: the same work
+// with four columns' code side by side took as long as one column at a time (41.5 and 43.7 us for the 13 layers of
+// MobileNetV1, 30 % kept, half of it for the padding's divisions); this takes 25.5.
+constexpr int kFillTurn = 4;
+typedef float fl4 __attribute__((ext_vector_type(4)));
 __global__ void __launch_bounds__(256) k_ld_fill(const LayerDev *layers, const Spread *sp, int n) {
-    __shared__ int wave_kept[4], wave_even[4], red[4];
+    __shared__ int wave_kept[kFillTurn][4], wave_even[kFillTurn][4], red[4];
+    __shared__ int list_col[256 * kFillTurn], list_at[256 * kFillTurn];
     const int li = layer_of(sp, n, blockIdx.x, &Spread::fill);
-    const LayerDev &L = layers[li];
+    const LayerDev L = layers[li];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int GS = L.GS, kk = L.kk, V = L.V, place = blockIdx.x - sp[li].fill;
-    const int si = place / GS, s = place - si * GS;
-    auto put_pad = [&](long long col, int s, int c0, int which) {
-        for (int q = 0; q < L.planes; ++q)
-            for (int i = 0; i < L.VV; ++i) L.o_w[(size_t)q * L.wplane + layout_w_index(GS, L.VV, col, s, i)] = 0.f;
-        const size_t oi = layout_off_index(GS, col, s);
-        for (int tb = 0; tb < L.noff; ++tb) L.o_off[(size_t)tb * L.offlen + oi] = layout_pad_off(c0, L.KC, L.k, tb, GS, which);
+    const int kk = L.kk, V = L.V, GS = L.GS, place = blockIdx.x - sp[li].fill;
+    const int gsh = GS == 4 ? 2 : GS == 2 ? 1 : 0;
+    const int si = place >> gsh, s = place & (GS - 1);
+    // layout_w_index of row 0 and layout_off_index, by shifts (both fit 31 bits, the host has checked)
+    auto w_index = [&](int col, int s) {
+        const int c = col & 15, cs = 4 - gsh;  // 16 / GS columns to a register
+        return L.VV < 4 ? col * L.VV : (((col & ~15) * 4) << gsh) + (c >> cs) * 64 + s * (64 >> gsh) + (c & ((1 << cs) - 1)) * 4;
+    };
+    auto off_index = [&](int col, int s) { return ((col & ~15) << gsh) + s * 16 + (col & 15); };
+    auto put_pad = [&](int col, int s, int c0, int which) {
+        float *w = L.o_w + w_index(col, s);
+        for (int q = 0; q < L.planes; ++q, w += L.wplane) {
+            if (L.VV == 4) *reinterpret_cast<fl4 *>(w) = fl4{0.f, 0.f, 0.f, 0.f};
+            else
+                for (int i = 0; i < L.VV; ++i) w[i] = 0.f;
+        }
+        int32_t *o = L.o_off + off_index(col, s);
+        for (int tb = 0; tb < L.noff; ++tb, o += L.offlen) *o = layout_pad_off(c0, L.KC, L.k, tb, GS, which);
     };
     if (si == L.nbundles * L.nchunks) {
-        for (int i = tid; i < (int)(L.ncol - L.used) * GS; i += 256) put_pad(L.used + i / GS, i % GS, 0, 0);
-        for (int g = tid; g <= L.G; g += 256) L.o_rp[g] = L.rp[g];
-        for (int g = tid; g < L.G; g += 256) L.o_order[g] = L.order[g];
+        for (int i = tid; i < (int)(L.ncol - L.used) << gsh; i += 256) put_pad((int)L.used + (i >> gsh), i & (GS - 1), 0, 0);
+        for (int g = tid; g <= L.G; g += 256) {
+            L.o_rp[g] = L.rp[g];
+            if (g < L.G) L.o_order[g] = L.order[g];
+        }
         return;
     }
-    const int b = si / L.nchunks, ch = si - b * L.nchunks;
+    const int b = L.nchunks == 1 ? si : si / L.nchunks, ch = si - b * L.nchunks;
     const int c0 = ch * L.KC, c_lo = c0 * kk, c_hi = min(L.Cin, c0 + L.KC) * kk;
     const Work wk = L.work[si];
     const int span = (wk.cnt + kSegAlign - 1) / kSegAlign * kSegAlign;
@@ -295,8 +331,9 @@ __global__ void __launch_bounds__(256) k_ld_fill(const LayerDev *layers, const S
     // a slot's columns: `front` from the start, `back` right-aligned at the end (with several groups per
     // wavefront: even slots take even channels to the front and odd ones to the back, odd slots the
     // other way round)
+    auto group_of = [&](int s) { return s == 0 ? wk.group[0] : s == 1 ? wk.group[1] : s == 2 ? wk.group[2] : wk.group[3]; };
     auto shape_of = [&](int s, int &kept, int &front, int &back) {
-        const int g = wk.group[s];
+        const int g = group_of(s);
         kept = g >= 0 ? L.cnt[(size_t)g * L.nchunks + ch] : 0;
         front = kept;
         back = 0;
@@ -306,78 +343,14 @@ __global__ void __launch_bounds__(256) k_ld_fill(const LayerDev *layers, const S
             back = kept - front;
         }
     };
-    const int g = wk.group[s];
-    int kept, front, back;
+    const int g = group_of(s);
+    int kept, front, back, mk = 0, mf = 0, mb = 0;
+    const bool mate = GS > 1 && group_of(s ^ 1) >= 0;
     shape_of(s, kept, front, back);
-    if (g >= 0) {
-        // first canonical index of the segment: the group's, and the chunks before this one
-        int before = 0;
-        for (int c = tid; c < ch; c += 256) before += L.cnt[(size_t)g * L.nchunks + c];
-        if (ch > 0) {
-#pragma unroll
-            for (int d = 32; d; d >>= 1) before += __shfl_down(before, d);
-            __syncthreads();
-            if (lane == 0) red[wave] = before;
-            __syncthreads();
-            before = red[0] + red[1] + red[2] + red[3];
-        }
-        const long long t0 = (long long)L.rp[g] + before;
-        const int steps = L.W ? c_hi - c_lo : kept;
-        int done = 0, done_even = 0;
-        for (int x0 = 0; x0 < steps; x0 += 256) {
-            const int x = x0 + tid;
-            int col = 0;
-            bool keep;
-            if (L.W) {
-                col = c_lo + x;
-                keep = x < steps && (!L.mask || L.mask[(size_t)g * L.K + col] != 0);
-            } else {
-                keep = x < steps;
-                if (keep) col = L.ci_in[t0 + x];
-            }
-            const bool even = keep && GS > 1 && (col & 1) == 0;
-            const unsigned long long bk = __ballot(keep), be = __ballot(even), below = (1ull << lane) - 1ull;
-            if (lane == 0) { wave_kept[wave] = __popcll(bk); wave_even[wave] = __popcll(be); }
-            __syncthreads();
-            int r = done + __popcll(bk & below), re = done_even + __popcll(be & below);
-            for (int w = 0; w < wave; ++w) { r += wave_kept[w]; re += wave_even[w]; }
-            if (keep) {
-                const long long t = t0 + r;
-                int j = r;
-                if (GS > 1) {
-                    const bool to_front = even == ((s & 1) == 0);
-                    const int rank = even ? re : r - re;
-                    j = to_front ? rank : wk.cnt - back + rank;
-                }
-                const long long at = (long long)wk.start + j;
-                L.o_ci[t] = col;
-                for (int v = 0; v < V; ++v) {
-                    const int row = g * V + v;
-                    const float val = L.W ? (row < L.Cout ? L.W[(size_t)row * L.K + col] : 0.f) : L.va_in[(size_t)t * V + v];
-                    const int q = V < 4 ? 0 : v / 4, i = V < 4 ? v : v % 4;
-                    L.o_va[(size_t)t * V + v] = val;
-                    L.o_w[(size_t)q * L.wplane + layout_w_index(GS, L.VV, at, s, i)] = val;
-                    if (L.o_cw) L.o_cw[(size_t)q * L.cwplane + (size_t)(first_rec + j / 9) * 64 + (j % 9) * 4 + i] = val;
-                }
-                const size_t oi = layout_off_index(GS, at, s);
-                for (int tb = 0; tb < L.noff; ++tb) L.o_off[(size_t)tb * L.offlen + oi] = layout_off_of(col, L.k, tb, GS);
-                if (L.o_cw && j % 9 == 0) {
-                    L.o_csel[first_rec + j / 9] = col / 9 - c0;
-                    for (int q = 0; q < L.planes; ++q)
-                        for (int i = 36; i < 64; ++i) L.o_cw[(size_t)q * L.cwplane + (size_t)(first_rec + j / 9) * 64 + i] = 0.f;
-                }
-            }
-            done += wave_kept[0] + wave_kept[1] + wave_kept[2] + wave_kept[3];
-            done_even += wave_even[0] + wave_even[1] + wave_even[2] + wave_even[3];
-            __syncthreads();
-        }
-    }
+    if (mate) shape_of(s ^ 1, mk, mf, mb);
     // padding: between front and back (one group per wavefront: behind the columns), and the rest
     // of the last run.  With several groups it selects the zero row of the other parity than the
     // partner slot's row at that step.
-    int mk = 0, mf = 0, mb = 0;
-    const bool mate = GS > 1 && wk.group[s ^ 1] >= 0;
-    if (mate) shape_of(s ^ 1, mk, mf, mb);
     const int from = front, to = wk.cnt - back;
     for (int x = tid; x < (to - from) + (span - wk.cnt); x += 256) {
         const int j = x < to - from ? from + x : wk.cnt + (x - (to - from));
@@ -387,7 +360,98 @@ __global__ void __launch_bounds__(256) k_ld_fill(const LayerDev *layers, const S
             const int parity = !mate ? -1 : j < mf ? fp : j >= wk.cnt - mb ? 1 - fp : -1;
             which = parity < 0 ? (s & 1) : (((c0 + L.KC) & 1) == parity ? 1 : 0);
         }
-        put_pad((long long)wk.start + j, s, c0, which);
+        put_pad(wk.start + j, s, c0, which);
+    }
+    if (g < 0) return;
+    // first canonical index of the segment: the group's, and the chunks before this one
+    int before = 0;
+    if (ch > 0) {
+        for (int c = tid; c < ch; c += 256) before += L.cnt[(size_t)g * L.nchunks + c];
+#pragma unroll
+        for (int d = 32; d; d >>= 1) before += __shfl_down(before, d);
+        if (lane == 0) red[wave] = before;
+        __syncthreads();
+        before = red[0] + red[1] + red[2] + red[3];
+    }
+    const long long t0 = (long long)L.rp[g] + before;
+    const int steps = L.W ? c_hi - c_lo : kept;
+    int done = 0, done_even = 0;
+    for (int x0 = 0; x0 < steps; x0 += 256 * kFillTurn) {
+        int col[kFillTurn];
+        bool keep[kFillTurn];
+#pragma unroll
+        for (int u = 0; u < kFillTurn; ++u) {
+            const int x = x0 + u * 256 + tid, xc = min(x, steps - 1);
+            col[u] = L.W ? c_lo + xc : L.ci_in[t0 + xc];
+            keep[u] = x < steps && (!L.W || !L.mask || L.mask[(size_t)g * L.K + col[u]] != 0);
+        }
+        const unsigned long long below = (1ull << lane) - 1ull;
+        int r[kFillTurn], re[kFillTurn];
+#pragma unroll
+        for (int u = 0; u < kFillTurn; ++u) {
+            const unsigned long long bk = __ballot(keep[u]), be = __ballot(keep[u] && (col[u] & 1) == 0);
+            if (lane == 0) { wave_kept[u][wave] = __popcll(bk); wave_even[u][wave] = __popcll(be); }
+            r[u] = __popcll(bk & below);
+            re[u] = __popcll(be & below);
+        }
+        __syncthreads();
+        const int done0 = done;
+#pragma unroll
+        for (int u = 0; u < kFillTurn; ++u) {
+            int rank = done + r[u], rank_even = done_even + re[u];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const int k = wave_kept[u][w], e = wave_even[u][w];
+                if (w < wave) { rank += k; rank_even += e; }
+                done += k;
+                done_even += e;
+            }
+            if (keep[u]) {
+                const bool even = (col[u] & 1) == 0, to_front = even == ((s & 1) == 0);
+                const int mine = even ? rank_even : rank - rank_even;
+                list_col[rank - done0] = col[u];
+                list_at[rank - done0] = GS == 1 ? rank : to_front ? mine : wk.cnt - back + mine;
+            }
+        }
+        __syncthreads();
+        for (int t = tid; t < done - done0; t += 256) {
+            const int c = list_col[t], at = list_at[t];
+            const long long canon = t0 + done0 + t;
+            float *w = L.o_w + w_index(wk.start + at, s), *va = L.o_va + canon * V;
+            const int rec = first_rec + at / 9, tap = at % 9;
+            float *cw = L.o_cw ? L.o_cw + (size_t)rec * 64 + tap * 4 : nullptr;
+            for (int v0 = 0; v0 < V; v0 += 4) {
+                fl4 val;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int row = g * V + v0 + i;
+                    val[i] = 0.f;
+                    if (v0 + i < V && (!L.W || row < L.Cout)) val[i] = L.W ? L.W[(size_t)row * L.K + c] : L.va_in[canon * V + v0 + i];
+                }
+                if (V >= 4) {
+                    *reinterpret_cast<fl4 *>(va + v0) = val;
+                    *reinterpret_cast<fl4 *>(w) = val;
+                    w += L.wplane;
+                    if (cw) {
+                        *reinterpret_cast<fl4 *>(cw) = val;
+                        cw += L.cwplane;
+                    }
+                } else {
+                    va[0] = w[0] = val[0];
+                    if (V == 2) va[1] = w[1] = val[1];
+                }
+            }
+            L.o_ci[canon] = c;
+            int32_t *o = L.o_off + off_index(wk.start + at, s);
+            for (int tb = 0; tb < L.noff; ++tb, o += L.offlen) *o = layout_off_of(c, L.k, tb, GS);
+            if (L.o_cw && tap == 0) {
+                L.o_csel[rec] = c / 9 - c0;
+                float *z = L.o_cw + (size_t)rec * 64 + 36;
+                for (int q = 0; q < L.planes; ++q, z += L.cwplane)
+                    for (int i = 0; i < 28; i += 4) *reinterpret_cast<fl4 *>(z + i) = fl4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -486,10 +550,6 @@ size_t carve(LayerDev *d, char *base, const LayerIn &in) {
     return o;
 }
 
-__global__ void k_ld_clear(int *scal, int n) {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) scal[i] = 0;
-}
-
 // All layers through the steps; out[i] receive the handles (all or none).
 int build_all(const LayerIn *in, int n, void *workspace, size_t workspace_bytes, hipStream_t st, alcs_packed_t **out) {
     for (int i = 0; i < n; ++i) out[i] = nullptr;
@@ -510,11 +570,13 @@ int build_all(const LayerIn *in, int n, void *workspace, size_t workspace_bytes,
     std::vector<LayerDev> L;
     std::vector<Spread> sp;
     std::vector<int> h_scal;
+    std::vector<char> header;  // what is uploaded: the scalars' zeros, the layers, their first workgroups
     std::vector<alcs_packed *> made;
     try {
         L.resize((size_t)n);
         sp.resize((size_t)n);
         h_scal.resize((size_t)n * kScalars);
+        header.resize(header_bytes(n));
         made.resize((size_t)n, nullptr);
     } catch (const std::bad_alloc &) {
         return ALCS_E_ALLOC;
@@ -556,16 +618,18 @@ int build_all(const LayerIn *in, int n, void *workspace, size_t workspace_bytes,
         if ((d.gs_even > 1 || d.gs_uneven > 1) && (d.V < 4 || d.k != 1 || d.nchunks != 1)) return fail(ALCS_E_INVALID_ARG);
         sp[(size_t)i] = Spread{(int)wg_count, (int)wg_rank, 0};
         wg_count += (long long)d.G * d.nchunks;
-        wg_rank += (d.G + 255) / 256;
+        wg_rank += (d.G + kRankGroups - 1) / kRankGroups;
         if (wg_count > INT32_MAX - 1024) return fail(ALCS_E_UNSUPPORTED);
     }
-    auto upload_tables = [&]() {
-        int r = check(hipMemcpyAsync(d_layers, L.data(), sizeof(LayerDev) * (size_t)n, hipMemcpyHostToDevice, st));
-        if (r == ALCS_OK) r = check(hipMemcpyAsync(d_spread, sp.data(), sizeof(Spread) * (size_t)n, hipMemcpyHostToDevice, st));
-        return r;
+    // (one copy from one host buffer: two of them and a kernel that clears the scalars took 15 us more a call)
+    const size_t at_layers = (size_t)((char *)d_layers - (char *)workspace), at_spread = (size_t)((char *)d_spread - (char *)workspace);
+    auto upload_tables = [&](size_t from) {
+        std::memcpy(header.data() + at_layers, L.data(), sizeof(LayerDev) * (size_t)n);
+        std::memcpy(header.data() + at_spread, sp.data(), sizeof(Spread) * (size_t)n);
+        const size_t end = at_spread + sizeof(Spread) * (size_t)n;
+        return check(hipMemcpyAsync((char *)workspace + from, header.data() + from, end - from, hipMemcpyHostToDevice, st));
     };
-    if ((rc = upload_tables()) != ALCS_OK) return fail(rc);
-    hipLaunchKernelGGL(k_ld_clear, dim3(1), dim3(256), 0, st, d_scal, kScalars * n);
+    if ((rc = upload_tables(0)) != ALCS_OK) return fail(rc);
     hipLaunchKernelGGL(k_ld_count, dim3((unsigned)wg_count), dim3(64), 0, st, d_layers, d_spread, n);
     hipLaunchKernelGGL(k_ld_rank, dim3((unsigned)wg_rank), dim3(256), 0, st, d_layers, d_spread, n);
     hipLaunchKernelGGL(k_ld_plan, dim3((unsigned)n), dim3(1024), 0, st, d_layers);
@@ -634,7 +698,7 @@ int build_all(const LayerIn *in, int n, void *workspace, size_t workspace_bytes,
         sp[(size_t)i].fill = (int)wg_fill;
         wg_fill += (long long)nseg * d.GS + 1;
     }
-    if ((rc = upload_tables()) != ALCS_OK) return fail(rc);
+    if ((rc = upload_tables(at_layers)) != ALCS_OK) return fail(rc);
     hipLaunchKernelGGL(k_ld_fill, dim3((unsigned)wg_fill), dim3(256), 0, st, d_layers, d_spread, n);
     if ((rc = check(hipGetLastError())) != ALCS_OK) return fail(rc);
     if ((rc = check(hipStreamSynchronize(st))) != ALCS_OK) return fail(rc);  // the temporaries are free again

@@ -243,3 +243,34 @@ def test_memory_of_freed_handles_can_be_given_back():
     alcs.alcs_release_memory()
     assert torch.cuda.mem_get_info()[0] >= free0 + 4 * W.numel() * 4
     alcs.alcs_pack_weights_device(W, None, 4).free()
+
+
+@pytest.mark.parametrize("Cout,Cin,k,V,sparsity", [
+    (4 * 63, 40, 1, 4, 0.6), (4 * 64, 40, 1, 4, 0.6), (4 * 65, 40, 1, 4, 0.6),         # 64 groups to a workgroup of the ranking
+    (4 * 1023, 12, 1, 4, 0.5), (4 * 1025, 12, 1, 4, 0.5),                               # 1024 lengths to a block of it
+    (24, 1023, 1, 4, 0.3), (24, 1024, 1, 8, 0.0), (24, 1025, 1, 16, 0.3), (18, 2300, 1, 4, 0.6),  # 1024 columns to a turn
+    (9, 1030, 1, 1, 0.2), (9, 1030, 1, 2, 0.2), (50, 130, 3, 16, 0.5), (20, 128, 3, 4, 0.0)])
+def test_layouts_at_the_edges_of_the_packing_kernels(Cout, Cin, k, V, sparsity):
+    import torch
+    rng = np.random.default_rng(4300 + Cout + Cin + V)
+    W = (rng.standard_normal((Cout, Cin, k, k)) * 0.2).astype(np.float32)
+    mask = uneven_mask((Cout + V - 1) // V, Cin, k, sparsity, rng)
+    host = alcs.alcs_pack_weights(W, mask, V)
+    devs = [alcs.alcs_pack_weights_device(torch.from_numpy(W).cuda(), torch.from_numpy(mask).cuda(), V)]
+    rp, ci, va = alcs.alcs_pack_csr_device(torch.from_numpy(W).cuda(), torch.from_numpy(mask).cuda(), V)
+    devs.append(alcs.alcs_pack_from_csr_device(rp, ci, va, Cout, Cin, k, V))
+    for dev in devs:
+        assert dev.selfcheck() == 0 and dev.layout_hash() == host.layout_hash()
+        for got, want in zip(dev.export(), oracle.pack(W, mask, V)):
+            assert got.tobytes() == want.tobytes()
+
+
+@pytest.mark.parametrize("layers", [63, 64, 65, 130])
+def test_more_layers_in_a_call_than_a_wavefront_has_lanes(layers):
+    import torch
+    rng = np.random.default_rng(4400 + layers)
+    Ws = [(rng.standard_normal((4 + i % 7, 3 + i % 5, 1, 1))).astype(np.float32) for i in range(layers)]
+    masks = [uneven_mask((W.shape[0] + 3) // 4, W.shape[1], 1, 0.4, rng) for W in Ws]
+    hs = alcs.alcs_pack_network_device([torch.from_numpy(W).cuda() for W in Ws], [torch.from_numpy(m).cuda() for m in masks], 4)
+    for h, W, m in zip(hs, Ws, masks):
+        assert h.layout_hash() == alcs.alcs_pack_weights(W, m, 4).layout_hash()
