@@ -424,9 +424,28 @@ __device__ double interpolate(const double *k, const double *t, int n, double s)
     return t[lo] + w * (t[hi] - t[lo]);
 }
 
+// The layers' tables as k_bisect_steps reads them: copies in LDS where they fit.  Evaluating a node is a chain of reads -
+// a layer's place in the tables, its ends, a search, two neighbours - one behind the other.  From LDS the four launches of
+// MobileNetV1's 13 layers take 65 us in all, from memory 80.  (Both limits: a workgroup's static LDS ends at 64 KB, and S
+// takes 24 of them; networks beyond them read memory.)
+constexpr int kStageKnots = 1536, kStageLayers = 256;
+struct StagedTables {
+    double k[kStageKnots], t[kStageKnots];
+    unsigned int seg[kStageLayers + 1];
+    int first[kStageLayers + 1], V[kStageLayers];
+};
+
+// Lane i of a double, i the same in every lane.
+__device__ __forceinline__ double lane_value(double x, int i) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const unsigned int lo = (unsigned int)__builtin_amdgcn_readlane((int)u, i), hi = (unsigned int)__builtin_amdgcn_readlane((int)(u >> 32), i);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+
 // Latency of the network that keeps the N largest blocks, by one wavefront: [lo, hi], equal where it
 // is exact.  Layers are summed in order, as the host would.
-__device__ __forceinline__ void latency_of(const BisectArgs &a, const unsigned int (*S)[kSpan], const Bisect &st,
+template <class Tables>
+__device__ __forceinline__ void latency_of(const BisectArgs &a, const Tables &tab, const unsigned int (*S)[kSpan], const Bisect &st,
                                            unsigned int N, int lane, double &t_lo, double &t_hi, bool &exact) {
 #pragma clang fp contract(off)
     const unsigned int n = a.par->n;
@@ -442,7 +461,7 @@ __device__ __forceinline__ void latency_of(const BisectArgs &a, const unsigned i
         unsigned int base = 0, extra = 0;
         if (l < a.L) {
             if (trivial) {
-                base = N == 0 ? 0 : a.seg[l + 1] - a.seg[l];
+                base = N == 0 ? 0 : tab.seg[l + 1] - tab.seg[l];
             } else {
                 for (int v = 0; v <= p.level; ++v) {
                     const unsigned int *row = cum_row(a, v, l);
@@ -464,16 +483,16 @@ __device__ __forceinline__ void latency_of(const BisectArgs &a, const unsigned i
             extra = p.rest > before ? min(extra, p.rest - before) : 0;
         }
         if (l < a.L) {
-            const int k0 = a.first[l], nk = a.first[l + 1] - k0;
+            const int k0 = tab.first[l], nk = tab.first[l + 1] - k0;
             if (exact) base += extra;
-            f_lo = interpolate(a.k + k0, a.t + k0, nk, (double)base * a.V[l]);
-            f_hi = exact ? f_lo : interpolate(a.k + k0, a.t + k0, nk, (double)(base + extra) * a.V[l]);
+            f_lo = interpolate(tab.k + k0, tab.t + k0, nk, (double)base * tab.V[l]);
+            f_hi = exact ? f_lo : interpolate(tab.k + k0, tab.t + k0, nk, (double)(base + extra) * tab.V[l]);
         }
         size += fabs(f_lo) + fabs(f_hi);
         const int cnt = min(64, a.L - l0);
-        for (int i = 0; i < cnt; ++i) lo = lo + __shfl(f_lo, i);
+        for (int i = 0; i < cnt; ++i) lo = lo + lane_value(f_lo, i);
         if (!exact)
-            for (int i = 0; i < cnt; ++i) hi = hi + __shfl(f_hi, i);
+            for (int i = 0; i < cnt; ++i) hi = hi + lane_value(f_hi, i);
     }
     if (exact) {
         hi = lo;
@@ -511,8 +530,10 @@ __global__ void k_bisect_init(BisectArgs a, SelectState *sel) {
 // w of the tree of the next four steps (node 1 the midpoint, node 2w / 2w + 1 the midpoint of the lower /
 // upper half), wavefront 0 the ends whose latency is not exact yet.  Ends with a request for more
 // counts, or with the result: N, its cut, and both latencies exact.
+template <bool STAGED>
 __global__ void __launch_bounds__(1024) k_bisect_steps(const BisectArgs a) {
     __shared__ unsigned int S[kLevels][kSpan];
+    __shared__ StagedTables staged;
     __shared__ Bisect st;
     __shared__ double node_lo[18], node_hi[18];
     __shared__ int stop;
@@ -529,6 +550,19 @@ __global__ void __launch_bounds__(1024) k_bisect_steps(const BisectArgs a) {
     for (int l = 0; l < kLevels; ++l)
         if (l == 0 || (l == 1 ? st.fine1 : st.fine2))
             for (int i = tid; i < kSpan; i += 1024) S[l][i] = cum_row(a, l, a.L)[i];
+    if constexpr (STAGED) {
+        const int knots = a.par->knots;
+        for (int i = tid; i < knots; i += 1024) { staged.k[i] = a.k[i]; staged.t[i] = a.t[i]; }
+        for (int i = tid; i <= a.L; i += 1024) {
+            staged.seg[i] = a.seg[i];
+            staged.first[i] = a.first[i];
+            if (i < a.L) staged.V[i] = a.V[i];
+        }
+    }
+    auto latency = [&](unsigned int N, double &lo, double &hi, bool &exact) __attribute__((always_inline)) {
+        if constexpr (STAGED) latency_of(a, staged, S, st, N, lane, lo, hi, exact);
+        else latency_of(a, a, S, st, N, lane, lo, hi, exact);
+    };
     const double budget = a.par->budget, eps = a.par->eps;
     for (int turn = 0; turn < kBisectRounds; ++turn) {
         __syncthreads();
@@ -542,13 +576,13 @@ __global__ void __launch_bounds__(1024) k_bisect_steps(const BisectArgs a) {
             }
             bool exact = false;
             double lo = 0, hi = 0;
-            if (y - x > 1) latency_of(a, S, st, x + (y - x) / 2, lane, lo, hi, exact);
+            if (y - x > 1) latency(x + (y - x) / 2, lo, hi, exact);
             if (lane == 0) { node_lo[wave] = lo; node_hi[wave] = hi; }
         } else {
             for (int e = 0; e < 2; ++e) {
                 double lo = e ? st.t1_lo : st.t0_lo, hi = e ? st.t1_hi : st.t0_hi;
                 bool exact;
-                if (!known(lo, hi)) latency_of(a, S, st, e ? st.N1 : st.N0, lane, lo, hi, exact);
+                if (!known(lo, hi)) latency(e ? st.N1 : st.N0, lo, hi, exact);
                 if (lane == 0) { node_lo[16 + e] = lo; node_hi[16 + e] = hi; }
             }
         }
@@ -903,13 +937,14 @@ static int project_on_device(const float *scores_dev, long long n, const long lo
     hipLaunchKernelGGL(k_bisect_init, dim3(std::min(256, (L + 1) * kBins / 1024)), dim3(256), 0, st, a, w.st);
     const unsigned hist_wgs = (unsigned)((n + kHistChunk - 1) / kHistChunk);
     const int chunks = chunks_for(n);
+    auto *steps = L <= kStageLayers && knots <= (size_t)kStageKnots ? k_bisect_steps<true> : k_bisect_steps<false>;
     Bisect res{};
     // (every batch of rounds decides at least one more step: the bound is never reached)
     for (int batch = 0; batch < 256 && !res.done; ++batch) {
         for (int round = 0; round < 3 + (batch == 0); ++round) {
             hipLaunchKernelGGL(k_bisect_hist, dim3(hist_wgs), dim3(256), 0, st, a);
             hipLaunchKernelGGL(k_bisect_cumulate, dim3(L + 1), dim3(256), 0, st, a);
-            hipLaunchKernelGGL(k_bisect_steps, dim3(1), dim3(1024), 0, st, a);
+            hipLaunchKernelGGL(steps, dim3(1), dim3(1024), 0, st, a);
         }
         if (mask_dev) {
             hipLaunchKernelGGL(k_select_ties<false>, dim3(chunks), dim3(256), 0, st, scores_dev, (unsigned long long)n, w.st);

@@ -224,3 +224,20 @@ def test_rejected_arguments():
     assert lib.alcs_block_scores(P(s), 4, 4, 1, 3, P(s), None) < 0          # V = 3
     assert lib.alcs_block_scores(P(s), 4, 4, 5, 4, P(s), None) < 0          # kernel = 5
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("layers,knots", [(256, 6), (257, 5), (128, 12), (128, 13), (24, 64)])
+def test_projection_at_the_limits_of_the_staged_tables(layers, knots):
+    """256 layers and 1536 table entries are copied to LDS, more are read from memory: the same result."""
+    import torch
+    rng = np.random.default_rng(3500 + layers + knots)
+    sizes = rng.integers(1, 60, layers)
+    sc = [(rng.random((int(m), 1, 1, 1)) ** 3).astype(np.float32) for m in sizes]
+    tables = [(np.arange(knots) * (4.0 * m / (knots - 1)), np.maximum.accumulate(2.0 + 0.02 * m * rng.random(knots))) for m in sizes]
+    starts = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    none, every = sum(t[0] for _, t in tables), sum(t[-1] for _, t in tables)
+    args = ([4] * layers, tables, 0.5, 0.5 + none + 0.4 * (every - none), 1e-4)
+    N, mask, t0, t1 = alcs.alcs_project_latency(torch.from_numpy(np.concatenate([s.reshape(-1) for s in sc])).cuda(), starts, *args)
+    Nr, masks_r, t0r, t1r = oracle.project_latency(sc, *args)
+    assert N == Nr and abs(t0 - t0r) <= 1e-9 * t0r and abs(t1 - t1r) <= 1e-9 * t1r
+    assert mask.cpu().numpy().tobytes() == np.concatenate([m.reshape(-1) for m in masks_r]).tobytes()
