@@ -1336,6 +1336,120 @@ __global__ void __launch_bounds__(1024) k_pw_split(const ConvArgs a) {
 }
 
 #if !ALCS_RESIDENT_ONLY
+// stage_pw's kRows form in two halves: the wavefront's first U items of rows [c0, c1) into registers, and from there
+// (and, beyond U items, straight from memory) into LDS.
+__device__ __forceinline__ int rows_shift(const ConvArgs &a, int q0) {
+    const int there = a.NP - q0;
+    return there <= 16 ? 0 : there <= 32 ? 1 : 2;
+}
+template <int U>
+__device__ __forceinline__ void fetch_rows_from(const ConvArgs &a, f4 (&v)[U], int q0, int c0, int c1, int i0, int nw, int lane) {
+    const int e16 = lane & 15, cq = lane >> 4, rows = c1 - c0;
+    const int pgs = rows_shift(a, q0), pgm = (1 << pgs) - 1;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int it = i0 + u * nw, e = (it & pgm) * 16 + e16, c = (it >> pgs) * 16 + cq * 4;
+        v[u] = f4{0, 0, 0, 0};
+        if (c < rows && q0 + e < a.NP) {
+            const io_t *src = a.X + (size_t)(q0 + e) * a.Cin + c0 + c;
+            if (c + 4 <= rows) v[u] = io_load4u(src);
+            else
+                for (int i = 0; i < 3; ++i)
+                    if (c + i < rows) v[u][i] = io_load1(src + i);
+        }
+    }
+}
+template <int U>
+__device__ __forceinline__ void fetch_rows(const ConvArgs &a, f4 (&v)[U], int q0, int c0, int c1, int wave, int nw, int lane) {
+    fetch_rows_from<U>(a, v, q0, c0, c1, wave, nw, lane);
+}
+template <int TP, int U>
+__device__ __forceinline__ void commit_rows(const ConvArgs &a, f4 (&v)[U], float *lds, int q0, int c0, int c1, int wave, int nw, int lane) {
+    const int e16 = lane & 15, cq = lane >> 4, rows = c1 - c0;
+    const int pgs = rows_shift(a, q0), pgm = (1 << pgs) - 1;
+    const int items = ((rows + 15) / 16) << pgs;
+    for (int i0 = wave; i0 < items; i0 += U * nw) {
+        if (i0 != wave) fetch_rows_from<U>(a, v, q0, c0, c1, i0, nw, lane);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int it = i0 + u * nw, e = (it & pgm) * 16 + e16, c = (it >> pgs) * 16 + cq * 4;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int k = (i + cq) & 3;  // (lane quads start with different words: different banks)
+                const float x = k == 0 ? v[u][0] : k == 1 ? v[u][1] : k == 2 ? v[u][2] : v[u][3];
+                if (c + k < rows) lds[(c + k) * TP + e] = x;
+            }
+        }
+    }
+}
+
+// Kernels that walk chunks (1x1 of many input channels, 3x3), in launches that would leave compute units idle: a wavefront
+// has one group, and a.ksplit wavefronts share it, each with a part of its columns in every chunk (k_pw_chunked_split,
+// k_conv3_split).  A launch of a few workgroups is a chain of chunks, each staged and then multiplied by wavefronts with
+// several groups one after the other; here the groups are dealt to as many workgroups as there are compute units, so that
+// a chunk's multiply is short, and the next chunk's rows, work record and weights are requested before it.
+struct Part {
+    int bundle, part;
+};
+__device__ __forceinline__ Part split_part(const ConvArgs &a, int wave) {
+    const int bundle = wave / a.ksplit;
+    return {bundle, wave - bundle * a.ksplit};
+}
+// A part's share of `total` columns (or records), in whole multiples of `unit`.
+__device__ __forceinline__ void split_range(const ConvArgs &a, int part, int unit, int &start, int &total) {
+    const int per = ((total + unit - 1) / unit + a.ksplit - 1) / a.ksplit * unit;
+    const int mine = max(0, min(per, total - part * per));
+    if (mine > 0) start += part * per;
+    total = mine;
+}
+// The parts' sums added through LDS (the chunks' memory, once everybody has read it), every wavefront finishing and
+// storing a share of the channels.
+template <int V, int PV, bool MF, int AC>
+__device__ __forceinline__ void finish_split(const ConvArgs &a, const Acc<V, PV, MF> &acc, float *lds, const Part &p, int wave,
+                                             int lane, int g, const PixOut<PV> &px) {
+    constexpr int UV = AC != kRows ? 1 : V < 4 ? V : 4;  // channels that are finished and stored together
+    const int ks = a.ksplit;
+    if (ks == 1) {
+        if (g >= 0) store_group_here<V, PV, MF, AC>(a, acc, g, px);
+        return;
+    }
+    __syncthreads();
+    float *red = lds + (size_t)wave * (V * PV * 64) + lane;
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+        for (int pv = 0; pv < PV; ++pv) red[(v * PV + pv) * 64] = acc.get(v, pv);
+    __syncthreads();
+    if (g < 0) return;
+    const float *sum = lds + (size_t)(p.bundle * ks) * (V * PV * 64) + lane;
+    const bool res = kFused && residual_of(a);
+#pragma unroll
+    for (int u = 0; u < V / UV; ++u) {
+        if (u % ks != p.part || g * V + u * UV >= a.Cout) continue;
+        float x[UV][PV];
+        Resid<UV, PV> rr;
+        if (res) load_residual<V, PV, AC, UV>(a, g, u * UV, px, rr);
+#pragma unroll
+        for (int i = 0; i < UV; ++i) {
+            const int v = u * UV + i;
+            const float bias = a.bias ? as_const(a.bias)[min(g * V + v, a.Cout - 1)] : 0.f;
+#pragma unroll
+            for (int pv = 0; pv < PV; ++pv) {
+                float o = 0.f;
+                for (int k = 0; k < ks; ++k) o += sum[(size_t)(k * V * PV + v * PV + pv) * 64];
+                o += bias;
+                if (res) o += rr.r[i][pv];
+                x[i][pv] = activate(a, o);
+            }
+        }
+        if constexpr (AC == kRows) {
+            store_rows<UV, PV>(a, g * V + u * UV, px, [&](int i, int pv) __attribute__((always_inline)) { return x[i][pv]; });
+        } else {
+            store_pixels<PV, AC>(a.Y + (size_t)(g * V + u) * a.P, px, x[0]);
+        }
+    }
+}
+
 // Mode 2: input channels streamed through LDS in chunks of KC; every wavefront owns
 // UG groups for the whole kernel and keeps their accumulators in registers.
 template <int V, int PV, int UG, bool MF, int AC>
@@ -1392,6 +1506,70 @@ __global__ void __launch_bounds__(512) k_pw_chunked(const ConvArgs a) {
             store_group_here<V, PV, MF, AC>(a, acc[u], load_work(a.work, (size_t)slot[u] * a.nchunks).group[0], px);
 }
 
+
+// The chunked kernel with parts.  Fully connected layers (kRows): 16 wavefronts, whose four items of 16 pixels x 16
+// channels each are a chunk of 256 channels, requested ahead; other images are staged as in the kernel above.
+// 80 to 90 % sparse: 2960->1000 on 56 rows, V=8, 120 -> 42 us; 4096->4096 on one row, V=4, 102 -> 40; 3544->1000 on 79 rows,
+// V=2, 178 -> 53 (without the rows ahead, on eight wavefronts, 58, 38 and 84).
+template <int V, bool MF, int AC>
+__global__ void __launch_bounds__(1024) k_pw_chunked_split(const ConvArgs a) {
+    extern __shared__ float lds[];
+    constexpr int TP = 64, U = 4;
+    const int logical = logical_wg(a);
+    if (logical >= a.total_wgs || skip(a, 8)) return;
+    const int pt = logical / a.ngt, gt = logical - pt * a.ngt;
+    const int q0 = pt * TP;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+    const int g_begin = gt * a.gpt;
+    const int ng = min(a.G, g_begin + a.gpt) - g_begin;
+    const Part mine = split_part(a, wave);
+    const int slot = mine.bundle < ng ? g_begin + mine.bundle : -1;
+    Acc<V, 1, MF> acc;
+    acc.zero();
+    for (int t = tid; t < TP; t += blockDim.x) lds[a.KC * TP + t] = 0.f;
+    Work wk = no_work(), wn = no_work();
+    Runs<V, MF> rn, rnext;
+    // (a record is turned into the wavefront's share a chunk after it was requested: to look at it is to wait for it)
+    auto record = [&](int ch) { return load_work(a.work, (size_t)slot * a.nchunks + ch); };
+    if (slot >= 0) {
+        wk = record(0);
+        if (a.nchunks > 1) wn = record(1);
+        split_range(a, mine.part, kSegAlign, wk.start, wk.cnt);
+        rn = load_runs<V, MF>(a, wk.start, wk.cnt, lane);
+    }
+    f4 v[U];
+    if constexpr (AC == kRows) fetch_rows<U>(a, v, q0, 0, min(a.Cin, a.KC), wave, nw, lane);
+    for (int ch = 0; ch < a.nchunks; ++ch) {
+        const int c0 = ch * a.KC, c1 = min(a.Cin, c0 + a.KC);
+        const bool more = ch + 1 < a.nchunks;
+        if (ch) __syncthreads();
+        if constexpr (AC == kRows) commit_rows<TP, U>(a, v, lds, q0, c0, c1, wave, nw, lane);
+        else stage_pw<TP, AC>(a, lds, q0, c0, c1, a.NP);
+        touch_runs<V, 1>(rn);
+        __syncthreads();
+        if (more) {
+            Work w2 = no_work();
+            if (slot >= 0) {
+                split_range(a, mine.part, kSegAlign, wn.start, wn.cnt);
+                rnext = load_runs<V, MF>(a, wn.start, wn.cnt, lane);
+                if (ch + 2 < a.nchunks) w2 = record(ch + 2);
+            }
+            if constexpr (AC == kRows) fetch_rows<U>(a, v, q0, c1, min(a.Cin, c1 + a.KC), wave, nw, lane);
+            if (slot >= 0 && !skip(a, 2))
+                mac_segment<V, 1, 0>(a, wk.start, wk.cnt, reinterpret_cast<const char *>(lds), lane * 4 - c0 * kRowBytes1, lane, rn, acc);
+            wk = wn;
+            wn = w2;
+            rn = rnext;
+        } else if (slot >= 0 && !skip(a, 2)) {
+            mac_segment<V, 1, 0>(a, wk.start, wk.cnt, reinterpret_cast<const char *>(lds), lane * 4 - c0 * kRowBytes1, lane, rn, acc);
+        }
+    }
+    PixOut<1> px;
+    pix_out<1, AC>(a, q0, lane, px, a.NP);
+    const int g = slot >= 0 ? load_work(a.work, (size_t)slot * a.nchunks).group[0] : -1;
+    if (!skip(a, 4)) finish_split<V, 1, MF, AC>(a, acc, lds, mine, wave, lane, g, px);
+}
 
 // Mode 4 (streaming): for layers whose time is the HBM stream of X and Y.  Workgroups
 // are persistent: each owns a contiguous range of the flattened pixel axis (all ranges
@@ -1526,18 +1704,17 @@ template <int V>
 struct Chans {
     static constexpr int N = chans_ahead<V>();
     float w[N][V / 4];
-    int sel;  // lane l: byte offset of the plane of channel l % 8
+    int sel;  // lane l: channel l % 8 of the chunk
 };
-template <int PLANE>
 __device__ __forceinline__ int load_chan_sel(const ConvArgs &a, int first, int j, int n, int lane) {
-    return a.csel[first + min(j + (lane & 7), max(n - 1, 0))] * PLANE;
+    return a.csel[first + min(j + (lane & 7), max(n - 1, 0))];
 }
 // The first channels of a segment; beyond the last one it is read again (record `first` exists for an empty one too:
 // the arrays end with a spare record).
-template <int V, int PLANE>
+template <int V>
 __device__ __forceinline__ Chans<V> load_chans(const ConvArgs &a, int first, int n, int lane) {
     Chans<V> c;
-    c.sel = load_chan_sel<PLANE>(a, first, 0, n, lane);
+    c.sel = load_chan_sel(a, first, 0, n, lane);
     auto some = [&](auto i0, auto count) {
 #pragma unroll
         for (int i = decltype(i0)::value; i < decltype(i0)::value + decltype(count)::value; ++i)
@@ -1561,8 +1738,8 @@ __device__ __forceinline__ void mac_channels(const ConvArgs &a, int first, int n
     constexpr int PLANE = halo_area3(STRIDE, TI, TALL) * 4;
     constexpr int NACC = Acc<V, PV, true>::NACC, N = Chans<V>::N;
     auto pass = [&](int j0) {
-        const int sel = c.sel;
-        if (j0 + N < n) c.sel = load_chan_sel<PLANE>(a, first, j0 + N, n, lane);
+        const int sel = c.sel * PLANE;  // (here and not behind the load, which would be waited for at once)
+        if (j0 + N < n) c.sel = load_chan_sel(a, first, j0 + N, n, lane);
         static_for<N>([&](auto ii) {
             constexpr int I = decltype(ii)::value;
             const int j = j0 + I;
@@ -1667,7 +1844,7 @@ __global__ void __launch_bounds__(512) k_conv3(const ConvArgs a) {
                     const cptr<int32_t> cwk = as_const(a.cwork) + 2 * ((size_t)slot[u] * a.nchunks + ch);
                     cfirst[u] = __builtin_amdgcn_readfirstlane(cwk[0]);
                     cn[u] = __builtin_amdgcn_readfirstlane(cwk[1]);
-                    cr[u] = load_chans<V, HA * 4>(a, cfirst[u], cn[u], lane);
+                    cr[u] = load_chans<V>(a, cfirst[u], cn[u], lane);
                 } else {
                     wk[u] = load_work(a.work, (size_t)slot[u] * a.nchunks + ch);
                     rn[u] = load_runs<V, MF>(a, wk[u].start, wk[u].cnt, lane);
@@ -1742,6 +1919,133 @@ __global__ void __launch_bounds__(512) k_conv3(const ConvArgs a) {
             store_group_here<V, PV, MF, kScattered>(a, acc[u], load_work(a.work, (size_t)slot[u] * a.nchunks).group[0], px);
 }
 
+
+// The 3x3 kernel with parts: 16 wavefronts, one group each or shared, the next chunk requested before this one is
+// multiplied (a thread keeps one halo position; its first U channels of a chunk go through registers).
+// 80 % sparse, V=4, one image: 64->64 @56x56 14.2 -> 8.5 us, 128->128 @28x28 23.8 -> 10.4, 256->256 @14x14 47 -> 17,
+// 512->512 @7x7 53 -> 17; 512->512 @7x7, N=16 61 -> 32.  What is left is a chain of 1.6 us a chunk: two barriers, the
+// rows' way into LDS, a round trip.
+template <int V, int STRIDE, int TI, bool MF, bool TALL, bool TS>
+__global__ void __launch_bounds__(1024) k_conv3_split(const ConvArgs a) {
+    static_assert(!TALL || (STRIDE == 1 && MF), "tall tiles: stride 1, MFMA form");
+    extern __shared__ float lds[];
+    constexpr int PV = TALL ? 2 : 1, PD = TALL ? tall_step3(TI) : 1;
+    constexpr int TW = tile_w3(TI), TH = tile_h3(TI), TROWS = tile_rows3(TI, TALL);
+    constexpr int COLS = halo_cols3(STRIDE, TI), PITCH = pitch3(STRIDE, TI), HA = halo_area3(STRIDE, TI, TALL);
+    constexpr int HPOS = halo_rows3(STRIDE, TI, TALL) * COLS;
+    constexpr int U = (32 + 1024 / HPOS - 1) / (1024 / HPOS);  // a thread's loads for 32 channels
+    const int logical = logical_wg(a);
+    if (logical >= a.total_wgs || skip(a, 8)) return;
+    const int pt = logical / a.ngt, gt = logical - pt * a.ngt;
+    const int tiles_per_img = a.tiles_x * a.tiles_y;
+    const int n = pt / tiles_per_img, trem = pt - n * tiles_per_img;
+    const int tyi = trem / a.tiles_x, txi = trem - tyi * a.tiles_x;
+    const int oy0 = tyi * TROWS, ox0 = txi * TW;
+    const int iy0 = oy0 * STRIDE - 1, ix0 = ox0 * STRIDE - 1;
+    const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g_begin = gt * a.gpt;
+    const int ng = min(a.G, g_begin + a.gpt) - g_begin;
+    const Part mine = split_part(a, wave);
+    const int slot = mine.bundle < ng ? g_begin + mine.bundle : -1;
+    Acc<V, PV, MF> acc;
+    acc.zero();
+    for (int t = tid; t < HA; t += nt) lds[a.KC * HA + t] = 0.f;  // the all-zero plane
+
+    // the chunk's share of the wavefront: columns, or channel records (see k_conv3)
+    struct Seg {
+        int start, cnt;
+    };
+    auto record = [&](int ch) __attribute__((always_inline)) {
+        Seg g{0, 0};
+        if constexpr (TS) {
+            const cptr<int32_t> cwk = as_const(a.cwork) + 2 * ((size_t)slot * a.nchunks + ch);
+            g.start = __builtin_amdgcn_readfirstlane(cwk[0]);
+            g.cnt = __builtin_amdgcn_readfirstlane(cwk[1]);
+        } else {
+            const Work w = load_work(a.work, (size_t)slot * a.nchunks + ch);
+            g.start = w.start;
+            g.cnt = w.cnt;
+        }
+        return g;
+    };
+    // (a record is turned into the wavefront's share a chunk after it was requested: to look at it is to wait for it)
+    auto share = [&](Seg &g) __attribute__((always_inline)) { split_range(a, mine.part, TS ? 1 : kSegAlign, g.start, g.cnt); };
+    Seg sk{0, 0}, sn{0, 0};
+    Runs<V, MF> rn, rnext;
+    Chans<TS ? V : 4> cr, cnext;
+    auto weights = [&](const Seg &g, Runs<V, MF> &r, Chans<TS ? V : 4> &c) __attribute__((always_inline)) {
+        if constexpr (TS) c = load_chans<V>(a, g.start, g.cnt, lane);
+        else r = load_runs<V, MF>(a, g.start, g.cnt, lane);
+    };
+    if (slot >= 0) {
+        sk = record(0);
+        if (a.nchunks > 1) sn = record(1);
+        share(sk);
+        weights(sk, rn, cr);
+    }
+    const int rpp = nt / HPOS;  // channels side by side (the launcher gives at least HPOS threads)
+    const int pos = tid % HPOS, r0 = tid / HPOS;
+    const int phy = pos / COLS, phx = pos - phy * COLS;
+    const bool pin = iy0 + phy >= 0 && iy0 + phy < a.H && ix0 + phx >= 0 && ix0 + phx < a.W;
+    const float *psrc = a.X + (size_t)n * a.Cin * a.Pin + (pin ? (size_t)(iy0 + phy) * a.W + ix0 + phx : 0);
+    const int pdst = phy * PITCH + halo_col3(STRIDE, TI, phx);
+    // Every thread loads and writes every time, rows beyond the last one as the last one: the same word to the same place
+    // as another thread, where a branch around each would be a chain of them.
+    float v[U];
+    auto fetch = [&](int c0, int c1, int r) __attribute__((always_inline)) {
+        const int last = c1 - c0 - 1;
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = psrc[(size_t)(c0 + min(r + u * rpp, last)) * a.Pin];
+    };
+    auto commit = [&](int rows, int r) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) lds[min(r + u * rpp, rows - 1) * HA + pdst] = pin ? v[u] : 0.f;
+    };
+    const char *ldsb = reinterpret_cast<const char *>(lds);
+    const int ly = lane / TW, lx = lane % TW;
+    const int lane_base = (ly * STRIDE) * PITCH + lx;
+    fetch(0, min(a.Cin, a.KC), r0);
+    for (int ch = 0; ch < a.nchunks; ++ch) {
+        const int c0 = ch * a.KC, c1 = min(a.Cin, c0 + a.KC);
+        const bool more = ch + 1 < a.nchunks;
+        if (ch) __syncthreads();
+        commit(c1 - c0, r0);
+        for (int r = U * rpp; r < c1 - c0; r += U * rpp) {  // (chunks of more than 32 channels)
+            fetch(c0, c1, r0 + r);
+            commit(c1 - c0, r0 + r);
+        }
+        __syncthreads();
+        Seg s2{0, 0};
+        if (more) {
+            if (slot >= 0) {
+                share(sn);
+                weights(sn, rnext, cnext);
+                if (ch + 2 < a.nchunks) s2 = record(ch + 2);
+            }
+            fetch(c1, min(a.Cin, c1 + a.KC), r0);
+        }
+        if (slot >= 0 && !skip(a, 2)) {
+            if constexpr (TS) mac_channels<V, STRIDE, TI, TALL>(a, sk.start, sk.cnt, ldsb, lane_base * 4, lane, cr, acc);
+            else mac_segment<V, PV, 0, 1, PD>(a, sk.start, sk.cnt, ldsb, (lane_base - c0 * HA) * 4, lane, rn, acc);
+        }
+        if (more) {
+            sk = sn;
+            sn = s2;
+            rn = rnext;
+            cr = cnext;
+        }
+    }
+    const int oy = oy0 + ly, ox = ox0 + lx;
+    PixOut<PV> px;
+#pragma unroll
+    for (int pv = 0; pv < PV; ++pv) {
+        px.valid[pv] = oy + pv * TH < a.Ho && ox < a.Wo;
+        px.yoff[pv] = (long long)n * a.Cout * a.P + (long long)(oy + pv * TH) * a.Wo + ox;
+    }
+    const int g = slot >= 0 ? load_work(a.work, (size_t)slot * a.nchunks).group[0] : -1;
+    if (!skip(a, 4)) finish_split<V, PV, MF, kScattered>(a, acc, lds, mine, wave, lane, g, px);
+}
 
 // Mode 5 (pipelined): the many-tile regime of wide 1x1 layers (four groups per wavefront, all
 // input channels of a 32-pixel tile in LDS).  With one tile per workgroup the phases of a tile -
@@ -1963,6 +2267,7 @@ static kern_t pick_chunked_ac(int pv, int ug) {
         }
         if (pv == 2) return ug == 2 ? k_pw_chunked<V, 2, 2, MF, AC> : k_pw_chunked<V, 2, 4, MF, AC>;
     }
+    if (ug == 1) return k_pw_chunked_split<V, MF, AC>;
     return ug == 2 ? k_pw_chunked<V, 1, 2, MF, AC> : k_pw_chunked<V, 1, 4, MF, AC>;
 }
 template <int V, bool MF>
@@ -1976,17 +2281,23 @@ static kern_t pick_chunked(int pv, Access ac, int ug) {
 template <int V, int TI, bool MF>
 static kern_t pick_conv3_shape(int stride, int ug, bool tall) {
     if constexpr (MF && V <= 8) {
-        if (tall && stride == 1) return ug == 2 ? k_conv3<V, 1, TI, 2, true, true> : k_conv3<V, 1, TI, 4, true, true>;
+        if (tall && stride == 1)
+            return ug == 1 ? k_conv3_split<V, 1, TI, true, true, false> : ug == 2 ? k_conv3<V, 1, TI, 2, true, true> : k_conv3<V, 1, TI, 4, true, true>;
     }
     if (tall) return nullptr;
+    if (ug == 1) return stride == 1 ? k_conv3_split<V, 1, TI, MF, false, false> : k_conv3_split<V, 2, TI, MF, false, false>;
     if (ug == 2) return stride == 1 ? k_conv3<V, 1, TI, 2, MF> : k_conv3<V, 2, TI, 2, MF>;
     return stride == 1 ? k_conv3<V, 1, TI, 4, MF> : k_conv3<V, 2, TI, 4, MF>;
 }
 // channel-record kernels (tap-shared pattern): MFMA form, V = 4 or 8
 template <int V, int TI>
 static kern_t pick_conv3_shared_shape(int stride, int ug, bool tall) {
-    if (tall && stride == 1) return ug == 2 ? k_conv3<V, 1, TI, 2, true, true, true> : k_conv3<V, 1, TI, 4, true, true, true>;
+    if (tall && stride == 1)
+        return ug == 1   ? k_conv3_split<V, 1, TI, true, true, true>
+               : ug == 2 ? k_conv3<V, 1, TI, 2, true, true, true>
+                         : k_conv3<V, 1, TI, 4, true, true, true>;
     if (tall) return nullptr;
+    if (ug == 1) return stride == 1 ? k_conv3_split<V, 1, TI, true, false, true> : k_conv3_split<V, 2, TI, true, false, true>;
     if (ug == 2) return stride == 1 ? k_conv3<V, 1, TI, 2, true, false, true> : k_conv3<V, 2, TI, 2, true, false, true>;
     return stride == 1 ? k_conv3<V, 1, TI, 4, true, false, true> : k_conv3<V, 2, TI, 4, true, false, true>;
 }
@@ -2029,6 +2340,25 @@ static int pick_ug(int G, int nw, int forced) {
     if (forced == 2 || forced == 4) return forced;
     return G <= 2 * nw ? 2 : 4;
 }
+
+#if !ALCS_RESIDENT_ONLY
+// Launches of fewer workgroups than compute units: as many group tiles as fill the chip once, `nw` wavefronts with at most
+// one group each; wavefronts without one share the others' columns (see Part).  One round, not two: every further workgroup
+// stages the tile's rows again (256->256 @14x14, N=4, 80 % sparse: 19.5 us in up to 256 workgroups, 36.5 in up to 512; 4096->1000
+// on 256 rows 65 and 125), and launches that fill the chip already keep their several groups per wavefront (128->128 @28x28, N=10:
+// 23 us, 34 as parts).
+static bool pick_parts(int cus, int nw, int &ug, ConvArgs &a) {
+    if ((long long)a.npt * a.ngt >= cus) return false;
+    int gpt = nw;
+    while (gpt > 1 && (long long)a.npt * ceil_div(a.G, gpt / 2) <= cus) gpt /= 2;
+    if (ceil_div(a.G, gpt) <= a.ngt) return false;  // no more workgroups than before
+    ug = 1;
+    a.gpt = gpt;
+    a.ngt = ceil_div(a.G, gpt);
+    a.ksplit = nw / gpt;
+    return true;
+}
+#endif
 
 // Vector registers per lane of a kernel (0 if the runtime cannot tell), looked up once.
 static int kernel_registers(kern_t k) {
@@ -2418,6 +2748,11 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             if (V * pv * ug > 128) ug = 2;  // accumulators of 4 groups would not fit the register file
             a.gpt = nw * ug;
             a.ngt = ceil_div(G, a.gpt);
+            const int pnw = ac == kRows ? 16 : 8;
+            if (pv == 1 && T.waves == 0 && T.ug == 0 && pick_parts(kCUs, pnw, ug, a)) {
+                nw = pnw;
+                lds = std::max(lds, a.ksplit > 1 ? nw * V * 64 * 4 : 0);
+            }
             switch (V) {
                 case 1: kern = pick_chunked<1, false>(pv, ac, ug); break;
                 case 2: kern = pick_chunked<2, false>(pv, ac, ug); break;
@@ -2462,6 +2797,10 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
         if (T.ug == 0 && ug == 4 && (long long)a.npt * ceil_div(G, nw * 4) <= kCUs && 2 * lds <= kMaxLds) ug = 2;
         a.gpt = nw * ug;
         a.ngt = ceil_div(G, a.gpt);
+        if (T.waves == 0 && T.ug == 0 && pick_parts(kCUs, 16, ug, a)) {
+            nw = 16;
+            lds = std::max(lds, a.ksplit > 1 ? nw * V * pv * 64 * 4 : 0);
+        }
         switch (V) {
             case 1: kern = pick_conv3<1, false>(stride, ti, ug, tall); break;
             case 2: kern = pick_conv3<2, false>(stride, ti, ug, tall); break;
