@@ -147,10 +147,11 @@ __device__ __forceinline__ void io_store4u(io_t *p, f4 v) { __builtin_nontempora
 #endif
 
 // How a kernel reaches the pixels of its tile in memory (a choice of the launcher, by the shape):
-//   kAligned    stride 1, pixels per image a multiple of 4: four neighbours are 16 bytes, aligned
+//   kAligned    output pixels per image a multiple of 4: four neighbours are 16 bytes, aligned; at stride 1 in X as
+//               well, at stride 2 (input width a multiple of 4) two of them are every other word of 16 bytes of X
 //   kUnaligned  stride 1, any other image of at least 4 pixels: 16 bytes at any address, and a quad
 //               may run from one image into the next
-//   kStrided    stride 2, or images of fewer than 4 pixels: one pixel at a time
+//   kStrided    any other image at stride 2, or of fewer than 4 pixels: one pixel at a time
 //   kRows       images of one pixel (a fully connected layer): the channels of a pixel are the
 //               contiguous axis, read 16 bytes at a time and transposed on the way into LDS
 //   kScattered  stores only: a lane's pixels lie in different rows (3x3 kernels)
@@ -602,8 +603,42 @@ __device__ __forceinline__ void stage_pw(const ConvArgs &a, float *lds, int q0, 
         const bool valid = q < q_end;
         const int n = valid ? q / a.P : 0;
         const int p = valid ? q - n * a.P : 0;
-        const io_t *src = a.X + ((size_t)n * a.Cin + c0) * a.P + p;
         float *dst = lds + quad * 4;
+        if (a.stride == 2) {
+            // A quad is two pairs of neighbours, each inside one row (rows have an even number of pixels): two 16-byte loads
+            // for what took four of 4 bytes, one pixel at a time (60 layers of mixed shapes 1.17x as fast; 168->24 @112x112, N=6,
+            // V=4, bfloat16 15.8 -> 9.7 us, 117->48 @112x112, N=18, V=1 20.3 -> 14.4, 256->512 @56x56, N=64 96 -> 94).
+            const int h0 = p / a.Wo, w0 = p - h0 * a.Wo;
+            const bool wraps = w0 + 2 >= a.Wo;
+            const int h1 = h0 + wraps, w1 = wraps ? 0 : w0 + 2;
+            const io_t *img = a.X + ((size_t)n * a.Cin + c0) * a.Pin;
+            const io_t *src0 = img + (size_t)(2 * h0) * a.W + 2 * w0, *src1 = img + (size_t)(2 * h1) * a.W + 2 * w1;
+            constexpr int U = 4;
+            int r = r0;
+            for (; r + (U - 1) * rpp < rows; r += U * rpp) {
+                f4 v[U], w[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    v[u] = w[u] = f4{0, 0, 0, 0};
+                    if (valid) {
+                        v[u] = io_load4(src0 + (size_t)(r + u * rpp) * a.Pin);
+                        w[u] = io_load4(src1 + (size_t)(r + u * rpp) * a.Pin);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) *reinterpret_cast<f4 *>(dst + (r + u * rpp) * TP) = f4{v[u][0], v[u][2], w[u][0], w[u][2]};
+            }
+            for (; r < rows; r += rpp) {
+                f4 v = f4{0, 0, 0, 0}, w = v;
+                if (valid) {
+                    v = io_load4(src0 + (size_t)r * a.Pin);
+                    w = io_load4(src1 + (size_t)r * a.Pin);
+                }
+                *reinterpret_cast<f4 *>(dst + r * TP) = f4{v[0], v[2], w[0], w[2]};
+            }
+            return;
+        }
+        const io_t *src = a.X + ((size_t)n * a.Cin + c0) * a.P + p;
         constexpr int U = 8;  // independent 16-byte loads in flight per thread
         int r = r0;
         for (; r + (U - 1) * rpp < rows; r += U * rpp) {
@@ -2464,7 +2499,9 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
 
     if (kernel == 1) {
         const bool vec = stride == 1 && (P % 4 == 0);
-        const Access ac = vec ? kAligned : kDw ? kUnaligned : (P == 1 && Pin == 1) ? kRows : (stride == 1 && P >= 4) ? kUnaligned : kStrided;
+        // (the images end with whole 16 bytes, and so does every row: nothing beyond the tensor is read)
+        const bool pairs = !kDw && stride == 2 && W % 4 == 0 && P % 4 == 0;
+        const Access ac = vec || pairs ? kAligned : kDw ? kUnaligned : (P == 1 && Pin == 1) ? kRows : (stride == 1 && P >= 4) ? kUnaligned : kStrided;
         // Most pixels per lane, one group per wavefront.  Strided: a pair is two loads and two stores anyway; it
         // pays where the multiply reads fewer LDS rows for it, not for a few wide groups, whose launch is staging
         // and better spread over twice the tiles (stride 2: 64->32 @97x97, N=45, V=8, bfloat16 18.3 us as pairs, 14.0
@@ -2472,8 +2509,10 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
         // wavefront meets a seam, and where the stores are most of the launch the pixel-by-pixel ones beside it cost
         // more than the quads save (75->1016 @7x7, N=198, V=16 54 us as quads, 28 not).
         const bool few_wide = V >= 8 && L.nbundles < 16, seams = V >= 8 && P < 256 && Cout >= 2 * Cin;
-        const int pv_can = ac == kRows ? 1 : ac == kStrided ? 2 : 4;
-        const int pv_most = (ac == kStrided && few_wide) || (ac == kUnaligned && (kDw ? V == 16 : seams)) ? 1 : pv_can;
+        // (pairs of 16-byte loads: the same, and quads only without a residual - 32->416 @56x56, N=177, V=4 119.6 us in quads,
+        // 115.9 not; 19->120 @112x128, N=9, V=16 8.8 us in quads, 6.7 with one pixel)
+        const int pv_can = ac == kRows ? 1 : ac == kStrided || (pairs && residual_dev) ? 2 : 4;
+        const int pv_most = ((ac == kStrided || pairs) && few_wide) || (ac == kUnaligned && (kDw ? V == 16 : seams)) ? 1 : pv_can;
         // streaming kernel: everything (two input tiles, packed weights) fits in LDS and
         // there are enough pixels to give every compute unit several tiles
         bool stream_ok = false;
@@ -2681,7 +2720,7 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
                 case 8: kern = pick_resident<8, true>(pv, ac, GS, a.residual != nullptr); break;
                 case 16: kern = pick_resident<16, true>(pv, ac, GS, a.residual != nullptr); break;
             }
-            if (GS == 4 && pv == 2 && vec && mfma && (long long)a.npt * a.ngt > 2LL * kCUs &&
+            if (GS == 4 && pv == 2 && ac == kAligned && mfma && (long long)a.npt * a.ngt > 2LL * kCUs &&
                 ((long long)P * sizeof(io_t)) % 128 != 0) {
                 switch (V) {
                     case 4: kern = k_pw_resident_cached<4>; break;

@@ -223,6 +223,49 @@ __device__ __forceinline__ void stage(const Args &a, char *lds, int q0, int q_en
     constexpr int TP = 64 * PV, RB = 128 * PV;
     const int tid = threadIdx.x, nt = blockDim.x;
     if constexpr (VEC) {
+        if (a.stride == 2) {
+            // a quad of output pixels is two pairs, each inside one row: every other element of 8 bytes (W is a multiple of 4;
+            // 35->160 @56x56, N=176, V=4 37.8 us one element at a time, 22.3 this way, 16->96 @112x112, N=146 42.7 and 27.7)
+            constexpr int NQ = TP / 4;
+            const int quad = tid % NQ, r0 = tid / NQ, rpp = nt / NQ;
+            const int q = q0 + quad * 4;
+            const bool valid = q < q_end;
+            const int n = valid ? q / a.P : 0;
+            const int p = valid ? q - n * a.P : 0;
+            const int h0 = p / a.Wo, w0 = p - h0 * a.Wo;
+            const bool wraps = w0 + 2 >= a.Wo;
+            const uint16_t *img = a.X + ((size_t)n * a.Cin) * a.Pin;
+            const uint16_t *src0 = img + (size_t)(2 * h0) * a.W + 2 * w0;
+            const uint16_t *src1 = img + (size_t)(2 * (h0 + wraps)) * a.W + (wraps ? 0 : 2 * (w0 + 2));
+            char *dst = lds + quad * 8;
+            constexpr int U = 4;
+            int r = r0;
+            for (; r + (U - 1) * rpp < a.Cin; r += U * rpp) {
+                u2 v[U], w[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    v[u] = w[u] = u2{0u, 0u};
+                    if (valid) {
+                        v[u] = *reinterpret_cast<const u2 *>(src0 + (size_t)(r + u * rpp) * a.Pin);
+                        w[u] = *reinterpret_cast<const u2 *>(src1 + (size_t)(r + u * rpp) * a.Pin);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    *reinterpret_cast<u2 *>(dst + (r + u * rpp) * RB) =
+                        u2{__builtin_amdgcn_perm(v[u].y, v[u].x, 0x05040100u), __builtin_amdgcn_perm(w[u].y, w[u].x, 0x05040100u)};
+            }
+            for (; r < a.Cin; r += rpp) {
+                u2 v = u2{0u, 0u}, w = v;
+                if (valid) {
+                    v = *reinterpret_cast<const u2 *>(src0 + (size_t)r * a.Pin);
+                    w = *reinterpret_cast<const u2 *>(src1 + (size_t)r * a.Pin);
+                }
+                *reinterpret_cast<u2 *>(dst + r * RB) =
+                    u2{__builtin_amdgcn_perm(v.y, v.x, 0x05040100u), __builtin_amdgcn_perm(w.y, w.x, 0x05040100u)};
+            }
+            return;
+        }
         if ((a.P & 7) == 0) {
             typedef unsigned int u4 __attribute__((ext_vector_type(4)));
             constexpr int NO = TP / 8;
@@ -544,7 +587,7 @@ extern "C" int alcs_sparse_conv_bf16_mfma(const alcs_packed_t *Wp, const uint16_
     a.N = N; a.Cin = Cin; a.Cout = Cout; a.H = H; a.W = W; a.Ho = Ho; a.Wo = Wo; a.stride = stride;
     a.P = (int)P; a.Pin = (int)Pin; a.NP = (int)NP;
     a.G = Wp->G;
-    const bool vec = stride == 1 && P % 4 == 0;
+    const bool vec = (stride == 1 || W % 4 == 0) && P % 4 == 0;
     // Two pixels per lane (128-pixel tiles, 256-byte rows) where the rows fit; one pixel per lane
     // (64-pixel tiles) beyond 638 input channels and for fewer than 4096 pixels in all, where the
     // many group tiles of a 128-pixel tile each stage twice the rows (512->1024 @7x7, N=32: 13.5 ->
