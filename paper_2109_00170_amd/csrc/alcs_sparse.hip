@@ -1418,6 +1418,12 @@ __device__ __forceinline__ void commit_rows(const ConvArgs &a, f4 (&v)[U], float
     }
 }
 
+// The wavefront's u-th group of a group tile: dealt in snake order over the length-sorted list, so that every wavefront has
+// as many groups, give or take one, and of as much work (33 groups were 32 and one, and 17 of them five wavefronts' work:
+// 60 3x3 layers of mixed shapes 1.06x as fast in the mean; 100->130 @57x43 stride 2, N=9 25.6 -> 23.3 us, 88->130 @112x112, N=10
+// 190 -> 133).
+__device__ __forceinline__ int dealt(int u, int wave, int nw) { return u * nw + ((u & 1) ? nw - 1 - wave : wave); }
+
 // Kernels that walk chunks (1x1 of many input channels, 3x3), in launches that would leave compute units idle: a wavefront
 // has one group, and a.ksplit wavefronts share it, each with a part of its columns in every chunk (k_pw_chunked_split,
 // k_conv3_split).  A launch of a few workgroups is a chain of chunks, each staged and then multiplied by wavefronts with
@@ -1506,7 +1512,7 @@ __global__ void __launch_bounds__(512) k_pw_chunked(const ConvArgs a) {
     Acc<V, PV, MF> acc[UG];
 #pragma unroll
     for (int u = 0; u < UG; ++u) {
-        const int idx = wave * UG + u;
+        const int idx = dealt(u, wave, blockDim.x >> 6);
         slot[u] = idx < ng ? g_begin + idx : -1;
         acc[u].zero();
     }
@@ -1845,7 +1851,7 @@ __global__ void __launch_bounds__(512) k_conv3(const ConvArgs a) {
     Acc<V, PV, MF> acc[UG];
 #pragma unroll
     for (int u = 0; u < UG; ++u) {
-        const int idx = wave * UG + u;
+        const int idx = dealt(u, wave, blockDim.x >> 6);
         slot[u] = idx < ng ? g_begin + idx : -1;
         acc[u].zero();
     }
@@ -2785,8 +2791,8 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             if (L.GS != 1) return ALCS_E_UNSUPPORTED;
             ug = pick_ug(G, nw, T.ug);
             if (V * pv * ug > 128) ug = 2;  // accumulators of 4 groups would not fit the register file
-            a.gpt = nw * ug;
-            a.ngt = ceil_div(G, a.gpt);
+            a.ngt = ceil_div(G, nw * ug);
+            a.gpt = ceil_div(G, a.ngt);
             const int pnw = ac == kRows ? 16 : 8;
             if (pv == 1 && T.waves == 0 && T.ug == 0 && pick_parts(kCUs, pnw, ug, a)) {
                 nw = pnw;
@@ -2834,8 +2840,8 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
         // per wavefront, so that two workgroups share a compute unit and one stages a chunk
         // while the other multiplies (512->512 @7x7, N=64: 102 -> 89 us).
         if (T.ug == 0 && ug == 4 && (long long)a.npt * ceil_div(G, nw * 4) <= kCUs && 2 * lds <= kMaxLds) ug = 2;
-        a.gpt = nw * ug;
-        a.ngt = ceil_div(G, a.gpt);
+        a.ngt = ceil_div(G, nw * ug);
+        a.gpt = ceil_div(G, a.ngt);
         if (T.waves == 0 && T.ug == 0 && pick_parts(kCUs, 16, ug, a)) {
             nw = 16;
             lds = std::max(lds, a.ksplit > 1 ? nw * V * pv * 64 * 4 : 0);
