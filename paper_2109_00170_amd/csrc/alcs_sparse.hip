@@ -2388,7 +2388,20 @@ static int pick_ug(int G, int nw, int forced) {
 // stages the tile's rows again (256->256 @14x14, N=4, 80 % sparse: 19.5 us in up to 256 workgroups, 36.5 in up to 512; 4096->1000
 // on 256 rows 65 and 125), and launches that fill the chip already keep their several groups per wavefront (128->128 @28x28, N=10:
 // 23 us, 34 as parts).
-static bool pick_parts(int cus, int nw, int &ug, ConvArgs &a) {
+// alone: chunks so large (3x3, 64 channels) that one workgroup fills a compute unit's LDS.  Eight wavefronts with several groups
+// each then have nobody to cover their waits for a chunk, 16 with the next chunk on its way do: 680->24 @56x56, N=58, V=4
+// 501 -> 359 us, 572->36 @112x112 stride 2, N=17 360 -> 220, 664->672 @14x19 stride 2, N=15, V=2 256 -> 151; 44 layers of 512 and
+// more channels 0.97 to 1.70x.  (Where two or more workgroups share a compute unit the smaller ones win: 60 other
+// layers 0.81x in the mean as parts.)
+static bool pick_parts(int cus, int nw, int &ug, ConvArgs &a, bool alone = false) {
+    if (alone && (long long)a.npt * a.ngt >= cus) {
+        ug = 1;
+        a.ngt = ceil_div(a.G, nw);
+        a.gpt = ceil_div(a.G, a.ngt);
+        a.ksplit = 1;
+        while (a.gpt * a.ksplit * 2 <= nw) a.ksplit *= 2;
+        return true;
+    }
     if ((long long)a.npt * a.ngt >= cus) return false;
     int gpt = nw;
     while (gpt > 1 && (long long)a.npt * ceil_div(a.G, gpt / 2) <= cus) gpt /= 2;
@@ -2842,7 +2855,7 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
         if (T.ug == 0 && ug == 4 && (long long)a.npt * ceil_div(G, nw * 4) <= kCUs && 2 * lds <= kMaxLds) ug = 2;
         a.ngt = ceil_div(G, nw * ug);
         a.gpt = ceil_div(G, a.ngt);
-        if (T.waves == 0 && T.ug == 0 && pick_parts(kCUs, 16, ug, a)) {
+        if (T.waves == 0 && T.ug == 0 && pick_parts(kCUs, 16, ug, a, 2 * lds > kMaxLds)) {
             nw = 16;
             lds = std::max(lds, a.ksplit > 1 ? nw * V * pv * 64 * 4 : 0);
         }

@@ -72,3 +72,11 @@ def test_fully_connected_chunks(V, N, Cin):
 @pytest.mark.parametrize("V,H,W,stride", [(2, 6, 6, 1), (2, 5, 5, 1), (1, 9, 7, 2), (2, 1, 3, 1)])
 def test_1x1_chunks_on_images(V, H, W, stride):
     check(workloads.Layer("pw", 700, 30, H, W, stride=stride, N=2, V=V, sparsity=0.8, w_std=0.1), 8600 + H + W)
+
+
+# launches of more workgroups than compute units whose chunks leave room for one workgroup on each
+@pytest.mark.parametrize("V,groups,stride,H,shared,waves", [(4, 5, 1, 12, False, 2), (4, 17, 1, 12, True, 1), (8, 16, 1, 12, False, 1),
+                                                            (1, 33, 2, 13, False, 1), (16, 3, 2, 13, True, 4), (2, 1, 2, 13, True, 16)])
+def test_3x3_large_chunks_in_many_workgroups(V, groups, stride, H, shared, waves):
+    L = workloads.Layer("alone", 75, V * groups - (V > 1), H, H, k=3, stride=stride, N=259, V=V, sparsity=0.8, w_std=0.1, tap_shared=shared)
+    check(L, 8700 + V + groups, bundle_waves=waves, options={"chunk_channels": 64})
