@@ -1013,6 +1013,97 @@ __global__ void __launch_bounds__(256) k_dense_gather(const DenseArgs a) {
     }
 }
 
+// Few tiles and many channels: 32 x 32 outputs per workgroup, whose 16 wavefronts share the channels.  On the staged tiles
+// such a launch is one chain of steps on a few compute units; here a wavefront has a sixteenth of the channels, loads its
+// operands for the float32 instruction straight from memory (nothing is read twice inside a wavefront but taps), one unit
+// ahead, and the sixteen sums meet in LDS.  A unit is two channels x 9 taps (3x3; lane half h has one) or 8 channels
+// (1x1; half h has four).  What bounds it is the float32 instruction and the taps' loads, a microsecond and a half a unit
+// round.  3x3: 128->8 @28x28, N=4 28 -> 11 us, 271->46 @28x28, N=2 58 -> 21, 832->24 @14x14, N=2 164 -> 55, 472->48 @20x20, N=10
+// 99 -> 37; 1x1: 264->184 @14x14, one image 11.5 -> 6.8, 895->32 @4x4, N=3 27 -> 12.  Sixteen short sums are also closer to
+// 64 bits than one long one: 1.2e-7 against 4.8e-7 at 184 channels x 9 taps.
+template <int KK>
+__global__ void __launch_bounds__(1024) k_dense_few(const DenseArgs a) {
+    constexpr int NW = 16, CU = KK == 9 ? 2 : 8, E = KK == 9 ? 9 : 4;  // wavefronts, channels per unit, elements per lane
+    __shared__ float red[NW][16][64];
+    const int id = blockIdx.x;
+    const int logical = (id % a.xcds) * a.wg_per_xcd + id / a.xcds;
+    if (logical >= a.total_wgs) return;
+    const int ntile = logical / a.mt, mtile = logical - ntile * a.mt;
+    const int m0 = mtile * 32;
+    const long long q0 = (long long)ntile * 32;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = lane >> 5, l32 = lane & 31;
+    const long long q = q0 + l32 < a.NP ? q0 + l32 : a.NP - 1;
+    const int n = (int)(q / a.P), p = (int)(q - (long long)n * a.P);
+    const int ho = p / a.Wo, wo = p - ho * a.Wo;
+    const float *w = a.Wt + (size_t)min(m0 + l32, a.Cout - 1) * a.K;
+    const float *x = a.X + (size_t)n * a.Cin * a.Pin;
+    // taps of the lane's pixel: offset inside a channel (0 where the tap lies outside), and which are there
+    int off[KK];
+    unsigned int there = 0;
+#pragma unroll
+    for (int t = 0; t < KK; ++t) {
+        const int iy = ho * a.stride + (KK == 9 ? t / 3 - 1 : 0), ix = wo * a.stride + (KK == 9 ? t % 3 - 1 : 0);
+        const bool in = iy >= 0 && iy < a.H && ix >= 0 && ix < a.W;
+        off[t] = in ? iy * a.W + ix : 0;
+        there |= (in ? 1u : 0u) << t;
+    }
+    struct Unit {
+        float a[E], b[E];
+    };
+    const int units = (a.Cin + CU - 1) / CU;
+    // (every load from an address that is valid; channels that are not there become zeros when they are used)
+    auto load = [&](int u, Unit &v) __attribute__((always_inline)) {
+        if constexpr (KK == 9) {
+            const int c = min(2 * u + h, a.Cin - 1);
+            const float *ws = w + (size_t)c * 9, *xs = x + (size_t)c * a.Pin;
+            const f4 w0 = *reinterpret_cast<const f4u *>(ws), w1 = *reinterpret_cast<const f4u *>(ws + 4);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) { v.a[t] = w0[t]; v.a[4 + t] = w1[t]; }
+            v.a[8] = ws[8];
+#pragma unroll
+            for (int t = 0; t < 9; ++t) v.b[t] = xs[off[t]];
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int c = min(8 * u + 4 * h + t, a.Cin - 1);
+                v.a[t] = w[c];
+                v.b[t] = x[(size_t)c * a.Pin + off[0]];
+            }
+        }
+    };
+    f16v acc[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.f;
+    auto multiply = [&](int u, const Unit &v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < E; ++t) {
+            const bool in = (KK == 9 ? 2 * u + h : 8 * u + 4 * h + t) < a.Cin;
+            const float wa = in ? v.a[t] : 0.f, xb = in && (KK == 1 || (there >> t & 1)) ? v.b[t] : 0.f;
+            acc[t & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(wa, xb, acc[t & 1], 0, 0, 0);
+        }
+    };
+    Unit v0, v1;
+    int u = wave;
+    if (u < units) load(u, v0);
+    for (; u < units; u += 2 * NW) {
+        if (u + NW < units) load(u + NW, v1);
+        multiply(u, v0);
+        if (u + NW >= units) break;
+        if (u + 2 * NW < units) load(u + 2 * NW, v0);
+        multiply(u + NW, v1);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[0][r] + acc[1][r];
+    __syncthreads();
+    // register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32: wavefront r finishes register r of all
+    const int o = m0 + 8 * (wave >> 2) + 4 * h + (wave & 3);
+    float sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) sum += red[k][wave][lane];
+    if (o < a.Cout && q0 + l32 < a.NP) a.Y[((size_t)n * a.Cout + o) * a.P + p] = sum + (a.bias ? a.bias[o] : 0.f);
+}
+
 typedef void (*dense_t)(const DenseArgs);
 static dense_t pick_dense(int kernel, const DensePlan &p) {
     if (p.kind == kDenseGather) return p.bm == 128 ? k_dense_gather<128> : k_dense_gather<64>;
@@ -1060,7 +1151,8 @@ extern "C" int alcs_dense_conv(const float *W_dev, const float *X_dev, const flo
     if (current_device_shape(&cus, &xcds) != ALCS_OK) return ALCS_E_HIP;
     a.xcds = xcds;
     const DensePlan plan = dense_plan(N, Cin, Cout, H, W, kernel, stride, cus);
-    const int BM = plan.bm, BN = plan.bn;
+    const bool few = dense_few(plan, a.NP, Cout, cus);
+    const int BM = few ? 32 : plan.bm, BN = few ? 32 : plan.bn;
     a.npos = plan.npos;
     const long long ntile = (a.NP + BN - 1) / BN;
     a.mt = (Cout + BM - 1) / BM;
@@ -1069,12 +1161,12 @@ extern "C" int alcs_dense_conv(const float *W_dev, const float *X_dev, const flo
     a.nt = (int)ntile;
     a.total_wgs = (int)total;
     a.wg_per_xcd = (int)((total + xcds - 1) / xcds);
-    const dense_t kern = pick_dense(kernel, plan);
-    if (plan.kind != kDenseGather) {
+    const dense_t kern = few ? (kernel == 3 ? k_dense_few<9> : k_dense_few<1>) : pick_dense(kernel, plan);
+    if (!few && plan.kind != kDenseGather) {
         const int rc = allow_lds((const void *)kern, plan.lds);
         if (rc != ALCS_OK) return rc;
     }
-    hipLaunchKernelGGL(kern, dim3(a.wg_per_xcd * xcds), dim3(plan.threads), plan.lds, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(kern, dim3(a.wg_per_xcd * xcds), dim3(few ? 1024 : plan.threads), few ? 0 : plan.lds, (hipStream_t)stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_hip_error((int)e); return ALCS_E_HIP; }
     return ALCS_OK;
