@@ -147,15 +147,18 @@ __device__ __forceinline__ void io_store4u(io_t *p, f4 v) { __builtin_nontempora
 #endif
 
 // How a kernel reaches the pixels of its tile in memory (a choice of the launcher, by the shape):
-//   kAligned    output pixels per image a multiple of 4: four neighbours are 16 bytes, aligned; at stride 1 in X as
-//               well, at stride 2 (input width a multiple of 4) two of them are every other word of 16 bytes of X
+//   kAligned    stride 1, pixels per image a multiple of 4: four neighbours are 16 bytes, aligned
+//   kPairs      stride 2, input width and output pixels per image multiples of 4: stored as kAligned, two neighbours
+//               are every other word of 16 bytes of X.  (A form of its own and no branch inside kAligned, whose kernels
+//               took 1 to 14 more registers for it and spilled scalars: 744->192 @28x30, N=66, V=1 326 us, 309 without.)
 //   kUnaligned  stride 1, any other image of at least 4 pixels: 16 bytes at any address, and a quad
 //               may run from one image into the next
 //   kStrided    any other image at stride 2, or of fewer than 4 pixels: one pixel at a time
 //   kRows       images of one pixel (a fully connected layer): the channels of a pixel are the
 //               contiguous axis, read 16 bytes at a time and transposed on the way into LDS
 //   kScattered  stores only: a lane's pixels lie in different rows (3x3 kernels)
-enum Access { kAligned = 0, kUnaligned = 1, kStrided = 2, kRows = 3, kScattered = 4 };
+enum Access { kAligned = 0, kUnaligned = 1, kStrided = 2, kRows = 3, kScattered = 4, kPairs = 5 };
+constexpr bool quads_out(int ac) { return ac == kAligned || ac == kPairs; }  // four output pixels are 16 bytes, aligned
 // An ordinary (write-back) store of two elements: for runs that cover cache lines only in part and
 // whose neighbours are written soon after by the same workgroup, so that the L2 merges them into
 // whole lines before they leave for memory.
@@ -596,18 +599,21 @@ template <int TP, int AC>
 __device__ __forceinline__ void stage_pw(const ConvArgs &a, float *lds, int q0, int c0, int c1, int q_end) {
     const int tid = threadIdx.x, nt = blockDim.x;
     const int rows = c1 - c0;
-    if constexpr (AC == kAligned) {
+    if constexpr (quads_out(AC)) {
         constexpr int NQ = TP / 4;
         const int quad = tid % NQ, r0 = tid / NQ, rpp = nt / NQ;
         const int q = q0 + quad * 4;
         const bool valid = q < q_end;
-        const int n = valid ? q / a.P : 0;
-        const int p = valid ? q - n * a.P : 0;
         float *dst = lds + quad * 4;
-        if (a.stride == 2) {
+        if constexpr (AC == kPairs) {
             // A quad is two pairs of neighbours, each inside one row (rows have an even number of pixels): two 16-byte loads
             // for what took four of 4 bytes, one pixel at a time (60 layers of mixed shapes 1.17x as fast; 168->24 @112x112, N=6,
             // V=4, bfloat16 15.8 -> 9.7 us, 117->48 @112x112, N=18, V=1 20.3 -> 14.4, 256->512 @56x56, N=64 96 -> 94).
+            // (The launcher gives no other stride.  The test stays because the compiler then asks for the arguments used below
+            // together with the first ones: 36 layers 0.985x without it, most of them launches of 4 to 6 us.)
+            if (a.stride != 2) return;
+            const int n = valid ? q / a.P : 0;
+            const int p = valid ? q - n * a.P : 0;
             const int h0 = p / a.Wo, w0 = p - h0 * a.Wo;
             const bool wraps = w0 + 2 >= a.Wo;
             const int h1 = h0 + wraps, w1 = wraps ? 0 : w0 + 2;
@@ -638,6 +644,8 @@ __device__ __forceinline__ void stage_pw(const ConvArgs &a, float *lds, int q0, 
             }
             return;
         }
+        const int n = valid ? q / a.P : 0;
+        const int p = valid ? q - n * a.P : 0;
         const io_t *src = a.X + ((size_t)n * a.Cin + c0) * a.P + p;
         constexpr int U = 8;  // independent 16-byte loads in flight per thread
         int r = r0;
@@ -946,7 +954,7 @@ __device__ __forceinline__ void pix_out(const ConvArgs &a, int q0, int lane, Pix
     for (int pv = 0; pv < PV; ++pv) {
         const int q = q0 + lane * PV + pv;
         px.valid[pv] = q < q_end;
-        if (AC == kAligned && pv > 0) {
+        if (quads_out(AC) && pv > 0) {
             px.yoff[pv] = px.yoff[0] + pv;
         } else if (AC == kRows) {
             px.yoff[pv] = px.valid[pv] ? (long long)q * a.Cout : 0;
@@ -961,7 +969,7 @@ __device__ __forceinline__ void pix_out(const ConvArgs &a, int q0, int lane, Pix
 template <int PV, int AC>
 __device__ __forceinline__ bool together(const PixOut<PV> &px) {
     if constexpr (PV == 1 || AC == kScattered || AC == kRows) return false;
-    if constexpr (AC == kAligned) return px.valid[0];
+    if constexpr (quads_out(AC)) return px.valid[0];
     return px.valid[PV - 1] && px.yoff[PV - 1] == px.yoff[0] + (PV - 1);
 }
 
@@ -971,15 +979,15 @@ __device__ __forceinline__ void load_pixels(const io_t *p, const PixOut<PV> &px,
     if constexpr (PV > 1 && AC != kScattered && AC != kRows) {
         if (together<PV, AC>(px)) {
             if constexpr (PV == 4) {
-                const f4 t = AC == kAligned ? io_load4(p + px.yoff[0]) : io_load4u(p + px.yoff[0]);
+                const f4 t = quads_out(AC) ? io_load4(p + px.yoff[0]) : io_load4u(p + px.yoff[0]);
                 x[0] = t[0]; x[1] = t[1]; x[2] = t[2]; x[3] = t[3];
             } else {
-                const f2 t = AC == kAligned ? io_load2(p + px.yoff[0]) : io_load2u(p + px.yoff[0]);
+                const f2 t = quads_out(AC) ? io_load2(p + px.yoff[0]) : io_load2u(p + px.yoff[0]);
                 x[0] = t[0]; x[1] = t[1];
             }
             return;
         }
-        if constexpr (AC == kAligned) return;
+        if constexpr (quads_out(AC)) return;
     }
 #pragma unroll
     for (int pv = 0; pv < PV; ++pv)
@@ -990,16 +998,16 @@ __device__ __forceinline__ void store_pixels(io_t *p, const PixOut<PV> &px, cons
     if constexpr (PV > 1 && AC != kScattered && AC != kRows) {
         if (together<PV, AC>(px)) {
             if constexpr (PV == 4) {
-                if constexpr (AC == kAligned) io_store4(p + px.yoff[0], f4{x[0], x[1], x[2], x[3]});
+                if constexpr (quads_out(AC)) io_store4(p + px.yoff[0], f4{x[0], x[1], x[2], x[3]});
                 else io_store4u(p + px.yoff[0], f4{x[0], x[1], x[2], x[3]});
             } else {
                 if constexpr (CACHED) io_store2_cached(p + px.yoff[0], f2{x[0], x[1]});
-                else if constexpr (AC == kAligned) io_store2(p + px.yoff[0], f2{x[0], x[1]});
+                else if constexpr (quads_out(AC)) io_store2(p + px.yoff[0], f2{x[0], x[1]});
                 else io_store2u(p + px.yoff[0], f2{x[0], x[1]});
             }
             return;
         }
-        if constexpr (AC == kAligned) return;
+        if constexpr (quads_out(AC)) return;
     }
 #pragma unroll
     for (int pv = 0; pv < PV; ++pv)
@@ -1267,9 +1275,9 @@ __global__ void __launch_bounds__(1024) k_pw_resident(const ConvArgs a) {
 // A tile's runs then cover lines in part, the neighbouring tiles - workgroups next in line, on the
 // same L2 - write the rest at about the same time, and the L2 merges them into whole lines
 // (512->512 @14x14, N=256, 90 % sparse: 89 -> 81 us; in a single round the streaming stores win).
-template <int V>
+template <int V, int AC>
 __global__ void __launch_bounds__(1024) k_pw_resident_cached(const ConvArgs a) {
-    pw_resident_body<V, 2, true, kAligned, 4, kNone, true>(a);
+    pw_resident_body<V, 2, true, AC, 4, kNone, true>(a);
 }
 // The same walk with a residual, one group per wavefront (fused epilogue).
 template <int V, int PV, bool MF, int AC>
@@ -2247,7 +2255,7 @@ template <int V, bool MF, int AC>
 static kern_t pick_resident_ac(int pv, int gs, bool res) {
     if constexpr (kFused) {
         if (res && gs == 1) {
-            if constexpr (AC == kAligned || AC == kUnaligned) {
+            if constexpr (quads_out(AC) || AC == kUnaligned) {
                 if (pv == 4) return k_pw_resident_res<V, 4, MF, AC>;
             }
             if constexpr (AC != kRows) {
@@ -2257,14 +2265,14 @@ static kern_t pick_resident_ac(int pv, int gs, bool res) {
         }
     }
     if constexpr (MF) {
-        if constexpr (AC == kAligned || AC == kUnaligned) {
+        if constexpr (quads_out(AC) || AC == kUnaligned) {
             if (gs == 2 && pv == 2) return k_pw_resident<V, 2, true, AC, 2>;
         }
         if (gs == 4 && pv == 2) return k_pw_resident<V, 2, true, AC, 4>;
         if (gs == 2) return k_pw_resident<V, 1, true, AC, 2>;
         if (gs == 4) return k_pw_resident<V, 1, true, AC, 4>;
     }
-    if constexpr (AC == kAligned || AC == kUnaligned) {
+    if constexpr (quads_out(AC) || AC == kUnaligned) {
         if (pv == 4) return k_pw_resident<V, 4, MF, AC, 1>;
     }
     if constexpr (AC != kRows) {
@@ -2276,10 +2284,19 @@ template <int V, bool MF>
 static kern_t pick_resident(int pv, Access ac, int gs, bool res = false) {
     if (ac == kAligned) return pick_resident_ac<V, MF, kAligned>(pv, gs, res);
     if constexpr (!kDw) {
+        if (ac == kPairs) return pick_resident_ac<V, MF, kPairs>(pv, gs, res);
         if (ac == kStrided) return pick_resident_ac<V, MF, kStrided>(pv, gs, res);
         if (ac == kRows) return pick_resident_ac<V, MF, kRows>(pv, gs, res);
     }
     return pick_resident_ac<V, MF, kUnaligned>(pv, gs, res);
+}
+
+template <int V>
+static kern_t pick_cached(Access ac) {
+    if constexpr (!kDw) {
+        if (ac == kPairs) return k_pw_resident_cached<V, kPairs>;
+    }
+    return k_pw_resident_cached<V, kAligned>;
 }
 
 template <int V, int AC>
@@ -2291,6 +2308,7 @@ template <int V>
 static kern_t pick_split(int pv, Access ac, int gs) {
     if (ac == kAligned) return pick_split_ac<V, kAligned>(pv, gs);
     if constexpr (!kDw) {
+        if (ac == kPairs) return pick_split_ac<V, kPairs>(pv, gs);
         if (ac == kStrided) return pick_split_ac<V, kStrided>(pv, gs);
         if (ac == kRows) return pick_split_ac<V, kRows>(pv, gs);
     }
@@ -2314,6 +2332,7 @@ static kern_t pick_chunked_ac(int pv, int ug) {
 template <int V, bool MF>
 static kern_t pick_chunked(int pv, Access ac, int ug) {
     if (ac == kAligned) return pick_chunked_ac<V, MF, kAligned>(pv, ug);
+    if (ac == kPairs) return pick_chunked_ac<V, MF, kPairs>(pv, ug);
     if (ac == kStrided) return pick_chunked_ac<V, MF, kStrided>(pv, ug);
     if (ac == kRows) return pick_chunked_ac<V, MF, kRows>(pv, ug);
     return pick_chunked_ac<V, MF, kUnaligned>(pv, ug);
@@ -2520,7 +2539,7 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
         const bool vec = stride == 1 && (P % 4 == 0);
         // (the images end with whole 16 bytes, and so does every row: nothing beyond the tensor is read)
         const bool pairs = !kDw && stride == 2 && W % 4 == 0 && P % 4 == 0;
-        const Access ac = vec || pairs ? kAligned : kDw ? kUnaligned : (P == 1 && Pin == 1) ? kRows : (stride == 1 && P >= 4) ? kUnaligned : kStrided;
+        const Access ac = vec ? kAligned : pairs ? kPairs : kDw ? kUnaligned : (P == 1 && Pin == 1) ? kRows : (stride == 1 && P >= 4) ? kUnaligned : kStrided;
         // Most pixels per lane, one group per wavefront.  Strided: a pair is two loads and two stores anyway; it
         // pays where the multiply reads fewer LDS rows for it, not for a few wide groups, whose launch is staging
         // and better spread over twice the tiles (stride 2: 64->32 @97x97, N=45, V=8, bfloat16 18.3 us as pairs, 14.0
@@ -2677,7 +2696,7 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             // (same 32-pixel tile; 512->512 @14x14: 17.4 -> 15.7 us).
             if (GS > 1) {
                 pv = (GS == 4 && (long long)(Cin + 2) * 32 * 4 <= kMaxLds) ? 2 : 1;
-                if (T.pv == 1 || (T.pv == 2 && (GS == 4 || ac == kAligned || ac == kUnaligned))) pv = T.pv;
+                if (T.pv == 1 || (T.pv == 2 && (GS == 4 || quads_out(ac) || ac == kUnaligned))) pv = T.pv;
             }
             const int TP = 64 * pv / GS;
             lds = (Cin + (GS > 1 ? 2 : 1)) * TP * 4;  // the rows and the zero row(s)
@@ -2739,12 +2758,12 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
                 case 8: kern = pick_resident<8, true>(pv, ac, GS, a.residual != nullptr); break;
                 case 16: kern = pick_resident<16, true>(pv, ac, GS, a.residual != nullptr); break;
             }
-            if (GS == 4 && pv == 2 && ac == kAligned && mfma && (long long)a.npt * a.ngt > 2LL * kCUs &&
+            if (GS == 4 && pv == 2 && quads_out(ac) && mfma && (long long)a.npt * a.ngt > 2LL * kCUs &&
                 ((long long)P * sizeof(io_t)) % 128 != 0) {
                 switch (V) {
-                    case 4: kern = k_pw_resident_cached<4>; break;
-                    case 8: kern = k_pw_resident_cached<8>; break;
-                    case 16: kern = k_pw_resident_cached<16>; break;
+                    case 4: kern = pick_cached<4>(ac); break;
+                    case 8: kern = pick_cached<8>(ac); break;
+                    case 16: kern = pick_cached<16>(ac); break;
                 }
             }
             // A kernel that holds more than 64 registers per lane fits fewer than 32 wavefronts

@@ -215,15 +215,18 @@ __device__ __forceinline__ void mac_segment(const Args &a, int start, int cnt, c
     for (int j0 = 16 * kRunsAhead; j0 < cnt; j0 += 16 * kRunsAhead) pass(j0);
 }
 
-// The tile's rows (64 * PV pixels, 128 * PV bytes each) from HBM to LDS.  VEC: stride 1 and P a
+// The tile's rows (64 * PV pixels, 128 * PV bytes each) from HBM to LDS.  kQuads: stride 1 and P a
 // multiple of 4, so that four consecutive pixels of the flattened axis lie in one image and their 8
-// bytes are aligned; with P a multiple of 8, eight pixels (16 bytes) per lane.
-template <int PV, bool VEC>
+// bytes are aligned; with P a multiple of 8, eight pixels (16 bytes) per lane.  kPairs: stride 2, W and P multiples
+// of 4, the same on the way out (a form of its own: the registers of a branch are paid by every kernel that has it).
+// kPixels: any other image, one element at a time.
+enum Access { kPixels = 0, kQuads = 1, kPairs = 2 };
+template <int PV, int AC>
 __device__ __forceinline__ void stage(const Args &a, char *lds, int q0, int q_end) {
     constexpr int TP = 64 * PV, RB = 128 * PV;
     const int tid = threadIdx.x, nt = blockDim.x;
-    if constexpr (VEC) {
-        if (a.stride == 2) {
+    if constexpr (AC != kPixels) {
+        if constexpr (AC == kPairs) {
             // a quad of output pixels is two pairs, each inside one row: every other element of 8 bytes (W is a multiple of 4;
             // 35->160 @56x56, N=176, V=4 37.8 us one element at a time, 22.3 this way, 16->96 @112x112, N=146 42.7 and 27.7)
             constexpr int NQ = TP / 4;
@@ -349,10 +352,10 @@ struct PixOut {
     bool ok[PV];
 };
 
-template <int PV, bool VEC>
+template <int PV, int AC>
 __device__ __forceinline__ PixOut<PV> pix_out(const Args &a, int q0, int lane, int q_end) {
     PixOut<PV> px;
-    if constexpr (VEC && PV == 2) {
+    if constexpr (AC != kPixels && PV == 2) {
         const int q = q0 + 2 * lane;  // P is even: both pixels lie in one image
         px.ok[0] = px.ok[1] = q < q_end;
         const int n = px.ok[0] ? q / a.P : 0;
@@ -376,7 +379,7 @@ __device__ __forceinline__ float activate(const Args &a, float v) {
     return v;
 }
 
-template <int V, int PV, bool VEC>
+template <int V, int PV, int AC>
 __device__ __forceinline__ void store_group(const Args &a, const Acc<V, PV> &acc, int g, const PixOut<PV> &px) {
     const cptr<float> bias = (cptr<float>)(uintptr_t)a.bias;
 #pragma unroll
@@ -387,7 +390,7 @@ __device__ __forceinline__ void store_group(const Args &a, const Acc<V, PV> &acc
             if (ch >= a.Cout) continue;
             const float b = a.bias ? bias[ch] : 0.f;
             const size_t co = (size_t)ch * a.P;
-            if constexpr (VEC && PV == 2) {
+            if constexpr (AC != kPixels && PV == 2) {
                 if (!px.ok[0]) continue;
                 float v0 = acc.get(q, 0, i) + b, v1 = acc.get(q, 1, i) + b;
                 if (a.residual) {
@@ -409,7 +412,7 @@ __device__ __forceinline__ void store_group(const Args &a, const Acc<V, PV> &acc
         }
 }
 
-template <int V, int PV, bool VEC>
+template <int V, int PV, int AC>
 __global__ void __launch_bounds__(1024) k_pw16(const Args a) {
     extern __shared__ char lds[];
     constexpr int RB = 128 * PV;
@@ -434,12 +437,12 @@ __global__ void __launch_bounds__(1024) k_pw16(const Args a) {
         run0 = load_runs<V>(a, w0.start, w0.cnt, lane);
         if (nth(1) < ng) w1 = load_work(a.work, g_begin + nth(1));
     }
-    stage<PV, VEC>(a, lds, q0, q_end);
+    stage<PV, AC>(a, lds, q0, q_end);
     if (tid < a.zero_rows * (RB / 4)) reinterpret_cast<unsigned int *>(lds + (size_t)a.Cin * RB)[tid] = 0u;  // the zero row(s)
     __syncthreads();
     if (!any) return;
     touch_runs<V>(run0);
-    const PixOut<PV> px = pix_out<PV, VEC>(a, q0, lane, q_end);
+    const PixOut<PV> px = pix_out<PV, AC>(a, q0, lane, q_end);
     const int base = lane * 2 * PV;
     for (int k = 0;; ++k) {
         const bool more = nth(k + 1) < ng;
@@ -452,7 +455,7 @@ __global__ void __launch_bounds__(1024) k_pw16(const Args a) {
         acc.zero();
         mac_segment<V, PV>(a, w0.start, w0.cnt, lds, base, lane, run0, acc);
         if (more) touch_runs<V>(run1);
-        store_group<V, PV, VEC>(a, acc, w0.group[0], px);
+        store_group<V, PV, AC>(a, acc, w0.group[0], px);
         if (!more) break;
         w0 = w1;
         w1 = w2;
@@ -490,9 +493,9 @@ __global__ void __launch_bounds__(256) k_layout16(const Work *work, const float 
 
 typedef void (*kern_t)(const Args);
 template <int V>
-static kern_t pick(int pv, bool vec) {
-    if (pv == 2) return vec ? k_pw16<V, 2, true> : k_pw16<V, 2, false>;
-    return vec ? k_pw16<V, 1, true> : k_pw16<V, 1, false>;
+static kern_t pick(int pv, Access ac) {
+    if (pv == 2) return ac == kQuads ? k_pw16<V, 2, kQuads> : ac == kPairs ? k_pw16<V, 2, kPairs> : k_pw16<V, 2, kPixels>;
+    return ac == kQuads ? k_pw16<V, 1, kQuads> : ac == kPairs ? k_pw16<V, 1, kPairs> : k_pw16<V, 1, kPixels>;
 }
 
 static int check(hipError_t e) {
@@ -587,7 +590,7 @@ extern "C" int alcs_sparse_conv_bf16_mfma(const alcs_packed_t *Wp, const uint16_
     a.N = N; a.Cin = Cin; a.Cout = Cout; a.H = H; a.W = W; a.Ho = Ho; a.Wo = Wo; a.stride = stride;
     a.P = (int)P; a.Pin = (int)Pin; a.NP = (int)NP;
     a.G = Wp->G;
-    const bool vec = (stride == 1 || W % 4 == 0) && P % 4 == 0;
+    const m16::Access ac = P % 4 != 0 ? m16::kPixels : stride == 1 ? m16::kQuads : W % 4 == 0 ? m16::kPairs : m16::kPixels;
     // Two pixels per lane (128-pixel tiles, 256-byte rows) where the rows fit; one pixel per lane
     // (64-pixel tiles) beyond 638 input channels and for fewer than 4096 pixels in all, where the
     // many group tiles of a 128-pixel tile each stage twice the rows (512->1024 @7x7, N=32: 13.5 ->
@@ -638,9 +641,9 @@ extern "C" int alcs_sparse_conv_bf16_mfma(const alcs_packed_t *Wp, const uint16_
     a.act = activation;
     m16::kern_t kern = nullptr;
     switch (Wp->V) {
-        case 4: kern = m16::pick<4>(pv, vec); break;
-        case 8: kern = m16::pick<8>(pv, vec); break;
-        default: kern = m16::pick<16>(pv, vec); break;
+        case 4: kern = m16::pick<4>(pv, ac); break;
+        case 8: kern = m16::pick<8>(pv, ac); break;
+        default: kern = m16::pick<16>(pv, ac); break;
     }
     if (lds > 64 * 1024) {
         rc = m16::check(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
