@@ -1,0 +1,54 @@
+// The share-out of groups in the kernels that walk chunks of channels (3x3, and 1x1 of many input channels): how many
+// groups a workgroup has, and where its wavefronts have one group each or parts of one (k_conv3_split, k_pw_chunked_split).
+// Plain C++, so that the tests can ask it without a GPU.
+#pragma once
+
+namespace alcs {
+
+struct PartsShape {
+    int cus;        // compute units
+    int nw;         // wavefronts of a workgroup as parts
+    int V;          // channels of a group
+    int G;          // groups
+    int npt;        // pixel tiles
+    int ngt, gpt;   // group tiles, and groups of one, of the kernels with eight wavefronts
+    bool three;     // 3x3
+    bool alone;     // 3x3: chunks so large that one workgroup fills a compute unit's LDS
+    bool wide;      // 3x3: two pixels per lane, 8 channels, by columns (a column is twice the work)
+    bool strided;   // 1x1: rows staged one pixel at a time
+    bool stride2;   // 1x1: at stride 2
+    bool uneven;    // the longest group has more than twice the mean
+    float chunk;    // kept columns of a group, in the mean: in a chunk
+    float all;      // and in all of them
+};
+struct Parts {
+    int ngt, gpt, ksplit;  // group tiles (0: not as parts), groups of one, wavefronts that share a group
+};
+
+inline Parts parts_plan(const PartsShape &s) {
+    auto ceil_div = [](long long a, long long b) { return (int)((a + b - 1) / b); };
+    const long long wgs = (long long)s.npt * s.ngt;
+    // Launches that fill the chip, alone on their compute units: eight wavefronts with several groups each have nobody to cover
+    // their waits for a chunk, 16 with the next chunk on its way do: 680->24 @56x56, N=58, V=4 501 -> 359 us, 572->36 @112x112
+    // stride 2, N=17 360 -> 220, 664->672 @14x19 stride 2, N=15, V=2 256 -> 151; 50 layers of 512 and more channels with groups of 4 and
+    // more 1.0 to 2.0x, two of them 0.96x.  (Where two or more workgroups share a compute unit the smaller ones win: 60 other
+    // layers 0.81x in the mean as parts.)
+    if (wgs >= s.cus) {
+        if (!s.alone) return {0, 0, 0};
+        const int ngt = ceil_div(s.G, s.nw), gpt = ceil_div(s.G, ngt);
+        int ks = 1;
+        while (gpt * ks * 2 <= s.nw) ks *= 2;
+        return {ngt, gpt, ks};
+    }
+    // Fewer workgroups than compute units: as many group tiles as fill the chip once, with at most one group per wavefront;
+    // wavefronts without one share the others' columns.  One round, not two: every further workgroup stages the tile's rows again
+    // (256->256 @14x14, N=4, 80 % sparse: 19.5 us in up to 256 workgroups, 36.5 in up to 512; 4096->1000 on 256 rows 65 and 125), and
+    // launches that fill the chip already keep their several groups per wavefront (128->128 @28x28, N=10: 23 us, 34 as parts).
+    int gpt = s.nw;
+    while (gpt > 1 && (long long)s.npt * ceil_div(s.G, gpt / 2) <= s.cus) gpt /= 2;
+    const int ngt = ceil_div(s.G, gpt);
+    if (ngt <= s.ngt) return {0, 0, 0};  // no more workgroups than before
+    return {ngt, gpt, s.nw / gpt};
+}
+
+}  // namespace alcs

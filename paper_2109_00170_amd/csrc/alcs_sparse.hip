@@ -29,6 +29,7 @@
 #include <utility>
 
 #include "alcs_internal.h"
+#include "alcs_parts_plan.h"
 #if ALCS_DW_STAGE
 #include "alcs_dw_strip.h"
 #include "alcs_dw_taps.h"
@@ -2402,33 +2403,14 @@ static int pick_ug(int G, int nw, int forced) {
 }
 
 #if !ALCS_RESIDENT_ONLY
-// Launches of fewer workgroups than compute units: as many group tiles as fill the chip once, `nw` wavefronts with at most
-// one group each; wavefronts without one share the others' columns (see Part).  One round, not two: every further workgroup
-// stages the tile's rows again (256->256 @14x14, N=4, 80 % sparse: 19.5 us in up to 256 workgroups, 36.5 in up to 512; 4096->1000
-// on 256 rows 65 and 125), and launches that fill the chip already keep their several groups per wavefront (128->128 @28x28, N=10:
-// 23 us, 34 as parts).
-// alone: chunks so large (3x3, 64 channels) that one workgroup fills a compute unit's LDS.  Eight wavefronts with several groups
-// each then have nobody to cover their waits for a chunk, 16 with the next chunk on its way do: 680->24 @56x56, N=58, V=4
-// 501 -> 359 us, 572->36 @112x112 stride 2, N=17 360 -> 220, 664->672 @14x19 stride 2, N=15, V=2 256 -> 151; 44 layers of 512 and
-// more channels 0.97 to 1.70x.  (Where two or more workgroups share a compute unit the smaller ones win: 60 other
-// layers 0.81x in the mean as parts.)
-static bool pick_parts(int cus, int nw, int &ug, ConvArgs &a, bool alone = false) {
-    if (alone && (long long)a.npt * a.ngt >= cus) {
-        ug = 1;
-        a.ngt = ceil_div(a.G, nw);
-        a.gpt = ceil_div(a.G, a.ngt);
-        a.ksplit = 1;
-        while (a.gpt * a.ksplit * 2 <= nw) a.ksplit *= 2;
-        return true;
-    }
-    if ((long long)a.npt * a.ngt >= cus) return false;
-    int gpt = nw;
-    while (gpt > 1 && (long long)a.npt * ceil_div(a.G, gpt / 2) <= cus) gpt /= 2;
-    if (ceil_div(a.G, gpt) <= a.ngt) return false;  // no more workgroups than before
+// (see alcs_parts_plan.h)
+static bool pick_parts(const PartsShape &shape, int &ug, ConvArgs &a) {
+    const Parts p = parts_plan(shape);
+    if (!p.ngt) return false;
     ug = 1;
-    a.gpt = gpt;
-    a.ngt = ceil_div(a.G, gpt);
-    a.ksplit = nw / gpt;
+    a.ngt = p.ngt;
+    a.gpt = p.gpt;
+    a.ksplit = p.ksplit;
     return true;
 }
 #endif
@@ -2531,6 +2513,13 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
 
     bool mfma = V >= 4;
     if (V == 4 && T.path == 1) mfma = false;
+#if !ALCS_RESIDENT_ONLY
+    PartsShape shape{};
+    shape.cus = kCUs; shape.V = V; shape.G = G;
+    shape.uneven = (int64_t)Wp->max_count * G > 2 * Wp->nnzb;
+    shape.all = (float)Wp->nnzb / G;
+    shape.chunk = shape.all / L.nchunks;
+#endif
     kern_t kern = nullptr;
     int lds = 0, nw = 0, pv = 1, mode = 0, ug = 4, ti = 0;
     long long wg_count = 0;  // workgroups, where that is not pixel tiles x group tiles
@@ -2825,9 +2814,12 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             if (V * pv * ug > 128) ug = 2;  // accumulators of 4 groups would not fit the register file
             a.ngt = ceil_div(G, nw * ug);
             a.gpt = ceil_div(G, a.ngt);
-            const int pnw = ac == kRows ? 16 : 8;
-            if (pv == 1 && T.waves == 0 && T.ug == 0 && pick_parts(kCUs, pnw, ug, a)) {
-                nw = pnw;
+            shape.nw = ac == kRows ? 16 : 8;
+            shape.npt = a.npt; shape.ngt = a.ngt; shape.gpt = a.gpt;
+            shape.strided = ac == kStrided;
+            shape.stride2 = ac == kStrided || ac == kPairs;
+            if (pv == 1 && T.waves == 0 && T.ug == 0 && pick_parts(shape, ug, a)) {
+                nw = shape.nw;
                 lds = std::max(lds, a.ksplit > 1 ? nw * V * 64 * 4 : 0);
             }
             switch (V) {
@@ -2874,8 +2866,13 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
         if (T.ug == 0 && ug == 4 && (long long)a.npt * ceil_div(G, nw * 4) <= kCUs && 2 * lds <= kMaxLds) ug = 2;
         a.ngt = ceil_div(G, nw * ug);
         a.gpt = ceil_div(G, a.ngt);
-        if (T.waves == 0 && T.ug == 0 && pick_parts(kCUs, 16, ug, a, 2 * lds > kMaxLds)) {
-            nw = 16;
+        shape.nw = 16;
+        shape.npt = a.npt; shape.ngt = a.ngt; shape.gpt = a.gpt;
+        shape.three = true;
+        shape.alone = 2 * lds > kMaxLds;
+        shape.wide = V == 8 && tall && !(Wp->dev.cw && T.path != 6);
+        if (T.waves == 0 && T.ug == 0 && pick_parts(shape, ug, a)) {
+            nw = shape.nw;
             lds = std::max(lds, a.ksplit > 1 ? nw * V * pv * 64 * 4 : 0);
         }
         switch (V) {
