@@ -32,10 +32,15 @@ inline Parts parts_plan(const PartsShape &s) {
     // their waits for a chunk, 16 with the next chunk on its way do: 680->24 @56x56, N=58, V=4 501 -> 359 us, 572->36 @112x112
     // stride 2, N=17 360 -> 220, 664->672 @14x19 stride 2, N=15, V=2 256 -> 151; 50 layers of 512 and more channels with groups of 4 and
     // more 1.0 to 2.0x, two of them 0.96x.  (Where two or more workgroups share a compute unit the smaller ones win: 60 other
-    // layers 0.81x in the mean as parts.)
+    // layers 0.81x in the mean as parts.)  With groups of one and two channels two wavefronts already keep a SIMD's vector unit
+    // busy: there it takes a short multiply (64 columns of a chunk), few more rounds, or groups of uneven length
+    // (576->31 @112x112 stride 2, N=8, V=1, 199 columns 556 us as parts, 431 not; 1056->152 @56x54 stride 2, N=12, V=1, 46 columns
+    // 617 and 782; 600->103 @84x84 stride 2, V=1, uneven 1426 and 1897; 48 such layers 1.05x in the mean by this).
     if (wgs >= s.cus) {
         if (!s.alone) return {0, 0, 0};
         const int ngt = ceil_div(s.G, s.nw), gpt = ceil_div(s.G, ngt);
+        const bool more_rounds = 2 * ceil_div((long long)s.npt * ngt, s.cus) > 3 * ceil_div(wgs, s.cus);
+        if (s.V < 4 && !s.uneven && more_rounds && s.chunk > 64) return {0, 0, 0};
         int ks = 1;
         while (gpt * ks * 2 <= s.nw) ks *= 2;
         return {ngt, gpt, ks};

@@ -37,3 +37,16 @@ def test_every_group_has_a_wavefront_and_every_wavefront_a_place():
         else:
             assert ngt > s["ngt"], (s, p)
     assert taken > 4000
+
+
+def test_small_groups_alone_on_their_compute_units():
+    # more rounds of a multiply that is not short: as it was; a short one, few more rounds, or uneven groups: as parts
+    big = dict(alone=True, nw=16)
+    assert parts_plan(V=1, G=31, npt=448, ngt=1, cols=199 * 9, nchunks=9, **big) is None
+    assert parts_plan(V=1, G=160, npt=182, ngt=5, cols=134 * 9, nchunks=9, **big) is None
+    assert parts_plan(V=2, G=20, npt=448, ngt=1, cols=223 * 9, nchunks=9, **big) is None
+    assert parts_plan(V=1, G=152, npt=168, ngt=5, cols=46 * 17, nchunks=17, **big) == (10, 16, 1)
+    assert parts_plan(V=2, G=144, npt=54, ngt=5, cols=181 * 12, nchunks=12, **big) == (9, 16, 1)
+    assert parts_plan(V=1, G=103, npt=429, ngt=4, cols=130 * 10, nchunks=10, uneven=True, **big) == (7, 15, 1)
+    for V in (4, 8, 16):
+        assert parts_plan(V=V, G=160, npt=182, ngt=5, cols=134 * 9, nchunks=9, **big) == (10, 16, 1)
