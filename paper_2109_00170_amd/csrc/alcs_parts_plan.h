@@ -53,6 +53,15 @@ inline Parts parts_plan(const PartsShape &s) {
     while (gpt > 1 && (long long)s.npt * ceil_div(s.G, gpt / 2) <= s.cus) gpt /= 2;
     const int ngt = ceil_div(s.G, gpt);
     if (ngt <= s.ngt) return {0, 0, 0};  // no more workgroups than before
+    // `nw` groups to a workgroup can be more than one round all the same, which pays
+    //   - for chunks that leave room for a second workgroup on a compute unit, or of 160 columns and more, or uneven groups of one
+    //     or two channels (1045->88 @56x76, N=6, V=4, 76 columns 207 us in 420 workgroups, 169 in 210; 683->118 @77x56 stride 2,
+    //     N=3, V=1 338 in 480, 236 in 240; 792->320 @56x56 stride 2, N=6, V=4, 178 columns 202 in 420, 227 in 252);
+    //   - for 1x1 rows at stride 1; at stride 2, whose every other word costs the bytes of both, in up to two rounds
+    //     (820->200 @30x30, N=14, V=2 55 us in 650 workgroups, 31 in 200; 1490->160 @28x19, N=12, V=2 63 in 270, 99 in 81).
+    const long long parts = (long long)s.npt * ngt;
+    if (s.alone && parts > s.cus && !(s.V < 4 ? s.uneven : s.chunk >= 160)) return {0, 0, 0};
+    if (s.stride2 && parts > 2LL * s.cus) return {0, 0, 0};
     return {ngt, gpt, s.nw / gpt};
 }
 

@@ -50,3 +50,18 @@ def test_small_groups_alone_on_their_compute_units():
     assert parts_plan(V=1, G=103, npt=429, ngt=4, cols=130 * 10, nchunks=10, uneven=True, **big) == (7, 15, 1)
     for V in (4, 8, 16):
         assert parts_plan(V=V, G=160, npt=182, ngt=5, cols=134 * 9, nchunks=9, **big) == (10, 16, 1)
+
+
+def test_more_than_one_round():
+    big = dict(alone=True, nw=16)
+    assert parts_plan(V=4, G=22, npt=210, ngt=1, cols=76 * 17, nchunks=17, **big) is None
+    assert parts_plan(V=4, G=43, npt=112, ngt=2, cols=46 * 10, nchunks=10, **big) is None
+    assert parts_plan(V=1, G=118, npt=60, ngt=4, cols=202 * 11, nchunks=11, **big) is None
+    assert parts_plan(V=4, G=80, npt=84, ngt=3, cols=178 * 13, nchunks=13, **big) == (5, 16, 1)
+    assert parts_plan(V=4, G=56, npt=56, ngt=2, cols=244 * 11, nchunks=11, **big) == (4, 16, 1)
+    assert parts_plan(V=2, G=268, npt=18, ngt=9, cols=167 * 11, nchunks=11, uneven=True, **big) == (17, 16, 1)
+    rows = dict(three=False, nw=8)
+    assert parts_plan(V=2, G=100, npt=50, ngt=4, cols=56, nchunks=4, strided=True, stride2=True, **rows) is None
+    assert parts_plan(V=1, G=20, npt=181, ngt=1, cols=256, nchunks=4, stride2=True, **rows) is None
+    assert parts_plan(V=2, G=80, npt=27, ngt=3, cols=570, nchunks=6, strided=True, stride2=True, **rows) == (10, 8, 1)
+    assert parts_plan(V=1, G=32, npt=233, ngt=1, cols=452, nchunks=5, **rows) == (4, 8, 1)
