@@ -62,6 +62,12 @@ inline Parts parts_plan(const PartsShape &s) {
     const long long parts = (long long)s.npt * ngt;
     if (s.alone && parts > s.cus && !(s.V < 4 ? s.uneven : s.chunk >= 160)) return {0, 0, 0};
     if (s.stride2 && parts > 2LL * s.cus) return {0, 0, 0};
+    // Rows that are staged one pixel at a time are loaded again by every further group tile, which wavefronts with a short
+    // multiply between them do not cover: up to two groups a wavefront, below 128 columns of a chunk, in more than a few
+    // workgroups (4000->22 @14x18 stride 2, N=19, V=8, 40 columns 115 us in 57 workgroups, 74 in 19; 1234->29 @4x5 stride 2, N=58,
+    // V=2, 144 columns 39 in 90, 43 in 6).
+    const int deep = ceil_div(s.gpt, 8);  // groups of a wavefront in the kernels with eight wavefronts
+    if (s.strided && s.gpt <= 16 && parts > 48 && deep * s.chunk < 128) return {0, 0, 0};
     return {ngt, gpt, s.nw / gpt};
 }
 

@@ -65,3 +65,15 @@ def test_more_than_one_round():
     assert parts_plan(V=1, G=20, npt=181, ngt=1, cols=256, nchunks=4, stride2=True, **rows) is None
     assert parts_plan(V=2, G=80, npt=27, ngt=3, cols=570, nchunks=6, strided=True, stride2=True, **rows) == (10, 8, 1)
     assert parts_plan(V=1, G=32, npt=233, ngt=1, cols=452, nchunks=5, **rows) == (4, 8, 1)
+
+
+def test_rows_staged_one_pixel_at_a_time():
+    rows = dict(three=False, nw=8, strided=True, stride2=True)
+    assert parts_plan(V=8, G=3, npt=19, ngt=1, cols=40 * 16, nchunks=16, **rows) is None
+    assert parts_plan(V=2, G=11, npt=9, ngt=1, cols=42 * 5, nchunks=5, **rows) is None
+    assert parts_plan(V=8, G=14, npt=11, ngt=1, cols=26 * 15, nchunks=15, **rows) is None
+    assert parts_plan(V=8, G=3, npt=1, ngt=1, cols=40 * 16, nchunks=16, **rows) == (3, 1, 8)
+    assert parts_plan(V=2, G=15, npt=6, ngt=1, cols=72 * 5, nchunks=5, **rows) == (15, 1, 8)
+    assert parts_plan(V=8, G=27, npt=7, ngt=1, cols=13 * 12, nchunks=12, **rows) == (27, 1, 8)
+    rows.update(strided=False)
+    assert parts_plan(V=2, G=11, npt=9, ngt=1, cols=42 * 5, nchunks=5, **rows) == (11, 1, 8)
