@@ -68,7 +68,14 @@ inline Parts parts_plan(const PartsShape &s) {
     // V=2, 144 columns 39 in 90, 43 in 6).
     const int deep = ceil_div(s.gpt, 8);  // groups of a wavefront in the kernels with eight wavefronts
     if (s.strided && s.gpt <= 16 && parts > 48 && deep * s.chunk < 128) return {0, 0, 0};
-    return {ngt, gpt, s.nw / gpt};
+    // A 3x3 multiply of a few columns is over before sixteen wavefronts are under way and have added their sums (8->32 @14x14
+    // stride 2, N=2, V=4, 17 columns a wavefront 5.5 us as parts, 3.8 not; 8->310 @14x14, N=2, V=8, 36 columns 6.5 and 10.4; 16->160
+    // @17x19 stride 2, N=23, V=8, 79 columns in two parts 8.6 and 6.9).  260 layers of one chunk are 1.06x as fast in the mean with these
+    // limits, between 0.86 and 1.4x, as with none.
+    const int ks = s.nw / gpt;
+    const float chain = deep * s.all * (s.wide ? 2 : 1);
+    if (s.three && chain < (s.gpt <= 8 ? 48 + 96.f / ks : ngt >= 8 * s.ngt ? 30 : 32 + 96.f / ks)) return {0, 0, 0};
+    return {ngt, gpt, ks};
 }
 
 }  // namespace alcs
