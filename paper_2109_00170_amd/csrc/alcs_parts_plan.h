@@ -17,6 +17,7 @@ struct PartsShape {
     bool wide;      // 3x3: two pixels per lane, 8 channels, by columns (a column is twice the work)
     bool strided;   // 1x1: rows staged one pixel at a time
     bool stride2;   // 1x1: at stride 2
+    bool unaligned; // 1x1: at stride 1, images of no multiple of 4 pixels
     bool uneven;    // the longest group has more than twice the mean
     float chunk;    // kept columns of a group, in the mean: in a chunk
     float all;      // and in all of them
@@ -33,14 +34,16 @@ inline Parts parts_plan(const PartsShape &s) {
     // stride 2, N=17 360 -> 220, 664->672 @14x19 stride 2, N=15, V=2 256 -> 151; 50 layers of 512 and more channels with groups of 4 and
     // more 1.0 to 2.0x, two of them 0.96x.  (Where two or more workgroups share a compute unit the smaller ones win: 60 other
     // layers 0.81x in the mean as parts.)  With groups of one and two channels two wavefronts already keep a SIMD's vector unit
-    // busy: there it takes a short multiply (64 columns of a chunk), few more rounds, or groups of uneven length
-    // (576->31 @112x112 stride 2, N=8, V=1, 199 columns 556 us as parts, 431 not; 1056->152 @56x54 stride 2, N=12, V=1, 46 columns
-    // 617 and 782; 600->103 @84x84 stride 2, V=1, uneven 1426 and 1897; 48 such layers 1.05x in the mean by this).
+    // busy: there it takes a short multiply (64 columns of a chunk), few more rounds, or groups of two channels and of
+    // uneven length in several group tiles, the first of which has all the longest (576->31 @112x112 stride 2, N=8, V=1, 199 columns
+    // 556 us as parts, 431 not; 1056->152 @56x54 stride 2, N=12, V=1, 46 columns 617 and 782; 48 such layers 1.05x in the mean by
+    // this; uneven, V=2, four tiles and more 1.04 to 1.5x as parts, fewer 0.58 to 0.96x, V=1 0.5 to 0.95x and thrice above 1).
+    const bool uneven = s.uneven && s.V > 1 && s.ngt >= (s.V < 4 ? 4 : 3);
     if (wgs >= s.cus) {
         if (!s.alone) return {0, 0, 0};
         const int ngt = ceil_div(s.G, s.nw), gpt = ceil_div(s.G, ngt);
         const bool more_rounds = 2 * ceil_div((long long)s.npt * ngt, s.cus) > 3 * ceil_div(wgs, s.cus);
-        if (s.V < 4 && !s.uneven && more_rounds && s.chunk > 64) return {0, 0, 0};
+        if (s.V < 4 && !uneven && more_rounds && s.chunk > 64) return {0, 0, 0};
         int ks = 1;
         while (gpt * ks * 2 <= s.nw) ks *= 2;
         return {ngt, gpt, ks};
@@ -54,14 +57,20 @@ inline Parts parts_plan(const PartsShape &s) {
     const int ngt = ceil_div(s.G, gpt);
     if (ngt <= s.ngt) return {0, 0, 0};  // no more workgroups than before
     // `nw` groups to a workgroup can be more than one round all the same, which pays
-    //   - for chunks that leave room for a second workgroup on a compute unit, or of 160 columns and more, or uneven groups of one
-    //     or two channels (1045->88 @56x76, N=6, V=4, 76 columns 207 us in 420 workgroups, 169 in 210; 683->118 @77x56 stride 2,
-    //     N=3, V=1 338 in 480, 236 in 240; 792->320 @56x56 stride 2, N=6, V=4, 178 columns 202 in 420, 227 in 252);
-    //   - for 1x1 rows at stride 1; at stride 2, whose every other word costs the bytes of both, in up to two rounds
-    //     (820->200 @30x30, N=14, V=2 55 us in 650 workgroups, 31 in 200; 1490->160 @28x19, N=12, V=2 63 in 270, 99 in 81).
+    //   - for chunks that leave room for a second workgroup on a compute unit, or of 160 columns and more of four channels and
+    //     more, or uneven groups as above (1045->88 @56x76, N=6, V=4, 76 columns 207 us in 420 workgroups, 169 in 210; 683->118
+    //     @77x56 stride 2, N=3, V=1 338 in 480, 236 in 240; 792->320 @56x56 stride 2, N=6, V=4, 178 columns 202 in 420, 227 in 252;
+    //     824->552 @28x20, N=5, V=4, uneven 293 in 270, 561 in 150);
+    //   - for 1x1 rows in up to two rounds, and with groups of four channels and more only for more than two groups a
+    //     wavefront (820->200 @30x30 stride 2, N=14, V=2 55 us in 650 workgroups, 31 in 200; 1490->160 @28x19 stride 2, N=12, V=2
+    //     63 in 270, 99 in 81; 130 layers at stride 1: in more than two rounds V=4 and more 0.69 to 1.17x, 0.9 in the mean, in up to
+    //     two with up to two groups 0.88 to 1.1x, with more 1.2 to 1.9x);
+    //   - in any number of rounds for 1x1 rows at stride 1 with groups of two channels (17 layers 1.03 to 1.5x), and of one where the
+    //     rows are aligned (8 layers 1.06 to 1.4x, one 0.92; not aligned five 0.79 to 0.87x).
     const long long parts = (long long)s.npt * ngt;
-    if (s.alone && parts > s.cus && !(s.V < 4 ? s.uneven : s.chunk >= 160)) return {0, 0, 0};
-    if (s.stride2 && parts > 2LL * s.cus) return {0, 0, 0};
+    if (s.alone && parts > s.cus && !uneven && (s.V < 4 || s.chunk < 160)) return {0, 0, 0};
+    if (!s.three && parts > 2LL * s.cus && (s.stride2 || s.V >= 4 || (s.V == 1 && s.unaligned))) return {0, 0, 0};
+    if (!s.three && parts > s.cus && s.V >= 4 && s.gpt <= 16) return {0, 0, 0};
     // Rows that are staged one pixel at a time are loaded again by every further group tile, which wavefronts with a short
     // multiply between them do not cover: up to two groups a wavefront, below 128 columns of a chunk, in more than a few
     // workgroups (4000->22 @14x18 stride 2, N=19, V=8, 40 columns 115 us in 57 workgroups, 74 in 19; 1234->29 @4x5 stride 2, N=58,

@@ -2818,6 +2818,7 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             shape.npt = a.npt; shape.ngt = a.ngt; shape.gpt = a.gpt;
             shape.strided = ac == kStrided;
             shape.stride2 = ac == kStrided || ac == kPairs;
+            shape.unaligned = ac == kUnaligned;
             if (pv == 1 && T.waves == 0 && T.ug == 0 && pick_parts(shape, ug, a)) {
                 nw = shape.nw;
                 lds = std::max(lds, a.ksplit > 1 ? nw * V * 64 * 4 : 0);

@@ -47,7 +47,9 @@ def test_small_groups_alone_on_their_compute_units():
     assert parts_plan(V=2, G=20, npt=448, ngt=1, cols=223 * 9, nchunks=9, **big) is None
     assert parts_plan(V=1, G=152, npt=168, ngt=5, cols=46 * 17, nchunks=17, **big) == (10, 16, 1)
     assert parts_plan(V=2, G=144, npt=54, ngt=5, cols=181 * 12, nchunks=12, **big) == (9, 16, 1)
-    assert parts_plan(V=1, G=103, npt=429, ngt=4, cols=130 * 10, nchunks=10, uneven=True, **big) == (7, 15, 1)
+    assert parts_plan(V=2, G=128, npt=168, ngt=4, cols=130 * 10, nchunks=10, uneven=True, **big) == (8, 16, 1)
+    assert parts_plan(V=2, G=92, npt=136, ngt=3, cols=130 * 10, nchunks=10, uneven=True, **big) is None
+    assert parts_plan(V=1, G=64, npt=324, ngt=2, cols=130 * 10, nchunks=10, uneven=True, **big) is None
     for V in (4, 8, 16):
         assert parts_plan(V=V, G=160, npt=182, ngt=5, cols=134 * 9, nchunks=9, **big) == (10, 16, 1)
 
@@ -60,11 +62,20 @@ def test_more_than_one_round():
     assert parts_plan(V=4, G=80, npt=84, ngt=3, cols=178 * 13, nchunks=13, **big) == (5, 16, 1)
     assert parts_plan(V=4, G=56, npt=56, ngt=2, cols=244 * 11, nchunks=11, **big) == (4, 16, 1)
     assert parts_plan(V=2, G=268, npt=18, ngt=9, cols=167 * 11, nchunks=11, uneven=True, **big) == (17, 16, 1)
+    assert parts_plan(V=1, G=268, npt=18, ngt=9, cols=167 * 11, nchunks=11, uneven=True, **big) is None
+    assert parts_plan(V=4, G=138, npt=30, ngt=5, cols=120 * 13, nchunks=13, uneven=True, **big) == (9, 16, 1)
+    assert parts_plan(V=4, G=17, npt=140, ngt=1, cols=120 * 13, nchunks=13, uneven=True, **big) is None
     rows = dict(three=False, nw=8)
     assert parts_plan(V=2, G=100, npt=50, ngt=4, cols=56, nchunks=4, strided=True, stride2=True, **rows) is None
     assert parts_plan(V=1, G=20, npt=181, ngt=1, cols=256, nchunks=4, stride2=True, **rows) is None
     assert parts_plan(V=2, G=80, npt=27, ngt=3, cols=570, nchunks=6, strided=True, stride2=True, **rows) == (10, 8, 1)
     assert parts_plan(V=1, G=32, npt=233, ngt=1, cols=452, nchunks=5, **rows) == (4, 8, 1)
+    assert parts_plan(V=4, G=28, npt=245, ngt=1, cols=400, nchunks=16, **rows) is None
+    assert parts_plan(V=1, G=136, npt=41, ngt=5, cols=147, nchunks=3, unaligned=True, **rows) is None
+    assert parts_plan(V=2, G=136, npt=49, ngt=5, cols=284, nchunks=4, unaligned=True, **rows) == (17, 8, 1)
+    assert parts_plan(V=4, G=52, npt=70, ngt=2, cols=640, nchunks=12, **rows) == (7, 8, 1)
+    assert parts_plan(V=16, G=9, npt=136, ngt=1, cols=880, nchunks=14, **rows) is None
+    assert parts_plan(V=2, G=16, npt=135, ngt=1, cols=234, nchunks=3, **rows) == (2, 8, 1)
 
 
 def test_rows_staged_one_pixel_at_a_time():
