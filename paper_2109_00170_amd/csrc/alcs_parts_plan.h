@@ -72,11 +72,11 @@ inline Parts parts_plan(const PartsShape &s) {
     if (!s.three && parts > 2LL * s.cus && (s.stride2 || s.V >= 4 || (s.V == 1 && s.unaligned))) return {0, 0, 0};
     if (!s.three && parts > s.cus && s.V >= 4 && s.gpt <= 16) return {0, 0, 0};
     // Rows that are staged one pixel at a time are loaded again by every further group tile, which wavefronts with a short
-    // multiply between them do not cover: up to two groups a wavefront, below 128 columns of a chunk, in more than a few
-    // workgroups (4000->22 @14x18 stride 2, N=19, V=8, 40 columns 115 us in 57 workgroups, 74 in 19; 1234->29 @4x5 stride 2, N=58,
-    // V=2, 144 columns 39 in 90, 43 in 6).
+    // multiply between them do not cover: up to two groups a wavefront, below 128 columns of a chunk (64 of 16 channels), in more
+    // than a few workgroups (4000->22 @14x18 stride 2, N=19, V=8, 40 columns 115 us in 57 workgroups, 74 in 19; 1234->29 @4x5
+    // stride 2, N=58, V=2, 144 columns 39 in 90, 43 in 6; 3145->232 @7x7 stride 2, N=22, V=16, 72 columns 92 in 90, 136 in 6).
     const int deep = ceil_div(s.gpt, 8);  // groups of a wavefront in the kernels with eight wavefronts
-    if (s.strided && s.gpt <= 16 && parts > 48 && deep * s.chunk < 128) return {0, 0, 0};
+    if (s.strided && s.gpt <= 16 && parts > 48 && deep * s.chunk < (s.V == 16 ? 64 : 128)) return {0, 0, 0};
     // A 3x3 multiply of a few columns is over before sixteen wavefronts are under way and have added their sums (8->32 @14x14
     // stride 2, N=2, V=4, 17 columns a wavefront 5.5 us as parts, 3.8 not; 8->310 @14x14, N=2, V=8, 36 columns 6.5 and 10.4; 16->160
     // @17x19 stride 2, N=23, V=8, 79 columns in two parts 8.6 and 6.9).  260 layers of one chunk are 1.06x as fast in the mean with these

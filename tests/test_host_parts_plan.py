@@ -86,6 +86,7 @@ def test_rows_staged_one_pixel_at_a_time():
     assert parts_plan(V=8, G=3, npt=1, ngt=1, cols=40 * 16, nchunks=16, **rows) == (3, 1, 8)
     assert parts_plan(V=2, G=15, npt=6, ngt=1, cols=72 * 5, nchunks=5, **rows) == (15, 1, 8)
     assert parts_plan(V=8, G=27, npt=7, ngt=1, cols=13 * 12, nchunks=12, **rows) == (27, 1, 8)
+    assert parts_plan(V=16, G=15, npt=6, ngt=1, cols=36 * 13, nchunks=13, **rows) == (15, 1, 8)
     rows.update(strided=False)
     assert parts_plan(V=2, G=11, npt=9, ngt=1, cols=42 * 5, nchunks=5, **rows) == (11, 1, 8)
 
