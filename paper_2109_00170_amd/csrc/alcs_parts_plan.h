@@ -83,7 +83,7 @@ inline Parts parts_plan(const PartsShape &s) {
     // limits, between 0.86 and 1.4x, as with none.
     const int ks = s.nw / gpt;
     const float chain = deep * s.all * (s.wide ? 2 : 1);
-    if (s.three && chain < (s.gpt <= 8 ? 48 + 96.f / ks : ngt >= 8 * s.ngt ? 30 : 32 + 96.f / ks)) return {0, 0, 0};
+    if (s.three && chain < (s.gpt <= 8 ? 48 + 128.f / ks : ngt >= 8 * s.ngt ? 30 : 32 + 128.f / ks)) return {0, 0, 0};
     return {ngt, gpt, ks};
 }
 

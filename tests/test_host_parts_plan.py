@@ -97,6 +97,8 @@ def test_few_columns():
     assert parts_plan(V=16, G=10, npt=112, ngt=1, cols=15) is None
     assert parts_plan(V=8, G=20, npt=69, ngt=2, cols=39) is None
     assert parts_plan(V=4, G=2, npt=63, ngt=1, cols=48, nchunks=2) is None
+    assert parts_plan(V=4, G=60, npt=19, ngt=4, cols=47) is None
+    assert parts_plan(V=4, G=4, npt=112, ngt=1, cols=61) is None
     assert parts_plan(V=8, G=39, npt=4, ngt=3, cols=18, gpt=13, wide=True) == (39, 1, 16)
     assert parts_plan(V=8, G=16, npt=14, ngt=1, cols=19) == (16, 1, 16)
     assert parts_plan(V=4, G=8, npt=2, ngt=1, cols=60) == (8, 1, 16)
