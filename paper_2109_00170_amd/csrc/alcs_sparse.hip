@@ -2813,7 +2813,7 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
             ug = pick_ug(G, nw, T.ug);
             if (V * pv * ug > 128) ug = 2;  // accumulators of 4 groups would not fit the register file
             a.ngt = ceil_div(G, nw * ug);
-            a.gpt = ceil_div(G, a.ngt);
+            a.gpt = groups_of_tile(G, a.ngt, a.npt, nw, ug, kCUs * std::max(1, kMaxLds / lds));
             shape.nw = ac == kRows ? 16 : 8;
             shape.npt = a.npt; shape.ngt = a.ngt; shape.gpt = a.gpt;
             shape.strided = ac == kStrided;

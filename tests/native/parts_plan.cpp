@@ -9,3 +9,7 @@ extern "C" void parts_plan(const int *i, const float *f, int *out) {
     const alcs::Parts p = alcs::parts_plan(s);
     out[0] = p.ngt; out[1] = p.gpt; out[2] = p.ksplit;
 }
+
+extern "C" int groups_of_tile(int G, int ngt, int npt, int nw, int ug, int slots) {
+    return alcs::groups_of_tile(G, ngt, npt, nw, ug, slots);
+}

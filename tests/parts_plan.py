@@ -28,3 +28,7 @@ def parts_plan(V, G, npt, ngt, cols, nchunks=1, nw=16, gpt=None, three=True, alo
                                               unaligned),
                           (ctypes.c_float * 2)(cols / nchunks, cols), out)
     return tuple(out) if out[0] else None
+
+
+def groups_of_tile(G, ngt, npt, nw, ug, slots):
+    return _library().groups_of_tile(G, ngt, npt, nw, ug, slots)

@@ -3,7 +3,7 @@
 import math
 import random
 
-from parts_plan import parts_plan
+from parts_plan import groups_of_tile, parts_plan
 
 
 def shapes(n):
@@ -105,3 +105,17 @@ def test_few_columns():
     assert parts_plan(V=8, G=5, npt=21, ngt=1, cols=30, wide=True) == (5, 1, 16)
     assert parts_plan(V=8, G=5, npt=21, ngt=1, cols=30) is None
     assert parts_plan(V=4, G=114, npt=10, ngt=8, cols=89) == (15, 8, 2)
+
+
+def test_groups_of_a_tile():
+    assert groups_of_tile(33, 2, 300, 8, 4, 512) == 17
+    assert groups_of_tile(129, 5, 117, 8, 4, 512) == 32     # 468 full tiles in a round, 585 even ones not
+    assert groups_of_tile(129, 5, 100, 8, 4, 512) == 26
+    assert groups_of_tile(129, 5, 400, 8, 4, 512) == 26
+    assert groups_of_tile(36, 2, 300, 8, 4, 512) == 18      # (wavefronts of three groups, not four)
+    for G in range(1, 700):
+        for ug in (2, 4):
+            ngt = -(-G // (8 * ug))
+            for npt in (1, 100, 512 // ngt + 1):
+                gpt = groups_of_tile(G, ngt, npt, 8, ug, 512)
+                assert gpt <= 8 * ug and -(-G // gpt) == ngt
