@@ -2885,12 +2885,16 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
         }
         // Handles with channel records (the pattern is shared by the nine taps) and groups of 4 or 8
         // channels walk records instead of columns; "path" = 6 keeps the column-by-column kernel, 7 asks for records.
-        // By default with tall tiles, and with one pixel per lane, groups of 4 and several chunks, where workgroups share a
-        // compute unit: the records' lines ahead are a chain of waits for a workgroup alone (110 such layers, 80 with
+        // By default with tall tiles.  One pixel per lane: groups of 4 and several chunks, where workgroups share a compute
+        // unit.  In k_conv3 the records' lines ahead are a chain of waits for a workgroup alone (110 such layers, 80 with
         // up to 256 workgroups: stride 1 0.88 to 0.99 of the column walk's speed, stride 2 0.86 to 1.03 on chunks of 64
         // channels and 0.97 to 1.04 on chunks of 32; in more workgroups 0.99 to 1.14 - 800->775 @7x9, N=9 145 us by columns,
-        // 165 by records, 495->502 @8x8, N=122 235 and 217, 466->151 @14x14 stride 2, N=232 109 and 98).
-        const bool one_px = V == 4 && L.nchunks > 1 && ((long long)a.npt * a.ngt > kCUs || (stride == 2 && L.KC <= 32));
+        // 165 by records, 495->502 @8x8, N=122 235 and 217, 466->151 @14x14 stride 2, N=232 109 and 98).  In k_conv3_split,
+        // whose next chunk's records are there before its multiply, the same line for groups of 4 (60 layers 0.98 to 1.06 beyond it,
+        // 0.96 to 1.08 on this side), and groups of 8 too (75 layers 1.02 to 1.20: 892->62 @7x7, N=60 31.9 us by columns, 28.2 by
+        // records).
+        const bool one_px = (V == 8 && ug == 1) ||
+                            (V == 4 && L.nchunks > 1 && ((long long)a.npt * a.ngt > kCUs || (stride == 2 && L.KC <= 32)));
         if (Wp->dev.cw && mfma && V <= 8 && T.path != 6 && (tall || one_px || T.path == 7)) {
             a.cw = Wp->dev.cw; a.csel = Wp->dev.csel; a.cwork = Wp->dev.cwork; a.cwplane = Wp->dev.cwplane;
             kern = V == 4 ? pick_conv3_shared<4>(stride, ti, ug, tall) : pick_conv3_shared<8>(stride, ti, ug, tall);

@@ -8,7 +8,7 @@ import pytest
 import oracle
 import paper_2109_00170_amd as alcs
 import workloads
-from gpu_util import TOL, rel_err
+from gpu_util import TOL, oracle_ref, rel_err, run_sparse
 
 pytestmark = pytest.mark.gpu
 
@@ -131,3 +131,16 @@ def test_more_than_1024_segments():
     L = workloads.Layer("ts_many", 96, 2080, 12, 12, k=3, N=1, V=4, sparsity=0.9, w_std=0.2, tap_shared=True)
     run(L, 6210)
     run(L, 6210, on_device=True)
+
+
+# Launches whose wavefronts have one group or a part of one walk records with groups of 8 channels; of 4 as others do.
+@pytest.mark.parametrize("V,Cin,H,stride,mode", [(8, 20, 7, 1, 7), (8, 70, 7, 1, 7), (8, 70, 13, 2, 7), (4, 70, 7, 1, 3), (4, 70, 13, 2, 7),
+                                                 (4, 24, 7, 1, 3)])
+def test_records_in_launches_of_few_workgroups(V, Cin, H, stride, mode):
+    L = workloads.Layer("few", Cin, 20 * V - 3, H, H, k=3, stride=stride, N=3, V=V, sparsity=0.5, w_std=0.1, tap_shared=True)
+    d = workloads.make_layer(L, 7700 + V + Cin + H, with_bias=True)
+    got, info = run_sparse(d)
+    assert info["mode"] == mode and info["waves"] == 16, info
+    assert rel_err(got, oracle_ref(d)) <= TOL
+    by_columns, info = run_sparse(d, options={"path": 6})
+    assert info["mode"] == 3 and info["waves"] == 16 and rel_err(by_columns, oracle_ref(d)) <= TOL, info
