@@ -19,9 +19,12 @@ def _library():
         return ctypes.CDLL(so)
 
 
-def dense_plan(k, stride, Cin, Cout, H, W, N, cus=256):
+def dense_plan(k, stride, Cin, Cout, H, W, N, cus=256, few=True):
     """(kernel size, "gather" / "float32" / "split", channels, pixels, positions per thread) of the tile, and its positions
-    and LDS bytes."""
-    out = (ctypes.c_int * 7)()
+    and LDS bytes; (kernel size, "few", 32, 32, 0) where the launch is left to the kernel of small launches
+    (few=False: the tile it would take otherwise)."""
+    out = (ctypes.c_int * 8)()
     _library().dense_plan((ctypes.c_int * 7)(N, Cin, Cout, H, W, k, stride), cus, out)
+    if few and out[7]:
+        return (k, "few", 32, 32, 0), 0, 64 * 1024
     return (k, KINDS[out[0]]) + tuple(out[1:4]), out[4], out[6]

@@ -31,6 +31,10 @@ def test_1x1(Cin, stride, Cout, H, W, N):
     check(1, stride, Cin, Cout, H, W, N, bias=Cin != 7)
 
 
+# (a launch of one round of small tiles, and the next larger one, which is not left to k_dense_few)
+ONE_ROUND = [((k, 1, 20, 32, 4, 8, N), kind) for k in (1, 3) for N, kind in ((256, "few"), (257, "float32"))]
+
+
 @pytest.mark.parametrize("k", [1, 3])
 @pytest.mark.parametrize("N", [256, 257])
 def test_around_one_round(k, N):
@@ -38,9 +42,12 @@ def test_around_one_round(k, N):
 
 
 # one shape for each float32 tile (and the gather) that test_dense_tiles names, in launches of more than one round of small tiles
-@pytest.mark.parametrize("k,stride,Cin,Cout,H,W,N", [
+LARGER = [
     (3, 1, 8, 32, 12, 11, 63), (3, 1, 9, 31, 4, 4, 513), (3, 1, 24, 33, 1, 1, 4097), (3, 1, 16, 65, 3, 2, 454), (3, 2, 17, 130, 15, 9, 41),
     (3, 2, 12, 40, 33, 58, 9), (3, 1, 5, 20, 3, 300, 10), (3, 2, 3, 32, 40, 224, 4), (3, 2, 8, 64, 64, 203, 2), (3, 2, 13, 300, 31, 146, 1),
-    (1, 1, 16, 16, 5, 3, 547), (1, 1, 32, 16, 5, 3, 547), (1, 1, 8, 40, 6, 5, 137), (1, 1, 31, 64, 1, 1, 4097), (1, 2, 64, 30, 31, 17, 57)])
+    (1, 1, 16, 16, 5, 3, 547), (1, 1, 32, 16, 5, 3, 547), (1, 1, 8, 40, 6, 5, 137), (1, 1, 31, 64, 1, 1, 4097), (1, 2, 64, 30, 31, 17, 57)]
+
+
+@pytest.mark.parametrize("k,stride,Cin,Cout,H,W,N", LARGER)
 def test_tiles_of_larger_launches(k, stride, Cin, Cout, H, W, N):
     check(k, stride, Cin, Cout, H, W, N)

@@ -1,8 +1,9 @@
 """The dense convolution's tiles (csrc/alcs_dense.hip) at the sizes where they can go wrong, against the
 oracle: channels that are no multiple of a step, channel and pixel tiles with a remainder, tiles over
 several images, 3x3 tiles of 64 pixels, and the layers that fall to the word-by-word kernel, on 64 and on
-128 channels.  That every tile shape and number of staged positions per thread the library can choose is among
-them is checked without a GPU (test_host_dense_plan.py)."""
+128 channels.  Shapes of fewer than 256 tiles of 32 x 32 outputs that do not run on split operands are k_dense_few's now: they keep
+their places as its ragged cases, and test_gpu_dense_few.py has larger launches of the tiles they stood for.  That every kernel the
+library can choose is among the shapes of the two files is checked without a GPU (test_host_dense_plan.py)."""
 import numpy as np
 import pytest
 
