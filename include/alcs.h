@@ -304,7 +304,8 @@ int alcs_dense_conv(const float *W_dev, const float *X_dev, const float *bias_de
  *   read at every launch:
  *     pixels_per_lane  1x1 kernels: 1, 2 or 4 (1 or 2 with several groups per wavefront);
  *                      3x3 kernel: 1 or 2 (2: tiles of twice the height, stride 1, V = 4 or 8)
- *     waves            wavefronts per workgroup
+ *     waves            wavefronts per workgroup (chunked 1x1 and 3x3 kernels: up to 8, and with this or
+ *                      groups_per_wave set a wavefront has groups of its own, never a part of one)
  *     group_tiles      number of workgroups that share one pixel tile
  *     path             1 = plain-FMA inner loop where it exists (V = 4), 2 = MFMA inner loop,
  *                      4 = persistent double-buffered 1x1 kernel with the weights in LDS where
@@ -313,12 +314,14 @@ int alcs_dense_conv(const float *W_dev, const float *X_dev, const float *bias_de
  *                      wherever it applies, 6 = never that kernel and, for 3x3 handles whose
  *                      pattern is shared by the nine taps, the column-by-column walk instead
  *                      of the walk over channel records; 7 = that record walk wherever it
- *                      exists (V = 4 or 8; the default takes it with pixels_per_lane 2 only)
+ *                      exists (V = 4 or 8; the default takes it with pixels_per_lane 2, and
+ *                      with 1 for some shapes)
  *     tile_width       output-tile width of the 3x3 kernel: 8, 16 or 32 (tile height 64/width)
  *     groups_per_wave  groups whose accumulators a wavefront of the chunked 1x1 kernel and of
  *                      the 3x3 kernel holds: 2 or 4 (automatic: 4, or 2 when the layer has few
  *                      groups, for V >= 8, or where halving lets two workgroups share a
- *                      compute unit)
+ *                      compute unit; or one, or a part of one, in launches of few workgroups
+ *                      and in 3x3 launches of one workgroup per compute unit)
  *     dw_own_taps      alcs_dw_sparse_conv_fused: every lane loads all nine taps of its pixel
  *                      instead of sharing them with its neighbours
  *     dw_one_kernel    alcs_dw_sparse_conv_fused: stay in one kernel even where the call would
@@ -509,7 +512,7 @@ int alcs_pack_weights_device(const float *W_dev, const uint8_t *mask_dev, int Co
  * 7 = 3x3 walking channel records (handles whose pattern is shared by the nine taps)),
  * pv, waves, workgroups, lds_bytes, group_tiles,
  * chunk_channels, path, group_slots, tile_width (3x3 only, else 0),
- * bundle_waves (mode 1: wavefronts that share a bundle of groups, else 1)} and returns how many
+ * bundle_waves (modes 1, 2, 3 and 7: wavefronts that share a bundle of groups, or a group, else 1)} and returns how many
  * were written.  For tests and benchmarks. */
 int alcs_last_launch(int *out, int cap);
 

@@ -1017,8 +1017,9 @@ __global__ void __launch_bounds__(256) k_dense_gather(const DenseArgs a) {
 // such a launch is one chain of steps on a few compute units; here a wavefront has a sixteenth of the channels, loads its
 // operands for the float32 instruction straight from memory (nothing is read twice inside a wavefront but taps), one unit
 // ahead, and the sixteen sums meet in LDS.  A unit is two channels x 9 taps (3x3; lane half h has one) or 8 channels
-// (1x1; half h has four).  What bounds it is the float32 instruction and the taps' loads, a microsecond and a half a unit
-// round.  3x3: 128->8 @28x28, N=4 28 -> 11 us, 271->46 @28x28, N=2 58 -> 21, 832->24 @14x14, N=2 164 -> 55, 472->48 @20x20, N=10
+// (1x1; half h has four).  What bounds it is the float32 instruction and the taps' loads: 3x3 two to two and a half
+// microseconds a round of sixteen units (832->24 has 26 of them, 472->48 15, 128->8 four).  3x3 holds 128 registers a lane, the most
+// that 16 wavefronts can, and spills four.  3x3: 128->8 @28x28, N=4 28 -> 11 us, 271->46 @28x28, N=2 58 -> 21, 832->24 @14x14, N=2 164 -> 55, 472->48 @20x20, N=10
 // 99 -> 37; 1x1: 264->184 @14x14, one image 11.5 -> 6.8, 895->32 @4x4, N=3 27 -> 12.  Sixteen short sums are also closer to
 // 64 bits than one long one: 1.2e-7 against 4.8e-7 at 184 channels x 9 taps.
 template <int KK>

@@ -122,7 +122,8 @@ inline DensePlan dense_plan(int N, int Cin, int Cout, int H, int W, int kernel, 
 }
 
 // Whether a launch is left to k_dense_few: tiles of 32 x 32 outputs that make one round of the chip, where the plan would
-// run float32.  110 such layers of 16 to 1024 channels: 1.2 to 3.6x as fast as the plan's tiles, one image or many; beyond one
+// run float32.  110 such layers of 16 to 1024 channels: 1.2 to 3.6x as fast as the plan's tiles, one image or many; 110 of 1 to 40
+// channels, most of whose wavefronts have no unit, 1.07 to 2.3x (3x3 4->8 @14x14, N=2 5.2 -> 3.7 us); beyond one
 // round a workgroup alone on its compute unit waits for memory (480 tiles of 136->77 @10x10 as fast, 711 of 439->270 @7x7 0.97x,
 // 1380 of 96->144 @14x14 0.53x).
 inline bool dense_few(const DensePlan &p, long long NP, int Cout, int cus) {

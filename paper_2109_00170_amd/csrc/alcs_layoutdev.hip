@@ -283,7 +283,8 @@ __global__ void __launch_bounds__(1024) k_ld_plan(const LayerDev *layers) {
 // requested together; then a thread per kept column moves its values, four rows and 16 bytes a store.  What such a small
 // launch waits for besides memory is its own code, each line of it fetched cold, and its address arithmetic: the same work
 // with four columns' code side by side took as long as one column at a time (41.5 and 43.7 us for the 13 layers of
-// MobileNetV1, 30 % kept, half of it for the padding's divisions); this takes 25.5.
+// MobileNetV1, 30 % kept, half of it for the padding's divisions); this takes 25.5.  (16.5 KB of LDS, the lists' 8 and the work
+// record, which the compiler keeps there for every thread; 53 scalars spilled.)
 constexpr int kFillTurn = 4;
 typedef float fl4 __attribute__((ext_vector_type(4)));
 __global__ void __launch_bounds__(256) k_ld_fill(const LayerDev *layers, const Spread *sp, int n) {

@@ -426,8 +426,10 @@ __device__ double interpolate(const double *k, const double *t, int n, double s)
 
 // The layers' tables as k_bisect_steps reads them: copies in LDS where they fit.  Evaluating a node is a chain of reads -
 // a layer's place in the tables, its ends, a search, two neighbours - one behind the other.  From LDS the four launches of
-// MobileNetV1's 13 layers take 65 us in all, from memory 80.  (Both limits: a workgroup's static LDS ends at 64 KB, and S
-// takes 24 of them; networks beyond them read memory.)
+// MobileNetV1's 13 layers take 65 us in all, from memory 80.  The limits are the arrays' sizes, room for 139 layers of 11
+// entries; networks beyond them read memory (a projection of 139 such layers 330 us, of 140 494; 256 layers of 6 463, 257 of 5
+// 530).  k_bisect_steps has 75 KB of LDS with them, 72 without: S takes 24, and 24 and 48 bytes a thread are private objects that
+// the compiler puts there; 28 bytes a lane stay in scratch.
 constexpr int kStageKnots = 1536, kStageLayers = 256;
 struct StagedTables {
     double k[kStageKnots], t[kStageKnots];
