@@ -88,12 +88,11 @@ inline Parts parts_plan(const PartsShape &s) {
     const int deep = ceil_div(s.gpt, 8);  // groups of a wavefront in the kernels with eight wavefronts
     if (s.strided && s.gpt <= 16 && parts > 48 && deep * s.chunk < (s.V == 16 ? 64 : 128)) return {0, 0, 0};
     // A 3x3 multiply of a few columns is over before sixteen wavefronts are under way and have added their sums (8->32 @14x14
-    // stride 2, N=2, V=4, 17 columns a wavefront 5.5 us as parts, 3.8 not; 8->310 @14x14, N=2, V=8, 36 columns 6.5 and 10.4; 16->160
-    // @17x19 stride 2, N=23, V=8, 79 columns in two parts 8.6 and 6.9).  260 layers of one chunk are 1.06x as fast in the mean with these
-    // limits, between 0.86 and 1.4x, as with none.
+    // stride 2, N=2, V=4, 17 columns a wavefront 5.5 us as parts, 3.8 not; 24->712 @7x7 stride 2, V=1, 60 columns 5.6 and 6.7).  760
+    // layers of up to 64 channels are 1.04x as fast in the mean with these limits as with none, none of them below 0.90x.
     const int ks = s.nw / gpt;
-    const float chain = deep * s.all * (s.wide ? 2 : 1);
-    if (s.three && chain < (s.gpt <= 8 ? 48 + 128.f / ks : ngt >= 8 * s.ngt ? 30 : 32 + 128.f / ks)) return {0, 0, 0};
+    const float chain = deep * s.all * (s.wide ? 2 : 1), few = s.gpt <= 8 ? 32 + 96.f / ks : ks < 4 ? 96.f / ks : 24;
+    if (s.three && chain < few) return {0, 0, 0};
     return {ngt, gpt, ks};
 }
 

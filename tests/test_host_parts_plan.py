@@ -95,15 +95,14 @@ def test_few_columns():
     assert parts_plan(V=4, G=8, npt=2, ngt=1, cols=17) is None
     assert parts_plan(V=4, G=5, npt=84, ngt=1, cols=4) is None
     assert parts_plan(V=16, G=10, npt=112, ngt=1, cols=15) is None
-    assert parts_plan(V=8, G=20, npt=69, ngt=2, cols=39) is None
-    assert parts_plan(V=4, G=2, npt=63, ngt=1, cols=48, nchunks=2) is None
-    assert parts_plan(V=4, G=60, npt=19, ngt=4, cols=47) is None
-    assert parts_plan(V=4, G=4, npt=112, ngt=1, cols=61) is None
-    assert parts_plan(V=8, G=39, npt=4, ngt=3, cols=18, gpt=13, wide=True) == (39, 1, 16)
-    assert parts_plan(V=8, G=16, npt=14, ngt=1, cols=19) == (16, 1, 16)
-    assert parts_plan(V=4, G=8, npt=2, ngt=1, cols=60) == (8, 1, 16)
-    assert parts_plan(V=8, G=5, npt=21, ngt=1, cols=30, wide=True) == (5, 1, 16)
+    assert parts_plan(V=4, G=2, npt=63, ngt=1, cols=30, nchunks=2) is None
     assert parts_plan(V=8, G=5, npt=21, ngt=1, cols=30) is None
+    assert parts_plan(V=8, G=5, npt=21, ngt=1, cols=30, wide=True) == (5, 1, 16)
+    assert parts_plan(V=4, G=8, npt=2, ngt=1, cols=60) == (8, 1, 16)
+    assert parts_plan(V=8, G=20, npt=69, ngt=2, cols=39) == (3, 8, 2)
+    assert parts_plan(V=8, G=39, npt=4, ngt=3, cols=18, gpt=13, wide=True) == (39, 1, 16)
+    assert parts_plan(V=8, G=58, npt=3, ngt=4, cols=13) == (58, 1, 16)
+    assert parts_plan(V=1, G=712, npt=1, ngt=45, cols=30, gpt=16) == (178, 4, 4)
     assert parts_plan(V=4, G=114, npt=10, ngt=8, cols=89) == (15, 8, 2)
 
 
