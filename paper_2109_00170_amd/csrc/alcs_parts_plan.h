@@ -28,6 +28,7 @@ struct PartsShape {
     bool strided;   // 1x1: rows staged one pixel at a time
     bool stride2;   // 1x1: at stride 2
     bool unaligned; // 1x1: at stride 1, images of no multiple of 4 pixels
+    bool shared;    // 3x3: every kept channel keeps its nine taps
     bool uneven;    // the longest group has more than twice the mean
     float chunk;    // kept columns of a group, in the mean: in a chunk
     float all;      // and in all of them
@@ -48,12 +49,18 @@ inline Parts parts_plan(const PartsShape &s) {
     // uneven length in several group tiles, the first of which has all the longest (576->31 @112x112 stride 2, N=8, V=1, 199 columns
     // 556 us as parts, 431 not; 1056->152 @56x54 stride 2, N=12, V=1, 46 columns 617 and 782; 48 such layers 1.05x in the mean by
     // this; uneven, V=2, four tiles and more 1.04 to 1.5x as parts, fewer 0.58 to 0.96x, V=1 0.5 to 0.95x and thrice above 1).
+    // A pattern shared by the taps keeps nine columns of a channel or none: single channels differ more over a chunk, and where a
+    // wavefront has one group instead of four the chunk lasts as long as its longest (0.58 to 0.70 of the time of twice the groups by the
+    // counts, 0.51 to 0.55 for other patterns).  There one and a half times the rounds are too many already, and twice as many for
+    // short multiplies too (648 groups @14x14 stride 2, N=18, 267 columns 724 us as parts, 636 not; 848->440 @28x28 stride 2, N=26, 60
+    // columns, twice the rounds 1183 and 944; 568->109 @28x28 stride 2, N=53, 44 columns, one and a half times 289 and 355).
     const bool uneven = s.uneven && s.V > 1 && s.ngt >= (s.V < 4 ? 4 : 3);
     if (wgs >= s.cus) {
         if (!s.alone) return {0, 0, 0};
         const int ngt = ceil_div(s.G, s.nw), gpt = ceil_div(s.G, ngt);
-        const bool more_rounds = 2 * ceil_div((long long)s.npt * ngt, s.cus) > 3 * ceil_div(wgs, s.cus);
-        if (s.V < 4 && !uneven && more_rounds && s.chunk > 64) return {0, 0, 0};
+        const int now = ceil_div(wgs, s.cus), then = ceil_div((long long)s.npt * ngt, s.cus);
+        const bool shared = s.shared && s.V == 1, more_rounds = 2 * then > 3 * now - shared;
+        if (s.V < 4 && !uneven && ((more_rounds && s.chunk > 64) || (shared && then >= 2 * now))) return {0, 0, 0};
         int ks = 1;
         while (gpt * ks * 2 <= s.nw) ks *= 2;
         return {ngt, gpt, ks};

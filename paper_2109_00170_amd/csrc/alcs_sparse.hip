@@ -2870,6 +2870,7 @@ static int launch_sparse(const alcs_packed_t *Wp, const io_t *X_dev, const float
         shape.nw = 16;
         shape.npt = a.npt; shape.ngt = a.ngt; shape.gpt = a.gpt;
         shape.three = true;
+        shape.shared = L.tap_shared;
         shape.alone = 2 * lds > kMaxLds;
         shape.wide = V == 8 && tall && !(Wp->dev.cw && T.path != 6);
         if (T.waves == 0 && T.ug == 0 && pick_parts(shape, ug, a)) {

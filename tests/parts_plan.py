@@ -19,13 +19,13 @@ def _library():
 
 
 def parts_plan(V, G, npt, ngt, cols, nchunks=1, nw=16, gpt=None, three=True, alone=False, wide=False, strided=False,
-               stride2=False, uneven=False, unaligned=False, cus=256):
+               stride2=False, uneven=False, unaligned=False, shared=False, cus=256):
     """(group tiles, groups of one, wavefronts that share a group), or None where the launch keeps several groups per
     wavefront.  `cols`: kept columns of a group, in the mean."""
     out = (ctypes.c_int * 3)()
     gpt = -(-G // ngt) if gpt is None else gpt
-    _library().parts_plan((ctypes.c_int * 14)(cus, nw, V, G, npt, ngt, gpt, three, alone, wide, strided, stride2, uneven,
-                                              unaligned),
+    _library().parts_plan((ctypes.c_int * 15)(cus, nw, V, G, npt, ngt, gpt, three, alone, wide, strided, stride2, uneven,
+                                              unaligned, shared),
                           (ctypes.c_float * 2)(cols / nchunks, cols), out)
     return tuple(out) if out[0] else None
 

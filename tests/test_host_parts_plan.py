@@ -54,6 +54,18 @@ def test_small_groups_alone_on_their_compute_units():
         assert parts_plan(V=V, G=160, npt=182, ngt=5, cols=134 * 9, nchunks=9, **big) == (10, 16, 1)
 
 
+def test_single_channels_with_a_shared_pattern():
+    # longer turns of a wavefront's one group: fewer rounds are few more than for other patterns
+    big = dict(V=1, alone=True, nw=16)
+    for shared in (False, True):
+        parts = dict(big, shared=shared)
+        assert (parts_plan(G=648, npt=18, ngt=21, cols=267 * 12, nchunks=12, **parts) is None) == shared
+        assert (parts_plan(G=440, npt=104, ngt=14, cols=60 * 14, nchunks=14, **parts) is None) == shared
+        assert parts_plan(G=109, npt=212, ngt=4, cols=44 * 9, nchunks=9, **parts) == (7, 16, 1)
+        assert parts_plan(G=110, npt=140, ngt=4, cols=79 * 17, nchunks=17, **parts) == (7, 16, 1)
+    assert parts_plan(G=440, npt=104, ngt=14, cols=60 * 14, nchunks=14, alone=True, nw=16, V=2, shared=True) == (28, 16, 1)
+
+
 def test_more_than_one_round():
     big = dict(alone=True, nw=16)
     assert parts_plan(V=4, G=22, npt=210, ngt=1, cols=76 * 17, nchunks=17, **big) is None
